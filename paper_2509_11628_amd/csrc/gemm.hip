@@ -9,6 +9,10 @@ Error launch_attention_simple(int dtype, const void* qkv, void* out, int64_t ldo
 bool gemm_mfma_supported(const void* A, int64_t lda, const void* W, int64_t ldw, int N, int K);
 Error launch_gemm_mfma(const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st);
 
+bool gemm_f32_supported(const void* A, int64_t lda, const void* W, int64_t ldw, int K);
+Error launch_gemm_f32(const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st);
+Error launch_attention_f32(int dtype, const void* qkv, void* out, int64_t ldo, int rows, int T, int H, int hd, hipStream_t st);
+
 bool attention_mfma_supported(const void* qkv, const void* out, int64_t ldo, int H, int hd);
 Error launch_attention_mfma(const void* qkv, void* out, int64_t ldo, int rows, int T, int H, int hd, hipStream_t st);
 
@@ -33,6 +37,7 @@ Error launch_gemm(int dtype, const void* A, int64_t lda, const void* W, int64_t 
   }
   if (dtype == SPECA_BF16 && gemm_mfma_supported(A, lda, W, ldw, N, K))
     return launch_gemm_mfma(A, lda, W, ldw, M, N, K, epi, st);
+  if (dtype == SPECA_F32 && gemm_f32_supported(A, lda, W, ldw, K)) return launch_gemm_f32(A, lda, W, ldw, M, N, K, epi, st);
   return launch_gemm_simple(dtype, A, lda, W, ldw, M, N, K, epi, st);
 }
 
@@ -40,6 +45,10 @@ Error launch_attention(int dtype, const void* qkv, void* out, int64_t ldo, int r
   if (!qkv || !out || rows < 1 || T < 1 || H < 1 || ldo < static_cast<int64_t>(H) * hd || ldo % 4) SPECA_FAIL(SPECA_EINVAL, "attention: bad arguments");
   if (dtype == SPECA_BF16 && attention_mfma_supported(qkv, out, ldo, H, hd))
     return launch_attention_mfma(qkv, out, ldo, rows, T, H, hd, st);
+  // the fp32 matrix instructions take 16-byte pieces of fp32 and 8-byte pieces of bf16 operands (head sizes are multiples of 8)
+  const uintptr_t piece = dtype == SPECA_BF16 ? 8 : 16;
+  if (reinterpret_cast<uintptr_t>(qkv) % piece == 0 && reinterpret_cast<uintptr_t>(out) % piece == 0)
+    return launch_attention_f32(dtype, qkv, out, ldo, rows, T, H, hd, st);
   return launch_attention_simple(dtype, qkv, out, ldo, rows, T, H, hd, st);
 }
 

@@ -1,0 +1,366 @@
+// fp32 GEMM and attention on the fp32 matrix instructions (v_mfma_f32_16x16x4_f32: 157 TFLOP/s on the chip, twice what
+// unpacked vector FMAs reach, and exact fp32 products and sums).
+//
+// The models that run in fp32 are small, so their launches are bound by latency, not by rate: a 512 x 384 x 1536 layer is
+// 4 us of matrix work, and a vector-FMA block walking K behind a barrier per 16 columns took 97 us (now 14; attention over
+// 256 keys of two rows x 6 heads 340 us with one query per thread, now 8; 4096^3 runs at 98 TFLOP/s).  Hence
+//   - no LDS and no barrier in the loops: a lane's operands come from memory as 16-byte pieces that are fragments as they
+//     stand.  The reduction index is a dummy, so lane l of a wave simply takes columns 4 (l / 16) .. + 3 of its row, and
+//     instruction c of the step consumes component c of both operands: one load feeds four instructions;
+//   - several steps of loads in flight in registers;
+//   - the four waves of a block share one output tile and split K (GEMM: steps of 16 dealt round robin) or the keys
+//     (attention: tiles of 16 keys), and their partial results meet once, in LDS, in wave order.  The split depends on K
+//     (on the number of keys) alone, so a row's bits depend neither on M nor on the tile.
+#include <type_traits>
+
+#include "epilogue.h"
+#include "gemm.h"
+
+namespace speca {
+
+namespace {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ floatx4 mfma4(float a, float b, floatx4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+
+// ---- GEMM ------------------------------------------------------------------------------------------------------
+// Block tile (16 TM) x (16 TN); weights are the first operand, so a lane holds four consecutive output features of one row.
+// PF = steps of loads in flight per wave.
+// KTAIL: K is no multiple of 16.
+template <int TM, int TN, int PF, int MODE, bool KTAIL>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int64_t lda, const float* __restrict__ W, int64_t ldw, int M, int N,
+                                                       int K, GemmEpi epi) {
+  constexpr int BM = 16 * TM, BN = 16 * TN;
+  constexpr int CST = BN + 4;                     // floats per staged row
+  __shared__ __align__(16) float part[4][BM * CST];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, kq = (lane >> 4) * 4;
+  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
+  const float* pa[TM];
+  const float* pw[TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const int m = m0 + i * 16 + l16;
+    pa[i] = A + static_cast<int64_t>(m < M ? m : M - 1) * lda;      // rows beyond M / N repeat the last one and are never stored
+  }
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const int n = n0 + j * 16 + l16;
+    pw[j] = W + static_cast<int64_t>(n < N ? n : N - 1) * ldw;
+  }
+  floatx4 acc[TN][TM];
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int i = 0; i < TM; ++i) acc[j][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+  const int n_all = (K + 15) / 16;                                  // steps of 16 columns
+  const int steps = (n_all - wave + 3) / 4;                         // this wave's: wave, wave + 4, ...
+  floatx4 ra[PF][TM], rw[PF][TN];
+  // A step past the end re-reads the last one (never consumed).  Columns past K re-read column 0 and are zeroed where they are
+  // consumed: a select next to the load would wait for it there.
+  auto load = [&](int s, floatx4 (&a)[TM], floatx4 (&w)[TN]) {
+    int k = (wave + 4 * (s < steps ? s : (steps > 0 ? steps - 1 : 0))) * 16 + kq;
+    if (KTAIL || steps == 0) k = k < K ? k : 0;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) a[i] = *reinterpret_cast<const floatx4*>(pa[i] + k);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) w[j] = *reinterpret_cast<const floatx4*>(pw[j] + k);
+  };
+#pragma unroll
+  for (int p = 0; p < PF; ++p) load(p, ra[p], rw[p]);
+  auto step = [&](int s, floatx4 (&a)[TM], floatx4 (&w)[TN]) {
+    if (KTAIL && (wave + 4 * s) * 16 + kq >= K) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) a[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < TN; ++j) w[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int i = 0; i < TM; ++i) acc[j][i] = mfma4(w[j][c], a[i][c], acc[j][i]);
+  };
+  // no branch around a load in the loop, so that the compiler counts the outstanding ones instead of draining them
+  int s = 0;
+  for (; s + PF <= steps; s += PF) {
+#pragma unroll
+    for (int p = 0; p < PF; ++p) {
+      step(s + p, ra[p], rw[p]);
+      load(s + p + PF, ra[p], rw[p]);
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < PF; ++p)
+    if (s + p < steps) step(s + p, ra[p], rw[p]);
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int i = 0; i < TM; ++i) *reinterpret_cast<floatx4*>(&part[wave][(i * 16 + l16) * CST + j * 16 + kq]) = acc[j][i];
+  __syncthreads();
+  constexpr int QPR = BN / 4;
+#pragma unroll
+  for (int q = tid; q < BM * QPR; q += 256) {
+    const int r = q / QPR, c = (q % QPR) * 4;
+    const int m = m0 + r, n = n0 + c;
+    if (m < M && n < N) {
+      float v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = ((part[0][r * CST + c + e] + part[1][r * CST + c + e]) + part[2][r * CST + c + e]) + part[3][r * CST + c + e];
+      epilogue_quad<float, MODE>(epi, m, n, v);
+    }
+  }
+}
+
+template <int TM, int TN, int PF>
+Error launch_f32_tile(const float* A, int64_t lda, const float* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st) {
+  const dim3 grid((N + 16 * TN - 1) / (16 * TN), (M + 16 * TM - 1) / (16 * TM));
+#define SPECA_LAUNCH(MODE_)                                                                                                  \
+  {                                                                                                                          \
+    if (K % 16) gemm_f32_kernel<TM, TN, PF, MODE_, true><<<grid, 256, 0, st>>>(A, lda, W, ldw, M, N, K, epi);                \
+    else gemm_f32_kernel<TM, TN, PF, MODE_, false><<<grid, 256, 0, st>>>(A, lda, W, ldw, M, N, K, epi);                      \
+  }
+  switch (epi.mode) {
+    case EPI_STORE: SPECA_LAUNCH(EPI_STORE) break;
+    case EPI_GELU: SPECA_LAUNCH(EPI_GELU) break;
+    case EPI_SILU: SPECA_LAUNCH(EPI_SILU) break;
+    case EPI_F32: SPECA_LAUNCH(EPI_F32) break;
+    case EPI_BRANCH: SPECA_LAUNCH(EPI_BRANCH) break;
+    default: SPECA_FAIL(SPECA_EINVAL, "gemm: epilogue mode %d", epi.mode);
+  }
+#undef SPECA_LAUNCH
+  SPECA_HIP(hipGetLastError());
+  return ok();
+}
+
+// ---- attention ----------------------------------------------------------------------------------------------------
+// One block = 16 QT queries of one (row, head); its four waves take the 16-key tiles w, w + 4, ... with an online softmax of
+// their own and merge at the end.  Transposed products as in the bf16 kernels: S^T[key][query] leaves lane l with keys
+// 4 (l / 16) .. + 3 of query l % 16, which is the second operand of the O^T product as it stands (instruction r takes keys
+// 4 q + r).  The head dimension is dealt to the 16-row tiles of O^T in pieces of four (tile i % 4 of group i / 4 owns
+// dimensions 64 g + 4 row + i), so a lane's values are 16-byte pieces of V and of the output.  Values of head size 72 past
+// 64 take single elements.  T = storage type of q, k, v and the output; arithmetic is fp32.
+template <typename T> __device__ inline floatx4 ld_quad(const T* p);
+template <> __device__ inline floatx4 ld_quad<float>(const float* p) { return *reinterpret_cast<const floatx4*>(p); }
+template <> __device__ inline floatx4 ld_quad<bf16_t>(const bf16_t* p) {
+  float v[4];
+  Store4<bf16_t>::ld(p, v);
+  return floatx4{v[0], v[1], v[2], v[3]};
+}
+template <typename T> __device__ inline float ld_one(const T* p);
+template <> __device__ inline float ld_one<float>(const float* p) { return *p; }
+template <> __device__ inline float ld_one<bf16_t>(const bf16_t* p) { return bf16_to_f32(p->bits); }
+
+template <typename T, int HD, int QT>
+__global__ __launch_bounds__(256) void attention_f32_kernel(const T* __restrict__ qkv, T* __restrict__ out, int64_t ldo, int Tn, int H, float scale_log2e) {
+  constexpr int KS = (HD + 15) / 16;              // steps of 16 dimensions in q k^T
+  constexpr int G = HD / 64;                      // groups of four tiles of O^T (64 dimensions)
+  constexpr int REM = HD - 64 * G;                // what is left: 8, 16 or 32 dimensions in tiles of 16
+  constexpr int RT = (REM + 15) / 16;
+  constexpr int DT = 4 * G + RT;
+  static_assert(HD % 8 == 0 && (REM == 0 || REM == 8 || REM == 16 || REM == 32), "head_dim");
+  constexpr int OST = 16 * DT + 4;                // floats per query in the merge buffer
+  __shared__ __align__(16) float merge[3][16 * OST];
+  __shared__ float stats[4][2][16];
+  const int row = blockIdx.z, head = blockIdx.y, q0 = blockIdx.x * 16 * QT;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g4 = lane >> 4;
+  const int64_t D = static_cast<int64_t>(H) * HD;
+  const T* base = qkv + static_cast<int64_t>(row) * Tn * 3 * D + head * HD;
+  const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+
+  floatx4 qf[QT][KS];
+#pragma unroll
+  for (int t = 0; t < QT; ++t) {
+    const int q = q0 + t * 16 + l16;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const int d = s * 16 + g4 * 4;
+      qf[t][s] = d < HD ? ld_quad(base + static_cast<int64_t>(q < Tn ? q : Tn - 1) * 3 * D + d) : zero;
+    }
+  }
+  floatx4 o[QT][DT];
+  float mrun[QT], lrun[QT];
+#pragma unroll
+  for (int t = 0; t < QT; ++t) {
+    mrun[t] = -INFINITY; lrun[t] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < DT; ++i) o[t][i] = zero;
+  }
+  const int ntiles = (Tn + 15) / 16;
+  floatx4 kf[KS];
+  auto load_k = [&](int kt) {
+    int key = kt * 16 + l16;
+    key = key < Tn ? key : Tn - 1;
+    const T* p = base + static_cast<int64_t>(key) * 3 * D + D + g4 * 4;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) kf[s] = s * 16 + g4 * 4 < HD ? ld_quad(p + s * 16) : zero;
+  };
+  if (wave < ntiles) load_k(wave);
+  for (int kt = wave; kt < ntiles; kt += 4) {
+    // this tile's values, on their way during the scores
+    floatx4 vf[4][G > 0 ? G : 1];
+    float vr[4][RT > 0 ? RT : 1];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      int key = kt * 16 + g4 * 4 + r;
+      key = key < Tn ? key : Tn - 1;
+      const T* p = base + static_cast<int64_t>(key) * 3 * D + 2 * D;
+#pragma unroll
+      for (int g = 0; g < G; ++g) vf[r][g] = ld_quad(p + g * 64 + l16 * 4);
+#pragma unroll
+      for (int i = 0; i < RT; ++i) vr[r][i] = i * 16 + l16 < REM ? ld_one(p + 64 * G + i * 16 + l16) : 0.0f;
+    }
+    floatx4 s[QT];
+#pragma unroll
+    for (int t = 0; t < QT; ++t) s[t] = zero;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int t = 0; t < QT; ++t) s[t] = mfma4(kf[ks][c], qf[t][ks][c], s[t]);
+    if (kt + 4 < ntiles) load_k(kt + 4);
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+      if (kt * 16 + 16 > Tn) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (kt * 16 + g4 * 4 + r >= Tn) s[t][r] = -INFINITY;
+      }
+      float tmax = fmaxf(fmaxf(s[t][0], s[t][1]), fmaxf(s[t][2], s[t][3]));
+      tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
+      tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+      const float mnew = fmaxf(mrun[t], tmax);
+      const float moff = mnew * scale_log2e;
+      const float corr = __builtin_amdgcn_exp2f(fmaf(mrun[t], scale_log2e, -moff));     // the first tile: exp2(-inf) = 0
+      float p[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(fmaf(s[t][r], scale_log2e, -moff));
+      lrun[t] = fmaf(lrun[t], corr, (p[0] + p[1]) + (p[2] + p[3]));
+      mrun[t] = mnew;
+#pragma unroll
+      for (int i = 0; i < DT; ++i) o[t][i] *= corr;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+#pragma unroll
+        for (int i = 0; i < 4 * G; ++i) o[t][i] = mfma4(vf[r][i / 4][i % 4], p[r], o[t][i]);
+#pragma unroll
+        for (int i = 0; i < RT; ++i) o[t][4 * G + i] = mfma4(vr[r][i], p[r], o[t][4 * G + i]);
+      }
+    }
+  }
+  // merge in wave order: every wave scales its sums to the common maximum; waves 1 .. 3 hand theirs over in LDS
+#pragma unroll
+  for (int t = 0; t < QT; ++t) {
+    float l = lrun[t];
+    l += __shfl_xor(l, 16, 64);
+    l += __shfl_xor(l, 32, 64);
+    if (t > 0) __syncthreads();
+    if (lane < 16) { stats[wave][0][l16] = mrun[t]; stats[wave][1][l16] = l; }
+    __syncthreads();
+    const float m = fmaxf(fmaxf(stats[0][0][l16], stats[1][0][l16]), fmaxf(stats[2][0][l16], stats[3][0][l16]));
+    float f[4], lsum = 0.0f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      f[w] = __builtin_amdgcn_exp2f((stats[w][0][l16] - m) * scale_log2e);            // a wave without a tile: exp2(-inf) = 0
+      lsum = fmaf(stats[w][1][l16], f[w], lsum);
+    }
+    const float mine = wave == 0 ? f[0] : wave == 1 ? f[1] : wave == 2 ? f[2] : f[3];
+    if (wave > 0) {
+#pragma unroll
+      for (int i = 0; i < DT; ++i) *reinterpret_cast<floatx4*>(&merge[wave - 1][l16 * OST + i * 16 + g4 * 4]) = o[t][i] * mine;
+    }
+    __syncthreads();
+    if (wave == 0) {
+      const float inv = 1.0f / lsum;
+      const int q = q0 + t * 16 + l16;
+#pragma unroll
+      for (int i = 0; i < DT; ++i) {
+        floatx4 v = o[t][i] * mine;
+#pragma unroll
+        for (int w = 0; w < 3; ++w) v += *reinterpret_cast<const floatx4*>(&merge[w][l16 * OST + i * 16 + g4 * 4]);
+        o[t][i] = v * inv;
+      }
+      if (q < Tn) {
+        T* op = out + (static_cast<int64_t>(row) * Tn + q) * ldo + head * HD;
+        // accumulator r of tile i of group g is dimension 64 g + 4 (4 g4 + r) + i
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const float v[4] = {o[t][4 * g][r], o[t][4 * g + 1][r], o[t][4 * g + 2][r], o[t][4 * g + 3][r]};
+            Store4<T>::st(op + g * 64 + 4 * (4 * g4 + r), v);
+          }
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+          const int d = i * 16 + g4 * 4;
+          const float v[4] = {o[t][4 * G + i][0], o[t][4 * G + i][1], o[t][4 * G + i][2], o[t][4 * G + i][3]};
+          if (d < REM) Store4<T>::st(op + 64 * G + d, v);
+        }
+      }
+    }
+  }
+}
+
+template <typename T, int HD>
+Error launch_attn_f32_hd(const void* qkv, void* out, int64_t ldo, int rows, int Tn, int H, hipStream_t st) {
+  const float sl2 = 1.4426950408889634f / sqrtf(static_cast<float>(HD));
+  // 32 queries per block read every key and value half as often; 16 keep the chip busy when there are few of them
+  if (static_cast<int64_t>((Tn + 31) / 32) * H * rows >= 512)
+    attention_f32_kernel<T, HD, 2><<<dim3((Tn + 31) / 32, H, rows), 256, 0, st>>>(static_cast<const T*>(qkv), static_cast<T*>(out), ldo, Tn, H, sl2);
+  else
+    attention_f32_kernel<T, HD, 1><<<dim3((Tn + 15) / 16, H, rows), 256, 0, st>>>(static_cast<const T*>(qkv), static_cast<T*>(out), ldo, Tn, H, sl2);
+  SPECA_HIP(hipGetLastError());
+  return ok();
+}
+
+template <typename T>
+Error launch_attn_f32_t(const void* qkv, void* out, int64_t ldo, int rows, int Tn, int H, int hd, hipStream_t st) {
+  switch (hd) {
+    case 16: return launch_attn_f32_hd<T, 16>(qkv, out, ldo, rows, Tn, H, st);
+    case 32: return launch_attn_f32_hd<T, 32>(qkv, out, ldo, rows, Tn, H, st);
+    case 64: return launch_attn_f32_hd<T, 64>(qkv, out, ldo, rows, Tn, H, st);
+    case 72: return launch_attn_f32_hd<T, 72>(qkv, out, ldo, rows, Tn, H, st);
+    case 128: return launch_attn_f32_hd<T, 128>(qkv, out, ldo, rows, Tn, H, st);
+  }
+  SPECA_FAIL(SPECA_EUNSUPPORTED, "attention: head_dim %d (supported: 16, 32, 64, 72, 128)", hd);
+}
+
+}  // namespace
+
+bool gemm_f32_supported(const void* A, int64_t lda, const void* W, int64_t ldw, int K) {
+  return K % 4 == 0 && lda % 4 == 0 && ldw % 4 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0;
+}
+
+static Error launch_f32_kind(int kind, const float* a, int64_t lda, const float* w, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st) {
+  switch (kind) {
+    case 0: return launch_f32_tile<4, 4, 2>(a, lda, w, ldw, M, N, K, epi, st);
+    case 1: return launch_f32_tile<2, 4, 3>(a, lda, w, ldw, M, N, K, epi, st);
+    case 2: return launch_f32_tile<2, 2, 4>(a, lda, w, ldw, M, N, K, epi, st);
+    case 3: return launch_f32_tile<1, 2, 6>(a, lda, w, ldw, M, N, K, epi, st);
+    default: return launch_f32_tile<1, 1, 8>(a, lda, w, ldw, M, N, K, epi, st);
+  }
+}
+
+Error launch_gemm_f32(const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st) {
+  if ((M + 63) / 64 > 65535) SPECA_FAIL(SPECA_EINVAL, "gemm: too many rows");
+  // The largest tile that still makes 128 blocks (one on every second compute unit): a block's waves read every operand
+  // piece once per tile, and that traffic costs more than idle units do down to there (512 x 1152 x 384: 144 blocks of 64 x 64
+  // 11.4 us, 576 of 32 x 32 12.8, 2304 of 16 x 16 18.1; 512 x 384 x 384 with 48 / 192 / 768 blocks: 11.1 / 5.6 / 7.6 us).
+  // Tiles more than twice as high as the problem only read rows again.
+  constexpr int bm[5] = {64, 32, 32, 16, 16}, bn[5] = {64, 64, 32, 32, 16};
+  int kind = 0;
+  while (kind < 4 && (bm[kind] > 2 * ((M + 15) / 16 * 16) || static_cast<int64_t>((M + bm[kind] - 1) / bm[kind]) * ((N + bn[kind] - 1) / bn[kind]) < 128)) ++kind;
+  return launch_f32_kind(kind, static_cast<const float*>(A), lda, static_cast<const float*>(W), ldw, M, N, K, epi, st);
+}
+
+Error launch_attention_f32(int dtype, const void* qkv, void* out, int64_t ldo, int rows, int T, int H, int hd, hipStream_t st) {
+  if (rows > 65535 || H > 65535) SPECA_FAIL(SPECA_EINVAL, "attention: grid too large");
+  return dtype == SPECA_BF16 ? launch_attn_f32_t<bf16_t>(qkv, out, ldo, rows, T, H, hd, st) : launch_attn_f32_t<float>(qkv, out, ldo, rows, T, H, hd, st);
+}
+
+}  // namespace speca

@@ -696,7 +696,7 @@ Error launch_tile(const void* A, int64_t lda, const void* W, int64_t ldw, int M,
 }  // namespace
 
 bool gemm_mfma_supported(const void* A, int64_t lda, const void* W, int64_t ldw, int N, int K) {
-  return (K % 8 == 0) && (lda % 8 == 0) && (ldw % 8 == 0) && (N % 8 == 0) && (reinterpret_cast<uintptr_t>(A) % 16 == 0) &&
+  return (K % 8 == 0) && (lda % 8 == 0) && (ldw % 8 == 0) && (N % 4 == 0) && (reinterpret_cast<uintptr_t>(A) % 16 == 0) &&
          (reinterpret_cast<uintptr_t>(W) % 16 == 0);
 }
 

@@ -1,5 +1,5 @@
-// Plain fp32-FMA tile kernels: the linear layers and attention of fp32 models (there is
-// no fp32 path through the bf16 matrix cores), and of shapes the MFMA kernels do not take.
+// Plain fp32-FMA tile kernels for operands that the matrix-core kernels do not take: rows
+// that are no whole number of 16-byte pieces, pointers that are not 16-byte aligned.
 // 64x64 output tile per 256-thread block, K staged through LDS in steps of 16, each
 // thread owns a 4x4 micro-tile.  K is walked in order, so a row's result does not depend
 // on M or on which other rows share the launch.
@@ -91,7 +91,6 @@ Error launch_simple_t(const void* A, int64_t lda, const void* W, int64_t ldw, in
 // softmax in fp32.  hd <= 128.
 constexpr int AT_Q = 64;      // queries per block
 constexpr int AT_K = 32;      // keys per LDS tile
-constexpr int HD_MAX = 128;
 
 template <typename T, int HD>
 __global__ __launch_bounds__(AT_Q) void attention_simple_kernel(const T* __restrict__ qkv, T* __restrict__ out, int64_t ldo, int Tn,

@@ -90,6 +90,20 @@ def test_linear_row_result_independent_of_m():
     assert torch.equal(full[4000:4096], bd.linear(a[4000:4096].contiguous(), w))
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 4, 4), (15, 20, 12), (17, 516, 260), (33, 1028, 20), (129, 1100, 16), (300, 2052, 100), (2100, 132, 72), (40, 64, 7)])
+def test_linear_f32_tiles(M, N, K):
+    """fp32 layers at the edges of every tile of the fp32 matrix kernel (16 to 64 rows and columns, K in four interleaved
+    parts of 16, tails of 4) and a K that only the plain kernel takes; a row's bits do not depend on M or on the tile."""
+    bd = _bd()
+    rng = np.random.default_rng(M + N + K)
+    a, w, b = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32), rng.standard_normal(N).astype(np.float32)
+    da, dw, db = _dev(a, "f32"), _dev(w, "f32"), _dev(b, "f32")
+    out = bd.linear(da, dw, db)
+    _check(out, odit.linear(a.astype(np.float64), w.astype(np.float64), b.astype(np.float64)), "f32", K)
+    r = M // 2
+    assert torch.equal(bd.linear(da[r:r + 1].contiguous(), dw, db)[0], out[r])
+
+
 @pytest.mark.parametrize("rows,T,H,hd", [(2, 16, 4, 16), (1, 100, 2, 72), (2, 256, 3, 72), (1, 77, 2, 64), (1, 300, 2, 128), (1, 64, 1, 32),
                                           (1, 256, 2, 128), (3, 200, 2, 64), (1, 257, 2, 72), (1, 33, 1, 128),
                                           (1, 2000, 2, 128), (1, 1111, 1, 72),       # many key tiles, ragged tail
