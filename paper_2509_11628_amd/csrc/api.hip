@@ -128,6 +128,35 @@ Error ensure_partial(speca_ctx* ctx, size_t floats) {
   return ok();
 }
 
+// A poll of a word in pinned memory sees the result about a microsecond after it was written; hipStreamSynchronize behind
+// three copies of a few bytes (thresholds in, errors and verdicts out) took another 20 us per verification.  The stream is
+// asked now and then as well, so a failed launch or a lost device ends the wait with its error.
+Error wait_verdict(speca_ctx* ctx, int n, const float* tau) {
+  VerifyScratch& v = ctx->vs;
+  int have = 0;
+  for (unsigned polls = 0;; ++polls) {
+    while (have < n) {
+      const uint64_t w = __atomic_load_n(v.verdict + have, __ATOMIC_ACQUIRE);
+      if (static_cast<uint32_t>(w >> 32) != v.launch) break;
+      const uint32_t bits = static_cast<uint32_t>(w);
+      std::memcpy(&v.h_err[have], &bits, sizeof(bits));
+      ++have;
+    }
+    if (have == n) break;
+    if (polls % 8192 == 8191) {
+      const hipError_t e = hipStreamQuery(ctx->stream);
+      if (e == hipErrorNotReady) continue;
+      if (e != hipSuccess) SPECA_FAIL(SPECA_EHIP, "verification failed: %s", hipGetErrorString(e));
+      if (static_cast<uint32_t>(__atomic_load_n(v.verdict + have, __ATOMIC_ACQUIRE) >> 32) != v.launch)
+        SPECA_FAIL(SPECA_EHIP, "the verification ended without a result for row %d", have);
+    }
+    __builtin_ia32_pause();
+  }
+  if (tau)
+    for (int i = 0; i < n; ++i) v.h_acc[i] = v.h_err[i] <= tau[i] ? 1 : 0;
+  return ok();
+}
+
 }  // namespace speca
 
 static bool cfg_ok(const speca_cfg* c, std::string* why) {
@@ -155,13 +184,8 @@ static void free_ctx(speca_ctx* ctx) {
   if (ctx->geom.base) (void)hipFree(ctx->geom.base);
   if (ctx->model_out) (void)hipFree(ctx->model_out);
   VerifyScratch& v = ctx->vs;
-  if (v.tau_dev) (void)hipFree(v.tau_dev);
-  if (v.err_dev) (void)hipFree(v.err_dev);
-  if (v.acc_dev) (void)hipFree(v.acc_dev);
   if (v.partial) (void)hipFree(v.partial);
-  if (v.h_tau) (void)hipHostFree(v.h_tau);
-  if (v.h_err) (void)hipHostFree(v.h_err);
-  if (v.h_acc) (void)hipHostFree(v.h_acc);
+  if (v.verdict) (void)hipHostFree(v.verdict);
   delete ctx;
 }
 
@@ -198,12 +222,10 @@ static Error create_impl(speca_ctx** out, const speca_model_desc* desc, const sp
     if (v >= 1 && v <= kMaxLanes) ctx->lanes = v;
   }
   VerifyScratch& v = ctx->vs;
-  SPECA_HIP(hipMalloc(&v.tau_dev, kMaxVerifyRows * sizeof(float)));
-  SPECA_HIP(hipMalloc(&v.err_dev, kMaxVerifyRows * sizeof(float)));
-  SPECA_HIP(hipMalloc(&v.acc_dev, kMaxVerifyRows));
-  SPECA_HIP(hipHostMalloc(&v.h_tau, kMaxVerifyRows * sizeof(float), hipHostMallocDefault));
-  SPECA_HIP(hipHostMalloc(&v.h_err, kMaxVerifyRows * sizeof(float), hipHostMallocDefault));
-  SPECA_HIP(hipHostMalloc(&v.h_acc, kMaxVerifyRows, hipHostMallocDefault));
+  SPECA_HIP(hipHostMalloc(reinterpret_cast<void**>(&v.verdict), kMaxVerifyRows * sizeof(uint64_t), hipHostMallocMapped | hipHostMallocCoherent));
+  std::memset(v.verdict, 0, kMaxVerifyRows * sizeof(uint64_t));
+  v.h_err.resize(kMaxVerifyRows);
+  v.h_acc.resize(kMaxVerifyRows);
   *out = ctx.release();
   return ok();
 }
@@ -345,22 +367,16 @@ static Error verify_impl(speca_ctx* ctx, const void* pred, const void* truth, in
   for (int r0 = 0; r0 < n_rows; r0 += kMaxVerifyRows) {
     const int n = std::min(kMaxVerifyRows, n_rows - r0);
     SPECA_TRY(ensure_partial(ctx, static_cast<size_t>(n) * verify_chunks(E) * 3));
-    if (tau) {
-      std::memcpy(v.h_tau, tau + r0, n * sizeof(float));
-      SPECA_HIP(hipMemcpyAsync(v.tau_dev, v.h_tau, n * sizeof(float), hipMemcpyHostToDevice, ctx->stream));
-    }
     const char* p = static_cast<const char*>(pred) + static_cast<size_t>(r0) * E * esz;
     const char* t = static_cast<const char*>(truth) + static_cast<size_t>(r0) * E * esz;
     {
       ProfScope ps(ctx, SPECA_PROF_VERIFY, 0.0, 2.0 * n * E * esz);
-      SPECA_TRY(launch_verify(metric, p, dtype, t, dtype, E, nullptr, nullptr, 0, n, eps, tau ? v.tau_dev : nullptr, v.partial,
-                              v.err_dev, v.acc_dev, ctx->stream));
+      SPECA_TRY(launch_verify(metric, p, dtype, t, dtype, E, nullptr, nullptr, 0, n, eps, v.partial, {nullptr, nullptr, nullptr, v.verdict, ++v.launch},
+                              ctx->stream));
     }
-    SPECA_HIP(hipMemcpyAsync(v.h_err, v.err_dev, n * sizeof(float), hipMemcpyDeviceToHost, ctx->stream));
-    if (tau) SPECA_HIP(hipMemcpyAsync(v.h_acc, v.acc_dev, n, hipMemcpyDeviceToHost, ctx->stream));
-    SPECA_HIP(hipStreamSynchronize(ctx->stream));
-    std::memcpy(err_out + r0, v.h_err, n * sizeof(float));
-    if (tau) std::memcpy(accept_out + r0, v.h_acc, n);
+    SPECA_TRY(wait_verdict(ctx, n, tau ? tau + r0 : nullptr));      // the last thing on the stream: everything before it is done too
+    std::memcpy(err_out + r0, v.h_err.data(), n * sizeof(float));
+    if (tau) std::memcpy(accept_out + r0, v.h_acc.data(), n);
   }
   return ok();
 }
@@ -387,8 +403,8 @@ static Error verify_static_impl(speca_ctx* ctx, const void* pred, const void* tr
     const int n = std::min(kMaxRows, n_rows - r0);
     const char* p = static_cast<const char*>(pred) + static_cast<size_t>(r0) * E * esz;
     const char* t = static_cast<const char*>(truth) + static_cast<size_t>(r0) * E * esz;
-    SPECA_TRY(launch_verify(metric, p, dtype, t, dtype, E, nullptr, nullptr, 0, n, eps, tau_dev ? tau_dev + r0 : nullptr, ctx->static_partial,
-                            err_dev + r0, accept_dev ? accept_dev + r0 : nullptr, ctx->stream));
+    SPECA_TRY(launch_verify(metric, p, dtype, t, dtype, E, nullptr, nullptr, 0, n, eps, ctx->static_partial,
+                            {tau_dev ? tau_dev + r0 : nullptr, err_dev + r0, accept_dev ? accept_dev + r0 : nullptr, nullptr, 0}, ctx->stream));
   }
   return ok();
 }
@@ -436,8 +452,9 @@ static Error spec_step_impl(speca_ctx* ctx, const void* x, const speca_cond* con
   SPECA_TRY(labels_for_rows(ctx, cond, &labels));
   SPECA_TRY(ctx->model->spec_step(ctx, static_cast<const float*>(x), ctx->batch_rows, cond, labels.data(), step, rows, n_rows,
                                   tau, pair_stride, static_cast<float*>(model_out)));
-  std::memcpy(err_out, ctx->vs.h_err, n_rows * sizeof(float));
-  std::memcpy(accept_out, ctx->vs.h_acc, n_rows);
+  SPECA_HIP(hipStreamSynchronize(ctx->stream));      // the finish of the listed rows runs behind the verdict
+  std::memcpy(err_out, ctx->vs.h_err.data(), n_rows * sizeof(float));
+  std::memcpy(accept_out, ctx->vs.h_acc.data(), n_rows);
   return ok();
 }
 

@@ -306,9 +306,7 @@ __global__ __launch_bounds__(kThreads) void verify_partial_kernel(const T* __res
 
 // Stage 2: one wave per row; lane l sums partials l, l+64, ... in order, then butterfly.
 template <int METRIC>
-__global__ __launch_bounds__(64) void verify_final_kernel(const float* __restrict__ partial, int n_chunks, float eps,
-                                                          const float* __restrict__ tau, float* __restrict__ err,
-                                                          uint8_t* __restrict__ accept) {
+__global__ __launch_bounds__(64) void verify_final_kernel(const float* __restrict__ partial, int n_chunks, float eps, VerifyOut out) {
   const int i = blockIdx.x;
   float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f;
   for (int c = threadIdx.x; c < n_chunks; c += 64) {
@@ -328,8 +326,13 @@ __global__ __launch_bounds__(64) void verify_final_kernel(const float* __restric
     if (METRIC == SPECA_METRIC_L2) e = sqrtf(a0) / (sqrtf(a1) + eps);
     else if (METRIC == SPECA_METRIC_COSINE) e = 1.0f - a0 / (sqrtf(a2) * sqrtf(a1) + eps);
     else e = a0 / (a1 + eps);
-    err[i] = e;
-    if (tau) accept[i] = e <= tau[i] ? 1 : 0;
+    if (out.verdict) {
+      const uint64_t word = static_cast<uint64_t>(out.launch) << 32 | __float_as_uint(e);
+      __hip_atomic_store(out.verdict + i, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    } else {
+      out.err[i] = e;
+      if (out.tau) out.accept[i] = e <= out.tau[i] ? 1 : 0;
+    }
   }
 }
 
@@ -435,6 +438,8 @@ Error launch_cache_warm(const CacheGeom& g, const RowTable& rt, int slot, hipStr
     mo = rt.order[i] > mo ? rt.order[i] : mo;
   }
   if (mo == 0) return ok();                            // first references: nothing old to read
+  // a cache that the 256 MB memory-side cache holds between two steps is not cold
+  if (static_cast<int64_t>(g.E) * g.n_slots * (g.m + 1) * g.batch_rows * static_cast<int64_t>(dtype_size(g.dtype)) < (int64_t{128} << 20)) return ok();
   const int esz = static_cast<int>(dtype_size(g.dtype));
   const int64_t bytes = g.E * esz;
   if (bytes % 16) return ok();                                // only a hint: skip odd geometries
@@ -480,8 +485,7 @@ static void dispatch_verify(const void* pred, const void* truth, int64_t E, cons
 
 template <int METRIC>
 static Error launch_verify_m(const void* pred, int pred_dtype, const void* truth, int truth_dtype, int64_t E, const CacheGeom* g,
-                             const RowTable* rt, int slot, int n_rows, float eps, const float* tau_dev, float* partial,
-                             float* err_dev, uint8_t* accept_dev, hipStream_t st) {
+                             const RowTable* rt, int slot, int n_rows, float eps, float* partial, const VerifyOut& out, hipStream_t st) {
   bool vec = (E % 8 == 0) && (reinterpret_cast<uintptr_t>(truth) % 16 == 0);
   if (g) vec = vec && (reinterpret_cast<uintptr_t>(g->base) % 16 == 0);
   else vec = vec && (reinterpret_cast<uintptr_t>(pred) % 16 == 0);
@@ -491,22 +495,21 @@ static Error launch_verify_m(const void* pred, int pred_dtype, const void* truth
   else if (!pb && tb) dispatch_verify<float, bf16_t, METRIC>(pred, truth, E, g, rt, slot, n_rows, partial, vec, st);
   else dispatch_verify<float, float, METRIC>(pred, truth, E, g, rt, slot, n_rows, partial, vec, st);
   SPECA_HIP(hipGetLastError());
-  verify_final_kernel<METRIC><<<n_rows, 64, 0, st>>>(partial, verify_chunks(E), eps, tau_dev, err_dev, accept_dev);
+  verify_final_kernel<METRIC><<<n_rows, 64, 0, st>>>(partial, verify_chunks(E), eps, out);
   SPECA_HIP(hipGetLastError());
   return ok();
 }
 
 Error launch_verify(int metric, const void* pred, int pred_dtype, const void* truth, int truth_dtype, int64_t E,
-                    const CacheGeom* g, const RowTable* rt, int slot, int n_rows, float eps, const float* tau_dev,
-                    float* partial, float* err_dev, uint8_t* accept_dev, hipStream_t st) {
+                    const CacheGeom* g, const RowTable* rt, int slot, int n_rows, float eps, float* partial, const VerifyOut& out, hipStream_t st) {
   // the cache form takes its rows from a row table; two tensors can be reduced for more rows at once
   if (n_rows <= 0 || n_rows > (g ? kMaxRows : kMaxVerifyRows)) SPECA_FAIL(SPECA_EINVAL, "verify: %d rows in one launch", n_rows);
   if (E <= 0) SPECA_FAIL(SPECA_EINVAL, "verify: elems_per_row = %lld", static_cast<long long>(E));
   switch (metric) {
-    case SPECA_METRIC_L2: return launch_verify_m<SPECA_METRIC_L2>(pred, pred_dtype, truth, truth_dtype, E, g, rt, slot, n_rows, eps, tau_dev, partial, err_dev, accept_dev, st);
-    case SPECA_METRIC_L1: return launch_verify_m<SPECA_METRIC_L1>(pred, pred_dtype, truth, truth_dtype, E, g, rt, slot, n_rows, eps, tau_dev, partial, err_dev, accept_dev, st);
-    case SPECA_METRIC_LINF: return launch_verify_m<SPECA_METRIC_LINF>(pred, pred_dtype, truth, truth_dtype, E, g, rt, slot, n_rows, eps, tau_dev, partial, err_dev, accept_dev, st);
-    case SPECA_METRIC_COSINE: return launch_verify_m<SPECA_METRIC_COSINE>(pred, pred_dtype, truth, truth_dtype, E, g, rt, slot, n_rows, eps, tau_dev, partial, err_dev, accept_dev, st);
+    case SPECA_METRIC_L2: return launch_verify_m<SPECA_METRIC_L2>(pred, pred_dtype, truth, truth_dtype, E, g, rt, slot, n_rows, eps, partial, out, st);
+    case SPECA_METRIC_L1: return launch_verify_m<SPECA_METRIC_L1>(pred, pred_dtype, truth, truth_dtype, E, g, rt, slot, n_rows, eps, partial, out, st);
+    case SPECA_METRIC_LINF: return launch_verify_m<SPECA_METRIC_LINF>(pred, pred_dtype, truth, truth_dtype, E, g, rt, slot, n_rows, eps, partial, out, st);
+    case SPECA_METRIC_COSINE: return launch_verify_m<SPECA_METRIC_COSINE>(pred, pred_dtype, truth, truth_dtype, E, g, rt, slot, n_rows, eps, partial, out, st);
   }
   SPECA_FAIL(SPECA_EINVAL, "verify: unknown metric %d", metric);
 }

@@ -14,17 +14,15 @@ namespace speca {
 
 struct Model;
 
-// Small pinned host area + device mirrors for the per-launch scalars that travel each
-// speculative step (thresholds in; errors and verdicts out).
+// The errors of a verification travel to the host without copies: the reduction's last kernel writes each row's error and
+// the number of the launch as one 64-bit word into pinned memory, where the host polls for that number.
 struct VerifyScratch {
-  float* tau_dev = nullptr;        // [kMaxVerifyRows]
-  float* err_dev = nullptr;        // [kMaxVerifyRows]
-  uint8_t* acc_dev = nullptr;      // [kMaxVerifyRows]
   float* partial = nullptr;        // [rows][chunks][3]
   size_t partial_cap = 0;          // floats
-  float* h_tau = nullptr;          // pinned [kMaxVerifyRows]
-  float* h_err = nullptr;          // pinned [kMaxVerifyRows]
-  uint8_t* h_acc = nullptr;        // pinned [kMaxVerifyRows]
+  uint64_t* verdict = nullptr;     // pinned [kMaxVerifyRows]: launch number << 32 | bits of the error
+  uint32_t launch = 0;             // number of the latest launch
+  std::vector<float> h_err;        // errors of the latest launch that was waited for
+  std::vector<uint8_t> h_acc;      // and, with thresholds, its verdicts
 };
 
 }  // namespace speca
@@ -102,6 +100,9 @@ void push_refs(speca_ctx* ctx, int step, const int32_t* rows, int n);
 // Forget every reference (a new trajectory).
 void clear_refs(speca_ctx* ctx);
 Error ensure_partial(speca_ctx* ctx, size_t floats);
+// Wait for the errors of the latest verification (n rows) and fill ctx->vs.h_err, h_acc (e <= tau, fp32; tau may be NULL).
+// Returns as soon as the reduction has delivered; what was enqueued behind it goes on running.
+Error wait_verdict(speca_ctx* ctx, int n, const float* tau);
 Error check_rows(const speca_ctx* ctx, const int32_t* rows, int n_rows);
 
 }  // namespace speca

@@ -11,8 +11,10 @@ struct RowLabels {
   int32_t v[kMaxRows];
 };
 
-Error launch_sinusoid(int dtype, void* emb, int n, int dim, float t, hipStream_t st);
-Error launch_cond_sum(int dtype, const float* temb, const void* y_table, const RowLabels& labels, int n, int D, void* sc, hipStream_t st);
+// emb[s][dim] of timesteps[s] (HOST), any number of steps
+Error launch_sinusoid(int dtype, void* emb, int n_steps, int dim, const float* timesteps, hipStream_t st);
+// sc[s * sc_rows + i] = silu(temb[s] + y_table[labels[i]]), s < n_steps, i < n
+Error launch_cond_sum(int dtype, const float* temb, int n_steps, const void* y_table, const RowLabels& labels, int n, int D, void* sc, int sc_rows, hipStream_t st);
 Error launch_patch_embed(int dtype, const float* x, const RowLabels& xrow, const void* Wp, const void* bp, const void* pos, float* h,
                          int n, int C, int Hh, int Ww, int p, int D, hipStream_t st);
 // y = LN(h) * (1 + scale[row]) + shift[row]; shift/scale rows are mod_stride floats apart.

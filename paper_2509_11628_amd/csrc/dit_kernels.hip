@@ -14,12 +14,17 @@ template <typename T> __device__ inline void stf(T* p, float v);
 template <> __device__ inline void stf<float>(float* p, float v) { *p = v; }
 template <> __device__ inline void stf<bf16_t>(bf16_t* p, float v) { p->bits = f32_to_bf16(v); }
 
-// emb[i][j] = cos(t w_j) for j < half, sin(t w_{j-half}) after; w_j = 10000^(-j/half)
+struct StepTimes {
+  float v[kMaxRows];
+};
+
+// emb[s][j] = cos(t_s w_j) for j < half, sin(t_s w_{j-half}) after; w_j = 10000^(-j/half)
 template <typename T>
-__global__ void sinusoid_kernel(T* __restrict__ emb, int n, int dim, float t) {
+__global__ void sinusoid_kernel(T* __restrict__ emb, int n, int dim, StepTimes times) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= n * dim) return;
-  const int j = idx % dim;
+  const int s = idx / dim, j = idx - s * dim;
+  const float t = times.v[s];
   const int half = dim / 2;
   const int jj = j < half ? j : j - half;
   // fp64 here: the angle reaches ~1e3 rad, where an fp32 frequency would cost 1e-4 of absolute accuracy
@@ -28,15 +33,15 @@ __global__ void sinusoid_kernel(T* __restrict__ emb, int n, int dim, float t) {
   stf(emb + idx, static_cast<float>(j < half ? cos(a) : sin(a)));
 }
 
-// c = temb + y_table[label];  sc = silu(c) in the model dtype (input of the modulation GEMMs)
+// c = temb + y_table[label];  sc = silu(c) in the model dtype (input of the modulation GEMMs); blockIdx.y = step
 template <typename T>
 __global__ void cond_sum_kernel(const float* __restrict__ temb, const T* __restrict__ y_table, RowLabels labels, int n, int D,
-                                T* __restrict__ sc) {
+                                T* __restrict__ sc, int sc_rows) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= n * D) return;
-  const int i = idx / D, d = idx - i * D;
-  const float c = temb[idx] + ldf(y_table + static_cast<int64_t>(labels.v[i]) * D + d);
-  stf(sc + idx, c / (1.0f + expf(-c)));
+  const int i = idx / D, d = idx - i * D, s = blockIdx.y;
+  const float c = temb[static_cast<int64_t>(s) * D + d] + ldf(y_table + static_cast<int64_t>(labels.v[i]) * D + d);
+  stf(sc + static_cast<int64_t>(s) * sc_rows * D + idx, c / (1.0f + expf(-c)));
 }
 
 // h[i][t][d] = sum_k patch(x_row)[t][k] Wp[d][k] + bp[d] + pos[t][d];  k = (c, pi, pj).
@@ -286,19 +291,27 @@ inline unsigned blocks_for(int64_t n, int per) { return static_cast<unsigned>((n
 
 }  // namespace
 
-Error launch_sinusoid(int dtype, void* emb, int n, int dim, float t, hipStream_t st) {
+Error launch_sinusoid(int dtype, void* emb, int n_steps, int dim, const float* timesteps, hipStream_t st) {
   if (dim % 2) SPECA_FAIL(SPECA_EINVAL, "freq_dim must be even");
-  if (dtype == SPECA_BF16) sinusoid_kernel<bf16_t><<<blocks_for(static_cast<int64_t>(n) * dim, 256), 256, 0, st>>>(static_cast<bf16_t*>(emb), n, dim, t);
-  else sinusoid_kernel<float><<<blocks_for(static_cast<int64_t>(n) * dim, 256), 256, 0, st>>>(static_cast<float*>(emb), n, dim, t);
-  SPECA_HIP(hipGetLastError());
+  for (int s0 = 0; s0 < n_steps; s0 += kMaxRows) {
+    const int n = n_steps - s0 < kMaxRows ? n_steps - s0 : kMaxRows;
+    StepTimes t{};
+    for (int i = 0; i < n; ++i) t.v[i] = timesteps[s0 + i];
+    const unsigned grid = blocks_for(static_cast<int64_t>(n) * dim, 256);
+    if (dtype == SPECA_BF16) sinusoid_kernel<bf16_t><<<grid, 256, 0, st>>>(static_cast<bf16_t*>(emb) + static_cast<int64_t>(s0) * dim, n, dim, t);
+    else sinusoid_kernel<float><<<grid, 256, 0, st>>>(static_cast<float*>(emb) + static_cast<int64_t>(s0) * dim, n, dim, t);
+    SPECA_HIP(hipGetLastError());
+  }
   return ok();
 }
 
-Error launch_cond_sum(int dtype, const float* temb, const void* y_table, const RowLabels& labels, int n, int D, void* sc, hipStream_t st) {
+Error launch_cond_sum(int dtype, const float* temb, int n_steps, const void* y_table, const RowLabels& labels, int n, int D, void* sc, int sc_rows, hipStream_t st) {
+  if (n_steps < 1 || n_steps > 65535 || n > kMaxRows) SPECA_FAIL(SPECA_EINVAL, "conditioning of %d steps, %d rows", n_steps, n);
+  const dim3 grid(blocks_for(static_cast<int64_t>(n) * D, 256), n_steps);
   if (dtype == SPECA_BF16)
-    cond_sum_kernel<bf16_t><<<blocks_for(static_cast<int64_t>(n) * D, 256), 256, 0, st>>>(temb, static_cast<const bf16_t*>(y_table), labels, n, D, static_cast<bf16_t*>(sc));
+    cond_sum_kernel<bf16_t><<<grid, 256, 0, st>>>(temb, static_cast<const bf16_t*>(y_table), labels, n, D, static_cast<bf16_t*>(sc), sc_rows);
   else
-    cond_sum_kernel<float><<<blocks_for(static_cast<int64_t>(n) * D, 256), 256, 0, st>>>(temb, static_cast<const float*>(y_table), labels, n, D, static_cast<float*>(sc));
+    cond_sum_kernel<float><<<grid, 256, 0, st>>>(temb, static_cast<const float*>(y_table), labels, n, D, static_cast<float*>(sc), sc_rows);
   SPECA_HIP(hipGetLastError());
   return ok();
 }

@@ -43,17 +43,20 @@ struct DiT final : Model {
   int32_t* gate_off_dev = nullptr;   // [2L][2] offset of each slot's gate inside a modulation row
   // trajectory-level modulation [S][batch_rows][mod_n] (see begin_trajectory)
   float* traj_mod = nullptr;
-  void* traj_sc = nullptr;
-  size_t traj_cap = 0;
+  void *traj_sc = nullptr, *traj_emb = nullptr, *traj_hid = nullptr;
+  float* traj_temb = nullptr;
+  size_t traj_cap = 0;               // rows x steps of traj_mod, traj_sc
+  int traj_steps_cap = 0;            // steps of traj_emb, traj_hid, traj_temb
   int traj_S = 0, traj_rows = 0;
   bool traj_on = false;
   // workspace for up to cap_rows rows
   int cap_rows = 0;
   void *emb = nullptr, *t_hid = nullptr, *sc = nullptr, *xn = nullptr, *qkv = nullptr, *att = nullptr, *f1 = nullptr;
+  const float* modp = nullptr;       // modulation of the current launch's compact rows: mod, or their rows of traj_mod
   float *temb = nullptr, *mod = nullptr, *h = nullptr, *h2 = nullptr, *feat = nullptr, *tok = nullptr;
 
   ~DiT() override {
-    for (void* p : {mod_w, mod_b, static_cast<void*>(gate_off_dev), static_cast<void*>(traj_mod), traj_sc})
+    for (void* p : {mod_w, mod_b, static_cast<void*>(gate_off_dev), static_cast<void*>(traj_mod), traj_sc, traj_emb, traj_hid, static_cast<void*>(traj_temb)})
       if (p) (void)hipFree(p);
     free_ws();
   }
@@ -94,64 +97,81 @@ struct DiT final : Model {
     return ok();
   }
 
-  // SiLU(c) of compact rows 0..n-1 (labels of rows[i]) at timestep t, into sc_out [n][D]
-  Error cond_vector(hipStream_t st, float t, const int32_t* labels_per_row, const int32_t* rows, int n, void* sc_out) {
-    RowLabels lab{};
-    for (int i = 0; i < n; ++i) lab.v[i] = labels_per_row[rows[i]];
-    SPECA_TRY(launch_sinusoid(d.dtype, emb, n, d.freq_dim, t, st));
+  // Timestep MLP of n_steps timesteps: temb_out[s] (fp32).  The rows of a launch share it.
+  Error time_vectors(hipStream_t st, const float* timesteps, int n_steps, void* emb_buf, void* hid_buf, float* temb_out) {
+    SPECA_TRY(launch_sinusoid(d.dtype, emb_buf, n_steps, d.freq_dim, timesteps, st));
     GemmEpi e1;
-    e1.mode = EPI_SILU; e1.bias = t_b1; e1.out = t_hid; e1.ldo = D;
-    SPECA_TRY(launch_gemm(d.dtype, emb, d.freq_dim, t_w1, d.freq_dim, n, D, d.freq_dim, e1, st));
+    e1.mode = EPI_SILU; e1.bias = t_b1; e1.out = hid_buf; e1.ldo = D;
+    SPECA_TRY(launch_gemm(d.dtype, emb_buf, d.freq_dim, t_w1, d.freq_dim, n_steps, D, d.freq_dim, e1, st));
     GemmEpi e2;
-    e2.mode = EPI_F32; e2.bias = t_b2; e2.out = temb; e2.ldo = D;
-    SPECA_TRY(launch_gemm(d.dtype, t_hid, D, t_w2, D, n, D, D, e2, st));
-    return launch_cond_sum(d.dtype, temb, y_table, lab, n, D, sc_out, st);
+    e2.mode = EPI_F32; e2.bias = t_b2; e2.out = temb_out; e2.ldo = D;
+    return launch_gemm(d.dtype, hid_buf, D, t_w2, D, n_steps, D, D, e2, st);
   }
 
-  // conditioning + modulation of all blocks for compact rows 0..n-1 at sampling step `step`
+  // modulation of all blocks for compact rows 0..n-1 at sampling step `step`, at modp
   Error conditioning(speca_ctx* ctx, float t, const int32_t* labels_per_row, int step, const int32_t* rows, int n) {
     hipStream_t st = ctx->stream;
     if (traj_on && step >= 0 && step < traj_S) {
-      // inside a trajectory the modulation of this step was computed up front: pick the rows
+      // inside a trajectory the modulation of every step was computed up front: neighbouring rows are used where they lie
+      const float* here = traj_mod + static_cast<int64_t>(step) * traj_rows * mod_n;
+      if (rows[n - 1] - rows[0] == n - 1) {
+        modp = here + static_cast<int64_t>(rows[0]) * mod_n;
+        return ok();
+      }
       ProfScope ps(ctx, SPECA_PROF_OTHER, 0.0, 2.0 * n * mod_n * 4);
       RowLabels idx{};
       for (int i = 0; i < n; ++i) idx.v[i] = rows[i];
-      return launch_gather_rows(SPECA_F32, traj_mod + static_cast<int64_t>(step) * traj_rows * mod_n, idx, mod, n, mod_n, st);
+      modp = mod;
+      return launch_gather_rows(SPECA_F32, here, idx, mod, n, mod_n, st);
     }
+    modp = mod;
     ProfScope ps(ctx, SPECA_PROF_OTHER, 2.0 * n * D * (d.freq_dim + D + static_cast<double>(mod_n)), static_cast<double>(mod_n) * D * esz);
-    SPECA_TRY(cond_vector(st, t, labels_per_row, rows, n, sc));
+    SPECA_TRY(time_vectors(st, &t, 1, emb, t_hid, temb));
+    RowLabels lab{};
+    for (int i = 0; i < n; ++i) lab.v[i] = labels_per_row[rows[i]];
+    SPECA_TRY(launch_cond_sum(d.dtype, temb, 1, y_table, lab, n, D, sc, n, st));
     GemmEpi e3;
     e3.mode = EPI_F32; e3.bias = mod_b; e3.out = mod; e3.ldo = mod_n;
     SPECA_TRY(launch_gemm(d.dtype, sc, D, mod_w, D, n, static_cast<int>(mod_n), D, e3, st));
     return ok();
   }
 
+  void free_traj() {
+    for (void* p : {static_cast<void*>(traj_mod), traj_sc, traj_emb, traj_hid, static_cast<void*>(traj_temb)})
+      if (p) (void)hipFree(p);
+    traj_mod = traj_temb = nullptr;
+    traj_sc = traj_emb = traj_hid = nullptr;
+    traj_cap = 0;
+    traj_steps_cap = 0;
+  }
+
+  // All steps and rows at once: four launches and one large GEMM per trajectory instead of five launches per step.
   Error begin_trajectory(speca_ctx* ctx, const speca_cond*, const int32_t* labels_per_row, const float* timesteps, int S) override {
     hipStream_t st = ctx->stream;
     const int R = ctx->batch_rows;
     const size_t total = static_cast<size_t>(S) * R;
-    if (total * mod_n * 4 > (static_cast<size_t>(8) << 30)) return ok();      // too large to be worth holding: per-step path
-    if (total > traj_cap) {
+    if (total * mod_n * 4 > (static_cast<size_t>(8) << 30) || S > 65535) return ok();   // too large to be worth holding: per-step path
+    if (total > traj_cap || S > traj_steps_cap) {
       SPECA_HIP(hipStreamSynchronize(st));
-      if (traj_mod) (void)hipFree(traj_mod);
-      if (traj_sc) (void)hipFree(traj_sc);
-      traj_mod = nullptr; traj_sc = nullptr; traj_cap = 0;
-      if (hipMalloc(reinterpret_cast<void**>(&traj_mod), total * mod_n * 4) != hipSuccess || hipMalloc(&traj_sc, total * D * esz) != hipSuccess) {
+      free_traj();
+      auto alloc = [](auto** p, size_t bytes) { return hipMalloc(reinterpret_cast<void**>(p), bytes) == hipSuccess; };
+      if (!alloc(&traj_mod, total * mod_n * 4) || !alloc(&traj_sc, total * D * esz) || !alloc(&traj_emb, static_cast<size_t>(S) * d.freq_dim * esz) ||
+          !alloc(&traj_hid, static_cast<size_t>(S) * D * esz) || !alloc(&traj_temb, static_cast<size_t>(S) * D * 4)) {
         (void)hipGetLastError();
-        if (traj_mod) (void)hipFree(traj_mod);
-        traj_mod = nullptr;
+        free_traj();
         return ok();                                                          // no room: per-step path
       }
       traj_cap = total;
+      traj_steps_cap = S;
     }
     ProfScope ps(ctx, SPECA_PROF_OTHER, 2.0 * total * D * static_cast<double>(mod_n), static_cast<double>(mod_n) * D * esz + total * mod_n * 4.0);
-    std::vector<int32_t> rows(cap_rows);
-    for (int s = 0; s < S; ++s)
-      for (int r0 = 0; r0 < R; r0 += cap_rows) {
-        const int n = std::min(cap_rows, R - r0);
-        for (int i = 0; i < n; ++i) rows[i] = r0 + i;
-        SPECA_TRY(cond_vector(st, timesteps[s], labels_per_row, rows.data(), n, static_cast<char*>(traj_sc) + (static_cast<size_t>(s) * R + r0) * D * esz));
-      }
+    SPECA_TRY(time_vectors(st, timesteps, S, traj_emb, traj_hid, traj_temb));
+    for (int r0 = 0; r0 < R; r0 += kMaxRows) {
+      const int n = std::min(kMaxRows, R - r0);
+      RowLabels lab{};
+      for (int i = 0; i < n; ++i) lab.v[i] = labels_per_row[r0 + i];
+      SPECA_TRY(launch_cond_sum(d.dtype, traj_temb, S, y_table, lab, n, D, static_cast<char*>(traj_sc) + static_cast<size_t>(r0) * D * esz, R, st));
+    }
     GemmEpi e;
     e.mode = EPI_F32; e.bias = mod_b; e.out = traj_mod; e.ldo = mod_n;
     SPECA_TRY(launch_gemm(d.dtype, traj_sc, D, mod_w, D, static_cast<int>(total), static_cast<int>(mod_n), D, e, st));
@@ -175,7 +195,7 @@ struct DiT final : Model {
     int shared = 0;     // lanes that run side by side (0: this one alone)
   };
   const float* mod_at(int l, int which, int o = 0) const {
-    return mod + static_cast<int64_t>(o) * mod_n + static_cast<int64_t>(l) * 6 * D + static_cast<int64_t>(which) * D;
+    return modp + static_cast<int64_t>(o) * mod_n + static_cast<int64_t>(l) * 6 * D + static_cast<int64_t>(which) * D;
   }
   template <typename P> P* at(P* base, const Lane& ln, int64_t per_row_bytes) const {
     return reinterpret_cast<P*>(reinterpret_cast<char*>(base) + static_cast<int64_t>(ln.o) * per_row_bytes);
@@ -291,7 +311,7 @@ struct DiT final : Model {
   Error final_layer(speca_ctx* ctx, const float* hs, const int32_t* rows, int n, float* model_out) {
     hipStream_t st = ctx->stream;
     const int64_t M = static_cast<int64_t>(n) * T;
-    const float* fm = mod + static_cast<int64_t>(L) * 6 * D;
+    const float* fm = modp + static_cast<int64_t>(L) * 6 * D;
     ProfScope ps(ctx, SPECA_PROF_OTHER, 2.0 * M * Kp * D, static_cast<double>(M) * D * (4 + 2 * esz));
     SPECA_TRY(launch_ln_modulate(d.dtype, hs, fm, fm + D, mod_n, xn, M, T, D, st));
     GemmEpi e;
@@ -344,32 +364,28 @@ struct DiT final : Model {
     // block does not wait for the whole cache.
     if (4 * lv >= 3 * L) {
       ProfScope ps(ctx, SPECA_PROF_FORECAST, 0.0, 2.0 * L * tens * Ed * esz + 3.0 * n * Ed * 4);
-      SPECA_TRY(launch_forecast_fold2(ctx->geom, rt, h, h, 2 * lv, h2, mod, mod_n, gate_off_dev, 0, 0, 2 * L, D, st));
+      SPECA_TRY(launch_forecast_fold2(ctx->geom, rt, h, h, 2 * lv, h2, modp, mod_n, gate_off_dev, 0, 0, 2 * L, D, st));
     } else {
       {
         ProfScope ps(ctx, SPECA_PROF_FORECAST, 0.0, 2.0 * lv * tens * Ed * esz + 2.0 * n * Ed * 4);
-        SPECA_TRY(launch_forecast_fold(ctx->geom, rt, h, h, mod, mod_n, gate_off_dev, 0, 0, 2 * lv, D, st));
+        SPECA_TRY(launch_forecast_fold(ctx->geom, rt, h, h, modp, mod_n, gate_off_dev, 0, 0, 2 * lv, D, st));
       }
       ProfScope ps(ctx, SPECA_PROF_FORECAST, 0.0, 2.0 * (L - lv) * tens * Ed * esz + 2.0 * n * Ed * 4);
-      SPECA_TRY(launch_forecast_fold(ctx->geom, rt, h, h2, mod, mod_n, gate_off_dev, 0, 2 * lv, 2 * L, D, st));
+      SPECA_TRY(launch_forecast_fold(ctx->geom, rt, h, h2, modp, mod_n, gate_off_dev, 0, 2 * lv, 2 * L, D, st));
     }
     // the verify block for real, on h
     SPECA_TRY(run_blocks(ctx, lv, lv + 1, h, n, nullptr, feat));
     // Eq. 4: forecast of slot 2lv+1 (formed on the fly from the cache) vs the recomputed feature
     VerifyScratch& v = ctx->vs;
     SPECA_TRY(ensure_partial(ctx, static_cast<size_t>(n) * verify_chunks(ctx->geom.E) * 3));
-    std::memcpy(v.h_tau, tau_per_row, n * sizeof(float));
-    SPECA_HIP(hipMemcpyAsync(v.tau_dev, v.h_tau, n * sizeof(float), hipMemcpyHostToDevice, st));
     {
       ProfScope ps(ctx, SPECA_PROF_VERIFY, 0.0, tens * Ed * esz + n * Ed * 4);
       SPECA_TRY(launch_verify(ctx->cfg.metric, nullptr, ctx->geom.dtype, feat, SPECA_F32, ctx->geom.E, &ctx->geom, &rt, 2 * lv + 1, n,
-                              ctx->cfg.eps, v.tau_dev, v.partial, v.err_dev, v.acc_dev, st));
+                              ctx->cfg.eps, v.partial, {nullptr, nullptr, nullptr, v.verdict, ++v.launch}, st));
     }
-    SPECA_HIP(hipMemcpyAsync(v.h_err, v.err_dev, n * sizeof(float), hipMemcpyDeviceToHost, st));
-    SPECA_HIP(hipMemcpyAsync(v.h_acc, v.acc_dev, n, hipMemcpyDeviceToHost, st));
     // finish every listed row from h2 while the verdict travels; rejected rows are overwritten by the fallback
     SPECA_TRY(final_layer(ctx, h2, rows, n, model_out));
-    SPECA_HIP(hipStreamSynchronize(st));
+    SPECA_TRY(wait_verdict(ctx, n, tau_per_row));
     if (pair_stride > 0) {
       std::vector<uint8_t> both(n);
       for (int i = 0; i < n; ++i) both[i] = v.h_acc[i] && v.h_acc[partner[i]];

@@ -68,11 +68,11 @@ __device__ inline void ld4_stream(const float* p, float* v) {
 }
 
 template <typename T, int MODE>
-__device__ inline void epilogue_apply(const GemmEpi& e, int m, int n, float v[4]);
+__device__ inline void epilogue_apply(const EpiArg<MODE>& e, int m, int n, float v[4]);
 
 // T = model / cache storage type.  MODE is a compile-time EpiMode.
 template <typename T, int MODE>
-__device__ inline void epilogue_quad(const GemmEpi& e, int m, int n, float v[4]) {
+__device__ inline void epilogue_quad(const EpiArg<MODE>& e, int m, int n, float v[4]) {
   if (e.bias) {
     float b[4];
     Store4<T>::ld(static_cast<const T*>(e.bias) + n, b);
@@ -84,15 +84,15 @@ __device__ inline void epilogue_quad(const GemmEpi& e, int m, int n, float v[4])
 
 // The epilogue after the bias has been added.
 template <typename T, int MODE>
-__device__ inline void epilogue_apply(const GemmEpi& e, int m, int n, float v[4]) {
-  if (MODE == EPI_STORE || MODE == EPI_GELU || MODE == EPI_SILU) {
+__device__ inline void epilogue_apply(const EpiArg<MODE>& e, int m, int n, float v[4]) {
+  if constexpr (MODE == EPI_STORE || MODE == EPI_GELU || MODE == EPI_SILU) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       if (MODE == EPI_GELU) v[i] = gelu_tanh_f(v[i]);
       if (MODE == EPI_SILU) v[i] = silu_f(v[i]);
     }
     Store4<T>::st(static_cast<T*>(e.out) + static_cast<int64_t>(m) * e.ldo + n, v);
-  } else if (MODE == EPI_F32) {
+  } else if constexpr (MODE == EPI_F32) {
     Store4<float>::st(static_cast<float*>(e.out) + static_cast<int64_t>(m) * e.ldo + n, v);
   } else {   // EPI_BRANCH
     const int i = m / e.tokens;

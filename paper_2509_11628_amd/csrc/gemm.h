@@ -4,6 +4,8 @@
 // contractions of reference steps) and a plain fp32-FMA tile kernel for fp32 models.
 #pragma once
 
+#include <type_traits>
+
 #include "common.h"
 
 namespace speca {
@@ -36,6 +38,19 @@ struct GemmEpi {
   CacheGeom g{};
   RowTable rt{};
 };
+
+// What a kernel is given of it: only the branch epilogue needs the cache geometry and the row table (1.9 KB of arguments
+// that every other launch would copy and carry for nothing).
+struct EpiPlain {
+  const void* bias;
+  void* out;
+  int64_t ldo;
+};
+template <int MODE> using EpiArg = std::conditional_t<MODE == EPI_BRANCH, GemmEpi, EpiPlain>;
+template <int MODE> inline EpiArg<MODE> epi_arg(const GemmEpi& e) {
+  if constexpr (MODE == EPI_BRANCH) return e;
+  else return {e.bias, e.out, e.ldo};
+}
 
 // M may be ragged; N % 4 == 0 and K % 8 == 0 are required (checked).
 Error launch_gemm(int dtype, const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi,

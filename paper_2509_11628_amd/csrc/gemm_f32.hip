@@ -30,7 +30,7 @@ __device__ __forceinline__ floatx4 mfma4(float a, float b, floatx4 c) { return _
 // KTAIL: K is no multiple of 16.
 template <int TM, int TN, int PF, int MODE, bool KTAIL>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int64_t lda, const float* __restrict__ W, int64_t ldw, int M, int N,
-                                                       int K, GemmEpi epi) {
+                                                       int K, EpiArg<MODE> epi) {
   constexpr int BM = 16 * TM, BN = 16 * TN;
   constexpr int CST = BN + 4;                     // floats per staged row
   __shared__ __align__(16) float part[4][BM * CST];
@@ -120,8 +120,8 @@ Error launch_f32_tile(const float* A, int64_t lda, const float* W, int64_t ldw, 
   const dim3 grid((N + 16 * TN - 1) / (16 * TN), (M + 16 * TM - 1) / (16 * TM));
 #define SPECA_LAUNCH(MODE_)                                                                                                  \
   {                                                                                                                          \
-    if (K % 16) gemm_f32_kernel<TM, TN, PF, MODE_, true><<<grid, 256, 0, st>>>(A, lda, W, ldw, M, N, K, epi);                \
-    else gemm_f32_kernel<TM, TN, PF, MODE_, false><<<grid, 256, 0, st>>>(A, lda, W, ldw, M, N, K, epi);                      \
+    if (K % 16) gemm_f32_kernel<TM, TN, PF, MODE_, true><<<grid, 256, 0, st>>>(A, lda, W, ldw, M, N, K, epi_arg<MODE_>(epi)); \
+    else gemm_f32_kernel<TM, TN, PF, MODE_, false><<<grid, 256, 0, st>>>(A, lda, W, ldw, M, N, K, epi_arg<MODE_>(epi));        \
   }
   switch (epi.mode) {
     case EPI_STORE: SPECA_LAUNCH(EPI_STORE) break;

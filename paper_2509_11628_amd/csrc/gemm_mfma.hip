@@ -77,7 +77,7 @@ __device__ __forceinline__ bool tile_coords(int tiles_m, int tiles_n, int group_
 // buffers it overlays must be dead (all waves past their last read, no load in flight).
 template <int BM, int BN, int WGM, int WGN, int MODE, int EH>
 __device__ __forceinline__ void tile_epilogue(floatx16 (&acc)[BN / WGN / 32][BM / WGM / 32], float* Cs, int m0, int n0, int M, int N,
-                                              const GemmEpi& epi) {
+                                              const EpiArg<MODE>& epi) {
   constexpr int NT = WGM * WGN * 64;
   constexpr int WM = BM / WGM, WN = BN / WGN;
   constexpr int TM = WM / 32, TN = WN / 32;
@@ -100,7 +100,7 @@ __device__ __forceinline__ void tile_epilogue(floatx16 (&acc)[BN / WGN / 32][BM 
   int i_first = 0;
   bool uniform = false;
   BranchRow<bf16_t> br;
-  if (MODE == EPI_BRANCH) {
+  if constexpr (MODE == EPI_BRANCH) {
     i_first = m0 / epi.tokens;
     uniform = i_first == m_last / epi.tokens;
     if (uniform) br = branch_row<bf16_t>(epi, i_first, m0);
@@ -123,7 +123,7 @@ __device__ __forceinline__ void tile_epilogue(floatx16 (&acc)[BN / WGN / 32][BM 
     __syncthreads();
     if (!live) continue;
     const int mh = m0 + h * EH;                      // first global row of this part
-    if (MODE == EPI_BRANCH) {
+    if constexpr (MODE == EPI_BRANCH) {
       // batches of EB rows: all loads of the batch are issued before its first store
       // (fewer when the accumulators of a later part are still live: 128 registers for a 64x128 wave tile)
       constexpr int EBMAX = (BM / EH > 1) ? 1 : 4;
@@ -190,7 +190,7 @@ __device__ __forceinline__ void tile_epilogue(floatx16 (&acc)[BN / WGN / 32][BM 
 template <int BM, int BN, int WGM, int WGN, int MODE, bool KTAIL, bool SF>
 __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const uint16_t* __restrict__ A, int64_t lda,
                                                                    const uint16_t* __restrict__ W, int64_t ldw, int M, int N, int K,
-                                                                   int tiles_m, int tiles_n, int group_m, GemmEpi epi) {
+                                                                   int tiles_m, int tiles_n, int group_m, EpiArg<MODE> epi) {
   constexpr int NT = WGM * WGN * 64;
   constexpr int WM = BM / WGM, WN = BN / WGN;      // wave tile
   constexpr int TM = WM / 32, TN = WN / 32;        // MFMA tiles per wave
@@ -351,7 +351,7 @@ constexpr int dlds_epilogue_rows(int BM, int BN, int NS) {
 template <int BM, int BN, int WGM, int WGN, int NS, int MODE>
 __global__ __launch_bounds__(WGM* WGN * 64) void gemm_dlds_kernel(const uint16_t* __restrict__ A, int64_t lda,
                                                                    const uint16_t* __restrict__ W, int64_t ldw, int M, int N, int K,
-                                                                   int tiles_m, int tiles_n, int group_m, GemmEpi epi) {
+                                                                   int tiles_m, int tiles_n, int group_m, EpiArg<MODE> epi) {
   constexpr int NW = WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN;
   constexpr int TM = WM / 32, TN = WN / 32;
@@ -634,7 +634,7 @@ Error launch_dlds(const void* A, int64_t lda, const void* W, int64_t ldw, int M,
       SPECA_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem))); \
       attr_set = true;                                                                                            \
     }                                                                                                             \
-    kern<<<grid, WGM * WGN * 64, smem, st>>>(a, lda, w, ldw, M, N, K, tiles_m, tiles_n, group_m, epi);             \
+    kern<<<grid, WGM * WGN * 64, smem, st>>>(a, lda, w, ldw, M, N, K, tiles_m, tiles_n, group_m, epi_arg<MODE_>(epi)); \
   }
   switch (epi.mode) {
     case EPI_STORE: SPECA_LAUNCH(EPI_STORE) break;
@@ -671,7 +671,7 @@ Error launch_tile(const void* A, int64_t lda, const void* W, int64_t ldw, int M,
       SPECA_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem))); \
       attr_set = true;                                                                                           \
     }                                                                                                            \
-    kern<<<grid, WGM * WGN * 64, smem, st>>>(a, lda, w, ldw, M, N, K, tiles_m, tiles_n, group_m, epi);            \
+    kern<<<grid, WGM * WGN * 64, smem, st>>>(a, lda, w, ldw, M, N, K, tiles_m, tiles_n, group_m, epi_arg<MODE_>(epi)); \
   }
 #define SPECA_LAUNCH(MODE_)                       \
   {                                               \

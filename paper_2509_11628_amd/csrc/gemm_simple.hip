@@ -18,7 +18,7 @@ constexpr int TM = 64, TN = 64, TK = 16;
 
 template <typename T, int MODE>
 __global__ __launch_bounds__(256) void gemm_simple_kernel(const T* __restrict__ A, int64_t lda, const T* __restrict__ W, int64_t ldw,
-                                                          int M, int N, int K, GemmEpi epi) {
+                                                          int M, int N, int K, EpiArg<MODE> epi) {
   __shared__ float As[TK][TM + 4];
   __shared__ float Ws[TK][TN + 4];
   const int tid = threadIdx.x;
@@ -75,11 +75,11 @@ Error launch_simple_t(const void* A, int64_t lda, const void* W, int64_t ldw, in
   const T* a = static_cast<const T*>(A);
   const T* w = static_cast<const T*>(W);
   switch (epi.mode) {
-    case EPI_STORE: gemm_simple_kernel<T, EPI_STORE><<<grid, 256, 0, st>>>(a, lda, w, ldw, M, N, K, epi); break;
-    case EPI_GELU: gemm_simple_kernel<T, EPI_GELU><<<grid, 256, 0, st>>>(a, lda, w, ldw, M, N, K, epi); break;
-    case EPI_SILU: gemm_simple_kernel<T, EPI_SILU><<<grid, 256, 0, st>>>(a, lda, w, ldw, M, N, K, epi); break;
-    case EPI_F32: gemm_simple_kernel<T, EPI_F32><<<grid, 256, 0, st>>>(a, lda, w, ldw, M, N, K, epi); break;
-    case EPI_BRANCH: gemm_simple_kernel<T, EPI_BRANCH><<<grid, 256, 0, st>>>(a, lda, w, ldw, M, N, K, epi); break;
+    case EPI_STORE: gemm_simple_kernel<T, EPI_STORE><<<grid, 256, 0, st>>>(a, lda, w, ldw, M, N, K, epi_arg<EPI_STORE>(epi)); break;
+    case EPI_GELU: gemm_simple_kernel<T, EPI_GELU><<<grid, 256, 0, st>>>(a, lda, w, ldw, M, N, K, epi_arg<EPI_GELU>(epi)); break;
+    case EPI_SILU: gemm_simple_kernel<T, EPI_SILU><<<grid, 256, 0, st>>>(a, lda, w, ldw, M, N, K, epi_arg<EPI_SILU>(epi)); break;
+    case EPI_F32: gemm_simple_kernel<T, EPI_F32><<<grid, 256, 0, st>>>(a, lda, w, ldw, M, N, K, epi_arg<EPI_F32>(epi)); break;
+    case EPI_BRANCH: gemm_simple_kernel<T, EPI_BRANCH><<<grid, 256, 0, st>>>(a, lda, w, ldw, M, N, K, epi_arg<EPI_BRANCH>(epi)); break;
     default: SPECA_FAIL(SPECA_EINVAL, "gemm: epilogue mode %d", epi.mode);
   }
   SPECA_HIP(hipGetLastError());

@@ -21,8 +21,16 @@ Error launch_cache_warm(const CacheGeom& g, const RowTable& rt, int slot, hipStr
 // partial: device scratch of n_rows * verify_chunks(E) * 3 floats.
 int verify_chunks(int64_t E);
 constexpr int kMaxVerifyRows = 1024;   // rows of one launch when prediction and truth are both tensors
+// Where the errors go: device arrays (accept[r] = err[r] <= tau[r] when tau is given), or, with `verdict`, words
+// launch << 32 | bits of the error in pinned host memory.
+struct VerifyOut {
+  const float* tau;
+  float* err;
+  uint8_t* accept;
+  uint64_t* verdict;
+  uint32_t launch;
+};
 Error launch_verify(int metric, const void* pred, int pred_dtype, const void* truth, int truth_dtype, int64_t E,
-                    const CacheGeom* g, const RowTable* rt, int slot, int n_rows, float eps, const float* tau_dev,
-                    float* partial, float* err_dev, uint8_t* accept_dev, hipStream_t st);
+                    const CacheGeom* g, const RowTable* rt, int slot, int n_rows, float eps, float* partial, const VerifyOut& out, hipStream_t st);
 
 }  // namespace speca

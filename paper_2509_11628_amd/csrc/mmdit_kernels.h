@@ -13,8 +13,8 @@ namespace speca {
 Error launch_qk_norm_rope(int dtype, void* qkv, int64_t ld, int64_t n_tokens, int tokens_per_row, int split_tok, int H, int hd,
                           const void* qn1, const void* kn1, const void* qn2, const void* kn2, const float* cos_t, const float* sin_t,
                           hipStream_t st);
-// sc = silu(a + b) in the model dtype; a, b fp32 [n][D].
-Error launch_silu_sum(int dtype, const float* a, const float* b, void* sc, int64_t n, hipStream_t st);
+// sc[s * n + i] = silu(a[s] + b[i]) in the model dtype; a fp32 [n_steps][D], b fp32 [n][D].
+Error launch_silu_sum(int dtype, const float* a, int n_steps, const float* b, int n, int D, void* sc, hipStream_t st);
 // Gather rows of a [rows_all][width] matrix (model dtype): dst[i] = src[idx[i]].
 Error launch_gather_rows(int dtype, const void* src, const RowLabels& idx, void* dst, int n, int64_t width, hipStream_t st);
 // patches[i][t][(c,pi,pj)] in the model dtype from fp32 latents x[row][C][F][H][W]; token t = (f, i, j).

@@ -83,11 +83,11 @@ __global__ __launch_bounds__(256) void qk_norm_rope_kernel(T* __restrict__ qkv, 
 }
 
 template <typename T>
-__global__ void silu_sum_kernel(const float* __restrict__ a, const float* __restrict__ b, T* __restrict__ sc, int64_t n) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+__global__ void silu_sum_kernel(const float* __restrict__ a, const float* __restrict__ b, T* __restrict__ sc, int64_t n, int D) {
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;      // blockIdx.y = step
   if (i >= n) return;
-  const float c = a[i] + b[i];
-  stf(sc + i, c / (1.0f + expf(-c)));
+  const float c = a[static_cast<int64_t>(blockIdx.y) * D + i % D] + b[i];
+  stf(sc + static_cast<int64_t>(blockIdx.y) * n + i, c / (1.0f + expf(-c)));
 }
 
 template <typename T>
@@ -157,9 +157,12 @@ Error launch_qk_norm_rope(int dtype, void* qkv, int64_t ld, int64_t n_tokens, in
   return ok();
 }
 
-Error launch_silu_sum(int dtype, const float* a, const float* b, void* sc, int64_t n, hipStream_t st) {
-  if (dtype == SPECA_BF16) silu_sum_kernel<bf16_t><<<nblk(n, 256), 256, 0, st>>>(a, b, static_cast<bf16_t*>(sc), n);
-  else silu_sum_kernel<float><<<nblk(n, 256), 256, 0, st>>>(a, b, static_cast<float*>(sc), n);
+Error launch_silu_sum(int dtype, const float* a, int n_steps, const float* b, int n, int D, void* sc, hipStream_t st) {
+  if (n_steps < 1 || n_steps > 65535) SPECA_FAIL(SPECA_EINVAL, "conditioning of %d steps", n_steps);
+  const int64_t nD = static_cast<int64_t>(n) * D;
+  const dim3 grid(nblk(nD, 256), n_steps);
+  if (dtype == SPECA_BF16) silu_sum_kernel<bf16_t><<<grid, 256, 0, st>>>(a, b, static_cast<bf16_t*>(sc), nD, D);
+  else silu_sum_kernel<float><<<grid, 256, 0, st>>>(a, b, static_cast<float*>(sc), nD, D);
   SPECA_HIP(hipGetLastError());
   return ok();
 }

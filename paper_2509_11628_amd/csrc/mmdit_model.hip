@@ -49,18 +49,22 @@ struct MMDiT final : Model {
   int32_t* gate_off_dev = nullptr;    // [n_slots][2]
   std::vector<int> first_slot;        // per block, plus end
   float* traj_mod = nullptr;          // [S][batch_rows][mod_n], see begin_trajectory
-  void* traj_sc = nullptr;
-  size_t traj_cap = 0;
+  void *traj_sc = nullptr, *traj_emb = nullptr, *traj_hid = nullptr, *traj_vhid = nullptr;
+  float *traj_temb = nullptr, *traj_vemb = nullptr;
+  size_t traj_cap = 0;                // rows x steps of traj_mod, traj_sc
+  int traj_steps_cap = 0, traj_rows_cap = 0;
   int traj_S = 0, traj_rows = 0;
   bool traj_on = false;
   int cap_rows = 0;
   void *emb = nullptr, *t_hid = nullptr, *v_in = nullptr, *v_hid = nullptr, *sc = nullptr, *patches = nullptr, *xn = nullptr, *qkv = nullptr,
        *att = nullptr, *f1 = nullptr, *cat = nullptr;
+  const float* modp = nullptr;        // modulation of the current launch's compact rows: mod, or their rows of traj_mod
   float *temb = nullptr, *vemb = nullptr, *mod = nullptr, *h = nullptr, *h2 = nullptr, *feat = nullptr, *tok = nullptr;
 
   ~MMDiT() override {
-    for (void* p : {mod_w, mod_b, static_cast<void*>(gate_off_dev), static_cast<void*>(traj_mod), traj_sc})
+    for (void* p : {mod_w, mod_b, static_cast<void*>(gate_off_dev)})
       if (p) (void)hipFree(p);
+    free_traj();
     free_ws();
   }
   void free_ws() {
@@ -104,67 +108,89 @@ struct MMDiT final : Model {
     return launch_gemm(d.dtype, A, lda, W, ldw, static_cast<int>(M), N, K, e, ctx->stream);
   }
 
-  // SiLU(vec) of compact rows 0..n-1 at timestep t, into sc_out [n][D]
-  Error cond_vector(speca_ctx* ctx, float t, const speca_cond* cond, const int32_t* rows, int n, void* sc_out) {
-    hipStream_t st = ctx->stream;
-    if (!cond->pooled) SPECA_FAIL(SPECA_EINVAL, "cond->pooled is NULL");
-    SPECA_TRY(launch_sinusoid(d.dtype, emb, n, d.freq_dim, t, st));
+  // Timestep MLP of n_steps timesteps: temb_out[s] (fp32).  The rows of a launch share it.
+  Error time_vectors(hipStream_t st, const float* timesteps, int n_steps, void* emb_buf, void* hid_buf, float* temb_out) {
+    SPECA_TRY(launch_sinusoid(d.dtype, emb_buf, n_steps, d.freq_dim, timesteps, st));
     GemmEpi e;
-    e.mode = EPI_SILU; e.bias = t_b1; e.out = t_hid; e.ldo = D;
-    SPECA_TRY(launch_gemm(d.dtype, emb, d.freq_dim, t_w1, d.freq_dim, n, D, d.freq_dim, e, st));
-    e = GemmEpi(); e.mode = EPI_F32; e.bias = t_b2; e.out = temb; e.ldo = D;
-    SPECA_TRY(launch_gemm(d.dtype, t_hid, D, t_w2, D, n, D, D, e, st));
-    RowLabels idx{};
-    for (int i = 0; i < n; ++i) idx.v[i] = rows[i];
-    SPECA_TRY(launch_gather_rows(d.dtype, cond->pooled, idx, v_in, n, d.vec_dim, st));
-    e = GemmEpi(); e.mode = EPI_SILU; e.bias = v_b1; e.out = v_hid; e.ldo = D;
-    SPECA_TRY(launch_gemm(d.dtype, v_in, d.vec_dim, v_w1, d.vec_dim, n, D, d.vec_dim, e, st));
-    e = GemmEpi(); e.mode = EPI_F32; e.bias = v_b2; e.out = vemb; e.ldo = D;
-    SPECA_TRY(launch_gemm(d.dtype, v_hid, D, v_w2, D, n, D, D, e, st));
-    return launch_silu_sum(d.dtype, temb, vemb, sc_out, static_cast<int64_t>(n) * D, st);
+    e.mode = EPI_SILU; e.bias = t_b1; e.out = hid_buf; e.ldo = D;
+    SPECA_TRY(launch_gemm(d.dtype, emb_buf, d.freq_dim, t_w1, d.freq_dim, n_steps, D, d.freq_dim, e, st));
+    e = GemmEpi(); e.mode = EPI_F32; e.bias = t_b2; e.out = temb_out; e.ldo = D;
+    return launch_gemm(d.dtype, hid_buf, D, t_w2, D, n_steps, D, D, e, st);
+  }
+  // MLP of the pooled text vectors in[n][vec_dim]: vemb_out[i] (fp32)
+  Error pooled_vectors(hipStream_t st, const void* in, int n, void* hid_buf, float* vemb_out) {
+    GemmEpi e;
+    e.mode = EPI_SILU; e.bias = v_b1; e.out = hid_buf; e.ldo = D;
+    SPECA_TRY(launch_gemm(d.dtype, in, d.vec_dim, v_w1, d.vec_dim, n, D, d.vec_dim, e, st));
+    e = GemmEpi(); e.mode = EPI_F32; e.bias = v_b2; e.out = vemb_out; e.ldo = D;
+    return launch_gemm(d.dtype, hid_buf, D, v_w2, D, n, D, D, e, st);
   }
 
+  // modulation of all blocks for compact rows 0..n-1 at sampling step `step`, at modp
   Error conditioning(speca_ctx* ctx, const speca_cond* cond, int step, const int32_t* rows, int n) {
     hipStream_t st = ctx->stream;
     if (traj_on && step >= 0 && step < traj_S) {
+      const float* here = traj_mod + static_cast<int64_t>(step) * traj_rows * mod_n;
+      if (rows[n - 1] - rows[0] == n - 1) {                       // neighbouring rows are used where they lie
+        modp = here + static_cast<int64_t>(rows[0]) * mod_n;
+        return ok();
+      }
       ProfScope ps(ctx, SPECA_PROF_OTHER, 0.0, 2.0 * n * mod_n * 4);
       RowLabels idx{};
       for (int i = 0; i < n; ++i) idx.v[i] = rows[i];
-      return launch_gather_rows(SPECA_F32, traj_mod + static_cast<int64_t>(step) * traj_rows * mod_n, idx, mod, n, mod_n, st);
+      modp = mod;
+      return launch_gather_rows(SPECA_F32, here, idx, mod, n, mod_n, st);
     }
+    modp = mod;
     ProfScope ps(ctx, SPECA_PROF_OTHER, 2.0 * n * D * static_cast<double>(mod_n), static_cast<double>(mod_n) * D * esz);
-    SPECA_TRY(cond_vector(ctx, cond->timestep, cond, rows, n, sc));
+    if (!cond->pooled) SPECA_FAIL(SPECA_EINVAL, "cond->pooled is NULL");
+    SPECA_TRY(time_vectors(st, &cond->timestep, 1, emb, t_hid, temb));
+    RowLabels idx{};
+    for (int i = 0; i < n; ++i) idx.v[i] = rows[i];
+    SPECA_TRY(launch_gather_rows(d.dtype, cond->pooled, idx, v_in, n, d.vec_dim, st));
+    SPECA_TRY(pooled_vectors(st, v_in, n, v_hid, vemb));
+    SPECA_TRY(launch_silu_sum(d.dtype, temb, 1, vemb, n, D, sc, st));
     GemmEpi e;
     e.mode = EPI_F32; e.bias = mod_b; e.out = mod; e.ldo = mod_n;
     return launch_gemm(d.dtype, sc, D, mod_w, D, n, static_cast<int>(mod_n), D, e, st);
   }
 
+  void free_traj() {
+    void* all[] = {traj_mod, traj_sc, traj_emb, traj_hid, traj_vhid, traj_temb, traj_vemb};
+    for (void* p : all)
+      if (p) (void)hipFree(p);
+    traj_mod = traj_temb = traj_vemb = nullptr;
+    traj_sc = traj_emb = traj_hid = traj_vhid = nullptr;
+    traj_cap = 0;
+    traj_steps_cap = traj_rows_cap = 0;
+  }
+
+  // All steps and rows at once: six launches and one large GEMM per trajectory instead of seven launches per step.
   Error begin_trajectory(speca_ctx* ctx, const speca_cond* cond, const int32_t*, const float* timesteps, int S) override {
     hipStream_t st = ctx->stream;
     const int R = ctx->batch_rows;
     const size_t total = static_cast<size_t>(S) * R;
-    if (total * mod_n * 4 > (static_cast<size_t>(8) << 30)) return ok();      // too large to be worth holding: per-step path
-    if (total > traj_cap) {
+    if (!cond->pooled) SPECA_FAIL(SPECA_EINVAL, "cond->pooled is NULL");
+    if (total * mod_n * 4 > (static_cast<size_t>(8) << 30) || S > 65535) return ok();   // too large to be worth holding: per-step path
+    if (total > traj_cap || S > traj_steps_cap || R > traj_rows_cap) {
       SPECA_HIP(hipStreamSynchronize(st));
-      if (traj_mod) (void)hipFree(traj_mod);
-      if (traj_sc) (void)hipFree(traj_sc);
-      traj_mod = nullptr; traj_sc = nullptr; traj_cap = 0;
-      if (hipMalloc(reinterpret_cast<void**>(&traj_mod), total * mod_n * 4) != hipSuccess || hipMalloc(&traj_sc, total * D * esz) != hipSuccess) {
+      free_traj();
+      auto alloc = [](auto** p, size_t bytes) { return hipMalloc(reinterpret_cast<void**>(p), bytes) == hipSuccess; };
+      const size_t s = S, r = R;
+      if (!alloc(&traj_mod, total * mod_n * 4) || !alloc(&traj_sc, total * D * esz) || !alloc(&traj_emb, s * d.freq_dim * esz) ||
+          !alloc(&traj_hid, s * D * esz) || !alloc(&traj_temb, s * D * 4) || !alloc(&traj_vhid, r * D * esz) || !alloc(&traj_vemb, r * D * 4)) {
         (void)hipGetLastError();
-        if (traj_mod) (void)hipFree(traj_mod);
-        traj_mod = nullptr;
-        return ok();
+        free_traj();
+        return ok();                                                          // no room: per-step path
       }
       traj_cap = total;
+      traj_steps_cap = S;
+      traj_rows_cap = R;
     }
     ProfScope ps(ctx, SPECA_PROF_OTHER, 2.0 * total * D * static_cast<double>(mod_n), static_cast<double>(mod_n) * D * esz + total * mod_n * 4.0);
-    std::vector<int32_t> rows(cap_rows);
-    for (int s = 0; s < S; ++s)
-      for (int r0 = 0; r0 < R; r0 += cap_rows) {
-        const int n = std::min(cap_rows, R - r0);
-        for (int i = 0; i < n; ++i) rows[i] = r0 + i;
-        SPECA_TRY(cond_vector(ctx, timesteps[s], cond, rows.data(), n, static_cast<char*>(traj_sc) + (static_cast<size_t>(s) * R + r0) * D * esz));
-      }
+    SPECA_TRY(time_vectors(st, timesteps, S, traj_emb, traj_hid, traj_temb));
+    SPECA_TRY(pooled_vectors(st, cond->pooled, R, traj_vhid, traj_vemb));
+    SPECA_TRY(launch_silu_sum(d.dtype, traj_temb, S, traj_vemb, R, D, traj_sc, st));
     GemmEpi e;
     e.mode = EPI_F32; e.bias = mod_b; e.out = traj_mod; e.ldo = mod_n;
     SPECA_TRY(launch_gemm(d.dtype, traj_sc, D, mod_w, D, static_cast<int>(total), static_cast<int>(mod_n), D, e, st));
@@ -220,7 +246,7 @@ struct MMDiT final : Model {
   Error dual_block(speca_ctx* ctx, int l, float* hs, int n, const RowTable* refresh_rt, float* truth_out) {
     hipStream_t st = ctx->stream;
     const int64_t NT = static_cast<int64_t>(n) * T;
-    const float* mi = mod + static_cast<int64_t>(l) * 12 * D;      // image modulation: shift_a, scale_a, gate_a, shift_m, scale_m, gate_m
+    const float* mi = modp + static_cast<int64_t>(l) * 12 * D;      // image modulation: shift_a, scale_a, gate_a, shift_m, scale_m, gate_m
     const float* mt = mi + 6 * D;                                   // text modulation
     const StreamW* sw[2] = {&txt[l], &img[l]};
     const float* sm[2] = {mt, mi};
@@ -273,7 +299,7 @@ struct MMDiT final : Model {
   Error single_block(speca_ctx* ctx, int l, float* hs, int n, const RowTable* refresh_rt, float* truth_out) {
     hipStream_t st = ctx->stream;
     const int64_t NT = static_cast<int64_t>(n) * T;
-    const float* ms = mod + base_s + static_cast<int64_t>(l) * 3 * D;     // shift, scale, gate
+    const float* ms = modp + base_s + static_cast<int64_t>(l) * 3 * D;     // shift, scale, gate
     const SingleW& w = single[l];
     const int Dc = D + Dm;
     {
@@ -304,7 +330,7 @@ struct MMDiT final : Model {
 
   Error final_layer(speca_ctx* ctx, const float* hs, const int32_t* rows, int n, float* model_out) {
     hipStream_t st = ctx->stream;
-    const float* fm = mod + base_f;
+    const float* fm = modp + base_f;
     ProfScope ps(ctx, SPECA_PROF_OTHER, 2.0 * n * Ti * Kp * D, static_cast<double>(n) * Ti * D * (4 + 2 * esz));
     for (int i = 0; i < n; ++i)
       SPECA_TRY(launch_ln_modulate(d.dtype, hs + (static_cast<int64_t>(i) * T + Tt) * D, fm + static_cast<int64_t>(i) * mod_n,
@@ -350,29 +376,24 @@ struct MMDiT final : Model {
     // one pass over the cache for both hidden states when the verify block sits in the last quarter of the stack
     if (4 * lv >= 3 * nb) {
       ProfScope ps(ctx, SPECA_PROF_FORECAST, 0.0, s_end * tens * Ed * esz + 3.0 * n * Ed * 4);
-      SPECA_TRY(launch_forecast_fold2(ctx->geom, rt, h, h, s_lv, h2, mod, mod_n, gate_off_dev, split, 0, s_end, D, st));
+      SPECA_TRY(launch_forecast_fold2(ctx->geom, rt, h, h, s_lv, h2, modp, mod_n, gate_off_dev, split, 0, s_end, D, st));
     } else {
       {
         ProfScope ps(ctx, SPECA_PROF_FORECAST, 0.0, s_lv * tens * Ed * esz + 2.0 * n * Ed * 4);
-        SPECA_TRY(launch_forecast_fold(ctx->geom, rt, h, h, mod, mod_n, gate_off_dev, split, 0, s_lv, D, st));
+        SPECA_TRY(launch_forecast_fold(ctx->geom, rt, h, h, modp, mod_n, gate_off_dev, split, 0, s_lv, D, st));
       }
       ProfScope ps(ctx, SPECA_PROF_FORECAST, 0.0, (s_end - s_lv) * tens * Ed * esz + 2.0 * n * Ed * 4);
-      SPECA_TRY(launch_forecast_fold(ctx->geom, rt, h, h2, mod, mod_n, gate_off_dev, split, s_lv, s_end, D, st));
+      SPECA_TRY(launch_forecast_fold(ctx->geom, rt, h, h2, modp, mod_n, gate_off_dev, split, s_lv, s_end, D, st));
     }
     SPECA_TRY(block(ctx, lv, h, n, nullptr, feat));
     VerifyScratch& v = ctx->vs;
     SPECA_TRY(ensure_partial(ctx, static_cast<size_t>(n) * verify_chunks(ctx->geom.E) * 3));
-    std::memcpy(v.h_tau, tau_per_row, n * sizeof(float));
-    SPECA_HIP(hipMemcpyAsync(v.tau_dev, v.h_tau, n * sizeof(float), hipMemcpyHostToDevice, st));
     {
       ProfScope ps(ctx, SPECA_PROF_VERIFY, 0.0, tens * Ed * esz + n * Ed * 4);
-      SPECA_TRY(launch_verify(ctx->cfg.metric, nullptr, ctx->geom.dtype, feat, SPECA_F32, ctx->geom.E, &ctx->geom, &rt, v_slot, n, ctx->cfg.eps,
-                              v.tau_dev, v.partial, v.err_dev, v.acc_dev, st));
+      SPECA_TRY(launch_verify(ctx->cfg.metric, nullptr, ctx->geom.dtype, feat, SPECA_F32, ctx->geom.E, &ctx->geom, &rt, v_slot, n, ctx->cfg.eps, v.partial, {nullptr, nullptr, nullptr, v.verdict, ++v.launch}, st));
     }
-    SPECA_HIP(hipMemcpyAsync(v.h_err, v.err_dev, n * sizeof(float), hipMemcpyDeviceToHost, st));
-    SPECA_HIP(hipMemcpyAsync(v.h_acc, v.acc_dev, n, hipMemcpyDeviceToHost, st));
     SPECA_TRY(final_layer(ctx, h2, rows, n, model_out));
-    SPECA_HIP(hipStreamSynchronize(st));
+    SPECA_TRY(wait_verdict(ctx, n, tau_per_row));
     return ok();
   }
 };

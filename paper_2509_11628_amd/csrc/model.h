@@ -19,8 +19,8 @@ struct Model {
   // in.  x row of cache row r is x + (r % x_mod) * latent_elems(); labels are per cache row.
   virtual Error full_step(speca_ctx* ctx, const float* x, int x_mod, const speca_cond* cond, const int32_t* labels_per_row,
                           int step, const int32_t* rows, int n, float* model_out) = 0;
-  // Speculative attempt (Sec. 3.2 steps 2-3).  Leaves errors/verdicts in ctx->vs.h_err / h_acc
-  // (entry i for rows[i]) after synchronising; accepted rows are finished into model_out.
+  // Speculative attempt (Sec. 3.2 steps 2-3).  Waits for the errors and leaves them and the verdicts in ctx->vs.h_err / h_acc
+  // (entry i for rows[i]); the finish of the rows into model_out is enqueued behind them and may still run.
   virtual Error spec_step(speca_ctx* ctx, const float* x, int x_mod, const speca_cond* cond, const int32_t* labels_per_row,
                           int step, const int32_t* rows, int n, const float* tau_per_row, int pair_stride,
                           float* model_out) = 0;
