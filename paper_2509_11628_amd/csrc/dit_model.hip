@@ -192,7 +192,6 @@ struct DiT final : Model {
   struct Lane {
     hipStream_t st;
     int o;
-    int shared = 0;     // lanes that run side by side (0: this one alone)
   };
   const float* mod_at(int l, int which, int o = 0) const {
     return modp + static_cast<int64_t>(o) * mod_n + static_cast<int64_t>(l) * 6 * D + static_cast<int64_t>(which) * D;
@@ -217,7 +216,7 @@ struct DiT final : Model {
       SPECA_TRY(launch_ln_modulate(d.dtype, hl, mod_at(l, 0, ln.o), mod_at(l, 1, ln.o), mod_n, xn_l, M, T, D, st));
     }
     GemmEpi e;
-    e.mode = EPI_STORE; e.bias = blk[l].qkv_b; e.out = qkv_l; e.ldo = 3 * D; e.shared_chip = ln.shared;
+    e.mode = EPI_STORE; e.bias = blk[l].qkv_b; e.out = qkv_l; e.ldo = 3 * D;
     {
       ProfScope ps(ctx, st, SPECA_PROF_GEMM, 2.0 * Md * 3 * D * D, (Md * 4 * D + 3.0 * D * D) * esz);
       SPECA_TRY(launch_gemm(d.dtype, xn_l, D, blk[l].qkv_w, D, static_cast<int>(M), 3 * D, D, e, st));
@@ -231,7 +230,6 @@ struct DiT final : Model {
       SPECA_TRY(launch_attention(d.dtype, qkv_l, att_l, D, n, T, H, hd, st));
     }
     GemmEpi b;
-    b.shared_chip = ln.shared;
     b.mode = EPI_BRANCH; b.bias = blk[l].proj_b; b.h = hl; b.ldh = D; b.gate = mod_at(l, 2, ln.o); b.gate_stride = mod_n; b.tokens = T;
     if (refresh_rt) { b.refresh = 1; b.slot = 2 * l; b.g = ctx->geom; b.rt = *refresh_rt; }
     ProfScope ps(ctx, st, SPECA_PROF_GEMM, 2.0 * Md * D * D, (Md * D + 1.0 * D * D) * esz + Md * D * 8);
@@ -258,14 +256,13 @@ struct DiT final : Model {
       SPECA_TRY(launch_cache_warm(ctx->geom, *refresh_rt, 2 * l + 1, st));
     }
     GemmEpi e;
-    e.mode = EPI_GELU; e.bias = blk[l].fc1_b; e.out = f1_l; e.ldo = Dm; e.shared_chip = ln.shared;
+    e.mode = EPI_GELU; e.bias = blk[l].fc1_b; e.out = f1_l; e.ldo = Dm;
     {
       ProfScope ps(ctx, st, SPECA_PROF_GEMM, 2.0 * Md * Dm * D, (Md * (D + Dm) + 1.0 * D * Dm) * esz);
       SPECA_TRY(launch_gemm(d.dtype, xn_l, D, blk[l].fc1_w, D, static_cast<int>(M), Dm, D, e, st));
     }
     GemmEpi b;
     b.bias = blk[l].fc2_b;
-    b.shared_chip = ln.shared;
     if (truth_out) {
       b.mode = EPI_F32; b.out = truth_out + ln.o * TD; b.ldo = D;
     } else {
@@ -280,11 +277,13 @@ struct DiT final : Model {
   // Blocks [l0, l1) for all n rows, the row groups of the split side by side (launches interleaved
   // block by block so the lanes stay in step).  refresh_rt / truth as in the branch functions.
   Error run_blocks(speca_ctx* ctx, int l0, int l1, float* hs, int n, const RowTable* refresh_rt, float* truth_last_mlp) {
-    // Row groups side by side pay off for whole batches: 16 rows in four groups of four run a reference step 7 % faster
-    // than serially.  Eight rows (half a batch recomputed after rejections) are faster as one launch sequence whose tiles
-    // are chosen for the whole chip (+7 % on a trajectory of split steps), and the single verify block of a
-    // speculative attempt is best in two groups (+1 %).
-    const int min_rows = n <= 8 ? n + 1 : (l1 - l0 == 1 ? 8 : 4);
+    // Two row groups side by side pay off where a GEMM of all rows is about one round of tiles: the epilogue of one group,
+    // which reads and writes the residual stream and the cache, then runs beside the matrix work of the other.  Measured on
+    // 20-step trajectories of the 28-block model at 256 tokens, one group / two groups in ms: 16 rows 49.5 / 47.0, 20 rows
+    // 57.4 / 55.4, 24 rows (more than one round: tiles overlap by themselves) 60.0 / 61.2, 32 rows 79.6 / 81.8; 10 rows are
+    // 6 % slower in two groups (a group fills too little of the chip), and three or four groups are never the best.
+    const int64_t tokens = static_cast<int64_t>(n) * T;
+    const int min_rows = tokens < 4096 || tokens > 5120 ? n + 1 : n / 2;
     const LaneSplit ls = split_lanes(ctx, n, min_rows);
     RowTable sub[kMaxLanes];
     if (refresh_rt)
@@ -293,11 +292,11 @@ struct DiT final : Model {
     Error body = [&]() -> Error {
       for (int l = l0; l < l1; ++l) {
         for (int k = 0; k < ls.n_lanes; ++k) {
-          const Lane ln{ctx->lane_stream[k], ls.first[k], ls.n_lanes > 1 ? ls.n_lanes : 0};
+          const Lane ln{ctx->lane_stream[k], ls.first[k]};
           SPECA_TRY(attn_branch(ctx, ln, l, hs, ls.first[k + 1] - ls.first[k], refresh_rt ? &sub[k] : nullptr));
         }
         for (int k = 0; k < ls.n_lanes; ++k) {
-          const Lane ln{ctx->lane_stream[k], ls.first[k], ls.n_lanes > 1 ? ls.n_lanes : 0};
+          const Lane ln{ctx->lane_stream[k], ls.first[k]};
           SPECA_TRY(mlp_branch(ctx, ln, l, hs, ls.first[k + 1] - ls.first[k], refresh_rt ? &sub[k] : nullptr,
                                l == l1 - 1 ? truth_last_mlp : nullptr));
         }

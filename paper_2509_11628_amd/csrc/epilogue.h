@@ -82,6 +82,13 @@ __device__ inline void epilogue_quad(const EpiArg<MODE>& e, int m, int n, float 
   epilogue_apply<T, MODE>(e, m, n, v);
 }
 
+// Element offset of output row m (rows of a group are ldo apart, groups out_gstride).
+__device__ inline int64_t out_row(const EpiPlain& e, int m) {
+  if (!e.out_group) return static_cast<int64_t>(m) * e.ldo;
+  const int g = m / e.out_group;
+  return g * e.out_gstride + static_cast<int64_t>(m - g * e.out_group) * e.ldo;
+}
+
 // The epilogue after the bias has been added.
 template <typename T, int MODE>
 __device__ inline void epilogue_apply(const EpiArg<MODE>& e, int m, int n, float v[4]) {
@@ -91,9 +98,9 @@ __device__ inline void epilogue_apply(const EpiArg<MODE>& e, int m, int n, float
       if (MODE == EPI_GELU) v[i] = gelu_tanh_f(v[i]);
       if (MODE == EPI_SILU) v[i] = silu_f(v[i]);
     }
-    Store4<T>::st(static_cast<T*>(e.out) + static_cast<int64_t>(m) * e.ldo + n, v);
+    Store4<T>::st(static_cast<T*>(e.out) + out_row(e, m) + n, v);
   } else if constexpr (MODE == EPI_F32) {
-    Store4<float>::st(static_cast<float*>(e.out) + static_cast<int64_t>(m) * e.ldo + n, v);
+    Store4<float>::st(static_cast<float*>(e.out) + out_row(e, m) + n, v);
   } else {   // EPI_BRANCH
     const int i = m / e.tokens;
     const int t = m - i * e.tokens;
@@ -120,7 +127,7 @@ __device__ inline void epilogue_apply(const EpiArg<MODE>& e, int m, int n, float
     }
     float g[4], hv[4];
     Store4<float>::ld(e.gate + static_cast<int64_t>(i) * e.gate_stride + n, g);
-    float* hp = e.h + static_cast<int64_t>(m) * e.ldh + n;
+    float* hp = e.h + i * e.h_gstride + static_cast<int64_t>(t) * e.ldh + n;
     Store4<float>::ld(hp, hv);
 #pragma unroll
     for (int q = 0; q < 4; ++q) hv[q] = fmaf(g[q], v[q], hv[q]);
@@ -153,7 +160,7 @@ __device__ inline void branch_load(const GemmEpi& e, int m, int n, BranchRegs<T>
       if (o < order) Store4<T>::ld(base + e.g.offset(e.slot, o, e.rt.row[i]) + pos, r.old[o]);
   }
   Store4<float>::ld(e.gate + static_cast<int64_t>(i) * e.gate_stride + n, r.g);
-  Store4<float>::ld(e.h + static_cast<int64_t>(m) * e.ldh + n, r.hv);
+  Store4<float>::ld(e.h + i * e.h_gstride + static_cast<int64_t>(t) * e.ldh + n, r.hv);
 }
 
 // v = accumulators + bias (already added by the caller)
@@ -179,7 +186,7 @@ __device__ inline void branch_finish(const GemmEpi& e, int m, int n, const float
   float hv[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) hv[q] = fmaf(r.g[q], v[q], r.hv[q]);
-  Store4<float>::st(e.h + static_cast<int64_t>(m) * e.ldh + n, hv);
+  Store4<float>::st(e.h + i * e.h_gstride + static_cast<int64_t>(t) * e.ldh + n, hv);
 }
 
 
@@ -194,6 +201,7 @@ struct BranchRow {
   float inv[SPECA_MAX_ORDER];
   T* d[SPECA_MAX_ORDER + 1];         // D^o of (slot, cache row), already offset by cache_elem_offset
   const float* gate;
+  float* h;                          // residual stream of the batch row
   int t0;                            // token index of tile row 0 inside the batch row
 };
 
@@ -209,24 +217,25 @@ __device__ inline BranchRow<T> branch_row(const GemmEpi& e, int i, int m0) {
 #pragma unroll
   for (int o = 0; o < SPECA_MAX_ORDER; ++o) b.inv[o] = (b.refresh && o < b.order) ? e.rt.w[i][o] : 0.0f;
   b.gate = e.gate + static_cast<int64_t>(i) * e.gate_stride;
+  b.h = e.h + i * e.h_gstride;
   b.t0 = m0 - i * e.tokens;
   return b;
 }
 
 template <typename T>
-__device__ inline void branch_load_u(const GemmEpi& e, const BranchRow<T>& b, int r, int m, int n, BranchRegs<T>& regs) {
+__device__ inline void branch_load_u(const GemmEpi& e, const BranchRow<T>& b, int r, int n, BranchRegs<T>& regs) {
   const int64_t pos = static_cast<int64_t>(b.t0 + r) * e.ldh + n;
 #pragma unroll
   for (int o = 0; o < SPECA_MAX_ORDER; ++o)
     if (o < b.order) ld4_stream(b.d[o] + pos, regs.old[o]);
-  Store4<float>::ld(e.h + static_cast<int64_t>(m) * e.ldh + n, regs.hv);    // the gate is per (batch row, n): the caller holds it
+  Store4<float>::ld(b.h + pos, regs.hv);    // the gate is per (batch row, n): the caller holds it
 }
 
 template <typename T>
-__device__ inline void branch_finish_u(const GemmEpi& e, const BranchRow<T>& b, int r, int m, int n, const float v[4], const float g[4],
+__device__ inline void branch_finish_u(const GemmEpi& e, const BranchRow<T>& b, int r, int n, const float v[4], const float g[4],
                                        BranchRegs<T>& regs) {
+  const int64_t pos = static_cast<int64_t>(b.t0 + r) * e.ldh + n;
   if (b.refresh) {
-    const int64_t pos = static_cast<int64_t>(b.t0 + r) * e.ldh + n;
     float cur[4] = {v[0], v[1], v[2], v[3]};
     st4_stream(b.d[0] + pos, cur);
 #pragma unroll
@@ -241,7 +250,7 @@ __device__ inline void branch_finish_u(const GemmEpi& e, const BranchRow<T>& b, 
   float hv[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) hv[q] = fmaf(g[q], v[q], regs.hv[q]);
-  Store4<float>::st(e.h + static_cast<int64_t>(m) * e.ldh + n, hv);
+  Store4<float>::st(b.h + pos, hv);
 }
 
 }  // namespace speca

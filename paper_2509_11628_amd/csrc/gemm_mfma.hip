@@ -1,11 +1,7 @@
-// bf16 MFMA GEMM for gfx950:  C[M,N] = A[M,K] * W[N,K]^T with fused epilogues.
+// bf16 MFMA GEMM for gfx950, large tiles:  C[M,N] = A[M,K] * W[N,K]^T with fused epilogues; and the choice of the tile for
+// every bf16 GEMM (small tiles: gemm_ring.hip).
 //
-// Tiling (wave64, v_mfma_f32_32x32x16_bf16):
-//   block tile BM x BN with WGM x WGN waves, wave tile (BM/WGM) x (BN/WGN);
-//   K is staged through LDS in steps of BK = 64 (double buffered, one barrier per step), with two
-//   further K-tiles in flight in registers (prefetch distance 2);
-//   global -> registers -> LDS with 16-byte accesses; LDS rows are padded by 16 bytes so that
-//   the 16-byte operand reads of 16 consecutive lanes fall into distinct banks.
+// Tiling (wave64, v_mfma_f32_32x32x16_bf16): block tile BM x BN with WGM x WGN waves, K staged through LDS in steps of 64.
 // Operand roles: the weight rows are the MFMA "A" operand and the token rows the "B" operand,
 // i.e. the instruction produces a tile of C^T.  A lane then owns, for one token, quads of
 // four consecutive output features, which is what the epilogues want (8-byte bf16 /
@@ -15,24 +11,15 @@
 // regardless of M, of the tile shape and of which rows share the launch.
 // Tiles are numbered so that the 8 XCDs (round-robin block dispatch) each work on a
 // contiguous range of tiles that share activations in their own L2.
-//
-// Two main loops share the tile numbering and the epilogue:
-//   gemm_dlds_kernel  operands go global -> LDS directly (global_load_lds_dwordx4: a wave writes 64
-//                     consecutive 16-byte chunks at a wave-uniform LDS address), no register staging,
-//                     no LDS stores; unpadded 128-byte LDS rows with an XOR swizzle of the chunk
-//                     position; ring of NS stages with one raw barrier per K-step, loads awaited with
-//                     vmcnt(0) by the waves that issued them.  Needs K % 64 == 0.  Tiles 256x128 and 256x256 (half the L2 -> LDS
-//                     bytes per FLOP of 128x128).
-//   gemm_mfma_kernel  the register-staged loop described above: K tails, small problems.
+// Operands go global -> LDS directly (global_load_lds_dwordx4: a wave writes 64 consecutive 16-byte chunks at a wave-uniform
+// LDS address), no register staging, no LDS stores; unpadded 128-byte LDS rows with an XOR swizzle of the chunk position;
+// ring of NS stages with one raw barrier per K-step, loads awaited with vmcnt(0) by the waves that issued them.
+// Needs K % 64 == 0.  Tiles 256x128 and 256x256 (half the L2 -> LDS bytes per FLOP of 128x128).
 
 #include <cmath>
 
-#include "epilogue.h"
-#include "gemm.h"
+#include "gemm_tile.h"
 
-#ifndef SPECA_EBU
-#define SPECA_EBU EB
-#endif
 #ifndef SPECA_SPREAD_LOADS
 #define SPECA_SPREAD_LOADS 1
 #endif
@@ -41,280 +28,7 @@ namespace speca {
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-
 constexpr int BK = 64;
-constexpr int LDS_STRIDE = BK + 8;   // elements; 144-byte rows
-
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));   // first-class vector: stays in registers
-
-// XCD-aware tile id: blocks b, b+8, b+16, ... run on the same XCD; give them neighbouring tiles
-// (the grid is rounded up to a multiple of 8; surplus blocks leave at once).  Inside an XCD's
-// range tiles are walked in groups of group_m M-panels, N fastest across the group's panels,
-// so that the tiles in flight at one time form a compact rectangle and share operand panels
-// in that XCD's L2.
-__device__ __forceinline__ bool tile_coords(int tiles_m, int tiles_n, int group_m, int* tm, int* tn) {
-  const int bid = blockIdx.x;
-  const int per_xcd = gridDim.x / 8;
-  const int tile = (bid % 8) * per_xcd + bid / 8;
-  if (tile >= tiles_m * tiles_n) return false;
-  const int per_group = group_m * tiles_n;
-  const int g = tile / per_group;
-  const int first = g * group_m;
-  const int h = tiles_m - first < group_m ? tiles_m - first : group_m;
-  const int r = tile - g * per_group;
-  *tm = first + r % h;
-  *tn = r / h;
-  return true;
-}
-
-// Epilogue of one block tile.  acc[i][j][4*jj + ii] = C[m][n] with m = wm*WM + j*32 + l32,
-// n = wn*WN + i*32 + 8*jj + 4*lhi + ii inside the tile.  The tile goes through LDS (fp32, rows padded
-// by 16 bytes: conflict-free for the 16-byte writes of 16 consecutive lanes), EH rows at a time, so
-// that every global access of the epilogue is a contiguous run along n: a half-wave covers one
-// 512-byte (fp32) / 256-byte (bf16) row segment.  Cs must hold EH x (BN + 4) floats; the operand
-// buffers it overlays must be dead (all waves past their last read, no load in flight).
-template <int BM, int BN, int WGM, int WGN, int MODE, int EH>
-__device__ __forceinline__ void tile_epilogue(floatx16 (&acc)[BN / WGN / 32][BM / WGM / 32], float* Cs, int m0, int n0, int M, int N,
-                                              const EpiArg<MODE>& epi) {
-  constexpr int NT = WGM * WGN * 64;
-  constexpr int WM = BM / WGM, WN = BN / WGN;
-  constexpr int TM = WM / 32, TN = WN / 32;
-  constexpr int CST = BN + 4;                        // floats per staged row
-  constexpr int QPR = BN / 4;                        // quads per row
-  constexpr int RPP = NT / QPR;                      // rows per pass
-  constexpr int PASSES = EH / RPP;
-  static_assert(BM % EH == 0 && EH % WM == 0 && NT % QPR == 0 && EH % RPP == 0, "epilogue shape");
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WGN, wn = wave % WGN;
-  const int l32 = lane & 31, lhi = lane >> 5;
-  const int qc = (tid % QPR) * 4, qr = tid / QPR;
-  const int n = n0 + qc;
-  const bool live = n < N;
-  float bias[4] = {0.f, 0.f, 0.f, 0.f};
-  if (live && epi.bias) Store4<bf16_t>::ld(static_cast<const bf16_t*>(epi.bias) + n, bias);
-  // block-uniform row table when the whole tile lies inside one batch row: scalar loads
-  const int m_last = (m0 + BM < M ? m0 + BM : M) - 1;
-  int i_first = 0;
-  bool uniform = false;
-  BranchRow<bf16_t> br;
-  if constexpr (MODE == EPI_BRANCH) {
-    i_first = m0 / epi.tokens;
-    uniform = i_first == m_last / epi.tokens;
-    if (uniform) br = branch_row<bf16_t>(epi, i_first, m0);
-  }
-#pragma unroll 1
-  for (int h = 0; h < BM / EH; ++h) {
-    __syncthreads();                                 // operand buffers / previous part consumed
-    if (wm * WM / EH == h) {
-#pragma unroll
-      for (int j = 0; j < TM; ++j)
-#pragma unroll
-        for (int i = 0; i < TN; ++i)
-#pragma unroll
-          for (int jj = 0; jj < 4; ++jj) {
-            const int r = wm * WM - h * EH + j * 32 + l32, c = wn * WN + i * 32 + 8 * jj + 4 * lhi;
-            *reinterpret_cast<float4*>(Cs + r * CST + c) =
-                make_float4(acc[i][j][4 * jj], acc[i][j][4 * jj + 1], acc[i][j][4 * jj + 2], acc[i][j][4 * jj + 3]);
-          }
-    }
-    __syncthreads();
-    if (!live) continue;
-    const int mh = m0 + h * EH;                      // first global row of this part
-    if constexpr (MODE == EPI_BRANCH) {
-      // batches of EB rows: all loads of the batch are issued before its first store
-      // (fewer when the accumulators of a later part are still live: 128 registers for a 64x128 wave tile)
-      constexpr int EBMAX = (BM / EH > 1) ? 1 : 4;
-      constexpr int EB = PASSES % EBMAX == 0 ? EBMAX : (PASSES % 2 == 0 ? 2 : 1);
-      if (uniform) {
-        constexpr int EBU = SPECA_EBU;
-        float g4[4];
-        Store4<float>::ld(br.gate + n, g4);
-        for (int p0 = 0; p0 < PASSES; p0 += EBU) {
-          BranchRegs<bf16_t> regs[EBU];
-#pragma unroll
-          for (int u = 0; u < EBU; ++u) {
-            const int r = qr + (p0 + u) * RPP;
-            if (mh + r < M) branch_load_u<bf16_t>(epi, br, h * EH + r, mh + r, n, regs[u]);
-          }
-#pragma unroll
-          for (int u = 0; u < EBU; ++u) {
-            const int r = qr + (p0 + u) * RPP;
-            if (mh + r < M) {
-              const float4 t = *reinterpret_cast<const float4*>(Cs + r * CST + qc);
-              const float v[4] = {t.x + bias[0], t.y + bias[1], t.z + bias[2], t.w + bias[3]};
-              branch_finish_u<bf16_t>(epi, br, h * EH + r, mh + r, n, v, g4, regs[u]);
-            }
-          }
-        }
-      } else {
-        for (int p0 = 0; p0 < PASSES; p0 += EB) {
-          BranchRegs<bf16_t> regs[EB];
-#pragma unroll
-          for (int u = 0; u < EB; ++u) {
-            const int m = mh + qr + (p0 + u) * RPP;
-            if (m < M) branch_load<bf16_t>(epi, m, n, regs[u]);
-          }
-#pragma unroll
-          for (int u = 0; u < EB; ++u) {
-            const int r = qr + (p0 + u) * RPP;
-            const int m = mh + r;
-            if (m < M) {
-              const float4 t = *reinterpret_cast<const float4*>(Cs + r * CST + qc);
-              const float v[4] = {t.x + bias[0], t.y + bias[1], t.z + bias[2], t.w + bias[3]};
-              branch_finish<bf16_t>(epi, m, n, v, regs[u]);
-            }
-          }
-        }
-      }
-    } else {
-#pragma unroll 4
-      for (int r = qr; r < EH; r += RPP) {
-        const int m = mh + r;
-        if (m < M) {
-          const float4 t = *reinterpret_cast<const float4*>(Cs + r * CST + qc);
-          float v[4] = {t.x + bias[0], t.y + bias[1], t.z + bias[2], t.w + bias[3]};
-          epilogue_apply<bf16_t, MODE>(epi, m, n, v);
-        }
-      }
-    }
-  }
-}
-
-// KTAIL: K is not a multiple of BK; the last operand tile is zero-filled by predicated loads.
-// SF ("store first"): the LDS stores of the next tile are issued ahead of the MFMAs of the current
-// one instead of behind them.  Measured: faster for long K loops on large outputs (K >= 2048:
-// +5..11 %), slower for short ones (K = 1152), so the host picks by shape.
-template <int BM, int BN, int WGM, int WGN, int MODE, bool KTAIL, bool SF>
-__global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const uint16_t* __restrict__ A, int64_t lda,
-                                                                   const uint16_t* __restrict__ W, int64_t ldw, int M, int N, int K,
-                                                                   int tiles_m, int tiles_n, int group_m, EpiArg<MODE> epi) {
-  constexpr int NT = WGM * WGN * 64;
-  constexpr int WM = BM / WGM, WN = BN / WGN;      // wave tile
-  constexpr int TM = WM / 32, TN = WN / 32;        // MFMA tiles per wave
-  constexpr int A_CHUNKS = BM * (BK / 8) / NT;     // 16-byte chunks per thread per stage
-  constexpr int W_CHUNKS = BN * (BK / 8) / NT;
-  static_assert(BM * (BK / 8) % NT == 0 && BN * (BK / 8) % NT == 0, "tile does not divide among the threads");
-  extern __shared__ __align__(16) uint16_t smem[];
-  uint16_t* As = smem;                              // [2][BM][LDS_STRIDE]
-  uint16_t* Ws = smem + 2 * BM * LDS_STRIDE;        // [2][BN][LDS_STRIDE]
-
-  int tm, tn;
-  if (!tile_coords(tiles_m, tiles_n, group_m, &tm, &tn)) return;
-  const int m0 = tm * BM, n0 = tn * BN;
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WGN, wn = wave % WGN;
-  const int l32 = lane & 31, lhi = lane >> 5;
-
-  floatx16 acc[TN][TM];
-#pragma unroll
-  for (int i = 0; i < TN; ++i)
-#pragma unroll
-    for (int j = 0; j < TM; ++j)
-#pragma unroll
-      for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.0f;
-
-  // Operand staging: two register sets, i.e. two K-tiles in flight per block (prefetch distance 2)
-  // on top of the LDS double buffer.  Loads are branch-free: rows beyond M / N are clamped to the
-  // last row (their results are never stored) and tiles beyond K re-read the last tile, so the
-  // compiler can count outstanding loads exactly instead of draining them at every branch.
-  const int nk = (K + BK - 1) / BK;
-  const uint16_t* pa[A_CHUNKS];
-  const uint16_t* pw[W_CHUNKS];
-  int kca[A_CHUNKS], kcw[W_CHUNKS];
-#pragma unroll
-  for (int c = 0; c < A_CHUNKS; ++c) {
-    const int id = tid + c * NT;
-    const int row = id >> 3;
-    kca[c] = (id & 7) * 8;
-    const int m = m0 + row < M ? m0 + row : M - 1;
-    pa[c] = A + static_cast<int64_t>(m) * lda + kca[c];
-  }
-#pragma unroll
-  for (int c = 0; c < W_CHUNKS; ++c) {
-    const int id = tid + c * NT;
-    const int row = id >> 3;
-    kcw[c] = (id & 7) * 8;
-    const int n = n0 + row < N ? n0 + row : N - 1;
-    pw[c] = W + static_cast<int64_t>(n) * ldw + kcw[c];
-  }
-  u32x4 ra0[A_CHUNKS], rw0[W_CHUNKS], ra1[A_CHUNKS], rw1[W_CHUNKS];
-  const u32x4 zero4 = {0u, 0u, 0u, 0u};
-
-#define SPECA_LOADG(ra, rw, kt_)                                                                               \
-  {                                                                                                            \
-    const int k0_ = ((kt_) < nk ? (kt_) : nk - 1) * BK;                                                        \
-    _Pragma("unroll") for (int c = 0; c < A_CHUNKS; ++c) {                                                     \
-      if (KTAIL) ra[c] = (k0_ + kca[c] < K) ? *reinterpret_cast<const u32x4*>(pa[c] + k0_) : zero4;            \
-      else ra[c] = *reinterpret_cast<const u32x4*>(pa[c] + k0_);                                               \
-    }                                                                                                          \
-    _Pragma("unroll") for (int c = 0; c < W_CHUNKS; ++c) {                                                     \
-      if (KTAIL) rw[c] = (k0_ + kcw[c] < K) ? *reinterpret_cast<const u32x4*>(pw[c] + k0_) : zero4;            \
-      else rw[c] = *reinterpret_cast<const u32x4*>(pw[c] + k0_);                                               \
-    }                                                                                                          \
-  }
-#define SPECA_STOREL(ra, rw, buf)                                                                              \
-  {                                                                                                            \
-    _Pragma("unroll") for (int c = 0; c < A_CHUNKS; ++c) {                                                     \
-      const int id = tid + c * NT;                                                                             \
-      *reinterpret_cast<u32x4*>(As + ((buf) * BM + (id >> 3)) * LDS_STRIDE + (id & 7) * 8) = ra[c];            \
-    }                                                                                                          \
-    _Pragma("unroll") for (int c = 0; c < W_CHUNKS; ++c) {                                                     \
-      const int id = tid + c * NT;                                                                             \
-      *reinterpret_cast<u32x4*>(Ws + ((buf) * BN + (id >> 3)) * LDS_STRIDE + (id & 7) * 8) = rw[c];            \
-    }                                                                                                          \
-  }
-#define SPECA_COMPUTE(buf)                                                                                     \
-  {                                                                                                            \
-    const uint16_t* as = As + ((buf) * BM + wm * WM + l32) * LDS_STRIDE + lhi * 8;                             \
-    const uint16_t* ws = Ws + ((buf) * BN + wn * WN + l32) * LDS_STRIDE + lhi * 8;                             \
-    _Pragma("unroll") for (int ks = 0; ks < BK / 16; ++ks) {                                                   \
-      bf16x8 fa[TM], fw[TN];                                                                                   \
-      _Pragma("unroll") for (int j = 0; j < TM; ++j) fa[j] = *reinterpret_cast<const bf16x8*>(as + j * 32 * LDS_STRIDE + ks * 16); \
-      _Pragma("unroll") for (int i = 0; i < TN; ++i) fw[i] = *reinterpret_cast<const bf16x8*>(ws + i * 32 * LDS_STRIDE + ks * 16); \
-      _Pragma("unroll") for (int i = 0; i < TN; ++i) _Pragma("unroll") for (int j = 0; j < TM; ++j)            \
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[i], fa[j], acc[i][j], 0, 0, 0);                  \
-    }                                                                                                          \
-  }
-
-  SPECA_LOADG(ra0, rw0, 0);
-  SPECA_LOADG(ra1, rw1, 1);
-  SPECA_STOREL(ra0, rw0, 0);
-  SPECA_LOADG(ra0, rw0, 2);
-  __syncthreads();
-  if (SF) {
-    for (int kt = 0; kt < nk; kt += 2) {
-      SPECA_STOREL(ra1, rw1, 1);             // tile kt+1 -> buffer 1 (last read before the previous barrier)
-      SPECA_LOADG(ra1, rw1, kt + 3);
-      SPECA_COMPUTE(0);                      // tile kt
-      __syncthreads();
-      SPECA_STOREL(ra0, rw0, 0);             // tile kt+2 -> buffer 0
-      SPECA_LOADG(ra0, rw0, kt + 4);
-      if (kt + 1 < nk) SPECA_COMPUTE(1);     // tile kt+1
-      __syncthreads();
-    }
-  } else {
-    for (int kt = 0; kt < nk; kt += 2) {
-      SPECA_COMPUTE(0);                      // tile kt
-      SPECA_STOREL(ra1, rw1, 1);             // tile kt+1 -> buffer 1
-      SPECA_LOADG(ra1, rw1, kt + 3);
-      __syncthreads();
-      if (kt + 1 < nk) SPECA_COMPUTE(1);     // tile kt+1
-      SPECA_STOREL(ra0, rw0, 0);             // tile kt+2 -> buffer 0
-      SPECA_LOADG(ra0, rw0, kt + 4);
-      __syncthreads();
-    }
-  }
-#undef SPECA_LOADG
-#undef SPECA_STOREL
-#undef SPECA_COMPUTE
-
-  tile_epilogue<BM, BN, WGM, WGN, MODE, BM>(acc, reinterpret_cast<float*>(smem), m0, n0, M, N, epi);
-}
 
 // ---------------------------------------------------------------------------------------------
 // Direct-to-LDS main loop.
@@ -328,20 +42,16 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const uint16_t
 // row groups wl, wl + NL, ... (NL loader waves, NL even, so swz depends only on the lane and the
 // parity of wl).  Rows beyond M / N are clamped to the last row (never stored).
 //
-// Completion of these loads is only ever awaited with vmcnt(0).  A partial wait ("all but the newest
-// six have landed") assumes they complete in issue order; they do not reliably: a 3-stage ring built
-// on vmcnt(6) passed every isolated test and then delivered stale operand rows (32-row groups, a few
-// launches per step) once four row groups ran side by side.  Two loads-in-flight stages with
-// vmcnt(0)-only waits are obtained by splitting the waves into two loader groups instead: group g
-// loads the K-steps of parity g, so at its wait a group has exactly one step outstanding (the one
-// everybody needs next) while the other group's step stays in flight.
+// What keeps a stage intact between its readers and its next loads: a wave waits for its own fragment reads (lgkmcnt(0))
+// BEFORE the barrier that hands the stage on.  The barrier builtin alone does not give that: matrix instructions, and with
+// them the waits for the fragments they use, are free to sink below it, and a load that hits in L2 then overtakes reads still
+// queued at the LDS (a 3-stage ring compiled that way delivered rows of a later stage, in groups of 32, a few launches per
+// step, once four row groups ran side by side and shared the LDS).  With three stages the waves form two loader groups: group
+// g loads the K-steps of parity g, so at its wait a group has exactly one step outstanding (the one everybody needs next)
+// while the other group's step stays in flight.
 // Ring discipline per K-step kt (NS = 2: every wave loads every step; NS = 3: two groups):
 //   the step's loader waves wait vmcnt(0); barrier (the step is in LDS, everyone is done reading the
 //   previous step's stage); the same waves issue step kt + NS - 1 into the stage just freed; compute.
-#define SPECA_GLL(src, dst)                                                                                       \
-  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src),                         \
-                                   (__attribute__((address_space(3))) void*)(dst), 16, 0, 0)
-
 // Rows of the tile staged through LDS per epilogue part: the whole tile when it fits into the ring's
 // LDS, else half of it (no LDS beyond the ring: 128x128 stays at 64 KiB, two blocks per CU with room).
 constexpr int dlds_epilogue_rows(int BM, int BN, int NS) {
@@ -349,7 +59,7 @@ constexpr int dlds_epilogue_rows(int BM, int BN, int NS) {
 }
 
 template <int BM, int BN, int WGM, int WGN, int NS, int MODE>
-__global__ __launch_bounds__(WGM* WGN * 64) void gemm_dlds_kernel(const uint16_t* __restrict__ A, int64_t lda,
+__global__ __launch_bounds__(WGM* WGN * 64) void gemm_dlds_kernel(const uint16_t* __restrict__ A, int64_t lda, int a_group, int64_t a_gstride,
                                                                    const uint16_t* __restrict__ W, int64_t ldw, int M, int N, int K,
                                                                    int tiles_m, int tiles_n, int group_m, EpiArg<MODE> epi) {
   constexpr int NW = WGM * WGN;
@@ -389,7 +99,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_dlds_kernel(const uint16_t
   for (int g = 0; g < AG; ++g) {
     const int row = (wl + g * NL) * 8 + lrow;
     const int m = m0 + row < M ? m0 + row : M - 1;
-    pa[g] = A + static_cast<int64_t>(m) * lda + lchunk * 8;
+    const int rg = a_group < M ? m / a_group : 0;
+    pa[g] = A + rg * a_gstride + static_cast<int64_t>(m - rg * a_group) * lda + lchunk * 8;
   }
 #pragma unroll
   for (int g = 0; g < WG; ++g) {
@@ -565,6 +276,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_dlds_kernel(const uint16_t
     }                                                                                                             \
   }
   constexpr int WAIT_VM0 = 0x0F70;                           // s_waitcnt vmcnt(0), other counters untouched
+  constexpr int WAIT_LDS = 0xC07F;                           // s_waitcnt lgkmcnt(0), other counters untouched
   // prologue: steps 0 .. NS-2, each by its loader waves
 #pragma unroll
   for (int s = 0; s < NS - 1; ++s)
@@ -575,8 +287,11 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_dlds_kernel(const uint16_t
 #define SPECA_STEP(kt_, cur_, new_, par_)                                                                         \
   {                                                                                                               \
     const bool mine_ = NS == 2 || grp == (par_);             /* wave-uniform */                                    \
+    __builtin_amdgcn_s_waitcnt(WAIT_LDS);                    /* my fragment reads: the next loads may overwrite them */ \
     if (mine_) __builtin_amdgcn_s_waitcnt(WAIT_VM0);         /* my only outstanding loads are those of this step */ \
+    asm volatile("" ::: "memory");                                                                                \
     __builtin_amdgcn_s_barrier();                                                                                 \
+    asm volatile("" ::: "memory");                                                                                \
     if (SPREAD || EARLY) {                                                                                        \
       if (mine_) SPECA_COMPUTE_L(cur_, new_, (kt_) + NS - 1)                                                      \
       else SPECA_COMPUTE(cur_)                                                                                    \
@@ -613,82 +328,37 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_dlds_kernel(const uint16_t
 }
 
 template <int BM, int BN, int WGM, int WGN, int NS>
-Error launch_dlds(const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st) {
-  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+Error launch_dlds(const Operands& o, const GemmEpi& epi, hipStream_t st) {
+  const int tiles_m = (o.M + BM - 1) / BM, tiles_n = (o.N + BN - 1) / BN;
   const int64_t nblk = static_cast<int64_t>(tiles_m) * tiles_n;
   if (nblk > 0x7FFFFFF0) SPECA_FAIL(SPECA_EINVAL, "gemm: too many tiles");
-  if (K % BK != 0 || K < BK) SPECA_FAIL(SPECA_EINVAL, "gemm: direct-to-LDS loop needs K %% 64 == 0");
+  if (o.K % BK != 0 || o.K < BK) SPECA_FAIL(SPECA_EINVAL, "gemm: the large tiles need K %% 64 == 0");
   constexpr int EH = dlds_epilogue_rows(BM, BN, NS);
   const size_t smem_ops = static_cast<size_t>(NS) * (BM + BN) * BK * sizeof(uint16_t);
   const size_t smem_epi = static_cast<size_t>(EH) * (BN + 4) * sizeof(float);
   const size_t smem = smem_ops > smem_epi ? smem_ops : smem_epi;
-  const uint16_t* a = static_cast<const uint16_t*>(A);
-  const uint16_t* w = static_cast<const uint16_t*>(W);
   dim3 grid(static_cast<unsigned>((nblk + 7) / 8 * 8));
   const int group_m = tiles_m < 4 ? tiles_m : 4;
 #define SPECA_LAUNCH(MODE_)                                                                                       \
-  {                                                                                                               \
+  case MODE_: {                                                                                                   \
     auto kern = gemm_dlds_kernel<BM, BN, WGM, WGN, NS, MODE_>;                                                    \
     static bool attr_set = false;   /* more than 64 KB of dynamic LDS must be requested once per kernel */          \
     if (smem > 64 * 1024 && !attr_set) {                                                                          \
       SPECA_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem))); \
       attr_set = true;                                                                                            \
     }                                                                                                             \
-    kern<<<grid, WGM * WGN * 64, smem, st>>>(a, lda, w, ldw, M, N, K, tiles_m, tiles_n, group_m, epi_arg<MODE_>(epi)); \
+    kern<<<grid, WGM * WGN * 64, smem, st>>>(o.a, o.lda, o.a_group, o.a_gstride, o.w, o.ldw, o.M, o.N, o.K, tiles_m, tiles_n, group_m, epi_arg<MODE_>(epi)); \
+    break;                                                                                                        \
   }
   switch (epi.mode) {
-    case EPI_STORE: SPECA_LAUNCH(EPI_STORE) break;
-    case EPI_GELU: SPECA_LAUNCH(EPI_GELU) break;
-    case EPI_SILU: SPECA_LAUNCH(EPI_SILU) break;
-    case EPI_F32: SPECA_LAUNCH(EPI_F32) break;
-    case EPI_BRANCH: SPECA_LAUNCH(EPI_BRANCH) break;
+    SPECA_LAUNCH(EPI_STORE)
+    SPECA_LAUNCH(EPI_GELU)
+    SPECA_LAUNCH(EPI_SILU)
+    SPECA_LAUNCH(EPI_F32)
+    SPECA_LAUNCH(EPI_BRANCH)
     default: SPECA_FAIL(SPECA_EINVAL, "gemm: epilogue mode %d", epi.mode);
   }
 #undef SPECA_LAUNCH
-  SPECA_HIP(hipGetLastError());
-  return ok();
-}
-
-template <int BM, int BN, int WGM, int WGN>
-Error launch_tile(const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st) {
-  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-  const int64_t nblk = static_cast<int64_t>(tiles_m) * tiles_n;
-  if (nblk > 0x7FFFFFF0) SPECA_FAIL(SPECA_EINVAL, "gemm: too many tiles");
-  const size_t smem_ops = static_cast<size_t>(2) * (BM + BN) * LDS_STRIDE * sizeof(uint16_t);
-  const size_t smem_epi = static_cast<size_t>(BM) * (BN + 4) * sizeof(float);
-  const size_t smem = smem_ops > smem_epi ? smem_ops : smem_epi;
-  const uint16_t* a = static_cast<const uint16_t*>(A);
-  const uint16_t* w = static_cast<const uint16_t*>(W);
-  dim3 grid(static_cast<unsigned>((nblk + 7) / 8 * 8));
-  const int group_m = tiles_m < 4 ? tiles_m : 4;
-  const bool ktail = K % BK != 0;
-  const bool store_first = K >= 2048 && static_cast<int64_t>(M) * N >= (int64_t{8} << 20);
-#define SPECA_LAUNCH2(MODE_, KT_, SF_)                                                                          \
-  {                                                                                                              \
-    auto kern = gemm_mfma_kernel<BM, BN, WGM, WGN, MODE_, KT_, SF_>;                                                 \
-    static bool attr_set = false;   /* more than 64 KB of dynamic LDS must be requested once per kernel */         \
-    if (smem > 64 * 1024 && !attr_set) {                                                                         \
-      SPECA_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem))); \
-      attr_set = true;                                                                                           \
-    }                                                                                                            \
-    kern<<<grid, WGM * WGN * 64, smem, st>>>(a, lda, w, ldw, M, N, K, tiles_m, tiles_n, group_m, epi_arg<MODE_>(epi)); \
-  }
-#define SPECA_LAUNCH(MODE_)                       \
-  {                                               \
-    if (ktail) SPECA_LAUNCH2(MODE_, true, false)  \
-    else if (store_first) SPECA_LAUNCH2(MODE_, false, true) \
-    else SPECA_LAUNCH2(MODE_, false, false)       \
-  }
-  switch (epi.mode) {
-    case EPI_STORE: SPECA_LAUNCH(EPI_STORE) break;
-    case EPI_GELU: SPECA_LAUNCH(EPI_GELU) break;
-    case EPI_SILU: SPECA_LAUNCH(EPI_SILU) break;
-    case EPI_F32: SPECA_LAUNCH(EPI_F32) break;
-    case EPI_BRANCH: SPECA_LAUNCH(EPI_BRANCH) break;
-    default: SPECA_FAIL(SPECA_EINVAL, "gemm: epilogue mode %d", epi.mode);
-  }
-#undef SPECA_LAUNCH
-#undef SPECA_LAUNCH2
   SPECA_HIP(hipGetLastError());
   return ok();
 }
@@ -696,38 +366,43 @@ Error launch_tile(const void* A, int64_t lda, const void* W, int64_t ldw, int M,
 }  // namespace
 
 bool gemm_mfma_supported(const void* A, int64_t lda, const void* W, int64_t ldw, int N, int K) {
-  return (K % 8 == 0) && (lda % 8 == 0) && (ldw % 8 == 0) && (N % 4 == 0) && (reinterpret_cast<uintptr_t>(A) % 16 == 0) &&
-         (reinterpret_cast<uintptr_t>(W) % 16 == 0);
+  // 2^23: offsets inside a tile are 32-bit byte counts (up to 128 rows of 2-byte elements from its first row)
+  return (K % 8 == 0) && (lda % 8 == 0) && (ldw % 8 == 0) && ldw <= (1 << 23) && (N % 4 == 0) &&
+         (reinterpret_cast<uintptr_t>(A) % 16 == 0) && (reinterpret_cast<uintptr_t>(W) % 16 == 0);
 }
 
 // ---- tile choice -------------------------------------------------------------------------------------------
-// Six kernels can run a given problem; which is fastest depends on how the tile count falls on the chip's compute
+// Thirteen kernels can run a given problem; which is fastest depends on how the tile count falls on the chip's compute
 // units more than on anything else (a 270-tile launch of one-block-per-CU tiles takes two rounds, a 252-tile one
 // takes one), and the row count M varies from call to call: per-sample rejection sends any number of guidance pairs
-// to the full pass and the lanes split a batch into row groups.  So the choice is made by a small cost model instead
-// of thresholds fitted to particular shapes:
-//     time(kernel) = (a + b * ceil(K / 64)) * depth,     depth = ceil(tiles / compute units),
-// where kernels whose LDS footprint lets a second block share a compute unit pay 0.65 of a round for every round
-// after the first.  a (launch, prologue, epilogue) and b (one 64-wide K-step) were measured in microseconds per
-// kernel on the block GEMMs of the DiT-XL/2 shape at M = 256 .. 4096 and on FLUX-sized problems with cold weights;
-// over those 45 problems the model's pick is within 2 % of the best kernel everywhere (the thresholds it replaces
-// lost 17-26 % at M = 1024, 2048, 2560 and 3072-3584).  Absolute times are off by up to 25 % on long-K problems,
-// where every kernel slows down alike; only the ranking is used.
+// to the full pass.  So the choice is made by a small cost model instead of thresholds fitted to particular shapes:
+//     time(kernel) = a + (c + b * ceil(K / 64)) * rounds,     depth = ceil(tiles / compute units),
+//     rounds = 1 + r * (depth - 1), or with two blocks on a compute unit  floor(depth / 2) * (1 + r) + depth % 2
+// a: launch; c: prologue and epilogue; b: one 64-wide K-step; r: what a further round, or the second block, costs.  Fitted to
+// 224 problems with cold weights (the layers of 384 to 3072 features at 16 to 8192 rows, and random sizes) so that the time
+// of the kernels picked is least (0.9 % above the best kernel of each on the mean) and the times themselves fit (12 % rms).
 struct TileKind {
   int bm, bn;
-  float a, b;          // microseconds
-  bool shares_cu;      // a second block fits beside the first
-  bool dlds;           // direct-to-LDS loop: K % 64 == 0, M >= 256
-  bool wide;           // 256-row tiles: M >= 256
+  float a, c, b, r;    // three in microseconds, a ratio
+  bool two;            // two blocks fit on a compute unit
+  bool whole_steps;    // K % 64 == 0
 };
-constexpr TileKind kTileKinds[6] = {
-    {256, 256, 8.0f, 1.115f, false, true, true},    // 0: direct-to-LDS, 2 stages
-    {256, 128, 4.1f, 0.844f, false, true, true},    // 1: direct-to-LDS, 2 stages
-    {256, 128, 5.4f, 0.710f, false, true, true},    // 2: direct-to-LDS, 3 stages
-    {256, 128, 5.6f, 0.810f, false, false, true},   // 3: register-staged
-    {128, 128, 5.3f, 0.574f, true, false, false},   // 4: register-staged, two blocks per compute unit
-    {128, 64, 4.2f, 0.400f, true, false, false},    // 5: register-staged
+constexpr TileKind kTileKinds[] = {
+    {256, 256, 2.2f, 7.52f, 1.442f, 1.02f, false, true},    // 0: large, 2 stages
+    {256, 128, 2.3f, 4.83f, 0.816f, 1.15f, false, true},    // 1: large, 3 stages
+    {128, 128, 0.8f, 6.40f, 0.535f, 1.00f, false, false},   // 2: ring of 4 stages x 64 columns
+    {128, 128, 0.9f, 3.71f, 0.771f, 0.31f, true, false},    // 3: ring of 2 x 64
+    {128, 64, 0.8f, 4.18f, 0.314f, 1.08f, false, false},    // 4: ring of 3 x 128
+    {128, 64, 2.1f, 1.41f, 0.379f, 0.66f, true, false},     // 5: ring of 3 x 64
+    {64, 64, 0.0f, 3.98f, 0.294f, 0.95f, false, false},     // 6: ring of 4 x 128
+    {32, 64, 0.0f, 3.67f, 0.266f, 0.98f, false, false},     // 7: ring of 4 x 128, two waves
+    {192, 128, 1.3f, 5.69f, 0.656f, 1.15f, false, false},   // 8: ring of 3 x 64
+    {128, 192, 1.3f, 6.75f, 0.882f, 0.42f, true, false},    // 9: ring of 2 x 64
+    {192, 192, 2.5f, 11.1f, 0.879f, 1.08f, false, false},   // 10: ring of 3 x 64
+    {96, 128, 0.0f, 4.72f, 0.435f, 1.07f, false, false},    // 11: ring of 4 x 64
+    {128, 96, 1.2f, 3.06f, 0.710f, 0.30f, true, false},     // 12: ring of 2 x 64
 };
+constexpr int kKinds = sizeof(kTileKinds) / sizeof(kTileKinds[0]);
 
 static int compute_units() {
   static const int n = [] {
@@ -744,18 +419,18 @@ static int compute_units() {
 static double tile_cost(const TileKind& t, int M, int N, int K) {
   const double tiles = static_cast<double>((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
   const double depth = std::ceil(tiles / compute_units());
-  const double one = t.a + t.b * ((K + BK - 1) / BK);
-  return t.shares_cu ? one * (1.0 + 0.65 * (depth - 1.0)) : one * depth;
+  const double odd = std::fmod(depth, 2.0);
+  const double rounds = t.two ? (depth - odd) / 2 * (1.0 + t.r) + odd : 1.0 + t.r * (depth - 1.0);
+  return t.a + (t.c + t.b * ((K + BK - 1) / BK)) * rounds;
 }
 
 // cheapest eligible kernel for the problem; *cost receives its modelled time
 static int pick_tile(int M, int N, int K, double* cost) {
   int best = -1;
   double bc = 0.0;
-  for (int k = 0; k < 6; ++k) {
+  for (int k = 0; k < kKinds; ++k) {
     const TileKind& t = kTileKinds[k];
-    if (t.dlds && (K % BK != 0 || K < BK)) continue;
-    if (t.wide && M < 256) continue;
+    if (t.whole_steps && (K % BK != 0 || K < BK)) continue;
     const double c = tile_cost(t, M, N, K);
     if (best < 0 || c < bc) { best = k; bc = c; }
   }
@@ -763,58 +438,47 @@ static int pick_tile(int M, int N, int K, double* cost) {
   return best;
 }
 
-static Error launch_kind(int kind, const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st) {
+static Error launch_kind(int kind, const Operands& o, const GemmEpi& epi, hipStream_t st) {
   switch (kind) {
-    case 0: return launch_dlds<256, 256, 4, 2, 2>(A, lda, W, ldw, M, N, K, epi, st);
-    case 1: return launch_dlds<256, 128, 4, 2, 2>(A, lda, W, ldw, M, N, K, epi, st);
-    case 2: return launch_dlds<256, 128, 4, 2, 3>(A, lda, W, ldw, M, N, K, epi, st);
-    case 3: return launch_tile<256, 128, 4, 2>(A, lda, W, ldw, M, N, K, epi, st);
-    case 4: return launch_tile<128, 128, 2, 2>(A, lda, W, ldw, M, N, K, epi, st);
-    default: return launch_tile<128, 64, 2, 2>(A, lda, W, ldw, M, N, K, epi, st);
+    case 0: return launch_dlds<256, 256, 4, 2, 2>(o, epi, st);
+    case 1: return launch_dlds<256, 128, 4, 2, 3>(o, epi, st);
+    default: return launch_gemm_ring(kind - 2, o, epi, st);
   }
 }
 
-// Row groups of one step that run side by side on their own streams (GemmEpi::shared_chip) share the compute units with
-// each other's kernels, which the model above does not price: planned for a quarter of the chip each, four lanes took
-// the large tiles of the whole batch and a step got 5 % slower.  What measured best there are the kernels that leave
-// room beside them: the 2-stage 256x128 ring (96 KiB of LDS, a 128x64 block of another lane still fits on the compute
-// unit), 128x64 tiles for the small N = 1152 GEMM, and the 3-stage ring only for a long-K GEMM of few tiles.
-static Error launch_shared(const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st) {
-  const int64_t t128 = static_cast<int64_t>((M + 127) / 128) * ((N + 127) / 128);
-  const int64_t t256 = static_cast<int64_t>((M + 255) / 256) * ((N + 127) / 128);
-  if (K % BK == 0 && K >= BK && M >= 256) {
-    if (K >= 2048 && t256 >= 32 && t256 < 100) return launch_dlds<256, 128, 4, 2, 3>(A, lda, W, ldw, M, N, K, epi, st);
-    if (t256 >= 100 && t256 < 256) return launch_dlds<256, 128, 4, 2, 2>(A, lda, W, ldw, M, N, K, epi, st);
-  }
-  double cost = 0.0;
-  if (t256 >= 256) return launch_kind(pick_tile(M, N, K, &cost), A, lda, W, ldw, M, N, K, epi, st);
-  if (t128 >= 200) return launch_tile<128, 128, 2, 2>(A, lda, W, ldw, M, N, K, epi, st);
-  return launch_tile<128, 64, 2, 2>(A, lda, W, ldw, M, N, K, epi, st);
-}
-
-Error launch_gemm_mfma(const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st) {
-  if (epi.shared_chip > 1) return launch_shared(A, lda, W, ldw, M, N, K, epi, st);
+Error launch_gemm_mfma(const Operands& o, const GemmEpi& epi, hipStream_t st) {
   double whole = 0.0;
-  const int kind = pick_tile(M, N, K, &whole);
-  // A little more than one round of 256x256 tiles (the 4096 x 4608 x 1152 fc1 GEMM: 288): the columns that make exactly one
-  // round go on the large tile, the remaining columns in a second launch (47 + 13 us against 61 us for the best single
-  // kernel).  Column ranges only shift pointers, so this is limited to the epilogues that store into `out`.
-  if (epi.mode != EPI_BRANCH && K % BK == 0 && K >= BK && M >= 256) {
-    const int tiles_m = (M + 255) / 256;
-    const int n1 = (compute_units() / tiles_m) * 256;
-    if (n1 >= 256 && n1 < N) {
+  const int kind = pick_tile(o.M, o.N, o.K, &whole);
+  // A little more than whole rounds of 256x256 tiles (the 4096 x 4608 x 1152 fc1 GEMM: 288): the columns that make whole
+  // rounds go on the large tile, the remaining columns in a second launch (47 + 13 us against 61 us for the best single
+  // kernel; 4096 x 9216 x 3072, 576 tiles: 236 -> 207 us).  Column ranges only shift pointers, so this is limited to the epilogues that store into `out`.
+  if (epi.mode != EPI_BRANCH && o.K % BK == 0 && o.K >= BK && o.M >= 256) {
+    const int tiles_m = (o.M + 255) / 256;
+    int head = 0;
+    for (int rounds = 1;; ++rounds) {
+      const int n1 = static_cast<int>(static_cast<int64_t>(rounds) * compute_units() / tiles_m) * 256;
+      if (n1 >= o.N) break;
       double rest = 0.0;
-      (void)pick_tile(M, N - n1, K, &rest);
-      if (tile_cost(kTileKinds[0], M, n1, K) + rest < 0.9 * whole) {
-        SPECA_TRY((launch_dlds<256, 256, 4, 2, 2>(A, lda, W, ldw, M, n1, K, epi, st)));
-        GemmEpi tail = epi;
-        if (epi.bias) tail.bias = static_cast<const uint16_t*>(epi.bias) + n1;
-        tail.out = epi.mode == EPI_F32 ? static_cast<void*>(static_cast<float*>(epi.out) + n1) : static_cast<void*>(static_cast<uint16_t*>(epi.out) + n1);
-        return launch_gemm_mfma(A, lda, static_cast<const uint16_t*>(W) + static_cast<int64_t>(n1) * ldw, ldw, M, N - n1, K, tail, st);
+      if (n1 >= 256) {
+        (void)pick_tile(o.M, o.N - n1, o.K, &rest);
+        rest += tile_cost(kTileKinds[0], o.M, n1, o.K);
+        if (rest < 0.96 * whole) { head = n1; whole = rest / 0.96; }
       }
     }
+    if (head) {
+      Operands first = o, tail = o;
+      first.N = head;
+      SPECA_TRY(launch_kind(0, first, epi, st));
+      GemmEpi te = epi;
+      if (epi.bias) te.bias = static_cast<const uint16_t*>(epi.bias) + head;
+      te.out = epi.mode == EPI_F32 ? static_cast<void*>(static_cast<float*>(epi.out) + head) : static_cast<void*>(static_cast<uint16_t*>(epi.out) + head);
+      tail.w += static_cast<int64_t>(head) * o.ldw;
+      tail.N = o.N - head;
+      double cost = 0.0;
+      return launch_kind(pick_tile(tail.M, tail.N, tail.K, &cost), tail, te, st);
+    }
   }
-  return launch_kind(kind, A, lda, W, ldw, M, N, K, epi, st);
+  return launch_kind(kind, o, epi, st);
 }
 
 }  // namespace speca

@@ -104,6 +104,25 @@ def test_linear_f32_tiles(M, N, K):
     assert torch.equal(bd.linear(da[r:r + 1].contiguous(), dw, db)[0], out[r])
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 16, 8), (33, 4, 128), (65, 140, 200), (3401, 264, 8), (257, 3304, 136), (771, 2500, 136), (1034, 3592, 384),
+                                   (132, 3408, 328), (1715, 3524, 248), (3839, 3224, 456), (2461, 3280, 456), (2348, 2528, 512), (3588, 4000, 64), (3437, 3460, 520),
+                                   (845, 3076, 6152), (500, 3076, 3080), (3603, 796, 1912)])
+def test_linear_bf16_tiles(M, N, K):
+    """bf16 layers at the edges of the tiles of 32x64 to 256x256 (ragged rows and columns, K tails of 8): sampled rows against
+    the oracle, and the same bits for a row computed alone (the smallest tile)."""
+    bd = _bd()
+    rng = np.random.default_rng(M + N + K)
+    a, w, b = si._store(rng.standard_normal((M, K)).astype(np.float32), "bf16"), si._store(rng.standard_normal((N, K)).astype(np.float32), "bf16"), \
+        si._store(rng.standard_normal(N).astype(np.float32), "bf16")
+    da, dw, db = _dev(a, "bf16"), _dev(w, "bf16"), _dev(b, "bf16")
+    out = bd.linear(da, dw, db)
+    rows = sorted({0, M // 3, M // 2, M - 1} | {r for t in (32, 64, 96, 128, 192, 256) for r in (t - 1, t, M // t * t - 1, M // t * t) if 0 <= r < M})
+    exp = odit.linear(a[rows].astype(np.float64), w.astype(np.float64), b.astype(np.float64))
+    _check(out[rows], exp, "bf16", K)
+    for r in (0, M - 1):
+        assert torch.equal(bd.linear(da[r:r + 1].contiguous(), dw, db)[0], out[r])
+
+
 @pytest.mark.parametrize("rows,T,H,hd", [(2, 16, 4, 16), (1, 100, 2, 72), (2, 256, 3, 72), (1, 77, 2, 64), (1, 300, 2, 128), (1, 64, 1, 32),
                                           (1, 256, 2, 128), (3, 200, 2, 64), (1, 257, 2, 72), (1, 33, 1, 128),
                                           (1, 2000, 2, 128), (1, 1111, 1, 72),       # many key tiles, ragged tail
