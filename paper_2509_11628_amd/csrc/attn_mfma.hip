@@ -13,14 +13,10 @@
 // accumulators: the MFMA reduction index is a dummy, so the keys are simply fed to the second
 // MFMA in the order the first one left them in the lane (keys 16t+4h+0..3, 16t+8+4h+0..3 for
 // half-wave h), and V^T is read from LDS in that same order.
-// V is transposed on its way into LDS (register transposes of 4-key x 8-dim blocks) into a swizzled,
-// key-permuted layout.
-// Three kernels: a tiled one (keys/values in 64-key tiles staged through registers, online softmax); for
-// head_dim 128 a tiled one whose tiles go global -> LDS directly and whose V^T fragments come from the
-// transposing LDS read (no staging, no register transposes; the next tile's scores are issued under the
-// current tile's softmax); and, for T <= 256, one that holds the whole sequence of a head in LDS and takes
-// the softmax in one pass.
-// head_dim is padded with zeros to a multiple of 16 for q k^T and of 32 for P V.
+// Two kernels: a tiled one (keys/values in 64-key tiles that go global -> LDS directly, V^T fragments from the transposing
+// LDS read, the next tile's scores issued under the current tile's online softmax) and, for T <= 256, one that holds the
+// whole sequence of a head in LDS (V transposed on its way there, in registers) and takes the softmax in one pass.
+// head_dim is padded with zeros to a multiple of 16 for q k^T and to a multiple of 32 for P V (results that are not stored).
 #include <type_traits>
 
 #include "gemm.h"
@@ -81,215 +77,19 @@ __device__ inline void vt_write_off(int d, int kb, int* lo, int* hi) {
   *hi = d * NK + (((c + 1) ^ sw) << 3) + 4 * half;
 }
 
-// Tiled kernel (T > 256): per 64-key tile, load the next tile into registers, compute the current one
-// from LDS (S^T, softmax, O^T), store the next tile to LDS, one barrier.  Registers are capped so that
-// two blocks share a CU (two waves per SIMD): the exponentials and conversions of one wave overlap
-// the MFMAs of the other.  A software-pipelined variant that issued S of tile k+1 before the softmax
-// of tile k needed > 256 registers (one wave per SIMD, accumulators shuttled through AGPRs: 190
-// register moves per tile) and measured 455 / 596 TFLOP/s at 4608 / 27 286 tokens against 565 / 741.
-template <int HD>
-__global__ __launch_bounds__(256, 2) void attention_mfma_kernel(const uint16_t* __restrict__ qkv, uint16_t* __restrict__ out, int64_t ldo,
-                                                             int T, int H, float scale_log2e) {
-  constexpr int HD16 = (HD + 15) / 16 * 16, HD32 = (HD + 31) / 32 * 32;
-  constexpr int KS = HD16 / 16;         // reduction steps of q k^T
-  constexpr int DT = HD32 / 32;         // 32-row tiles of O^T
-  constexpr int KST = HD16 + 8;         // LDS row stride of the key tile (elements)
-  constexpr int VTILE = HD32 * 64;      // elements of one transposed value tile (see vt_read_off)
-  constexpr int CH = HD / 8;            // 16-byte chunks per key/value row
-  constexpr int K_CHUNKS = (64 * CH + 255) / 256;
-  static_assert(HD % 8 == 0, "head_dim must be a multiple of 8");
-  extern __shared__ __align__(16) uint16_t smem[];
-  uint16_t* Ks = smem;                        // [2][64][KST]
-  uint16_t* Vt = smem + 2 * 64 * KST;         // [2][VTILE]
-
-  const int row = blockIdx.z, head = blockIdx.y, q0 = blockIdx.x * 128;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l32 = lane & 31, lhi = lane >> 5;
-  const int64_t D = static_cast<int64_t>(H) * HD;
-  const uint16_t* base = qkv + static_cast<int64_t>(row) * T * 3 * D + head * HD;
-
-  // zero padding of both buffers: key columns [HD, HD16) and value rows [HD, HD32); never overwritten
-  if (HD16 > HD)
-    for (int i = tid; i < 2 * 64 * (HD16 - HD); i += 256) Ks[(i / (HD16 - HD)) * KST + HD + i % (HD16 - HD)] = 0;
-  if (HD32 > HD)
-    for (int i = tid; i < 2 * (HD32 - HD) * 64; i += 256) {
-      const int b = i / ((HD32 - HD) * 64), r = (i / 64) % (HD32 - HD), c = i % 64;
-      Vt[b * VTILE + (HD + r) * 64 + c] = 0;      // whole rows: the order inside a row does not matter
-    }
-
-  // the wave's 32 queries as B operand, resident in registers
-  Frag qf[KS];
-  {
-    const int q = q0 + wave * 32 + l32;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const int d = ks * 16 + lhi * 8;
-      qf[ks].u = (q < T && d < HD) ? *reinterpret_cast<const uint4*>(base + static_cast<int64_t>(q) * 3 * D + d) : make_uint4(0, 0, 0, 0);
-    }
-  }
-
-  floatx16 o[DT];
-#pragma unroll
-  for (int i = 0; i < DT; ++i)
-#pragma unroll
-    for (int q = 0; q < 16; ++q) o[i][q] = 0.0f;
-  float mrun = -INFINITY, lrun = 0.0f;     // running max of the raw scores and this lane's partial sum
-
-  uint4 rk[K_CHUNKS], rv[4];
-  const bool v_thread = tid < 16 * CH;          // 4 keys x 8 dims per thread
-  // The 4-key blocks are numbered so that the two blocks a 32-lane write phase touches differ in the
-  // half of the 16-byte chunk they fill (2-deep bank conflicts at most).
-  const int v_a = tid / CH, v_dc = tid % CH;
-  const int v_k4 = (v_a & ~3) | ((v_a & 1) << 1) | ((v_a >> 1) & 1);
-  auto load_global = [&](int k0) {
-#pragma unroll
-    for (int c = 0; c < K_CHUNKS; ++c) {
-      const int id = tid + c * 256;
-      const int key = id / CH, dc = id - key * CH;
-      rk[c] = (id < 64 * CH && k0 + key < T) ? *reinterpret_cast<const uint4*>(base + static_cast<int64_t>(k0 + key) * 3 * D + D + dc * 8)
-                                             : make_uint4(0, 0, 0, 0);
-    }
-    if (v_thread) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int key = k0 + v_k4 * 4 + i;
-        rv[i] = key < T ? *reinterpret_cast<const uint4*>(base + static_cast<int64_t>(key) * 3 * D + 2 * D + v_dc * 8) : make_uint4(0, 0, 0, 0);
-      }
-    }
-  };
-  auto store_lds = [&](int buf) {
-#pragma unroll
-    for (int c = 0; c < K_CHUNKS; ++c) {
-      const int id = tid + c * 256;
-      const int key = id / CH, dc = id - key * CH;
-      if (id < 64 * CH) *reinterpret_cast<uint4*>(Ks + (buf * 64 + key) * KST + dc * 8) = rk[c];
-    }
-    if (v_thread) {
-      // rv[i] = 8 dims of key i  ->  8 rows (dims) of 4 keys
-      const uint32_t w[4][4] = {{rv[0].x, rv[0].y, rv[0].z, rv[0].w}, {rv[1].x, rv[1].y, rv[1].z, rv[1].w},
-                                {rv[2].x, rv[2].y, rv[2].z, rv[2].w}, {rv[3].x, rv[3].y, rv[3].z, rv[3].w}};
-      const int c_ = 2 * (v_k4 >> 2) + (v_k4 & 1), h_ = (v_k4 >> 1) & 1;
-#pragma unroll
-      for (int dd = 0; dd < 8; ++dd) {
-        const int d_ = v_dc * 8 + dd;
-        uint32_t r[2];
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-          const uint32_t a = w[2 * kk][dd >> 1], b = w[2 * kk + 1][dd >> 1];
-          r[kk] = (dd & 1) ? ((a >> 16) | (b & 0xFFFF0000u)) : ((a & 0xFFFFu) | (b << 16));
-        }
-        *reinterpret_cast<uint2*>(Vt + buf * VTILE + d_ * 64 + ((c_ ^ vt_swz<64>(d_)) << 3) + 4 * h_) = make_uint2(r[0], r[1]);
-      }
-    }
-  };
-
-  const int ntiles = (T + 63) / 64;
-  load_global(0);
-  store_lds(0);
-  __syncthreads();
-  for (int kt = 0; kt < ntiles; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < ntiles) load_global((kt + 1) * 64);
-
-    // S^T for the two 32-key sub-tiles
-    floatx16 s[2];
-#pragma unroll
-    for (int st = 0; st < 2; ++st) {
-#pragma unroll
-      for (int q = 0; q < 16; ++q) s[st][q] = 0.0f;
-      const uint16_t* kp = Ks + (buf * 64 + st * 32 + l32) * KST + lhi * 8;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        Frag kf;
-        kf.u = *reinterpret_cast<const uint4*>(kp + ks * 16);
-        s[st] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf.v, qf[ks].v, s[st], 0, 0, 0);
-      }
-    }
-    // mask the ragged tail (last tile only), row max of the raw scores over the lane pair
-    const int kbase = kt * 64;
-    if (kbase + 64 > T) {
-#pragma unroll
-      for (int st = 0; st < 2; ++st)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-          const int key = kbase + st * 32 + 8 * (q >> 2) + 4 * lhi + (q & 3);
-          if (key >= T) s[st][q] = -INFINITY;
-        }
-    }
-    float tmax = -INFINITY;
-#pragma unroll
-    for (int st = 0; st < 2; ++st)
-#pragma unroll
-      for (int q = 0; q < 16; ++q) tmax = fmaxf(tmax, s[st][q]);
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-    // mrun is the running maximum of the RAW scores; the scale (> 0) and log2(e) enter in one fma per score
-    const float mnew = fmaxf(mrun, tmax);
-    const float moff = mnew * scale_log2e;
-    float psum = 0.0f;
-#pragma unroll
-    for (int st = 0; st < 2; ++st)
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const float p = fast_exp2(fmaf(s[st][q], scale_log2e, -moff));
-        s[st][q] = p;
-        psum += p;
-      }
-    if (__any(mnew != mrun)) {       // the running maximum moved somewhere in the wave: rescale (rare after the first tiles)
-      const float corr = fast_exp2(mrun * scale_log2e - moff);
-      lrun *= corr;
-#pragma unroll
-      for (int i = 0; i < DT; ++i)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) o[i][q] *= corr;
-      mrun = mnew;
-    }
-    lrun += psum;
-
-    // O^T += V^T P^T, four reduction steps of 16 keys
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int st = t >> 1, j0 = (t & 1) * 8;      // accumulator entries j0 .. j0+7 of sub-tile st
-      Frag pf;
-      pf.u = make_uint4(cvt_pk_bf16(s[st][j0], s[st][j0 + 1]), cvt_pk_bf16(s[st][j0 + 2], s[st][j0 + 3]),
-                        cvt_pk_bf16(s[st][j0 + 4], s[st][j0 + 5]), cvt_pk_bf16(s[st][j0 + 6], s[st][j0 + 7]));
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
-        Frag vf;
-        vf.u = *reinterpret_cast<const uint4*>(Vt + buf * VTILE + vt_read_off<64>(dt * 32 + l32, t, lhi));
-        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.v, pf.v, o[dt], 0, 0, 0);
-      }
-    }
-    if (kt + 1 < ntiles) store_lds(buf ^ 1);
-    __syncthreads();
-  }
-
-  const float ltot = lrun + __shfl_xor(lrun, 32, 64);
-  const float inv = 1.0f / ltot;
-  const int q = q0 + wave * 32 + l32;
-  if (q < T) {
-    uint16_t* op = out + (static_cast<int64_t>(row) * T + q) * ldo + head * HD;
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        const int d = dt * 32 + 8 * jj + 4 * lhi;
-        if (d < HD) {
-          uint2 r;
-          r.x = cvt_pk_bf16(o[dt][4 * jj] * inv, o[dt][4 * jj + 1] * inv);
-          r.y = cvt_pk_bf16(o[dt][4 * jj + 2] * inv, o[dt][4 * jj + 3] * inv);
-          *reinterpret_cast<uint2*>(op + d) = r;
-        }
-      }
-  }
-}
-
 // ---------------------------------------------------------------------------------------------
-// Tiled kernel for head_dim 128 whose key and value tiles go global -> LDS directly
+// Tiled kernel whose key and value tiles go global -> LDS directly
 // (global_load_lds_dwordx4: lane l's 16 bytes land at the wave-uniform LDS address + 16 l) and whose
 // V^T operand is formed by the transposing LDS read, so nothing is staged or transposed in registers.
+// Bound by the vector unit (exponentials, maxima and conversions of the softmax) beside the matrix cores at long
+// sequences, by the latency of one block's chain of tiles at short ones.  Narrow heads took a kernel before that staged
+// keys and values in registers and transposed V there, with neither a tile's scores nor its loads under the softmax
+// (us, before -> now): 4 rows x 1025 tokens x 16 heads of 72 73.5 -> 64.3, 16 x 1024 174 -> 155, 1 x 4096 137 -> 122;
+// heads of 64: 2 x 2048 x 6 50.4 -> 42.4, 1 x 8000 x 24 549 -> 547.  The old kernel at three blocks per compute unit (168
+// registers) was slower than at two: 1 x 4096 x 16 heads of 72 188.
 //
-// Both tiles are stored row-major as they are in memory: 64 keys x 256 bytes (16 chunks of 16 bytes).
-// One load instruction covers 4 rows; lane l supplies the chunk stored at position l % 16 of row l / 16.
+// Both tiles are stored row-major as they are in memory: 64 keys x 2 HD bytes, one load instruction per 64 chunks of 16
+// bytes.  For head_dim 128 (rows of 16 chunks; the narrower ones follow):
 // Keys:   S^T = K q^T reads, per lane, chunk 2 ks + h of row l32 (ds_read_b128); chunk c of row r sits at
 //         position c ^ (r & 15), so the 16 lanes of a read phase touch all 64 banks once.
 // Values: ds_read_b64_tr_b16, per group of 16 lanes: lane j points at 4 consecutive dims
@@ -299,23 +99,40 @@ __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(const uint16_t* 
 //         accumulators hand P^T to the second MFMA.  The four rows a half-wave reads are moved to
 //         different 64-byte bank groups: chunk c of row r sits at position
 //         c ^ (4 (r & 3) + ((r >> 2) & 3)).
+// head_dim 64: rows of 128 bytes share the banks in pairs, so keys are swizzled by (r & 7) ^ ((r >> 3) & 1) and values by
+// the second bit of the row alone (rows r and r + 2 of one read).  head_dim 72: rows of 144 bytes spread over the banks by
+// themselves.  Its last score step covers columns 64 .. 79: the lanes of the upper half read zeros (not the next row: it
+// may hold infinities), and value dims 72 .. 95 repeat a chunk, for results that are never stored.
 // Rows beyond T are read from row T - 1 (valid memory): their scores are masked to -inf, so their
 // probabilities are exactly 0 and the finite values they multiply do not matter.
-// Ring: two buffers; per tile the waves wait for their own loads with vmcnt(0) (the only safe wait
-// for these loads), one barrier, loads of the next tile are issued into the buffer just freed.
+// Ring: two buffers; per tile the waves wait for their own loads with vmcnt(0) (all that are outstanding),
+// one barrier, loads of the next tile are issued into the buffer just freed.
 #define SPECA_ATTN_GLL(src, dst)                                                                                  \
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src),                         \
                                    (__attribute__((address_space(3))) void*)(dst), 16, 0, 0)
 typedef short short4v __attribute__((ext_vector_type(4)));
 
-template <bool PIPE>
+// element offset inside a row of the stored chunk c of row r (involutions: the loader uses them the other way round)
+template <int HD>
+__device__ inline int key_chunk(int c, int r) {
+  return HD == 128 ? c ^ (r & 15) : HD == 64 ? c ^ (r & 7) ^ ((r >> 3) & 1) : c;
+}
+template <int HD>
+__device__ inline int value_chunk(int c, int r) {
+  return HD == 128 ? c ^ (4 * (r & 3) + ((r >> 2) & 3)) : HD == 64 ? c ^ (4 * ((r >> 1) & 1)) : c;
+}
+
+template <int HD>
 __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* __restrict__ qkv, uint16_t* __restrict__ out, int64_t ldo,
                                                             int T, int H, float scale_log2e) {
-  constexpr int HD = 128, KS = 8, DT = 4;
+  constexpr int CH = HD / 8;                  // 16-byte chunks of a row, and load instructions of a tile
+  constexpr int KS = (HD + 15) / 16, DT = (HD + 31) / 32;
+  constexpr int LPW = (CH + 3) / 4;           // load instructions per wave and tile
   constexpr int TILE = 64 * HD;               // elements of one key or value tile
   extern __shared__ __align__(16) uint16_t smem[];
-  uint16_t* Ks = smem;                        // [2][64][128]
-  uint16_t* Vs = smem + 2 * TILE;             // [2][64][128]
+  uint16_t* Ks = smem;                        // [2][64][HD]
+  uint16_t* Vs = smem + 2 * TILE;             // [2][64][HD]
+  uint16_t* zero = smem + 4 * TILE;           // head_dim 72: the key columns 72 .. 79 of the last step
 
   const int row = blockIdx.z, head = blockIdx.y, q0 = blockIdx.x * 128;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -328,7 +145,9 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
     const int q = q0 + wave * 32 + l32;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-      qf[ks].u = q < T ? *reinterpret_cast<const uint4*>(base + static_cast<int64_t>(q) * 3 * D + ks * 16 + lhi * 8) : make_uint4(0, 0, 0, 0);
+      qf[ks].u = q < T && (2 * ks + 1 < CH || lhi == 0) ? *reinterpret_cast<const uint4*>(base + static_cast<int64_t>(q) * 3 * D + ks * 16 + lhi * 8)
+                                                        : make_uint4(0, 0, 0, 0);
+    if (2 * KS > CH && tid < 8) zero[tid] = 0;
   }
   floatx16 o[DT];
 #pragma unroll
@@ -337,37 +156,43 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
     for (int q = 0; q < 16; ++q) o[i][q] = 0.0f;
   float mrun = -INFINITY, lrun = 0.0f;
 
-  // loader: wave w issues instructions i = w, w + 4, w + 8, w + 12 of each tile (16 per tile, 4 rows each);
-  // lane -> row 4 i + lane / 16, stored position lane % 16
-  const int lr = lane >> 4, lp = lane & 15;
-  // The source chunk of a lane does not depend on the instruction (rows 4 i + lr with i = wave + 4 g: r & 15 and
-  // the value swizzle only see 4 wave + lr), so a tile's addresses are one per-lane 32-bit offset on top of a
-  // wave-uniform row pointer: no per-load vector arithmetic.  Only a ragged last tile clamps rows per lane.
+  // Loader: wave w issues instructions i = w, w + 4, ... of a tile's CH; lane -> chunk slot 64 i + lane, row slot / CH.
+  // With whole rows per lane group (head_dim 128: rows 4 i + lane / 16) the source chunk does not depend on the
+  // instruction (r & 15 and the value swizzle only see 4 wave + lane / 16), so a tile's addresses are one per-lane 32-bit
+  // offset on top of a wave-uniform row pointer; else there is one offset per instruction.  Only a ragged last tile clamps
+  // rows per lane.
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const int row3d = static_cast<int>(3 * D);
-  const int koff = lr * row3d + static_cast<int>(D) + ((lp ^ ((4 * wave_u + lr) & 15)) << 3);
-  const int voff = lr * row3d + 2 * static_cast<int>(D) + ((lp ^ (4 * lr + (wave_u & 3))) << 3);
-  auto issue = [&](int k0, int buf, uint16_t* dst, int off) {
+  constexpr int OFFS = HD == 128 ? 1 : LPW, RSTEP = HD == 128 ? 4 : 0;
+  int koff[OFFS], voff[OFFS];
+#pragma unroll
+  for (int g = 0; g < OFFS; ++g) {
+    const int slot = (wave_u + 4 * g) * 64 + lane, r = HD == 128 ? 4 * wave_u + (lane >> 4) : static_cast<unsigned>(slot) / CH, p = slot - r * CH;
+    const int rr = HD == 128 ? lane >> 4 : r;
+    koff[g] = rr * row3d + static_cast<int>(D) + (key_chunk<HD>(p, r) << 3);
+    voff[g] = rr * row3d + 2 * static_cast<int>(D) + (value_chunk<HD>(p, r) << 3);
+  }
+  auto issue = [&](int k0, int buf, uint16_t* dst, const int (&off)[OFFS]) {
     if (k0 + 64 <= T) {
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
+      for (int g = 0; g < LPW; ++g) {
         const int i = wave_u + 4 * g;
-        const uint16_t* ub = base + static_cast<int64_t>(k0 + 4 * i) * row3d;      // wave-uniform
-        SPECA_ATTN_GLL(ub + off, dst + buf * TILE + i * 512);
+        const uint16_t* ub = base + static_cast<int64_t>(k0 + RSTEP * i) * row3d;      // wave-uniform
+        if (CH % 4 == 0 || i < CH) SPECA_ATTN_GLL(ub + off[OFFS == 1 ? 0 : g], dst + buf * TILE + i * 512);
       }
     } else {
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int i = wave_u + 4 * g;
-        int key = k0 + 4 * i + lr;
-        key = key < T ? key : T - 1;
-        SPECA_ATTN_GLL(base + static_cast<int64_t>(key) * row3d + (off - lr * row3d), dst + buf * TILE + i * 512);
+      for (int g = 0; g < LPW; ++g) {
+        const int i = wave_u + 4 * g, rr = HD == 128 ? lane >> 4 : static_cast<unsigned>(i * 64 + lane) / CH;
+        const int key = k0 + RSTEP * i + rr < T ? k0 + RSTEP * i + rr : T - 1;
+        if (CH % 4 == 0 || i < CH) SPECA_ATTN_GLL(base + static_cast<int64_t>(key) * row3d + (off[OFFS == 1 ? 0 : g] - rr * row3d), dst + buf * TILE + i * 512);
       }
     }
   };
   auto issue_k = [&](int k0, int buf) { issue(k0, buf, Ks, koff); };
   auto issue_v = [&](int k0, int buf) { issue(k0, buf, Vs, voff); };
-  const int kpos_sw = l32 & 15;               // key row l32 (+32): r & 15
+  // a wave whose queries all lie beyond T only loads (1025 tokens: three waves of every ninth block)
+  const bool active = HD == 128 || q0 + wave_u * 32 < T;
   // value reader: 16-lane group g = lane / 16, j = lane % 16: key k0 + j / 4 with k0 = 16 t + 4 (g >> 1) (+ 8),
   // dims dt * 32 + 16 (g & 1) + 4 (j % 4) .. + 3: chunk dt * 4 + 2 (g & 1) + (j % 4) / 2, half (j % 2)
   const int vg = lane >> 4, vj = lane & 15;
@@ -385,7 +210,9 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         Frag kf;
-        kf.u = *reinterpret_cast<const uint4*>(kp + (((2 * ks + lhi) ^ kpos_sw) << 3));
+        const uint16_t* kc = kp + (key_chunk<HD>(2 * ks + lhi, l32) << 3);       // rows + 32 are swizzled alike
+        if (2 * ks + 1 >= CH && lhi) kc = zero;
+        kf.u = *reinterpret_cast<const uint4*>(kc);
         s[st] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf.v, qf[ks].v, s[st], 0, 0, 0);
       }
     }
@@ -419,13 +246,13 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
         s[st][q] = p;
         psum += p;
       }
-    if (PIPE && !decltype(masked)::value) {
+    if (!decltype(masked)::value) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
+      for (int i = 0; i < 2 * KS; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);     // one key fragment read
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);     // one MFMA of the next tile's scores
-        __builtin_amdgcn_sched_group_barrier(0x400, 2, 0);     // two exponentials of this tile's softmax
-        __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);     // seven of its other vector instructions
+        __builtin_amdgcn_sched_group_barrier(0x400, HD == 128 ? 2 : HD == 72 ? 3 : 4, 0);     // two (three, four) exponentials of this tile's softmax
+        __builtin_amdgcn_sched_group_barrier(0x002, HD == 128 ? 7 : HD == 72 ? 11 : 14, 0);   // seven (eleven, fourteen) of its other vector instructions
       }
     }
     if (__any(mnew != mrun)) {
@@ -445,14 +272,13 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
       pf.u = make_uint4(cvt_pk_bf16(s[st][j0], s[st][j0 + 1]), cvt_pk_bf16(s[st][j0 + 2], s[st][j0 + 3]),
                         cvt_pk_bf16(s[st][j0 + 4], s[st][j0 + 5]), cvt_pk_bf16(s[st][j0 + 6], s[st][j0 + 7]));
       const int ka = 16 * t + vkey0, kb = ka + 8;                  // rows of the two transposing reads
-      const int swa = 4 * (ka & 3) + ((ka >> 2) & 3), swb = 4 * (kb & 3) + ((kb >> 2) & 3);
       const uint16_t* va = Vs + vb * TILE + ka * HD + vhalf;
       const uint16_t* vbp = Vs + vb * TILE + kb * HD + vhalf;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) {
-        const int c = dt * 4 + vchunk0;
-        const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(va + ((c ^ swa) << 3)));
-        const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(vbp + ((c ^ swb) << 3)));
+        const int c = CH % 4 == 0 || dt * 4 + vchunk0 < CH ? dt * 4 + vchunk0 : CH - 1;      // dims beyond HD: any, never stored
+        const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(va + (value_chunk<HD>(c, ka) << 3)));
+        const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(vbp + (value_chunk<HD>(c, kb) << 3)));
         union { short4v h[2]; bf16x8 v; } vf;
         vf.h[0] = lo; vf.h[1] = hi;
         o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.v, pf.v, o[dt], 0, 0, 0);
@@ -461,19 +287,7 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
   };
 
   const int ntiles = (T + 63) / 64;
-  if (!PIPE) {
-    issue_k(0, 0);
-    issue_v(0, 0);
-    for (int kt = 0; kt < ntiles; ++kt) {
-      const int buf = kt & 1;
-      __builtin_amdgcn_s_waitcnt(0x0F70);        // vmcnt(0): this wave's loads of tile kt (nothing else is outstanding)
-      __syncthreads();                           // tile kt is in LDS; everyone is done with the other buffer
-      if (kt + 1 < ntiles) { issue_k((kt + 1) * 64, buf ^ 1); issue_v((kt + 1) * 64, buf ^ 1); }
-      floatx16 s[2];
-      scores(s, buf);
-      softmax_pv(s, kt, buf, std::true_type());
-    }
-  } else {
+  {
     // The scores of tile kt + 1 are issued before the softmax of tile kt: their MFMAs run while the vector
     // unit takes exponentials.  Keys are therefore fetched two tiles ahead, values one: at the top of
     // iteration kt the wave's outstanding loads are K(kt + 1) and V(kt), both awaited with vmcnt(0);
@@ -484,7 +298,7 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
     __syncthreads();
     if (1 < ntiles) issue_k(64, 1);
     issue_v(0, 0);
-    scores(sa, 0);
+    if (active) scores(sa, 0);
     // All tiles but the last: no tail mask and no condition between the score MFMAs of tile kt + 1 and the
     // softmax of tile kt, so both sit in one scheduling region; the group barriers ask for one key-fragment
     // read and one MFMA per two exponentials and seven other vector instructions (the wave issues in order:
@@ -495,8 +309,10 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
     __syncthreads();                                                                                              \
     if ((kt_) + 2 < ntiles) issue_k(((kt_) + 2) * 64, (kt_) & 1);                                                 \
     issue_v(((kt_) + 1) * 64, ((kt_) + 1) & 1);                                                                   \
-    scores(SN, ((kt_) + 1) & 1);                                                                                  \
-    softmax_pv(SC, (kt_), (kt_) & 1, std::false_type());                                                          \
+    if (active) {                                                                                                 \
+      scores(SN, ((kt_) + 1) & 1);                                                                                \
+      softmax_pv(SC, (kt_), (kt_) & 1, std::false_type());                                                        \
+    }                                                                                                             \
   }
     int kt = 0;
     for (; kt + 2 < ntiles; kt += 2) {
@@ -507,11 +323,11 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
       SPECA_ATTN_ITER(kt, sa, sb);
       __builtin_amdgcn_s_waitcnt(0x0F70);
       __syncthreads();
-      softmax_pv(sb, kt + 1, (kt + 1) & 1, std::true_type());
+      if (active) softmax_pv(sb, kt + 1, (kt + 1) & 1, std::true_type());
     } else {                                   // one tile left, its scores are in sa
       __builtin_amdgcn_s_waitcnt(0x0F70);
       __syncthreads();
-      softmax_pv(sa, kt, kt & 1, std::true_type());
+      if (active) softmax_pv(sa, kt, kt & 1, std::true_type());
     }
 #undef SPECA_ATTN_ITER
   }
@@ -526,6 +342,7 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
 #pragma unroll
       for (int jj = 0; jj < 4; ++jj) {
         const int d = dt * 32 + 8 * jj + 4 * lhi;
+        if (dt * 32 + 8 * jj >= HD) continue;
         uint2 r;
         r.x = cvt_pk_bf16(o[dt][4 * jj] * inv, o[dt][4 * jj + 1] * inv);
         r.y = cvt_pk_bf16(o[dt][4 * jj + 2] * inv, o[dt][4 * jj + 3] * inv);
@@ -765,8 +582,6 @@ __global__ __launch_bounds__(512) void attention_mfma_whole_kernel(const uint16_
 
 template <int HD>
 Error launch_hd(const void* qkv, void* out, int64_t ldo, int rows, int T, int H, hipStream_t st) {
-  constexpr int HD16 = (HD + 15) / 16 * 16, HD32 = (HD + 31) / 32 * 32;
-  const size_t smem = static_cast<size_t>(2) * (64 * (HD16 + 8) + HD32 * 64) * sizeof(uint16_t);
   // (the whole-sequence kernel stores 16-byte chunks of the output when it stages them through LDS)
   if (T <= 256 && (!whole_stages_output(HD) || (ldo % 8 == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0))) {
     constexpr size_t smem_w = whole_lds_bytes(HD, whole_stages_output(HD));
@@ -782,24 +597,14 @@ Error launch_hd(const void* qkv, void* out, int64_t ldo, int rows, int T, int H,
     SPECA_HIP(hipGetLastError());
     return ok();
   }
-  // head_dim 128: direct-to-LDS tiles with the transposing read, scores of the next tile under the softmax
-  if (HD == 128) {
-    constexpr size_t smem_d = static_cast<size_t>(4) * 64 * 128 * sizeof(uint16_t);
-    dim3 grid_d((T + 127) / 128, H, rows);
-    const float sl2 = 1.4426950408889634f / sqrtf(128.0f);
-    attention_dma_kernel<true><<<grid_d, 256, smem_d, st>>>(static_cast<const uint16_t*>(qkv), static_cast<uint16_t*>(out), ldo, T, H, sl2);
-    SPECA_HIP(hipGetLastError());
-    return ok();
-  }
-  auto kern = attention_mfma_kernel<HD>;
+  constexpr size_t smem = static_cast<size_t>(4) * 64 * HD * sizeof(uint16_t) + (HD % 16 ? 16 : 0);
   static bool attr_set = false;
   if (smem > 64 * 1024 && !attr_set) {
-    SPECA_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(attention_mfma_kernel<HD>), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem)));
+    SPECA_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(attention_dma_kernel<HD>), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem)));
     attr_set = true;
   }
-  dim3 grid((T + 127) / 128, H, rows);
-  const float scale_log2e = 1.4426950408889634f / sqrtf(static_cast<float>(HD));
-  kern<<<grid, 256, smem, st>>>(static_cast<const uint16_t*>(qkv), static_cast<uint16_t*>(out), ldo, T, H, scale_log2e);
+  const float sl2 = 1.4426950408889634f / sqrtf(static_cast<float>(HD));
+  attention_dma_kernel<HD><<<dim3((T + 127) / 128, H, rows), 256, smem, st>>>(static_cast<const uint16_t*>(qkv), static_cast<uint16_t*>(out), ldo, T, H, sl2);
   SPECA_HIP(hipGetLastError());
   return ok();
 }

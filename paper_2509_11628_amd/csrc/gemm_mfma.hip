@@ -366,7 +366,7 @@ Error launch_dlds(const Operands& o, const GemmEpi& epi, hipStream_t st) {
 }  // namespace
 
 bool gemm_mfma_supported(const void* A, int64_t lda, const void* W, int64_t ldw, int N, int K) {
-  // 2^23: offsets inside a tile are 32-bit byte counts (up to 128 rows of 2-byte elements from its first row)
+  // 2^23: offsets inside a tile are 32-bit byte counts (up to 191 rows of 2-byte elements from its first row)
   return (K % 8 == 0) && (lda % 8 == 0) && (ldw % 8 == 0) && ldw <= (1 << 23) && (N % 4 == 0) &&
          (reinterpret_cast<uintptr_t>(A) % 16 == 0) && (reinterpret_cast<uintptr_t>(W) % 16 == 0);
 }

@@ -141,6 +141,23 @@ def test_attention(rows, T, H, hd, dtype):
     assert np.max(np.abs(got - exp)) <= (2e-5 if dtype == "f32" else 1.2e-2) * scale
 
 
+@pytest.mark.parametrize("T", [257, 288, 320, 384, 449, 1025])      # 1, 32, 0 queries in the last block of 128; keys 1, 32, 0 past a tile of 64
+@pytest.mark.parametrize("hd", [64, 72])
+def test_attention_tiles_of_narrow_heads(T, hd):
+    """bf16 heads of 64 and 72: rows that share no multiple of 128 bytes, waves without queries, the column step past the head."""
+    bd = _bd()
+    rows, H = 2, 3
+    rng = np.random.default_rng(T * hd)
+    qkv = si._store(rng.standard_normal((rows, T, 3, H, hd)).astype(np.float32), "bf16")
+    dq = _dev(qkv.reshape(rows, T, 3 * H * hd), "bf16")
+    got = bd.attention(dq, H)
+    q, k, v = (qkv[:, :, i].transpose(0, 2, 1, 3).astype(np.float64) for i in range(3))
+    exp = odit.attention(q, k, v).transpose(0, 2, 1, 3).reshape(rows, T, H * hd)
+    # probabilities and the output are rounded to bf16 on the device (2^-9 relative each)
+    assert np.max(np.abs(got.float().cpu().numpy().astype(np.float64) - exp)) <= 1.2e-2 * np.max(np.abs(exp))
+    assert torch.equal(bd.attention(dq[1:].contiguous(), H)[0], got[1])
+
+
 @pytest.mark.parametrize("T,hd", [(256, 72), (200, 72), (96, 64)])
 def test_attention_short_sequence_into_an_output_at_8_byte_alignment(T, hd):
     """The whole-sequence kernel (T <= 256) stores 16-byte chunks; an output that is only 8-byte aligned takes the tiled
