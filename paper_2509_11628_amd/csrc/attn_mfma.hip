@@ -103,8 +103,8 @@ __device__ inline void vt_write_off(int d, int kb, int* lo, int* hi) {
 // the second bit of the row alone (rows r and r + 2 of one read).  head_dim 72: rows of 144 bytes spread over the banks by
 // themselves.  Its last score step covers columns 64 .. 79: the lanes of the upper half read zeros (not the next row: it
 // may hold infinities), and value dims 72 .. 95 repeat a chunk, for results that are never stored.
-// Rows beyond T are read from row T - 1 (valid memory): their scores are masked to -inf, so their
-// probabilities are exactly 0 and the finite values they multiply do not matter.
+// Rows beyond T are zeros (kZeroRow): their scores are masked to -inf, and the probability 0 they get must not meet an
+// infinite value (0 x inf is NaN), as it would in a copy of row T - 1.
 // Ring: two buffers; per tile the waves wait for their own loads with vmcnt(0) (all that are outstanding),
 // one barrier, loads of the next tile are issued into the buffer just freed.
 #define SPECA_ATTN_GLL(src, dst)                                                                                  \
@@ -121,6 +121,9 @@ template <int HD>
 __device__ inline int value_chunk(int c, int r) {
   return HD == 128 ? c ^ (4 * (r & 3) + ((r >> 2) & 3)) : HD == 64 ? c ^ (4 * ((r >> 1) & 1)) : c;
 }
+
+// 16 bytes of zeros: what a lane loads for keys and values past T
+__device__ __align__(16) const uint32_t kZeroRow[4] = {0u, 0u, 0u, 0u};
 
 template <int HD>
 __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* __restrict__ qkv, uint16_t* __restrict__ out, int64_t ldo,
@@ -159,7 +162,7 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
   // Loader: wave w issues instructions i = w, w + 4, ... of a tile's CH; lane -> chunk slot 64 i + lane, row slot / CH.
   // With whole rows per lane group (head_dim 128: rows 4 i + lane / 16) the source chunk does not depend on the
   // instruction (r & 15 and the value swizzle only see 4 wave + lane / 16), so a tile's addresses are one per-lane 32-bit
-  // offset on top of a wave-uniform row pointer; else there is one offset per instruction.  Only a ragged last tile clamps
+  // offset on top of a wave-uniform row pointer; else there is one offset per instruction.  Only a ragged last tile looks at
   // rows per lane.
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const int row3d = static_cast<int>(3 * D);
@@ -184,8 +187,9 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
 #pragma unroll
       for (int g = 0; g < LPW; ++g) {
         const int i = wave_u + 4 * g, rr = HD == 128 ? lane >> 4 : static_cast<unsigned>(i * 64 + lane) / CH;
-        const int key = k0 + RSTEP * i + rr < T ? k0 + RSTEP * i + rr : T - 1;
-        if (CH % 4 == 0 || i < CH) SPECA_ATTN_GLL(base + static_cast<int64_t>(key) * row3d + (off[OFFS == 1 ? 0 : g] - rr * row3d), dst + buf * TILE + i * 512);
+        const int key = k0 + RSTEP * i + rr;
+        const uint16_t* src = key < T ? base + static_cast<int64_t>(key) * row3d + (off[OFFS == 1 ? 0 : g] - rr * row3d) : reinterpret_cast<const uint16_t*>(kZeroRow);
+        if (CH % 4 == 0 || i < CH) SPECA_ATTN_GLL(src, dst + buf * TILE + i * 512);
       }
     }
   };

@@ -226,6 +226,16 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(const T* __restrict_
 #pragma unroll
         for (int t = 0; t < QT; ++t) s[t] = mfma4(kf[ks][c], qf[t][ks][c], s[t]);
     if (kt + 4 < ntiles) load_k(kt + 4);
+    if (kt * 16 + 16 > Tn) {                       // keys past the end: probability 0, which must not meet an infinite value
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if (kt * 16 + g4 * 4 + r < Tn) continue;
+#pragma unroll
+        for (int g = 0; g < G; ++g) vf[r][g] = zero;
+#pragma unroll
+        for (int i = 0; i < RT; ++i) vr[r][i] = 0.0f;
+      }
+    }
 #pragma unroll
     for (int t = 0; t < QT; ++t) {
       if (kt * 16 + 16 > Tn) {

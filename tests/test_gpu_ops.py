@@ -158,6 +158,25 @@ def test_attention_tiles_of_narrow_heads(T, hd):
     assert torch.equal(bd.attention(dq[1:].contiguous(), H)[0], got[1])
 
 
+@pytest.mark.parametrize("T,hd,dtype", [(257, 64, "bf16"), (300, 72, "bf16"), (1025, 72, "bf16"), (300, 128, "bf16"), (200, 72, "bf16"), (33, 16, "bf16"),
+                                        (17, 32, "f32"), (33, 64, "f32"), (300, 72, "f32"), (77, 128, "f32")])
+def test_attention_infinite_value_in_the_last_row(T, hd, dtype):
+    """A ragged last key tile holds keys past T with probability 0; they must not be copies of the last value row, where an
+    infinity would turn into NaN (0 x inf).  The infinite dimension is infinite for every query, all others keep their bits."""
+    bd = _bd()
+    H = 2
+    rng = np.random.default_rng(T + hd)
+    qkv = rng.standard_normal((1, T, 3, H, hd)).astype(np.float32)
+    qkv[0, T - 1, 2, 1, 3] = 0.0
+    base = bd.attention(_dev(qkv.reshape(1, T, -1), dtype), H)
+    qkv[0, T - 1, 2, 1, 3] = np.inf
+    got = bd.attention(_dev(qkv.reshape(1, T, -1), dtype), H)
+    assert bool((got[0, :, hd + 3] == float("inf")).all())
+    keep = torch.ones(H * hd, dtype=torch.bool, device="cuda")
+    keep[hd + 3] = False
+    assert torch.equal(got[..., keep], base[..., keep])
+
+
 @pytest.mark.parametrize("T,hd", [(256, 72), (200, 72), (96, 64)])
 def test_attention_short_sequence_into_an_output_at_8_byte_alignment(T, hd):
     """The whole-sequence kernel (T <= 256) stores 16-byte chunks; an output that is only 8-byte aligned takes the tiled
