@@ -247,7 +247,9 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(const T* __restrict_
       tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
       tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
       const float mnew = fmaxf(mrun[t], tmax);
-      const float moff = mnew * scale_log2e;
+      // A wave may see nothing but scores of -inf in its tiles (an infinite key): weight 0 then, and not -inf - (-inf).  Only a
+      // query whose every score is -inf has no softmax; the merge makes that NaN.
+      const float moff = mnew == -INFINITY ? 0.0f : mnew * scale_log2e;
       const float corr = __builtin_amdgcn_exp2f(fmaf(mrun[t], scale_log2e, -moff));     // the first tile: exp2(-inf) = 0
       float p[4];
 #pragma unroll

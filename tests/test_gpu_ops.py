@@ -177,6 +177,25 @@ def test_attention_infinite_value_in_the_last_row(T, hd, dtype):
     assert torch.equal(got[..., keep], base[..., keep])
 
 
+@pytest.mark.parametrize("T,hd,dtype,first,last", [(17, 64, "f32", 16, 17), (40, 16, "f32", 32, 40), (17, 16, "bf16", 16, 17), (300, 72, "f32", 288, 300),
+                                                   (70, 128, "f32", 16, 32), (70, 32, "bf16", 48, 70)])
+def test_attention_keys_of_minus_infinity(T, hd, dtype, first, last):
+    """Scores of -inf over whole 16-key tiles, so that a wave of the fp32 kernel sees no finite score: those keys have weight 0
+    and the result is the attention over the others (fp32 rounding; bf16 rounds the result once)."""
+    bd = _bd()
+    rng = np.random.default_rng(T + hd)
+    qkv = si._store(rng.standard_normal((1, T, 3, 1, hd)).astype(np.float32), dtype)
+    qkv[:, :, :2] = np.abs(qkv[:, :, :2])                      # positive queries: every score against a key of -inf is -inf
+    rest = np.r_[0:first, last:T]
+    q, k, v = (qkv[:, :, i].transpose(0, 2, 1, 3).astype(np.float64) for i in range(3))
+    exp = odit.attention(q, k[:, :, rest], v[:, :, rest]).transpose(0, 2, 1, 3).reshape(1, T, hd)
+    qkv[0, first:last, 1] = -np.inf
+    got = bd.attention(_dev(qkv.reshape(1, T, -1), dtype), 1).float().cpu().numpy().astype(np.float64)
+    assert np.max(np.abs(got - exp)) <= (1e-5 if dtype == "f32" else 2.0 ** -8) * np.max(np.abs(exp))
+    qkv[0, :, 1] = -np.inf                                     # no finite score at all: no softmax
+    assert np.isnan(bd.attention(_dev(qkv.reshape(1, T, -1), dtype), 1).float().cpu().numpy()).all()
+
+
 @pytest.mark.parametrize("T,hd", [(256, 72), (200, 72), (96, 64)])
 def test_attention_short_sequence_into_an_output_at_8_byte_alignment(T, hd):
     """The whole-sequence kernel (T <= 256) stores 16-byte chunks; an output that is only 8-byte aligned takes the tiled
