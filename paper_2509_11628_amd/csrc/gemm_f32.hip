@@ -36,7 +36,9 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
   __shared__ __align__(16) float part[4][BM * CST];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, kq = (lane >> 4) * 4;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
+  const int64_t mt = static_cast<int64_t>(blockIdx.z) * gridDim.y + blockIdx.y;      // more than 32768 row tiles go on in z
+  if (mt * BM >= M) return;
+  const int m0 = static_cast<int>(mt) * BM, n0 = blockIdx.x * BN;
   const float* pa[TM];
   const float* pw[TN];
 #pragma unroll
@@ -119,7 +121,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
 template <int TM, int TN, int PF>
 Error launch_f32_tile(const float* A, int64_t lda, int a_group, int64_t a_gstride, const float* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi,
                       hipStream_t st) {
-  const dim3 grid((N + 16 * TN - 1) / (16 * TN), (M + 16 * TM - 1) / (16 * TM));
+  const unsigned row_tiles = (M + 16 * TM - 1) / (16 * TM), grid_y = row_tiles < 32768 ? row_tiles : 32768;
+  const dim3 grid((N + 16 * TN - 1) / (16 * TN), grid_y, (row_tiles + grid_y - 1) / grid_y);
 #define SPECA_LAUNCH(MODE_)                                                                                                  \
   {                                                                                                                          \
     if (K % 16) gemm_f32_kernel<TM, TN, PF, MODE_, true><<<grid, 256, 0, st>>>(A, lda, a_group, a_gstride, W, ldw, M, N, K, epi_arg<MODE_>(epi)); \
@@ -157,7 +160,7 @@ template <> __device__ inline float ld_one<float>(const float* p) { return *p; }
 template <> __device__ inline float ld_one<bf16_t>(const bf16_t* p) { return bf16_to_f32(p->bits); }
 
 template <typename T, int HD, int QT>
-__global__ __launch_bounds__(256) void attention_f32_kernel(const T* __restrict__ qkv, T* __restrict__ out, int64_t ldo, int Tn, int H, float scale_log2e) {
+__global__ __launch_bounds__(256) void attention_f32_kernel(const T* __restrict__ qkv, T* __restrict__ out, int64_t ldo, int Tn, int64_t D, float scale_log2e) {
   constexpr int KS = (HD + 15) / 16;              // steps of 16 dimensions in q k^T
   constexpr int G = HD / 64;                      // groups of four tiles of O^T (64 dimensions)
   constexpr int REM = HD - 64 * G;                // what is left: 8, 16 or 32 dimensions in tiles of 16
@@ -170,8 +173,7 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(const T* __restrict_
   const int row = blockIdx.z, head = blockIdx.y, q0 = blockIdx.x * 16 * QT;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g4 = lane >> 4;
-  const int64_t D = static_cast<int64_t>(H) * HD;
-  const T* base = qkv + static_cast<int64_t>(row) * Tn * 3 * D + head * HD;
+  const T* base = qkv + static_cast<int64_t>(row) * Tn * 3 * D + head * HD;      // D = heads x HD, of which this launch may cover a part
   const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
 
   floatx4 qf[QT][KS];
@@ -323,12 +325,20 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(const T* __restrict_
 template <typename T, int HD>
 Error launch_attn_f32_hd(const void* qkv, void* out, int64_t ldo, int rows, int Tn, int H, hipStream_t st) {
   const float sl2 = 1.4426950408889634f / sqrtf(static_cast<float>(HD));
+  const int64_t D = static_cast<int64_t>(H) * HD;
   // 32 queries per block read every key and value half as often; 16 keep the chip busy when there are few of them
-  if (static_cast<int64_t>((Tn + 31) / 32) * H * rows >= 512)
-    attention_f32_kernel<T, HD, 2><<<dim3((Tn + 31) / 32, H, rows), 256, 0, st>>>(static_cast<const T*>(qkv), static_cast<T*>(out), ldo, Tn, H, sl2);
-  else
-    attention_f32_kernel<T, HD, 1><<<dim3((Tn + 15) / 16, H, rows), 256, 0, st>>>(static_cast<const T*>(qkv), static_cast<T*>(out), ldo, Tn, H, sl2);
-  SPECA_HIP(hipGetLastError());
+  const bool two = static_cast<int64_t>((Tn + 31) / 32) * H * rows >= 512;
+  const unsigned blocks = two ? (Tn + 31) / 32 : (Tn + 15) / 16;
+  constexpr int kMost = 65535;                    // rows and heads of one grid
+  for (int r0 = 0; r0 < rows; r0 += kMost)
+    for (int h0 = 0; h0 < H; h0 += kMost) {
+      const dim3 grid(blocks, H - h0 < kMost ? H - h0 : kMost, rows - r0 < kMost ? rows - r0 : kMost);
+      const T* q = static_cast<const T*>(qkv) + static_cast<int64_t>(r0) * Tn * 3 * D + static_cast<int64_t>(h0) * HD;
+      T* o = static_cast<T*>(out) + static_cast<int64_t>(r0) * Tn * ldo + static_cast<int64_t>(h0) * HD;
+      if (two) attention_f32_kernel<T, HD, 2><<<grid, 256, 0, st>>>(q, o, ldo, Tn, D, sl2);
+      else attention_f32_kernel<T, HD, 1><<<grid, 256, 0, st>>>(q, o, ldo, Tn, D, sl2);
+      SPECA_HIP(hipGetLastError());
+    }
   return ok();
 }
 
@@ -361,7 +371,6 @@ static Error launch_f32_kind(int kind, const float* a, int64_t lda, int a_group,
 }
 
 Error launch_gemm_f32(const void* A, int64_t lda, int a_group, int64_t a_gstride, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st) {
-  if ((M + 63) / 64 > 65535) SPECA_FAIL(SPECA_EINVAL, "gemm: too many rows");
   // The largest tile that still makes 128 blocks (one on every second compute unit): a block's waves read every operand
   // piece once per tile, and that traffic costs more than idle units do down to there (512 x 1152 x 384: 144 blocks of 64 x 64
   // 11.4 us, 576 of 32 x 32 12.8, 2304 of 16 x 16 18.1; 512 x 384 x 384 with 48 / 192 / 768 blocks: 11.1 / 5.6 / 7.6 us).
@@ -373,7 +382,6 @@ Error launch_gemm_f32(const void* A, int64_t lda, int a_group, int64_t a_gstride
 }
 
 Error launch_attention_f32(int dtype, const void* qkv, void* out, int64_t ldo, int rows, int T, int H, int hd, hipStream_t st) {
-  if (rows > 65535 || H > 65535) SPECA_FAIL(SPECA_EINVAL, "attention: grid too large");
   return dtype == SPECA_BF16 ? launch_attn_f32_t<bf16_t>(qkv, out, ldo, rows, T, H, hd, st) : launch_attn_f32_t<float>(qkv, out, ldo, rows, T, H, hd, st);
 }
 

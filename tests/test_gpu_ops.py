@@ -196,6 +196,26 @@ def test_attention_keys_of_minus_infinity(T, hd, dtype, first, last):
     assert np.isnan(bd.attention(_dev(qkv.reshape(1, T, -1), dtype), 1).float().cpu().numpy()).all()
 
 
+@pytest.mark.parametrize("rows,H,dtype", [(65541, 1, "f32"), (65541, 1, "bf16"), (1, 65541, "f32")])
+def test_attention_of_more_rows_or_heads_than_a_grid_dimension(rows, H, dtype):
+    bd = _bd()
+    T, hd = 3, 16
+    rng = np.random.default_rng(5)
+    qkv = si._store(rng.standard_normal((rows, T, 3, H, hd)).astype(np.float32), dtype)
+    got = bd.attention(_dev(qkv.reshape(rows, T, -1), dtype), H).float().cpu().numpy().astype(np.float64)
+    q, k, v = (qkv[:, :, i].transpose(0, 2, 1, 3).astype(np.float64) for i in range(3))
+    exp = odit.attention(q, k, v).transpose(0, 2, 1, 3).reshape(rows, T, H * hd)
+    assert np.max(np.abs(got - exp)) <= (1e-5 if dtype == "f32" else 2.0 ** -8) * np.max(np.abs(exp))
+
+
+def test_linear_f32_of_more_row_tiles_than_a_grid_dimension():
+    bd = _bd()
+    M, N, K = 64 * 65536 + 70, 4, 4                            # tiles of 64 rows
+    rng = np.random.default_rng(6)
+    a, w = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
+    _check(bd.linear(_dev(a, "f32"), _dev(w, "f32")), odit.linear(a.astype(np.float64), w.astype(np.float64), None), "f32", K)
+
+
 @pytest.mark.parametrize("T,hd", [(256, 72), (200, 72), (96, 64)])
 def test_attention_short_sequence_into_an_output_at_8_byte_alignment(T, hd):
     """The whole-sequence kernel (T <= 256) stores 16-byte chunks; an output that is only 8-byte aligned takes the tiled
