@@ -21,6 +21,7 @@ struct VerifyScratch {
   size_t partial_cap = 0;          // floats
   uint64_t* verdict = nullptr;     // pinned [kMaxVerifyRows]: launch number << 32 | bits of the error
   uint32_t launch = 0;             // number of the latest launch
+  hipEvent_t ended = nullptr;      // recorded behind the last launch of a speca_verify
   std::vector<float> h_err;        // errors of the latest launch that was waited for
   std::vector<uint8_t> h_acc;      // and, with thresholds, its verdicts
 };

@@ -179,6 +179,27 @@ def test_verify_parity(dtype, E):
     ctx.close()
 
 
+def test_verify_leaves_the_stream_idle():
+    """The errors travel through pinned memory that the host polls; the call still synchronises the stream, as every call that
+    returns host results does."""
+    import ctypes as C
+    sp = _sp()
+    from paper_2509_11628_amd import binding as bd
+    rows, E = 2, 1024
+    p = torch.randn((rows, E), device="cuda"); t = p + 0.1 * torch.randn_like(p)
+    ctx = sp.Context(sp.cache_only_desc(1, 1, 8, bd.F32))
+    err = np.zeros(rows, np.float32)
+    args = (ctx.h, C.c_void_p(p.data_ptr()), C.c_void_p(t.data_ptr()), rows, E, bd.F32, None, 1e-8, bd._p(err, C.c_float), None)
+    stream = torch.cuda.current_stream()
+    torch.cuda.synchronize()
+    idle = 0
+    for _ in range(200):
+        assert ctx.lib.speca_verify(*args) == bd.OK
+        idle += stream.query()
+    ctx.close()
+    assert idle == 200
+
+
 def test_verify_is_bit_reproducible_and_row_independent():
     sp = _sp()
     from paper_2509_11628_amd import binding as bd
