@@ -82,13 +82,6 @@ __device__ inline void epilogue_quad(const EpiArg<MODE>& e, int m, int n, float 
   epilogue_apply<T, MODE>(e, m, n, v);
 }
 
-// Element offset of output row m (rows of a group are ldo apart, groups out_gstride).
-__device__ inline int64_t out_row(const EpiPlain& e, int m) {
-  if (!e.out_group) return static_cast<int64_t>(m) * e.ldo;
-  const int g = m / e.out_group;
-  return g * e.out_gstride + static_cast<int64_t>(m - g * e.out_group) * e.ldo;
-}
-
 // The epilogue after the bias has been added.
 template <typename T, int MODE>
 __device__ inline void epilogue_apply(const EpiArg<MODE>& e, int m, int n, float v[4]) {
@@ -98,9 +91,9 @@ __device__ inline void epilogue_apply(const EpiArg<MODE>& e, int m, int n, float
       if (MODE == EPI_GELU) v[i] = gelu_tanh_f(v[i]);
       if (MODE == EPI_SILU) v[i] = silu_f(v[i]);
     }
-    Store4<T>::st(static_cast<T*>(e.out) + out_row(e, m) + n, v);
+    Store4<T>::st(static_cast<T*>(e.out) + static_cast<int64_t>(m) * e.ldo + n, v);
   } else if constexpr (MODE == EPI_F32) {
-    Store4<float>::st(static_cast<float*>(e.out) + out_row(e, m) + n, v);
+    Store4<float>::st(static_cast<float*>(e.out) + static_cast<int64_t>(m) * e.ldo + n, v);
   } else {   // EPI_BRANCH
     const int i = m / e.tokens;
     const int t = m - i * e.tokens;
@@ -127,7 +120,7 @@ __device__ inline void epilogue_apply(const EpiArg<MODE>& e, int m, int n, float
     }
     float g[4], hv[4];
     Store4<float>::ld(e.gate + static_cast<int64_t>(i) * e.gate_stride + n, g);
-    float* hp = e.h + i * e.h_gstride + static_cast<int64_t>(t) * e.ldh + n;
+    float* hp = e.h + static_cast<int64_t>(m) * e.ldh + n;
     Store4<float>::ld(hp, hv);
 #pragma unroll
     for (int q = 0; q < 4; ++q) hv[q] = fmaf(g[q], v[q], hv[q]);
@@ -160,7 +153,7 @@ __device__ inline void branch_load(const GemmEpi& e, int m, int n, BranchRegs<T>
       if (o < order) Store4<T>::ld(base + e.g.offset(e.slot, o, e.rt.row[i]) + pos, r.old[o]);
   }
   Store4<float>::ld(e.gate + static_cast<int64_t>(i) * e.gate_stride + n, r.g);
-  Store4<float>::ld(e.h + i * e.h_gstride + static_cast<int64_t>(t) * e.ldh + n, r.hv);
+  Store4<float>::ld(e.h + static_cast<int64_t>(m) * e.ldh + n, r.hv);
 }
 
 // v = accumulators + bias (already added by the caller)
@@ -186,7 +179,7 @@ __device__ inline void branch_finish(const GemmEpi& e, int m, int n, const float
   float hv[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) hv[q] = fmaf(r.g[q], v[q], r.hv[q]);
-  Store4<float>::st(e.h + i * e.h_gstride + static_cast<int64_t>(t) * e.ldh + n, hv);
+  Store4<float>::st(e.h + static_cast<int64_t>(m) * e.ldh + n, hv);
 }
 
 
@@ -217,7 +210,7 @@ __device__ inline BranchRow<T> branch_row(const GemmEpi& e, int i, int m0) {
 #pragma unroll
   for (int o = 0; o < SPECA_MAX_ORDER; ++o) b.inv[o] = (b.refresh && o < b.order) ? e.rt.w[i][o] : 0.0f;
   b.gate = e.gate + static_cast<int64_t>(i) * e.gate_stride;
-  b.h = e.h + i * e.h_gstride;
+  b.h = e.h + static_cast<int64_t>(i) * e.tokens * e.ldh;
   b.t0 = m0 - i * e.tokens;
   return b;
 }

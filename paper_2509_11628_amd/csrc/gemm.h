@@ -24,12 +24,9 @@ struct GemmEpi {
   const void* bias = nullptr;     // [N] model dtype
   void* out = nullptr;            // STORE/GELU/SILU/F32 destination
   int64_t ldo = 0;
-  int out_group = 0;              // > 0: output rows come in groups of this many, out_gstride elements apart
-  int64_t out_gstride = 0;
   // EPI_BRANCH
   float* h = nullptr;             // [M][N] fp32 residual stream
   int64_t ldh = 0;
-  int64_t h_gstride = 0;          // elements of h between rows of the batch (0: tokens * ldh)
   const float* gate = nullptr;    // gate[(m / tokens) * gate_stride + n]
   int64_t gate_stride = 0;
   int tokens = 1;                 // tokens per row: m = i * tokens + t
@@ -46,22 +43,16 @@ struct EpiPlain {
   const void* bias;
   void* out;
   int64_t ldo;
-  int out_group;
-  int64_t out_gstride;
 };
 template <int MODE> using EpiArg = std::conditional_t<MODE == EPI_BRANCH, GemmEpi, EpiPlain>;
 template <int MODE> inline EpiArg<MODE> epi_arg(const GemmEpi& e) {
   if constexpr (MODE == EPI_BRANCH) return e;
-  else return {e.bias, e.out, e.ldo, e.out_group, e.out_gstride};
+  else return {e.bias, e.out, e.ldo};
 }
 
 // M may be ragged; N % 4 == 0 is required (checked).
 Error launch_gemm(int dtype, const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi,
                   hipStream_t st);
-// The rows of A in groups: row m lies at A + (m / a_group) * a_gstride + (m % a_group) * lda.  One launch covers the token
-// ranges of several batch rows that share the weights.
-Error launch_gemm_grouped(int dtype, const void* A, int64_t lda, int a_group, int64_t a_gstride, const void* W, int64_t ldw, int M, int N, int K,
-                          const GemmEpi& epi, hipStream_t st);
 
 // softmax(q k^T / sqrt(hd)) v without mask.  qkv: [rows][T][3][H][hd] (model dtype),
 // out: [rows][T][ldo] with the H*hd result in the first columns (ldo >= H*hd, ldo % 4 == 0).

@@ -3,14 +3,14 @@
 
 namespace speca {
 
-Error launch_gemm_simple(int dtype, const void* A, int64_t lda, int a_group, int64_t a_gstride, const void* W, int64_t ldw, int M, int N, int K,
+Error launch_gemm_simple(int dtype, const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K,
                          const GemmEpi& epi, hipStream_t st);
 Error launch_attention_simple(int dtype, const void* qkv, void* out, int64_t ldo, int rows, int T, int H, int hd, hipStream_t st);
 bool gemm_mfma_supported(const void* A, int64_t lda, const void* W, int64_t ldw, int N, int K);
 Error launch_gemm_mfma(const Operands& o, const GemmEpi& epi, hipStream_t st);
 
 bool gemm_f32_supported(const void* A, int64_t lda, const void* W, int64_t ldw, int K);
-Error launch_gemm_f32(const void* A, int64_t lda, int a_group, int64_t a_gstride, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st);
+Error launch_gemm_f32(const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st);
 Error launch_attention_f32(int dtype, const void* qkv, void* out, int64_t ldo, int rows, int T, int H, int hd, hipStream_t st);
 
 bool attention_mfma_supported(const void* qkv, const void* out, int64_t ldo, int H, int hd);
@@ -18,16 +18,8 @@ Error launch_attention_mfma(const void* qkv, void* out, int64_t ldo, int rows, i
 
 Error launch_gemm(int dtype, const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi,
                   hipStream_t st) {
-  return launch_gemm_grouped(dtype, A, lda, M < 1 ? 1 : M, 0, W, ldw, M, N, K, epi, st);
-}
-
-Error launch_gemm_grouped(int dtype, const void* A, int64_t lda, int a_group, int64_t a_gstride, const void* W, int64_t ldw, int M, int N, int K,
-                          const GemmEpi& epi_in, hipStream_t st) {
   if (!A || !W) SPECA_FAIL(SPECA_EINVAL, "gemm: NULL operand");
   if (M < 1 || N < 4 || K < 1 || N % 4) SPECA_FAIL(SPECA_EINVAL, "gemm: M=%d N=%d K=%d (N must be a multiple of 4)", M, N, K);
-  if (a_group < 1 || (a_group < M && a_gstride < a_group * lda)) SPECA_FAIL(SPECA_EINVAL, "gemm: row groups");
-  GemmEpi epi = epi_in;
-  if (epi.mode == EPI_BRANCH && !epi.h_gstride) epi.h_gstride = epi.tokens * epi.ldh;
   if (lda < K || ldw < K) SPECA_FAIL(SPECA_EINVAL, "gemm: leading dimensions smaller than K");
   if (epi.mode == EPI_BRANCH) {
     if (!epi.h || !epi.gate || epi.tokens < 1 || epi.ldh != N) SPECA_FAIL(SPECA_EINVAL, "gemm: branch epilogue arguments");
@@ -43,13 +35,12 @@ Error launch_gemm_grouped(int dtype, const void* A, int64_t lda, int a_group, in
   } else if (!epi.out || epi.ldo < N) {
     SPECA_FAIL(SPECA_EINVAL, "gemm: output missing");
   }
-  // how far the rows of one tile lie apart: the matrix kernels take byte offsets of 32 bits inside a tile
-  const int64_t reach = a_group < M ? (256 / a_group + 2) * a_gstride : 256 * lda;
-  if (dtype == SPECA_BF16 && reach < (int64_t{1} << 31) && gemm_mfma_supported(A, lda, W, ldw, N, K) && a_gstride % 8 == 0)
-    return launch_gemm_mfma({static_cast<const uint16_t*>(A), lda, a_group, a_gstride, static_cast<const uint16_t*>(W), ldw, M, N, K}, epi, st);
-  if (dtype == SPECA_F32 && gemm_f32_supported(A, lda, W, ldw, K) && a_gstride % 4 == 0)
-    return launch_gemm_f32(A, lda, a_group, a_gstride, W, ldw, M, N, K, epi, st);
-  return launch_gemm_simple(dtype, A, lda, a_group, a_gstride, W, ldw, M, N, K, epi, st);
+  // 2^23: the matrix kernels take byte offsets of 32 bits inside a tile
+  if (dtype == SPECA_BF16 && lda <= (1 << 23) && gemm_mfma_supported(A, lda, W, ldw, N, K))
+    return launch_gemm_mfma({static_cast<const uint16_t*>(A), lda, static_cast<const uint16_t*>(W), ldw, M, N, K}, epi, st);
+  if (dtype == SPECA_F32 && gemm_f32_supported(A, lda, W, ldw, K))
+    return launch_gemm_f32(A, lda, W, ldw, M, N, K, epi, st);
+  return launch_gemm_simple(dtype, A, lda, W, ldw, M, N, K, epi, st);
 }
 
 Error launch_attention(int dtype, const void* qkv, void* out, int64_t ldo, int rows, int T, int H, int hd, hipStream_t st) {

@@ -29,7 +29,7 @@ __device__ __forceinline__ floatx4 mfma4(float a, float b, floatx4 c) { return _
 // PF = steps of loads in flight per wave.
 // KTAIL: K is no multiple of 16.
 template <int TM, int TN, int PF, int MODE, bool KTAIL>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int64_t lda, int a_group, int64_t a_gstride, const float* __restrict__ W, int64_t ldw, int M, int N,
+__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int64_t lda, const float* __restrict__ W, int64_t ldw, int M, int N,
                                                        int K, EpiArg<MODE> epi) {
   constexpr int BM = 16 * TM, BN = 16 * TN;
   constexpr int CST = BN + 4;                     // floats per staged row
@@ -44,8 +44,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     const int m = m0 + i * 16 + l16;
-    const int mc = m < M ? m : M - 1, rg = mc / a_group;
-    pa[i] = A + rg * a_gstride + static_cast<int64_t>(mc - rg * a_group) * lda;      // rows beyond M / N repeat the last one and are never stored
+    pa[i] = A + static_cast<int64_t>(m < M ? m : M - 1) * lda;      // rows beyond M / N repeat the last one and are never stored
   }
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
@@ -119,14 +118,14 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
 }
 
 template <int TM, int TN, int PF>
-Error launch_f32_tile(const float* A, int64_t lda, int a_group, int64_t a_gstride, const float* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi,
+Error launch_f32_tile(const float* A, int64_t lda, const float* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi,
                       hipStream_t st) {
   const unsigned row_tiles = (M + 16 * TM - 1) / (16 * TM), grid_y = row_tiles < 32768 ? row_tiles : 32768;
   const dim3 grid((N + 16 * TN - 1) / (16 * TN), grid_y, (row_tiles + grid_y - 1) / grid_y);
 #define SPECA_LAUNCH(MODE_)                                                                                                  \
   {                                                                                                                          \
-    if (K % 16) gemm_f32_kernel<TM, TN, PF, MODE_, true><<<grid, 256, 0, st>>>(A, lda, a_group, a_gstride, W, ldw, M, N, K, epi_arg<MODE_>(epi)); \
-    else gemm_f32_kernel<TM, TN, PF, MODE_, false><<<grid, 256, 0, st>>>(A, lda, a_group, a_gstride, W, ldw, M, N, K, epi_arg<MODE_>(epi));        \
+    if (K % 16) gemm_f32_kernel<TM, TN, PF, MODE_, true><<<grid, 256, 0, st>>>(A, lda, W, ldw, M, N, K, epi_arg<MODE_>(epi)); \
+    else gemm_f32_kernel<TM, TN, PF, MODE_, false><<<grid, 256, 0, st>>>(A, lda, W, ldw, M, N, K, epi_arg<MODE_>(epi));        \
   }
   switch (epi.mode) {
     case EPI_STORE: SPECA_LAUNCH(EPI_STORE) break;
@@ -360,17 +359,17 @@ bool gemm_f32_supported(const void* A, int64_t lda, const void* W, int64_t ldw, 
   return K % 4 == 0 && lda % 4 == 0 && ldw % 4 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0;
 }
 
-static Error launch_f32_kind(int kind, const float* a, int64_t lda, int a_group, int64_t a_gstride, const float* w, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st) {
+static Error launch_f32_kind(int kind, const float* a, int64_t lda, const float* w, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st) {
   switch (kind) {
-    case 0: return launch_f32_tile<4, 4, 2>(a, lda, a_group, a_gstride, w, ldw, M, N, K, epi, st);
-    case 1: return launch_f32_tile<2, 4, 3>(a, lda, a_group, a_gstride, w, ldw, M, N, K, epi, st);
-    case 2: return launch_f32_tile<2, 2, 4>(a, lda, a_group, a_gstride, w, ldw, M, N, K, epi, st);
-    case 3: return launch_f32_tile<1, 2, 6>(a, lda, a_group, a_gstride, w, ldw, M, N, K, epi, st);
-    default: return launch_f32_tile<1, 1, 8>(a, lda, a_group, a_gstride, w, ldw, M, N, K, epi, st);
+    case 0: return launch_f32_tile<4, 4, 2>(a, lda, w, ldw, M, N, K, epi, st);
+    case 1: return launch_f32_tile<2, 4, 3>(a, lda, w, ldw, M, N, K, epi, st);
+    case 2: return launch_f32_tile<2, 2, 4>(a, lda, w, ldw, M, N, K, epi, st);
+    case 3: return launch_f32_tile<1, 2, 6>(a, lda, w, ldw, M, N, K, epi, st);
+    default: return launch_f32_tile<1, 1, 8>(a, lda, w, ldw, M, N, K, epi, st);
   }
 }
 
-Error launch_gemm_f32(const void* A, int64_t lda, int a_group, int64_t a_gstride, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st) {
+Error launch_gemm_f32(const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st) {
   // The largest tile that still makes 128 blocks (one on every second compute unit): a block's waves read every operand
   // piece once per tile, and that traffic costs more than idle units do down to there (512 x 1152 x 384: 144 blocks of 64 x 64
   // 11.4 us, 576 of 32 x 32 12.8, 2304 of 16 x 16 18.1; 512 x 384 x 384 with 48 / 192 / 768 blocks: 11.1 / 5.6 / 7.6 us).
@@ -378,7 +377,7 @@ Error launch_gemm_f32(const void* A, int64_t lda, int a_group, int64_t a_gstride
   constexpr int bm[5] = {64, 32, 32, 16, 16}, bn[5] = {64, 64, 32, 32, 16};
   int kind = 0;
   while (kind < 4 && (bm[kind] > 2 * ((M + 15) / 16 * 16) || static_cast<int64_t>((M + bm[kind] - 1) / bm[kind]) * ((N + bn[kind] - 1) / bn[kind]) < 128)) ++kind;
-  return launch_f32_kind(kind, static_cast<const float*>(A), lda, a_group, a_gstride, static_cast<const float*>(W), ldw, M, N, K, epi, st);
+  return launch_f32_kind(kind, static_cast<const float*>(A), lda, static_cast<const float*>(W), ldw, M, N, K, epi, st);
 }
 
 Error launch_attention_f32(int dtype, const void* qkv, void* out, int64_t ldo, int rows, int T, int H, int hd, hipStream_t st) {

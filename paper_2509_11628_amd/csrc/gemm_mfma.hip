@@ -59,7 +59,7 @@ constexpr int dlds_epilogue_rows(int BM, int BN, int NS) {
 }
 
 template <int BM, int BN, int WGM, int WGN, int NS, int MODE>
-__global__ __launch_bounds__(WGM* WGN * 64) void gemm_dlds_kernel(const uint16_t* __restrict__ A, int64_t lda, int a_group, int64_t a_gstride,
+__global__ __launch_bounds__(WGM* WGN * 64) void gemm_dlds_kernel(const uint16_t* __restrict__ A, int64_t lda,
                                                                    const uint16_t* __restrict__ W, int64_t ldw, int M, int N, int K,
                                                                    int tiles_m, int tiles_n, int group_m, EpiArg<MODE> epi) {
   constexpr int NW = WGM * WGN;
@@ -99,8 +99,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_dlds_kernel(const uint16_t
   for (int g = 0; g < AG; ++g) {
     const int row = (wl + g * NL) * 8 + lrow;
     const int m = m0 + row < M ? m0 + row : M - 1;
-    const int rg = a_group < M ? m / a_group : 0;
-    pa[g] = A + rg * a_gstride + static_cast<int64_t>(m - rg * a_group) * lda + lchunk * 8;
+    pa[g] = A + static_cast<int64_t>(m) * lda + lchunk * 8;
   }
 #pragma unroll
   for (int g = 0; g < WG; ++g) {
@@ -347,7 +346,7 @@ Error launch_dlds(const Operands& o, const GemmEpi& epi, hipStream_t st) {
       SPECA_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem))); \
       attr_set = true;                                                                                            \
     }                                                                                                             \
-    kern<<<grid, WGM * WGN * 64, smem, st>>>(o.a, o.lda, o.a_group, o.a_gstride, o.w, o.ldw, o.M, o.N, o.K, tiles_m, tiles_n, group_m, epi_arg<MODE_>(epi)); \
+    kern<<<grid, WGM * WGN * 64, smem, st>>>(o.a, o.lda, o.w, o.ldw, o.M, o.N, o.K, tiles_m, tiles_n, group_m, epi_arg<MODE_>(epi)); \
     break;                                                                                                        \
   }
   switch (epi.mode) {

@@ -75,9 +75,9 @@ constexpr size_t lds_bytes(int BM, int BN, int NS, int KS) {
   return ring > epi ? ring : epi;
 }
 
-// Row m of A lies at A + (m / a_group) * a_gstride + (m % a_group) * lda (elements).  KTAIL: K is no multiple of a stage.
+// KTAIL: K is no multiple of a stage.
 template <int BM, int BN, int WGM, int WGN, int NS, int KS, bool STAGE_AHEAD, int MODE, bool KTAIL>
-__global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(const uint16_t* __restrict__ A, int64_t lda, int a_group, int64_t a_gstride,
+__global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(const uint16_t* __restrict__ A, int64_t lda,
                                                         const uint16_t* __restrict__ W, int64_t ldw, int M, int N, int K, int tiles_m, int tiles_n,
                                                         int group_m, EpiArg<MODE> epi) {
   constexpr int NW = WGM * WGN;
@@ -121,18 +121,14 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(const uint16_t
   // repeat the last one (never stored).
   const int lrow = lane / CPR;
   auto chunk = [&](int g) { return (lane % CPR) ^ (KS == 2 ? lrow ^ (g & 1) : (g & 3) * 4 + lrow); };
-  const bool grouped = a_group < M;
-  const int g_first = grouped ? m0 / a_group : 0;
-  const char* ba = reinterpret_cast<const char*>(A + g_first * a_gstride + static_cast<int64_t>(m0 - g_first * a_group) * lda);
+  const char* ba = reinterpret_cast<const char*>(A + static_cast<int64_t>(m0) * lda);
   const char* bw = reinterpret_cast<const char*>(W + static_cast<int64_t>(n0) * ldw);
   uint32_t voff[LPW];
 #pragma unroll
   for (int u = 0; u < LPW; ++u) {
     if (u < AL) {
       const int g = wave + NW * u, r = g * GR + lrow;
-      const int m = m0 + r < M ? m0 + r : M - 1;
-      const int grp = grouped ? m / a_group : 0;
-      voff[u] = static_cast<uint32_t>(((grp - g_first) * a_gstride + static_cast<int64_t>(m - grp * a_group - (m0 - g_first * a_group)) * lda) * 2 + chunk(g) * 16);
+      voff[u] = static_cast<uint32_t>(static_cast<int64_t>(m0 + r < M ? r : M - 1 - m0) * lda * 2 + chunk(g) * 16);
     } else {
       const int g = wave + NW * (u - AL), r = g * GR + lrow;
       voff[u] = static_cast<uint32_t>(static_cast<int64_t>(n0 + r < N ? r : N - 1 - n0) * ldw * 2 + chunk(g) * 16);
@@ -273,7 +269,7 @@ Error launch_mode(const Operands& o, const GemmEpi& epi, hipStream_t st) {
     attr_set = true;
   }
   const int group_m = tiles_m < 4 ? tiles_m : 4;
-  kern<<<static_cast<unsigned>((nblk + 7) / 8 * 8), WGM * WGN * 64, smem, st>>>(o.a, o.lda, o.a_group, o.a_gstride, o.w, o.ldw, o.M, o.N, o.K, tiles_m, tiles_n, group_m,
+  kern<<<static_cast<unsigned>((nblk + 7) / 8 * 8), WGM * WGN * 64, smem, st>>>(o.a, o.lda, o.w, o.ldw, o.M, o.N, o.K, tiles_m, tiles_n, group_m,
                                                                     epi_arg<MODE>(epi));
   SPECA_HIP(hipGetLastError());
   return ok();

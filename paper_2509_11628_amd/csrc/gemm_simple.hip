@@ -17,7 +17,7 @@ template <> __device__ inline float ld_as_f32<bf16_t>(const bf16_t* p) { return 
 constexpr int TM = 64, TN = 64, TK = 16;
 
 template <typename T, int MODE>
-__global__ __launch_bounds__(256) void gemm_simple_kernel(const T* __restrict__ A, int64_t lda, int a_group, int64_t a_gstride,
+__global__ __launch_bounds__(256) void gemm_simple_kernel(const T* __restrict__ A, int64_t lda,
                                                           const T* __restrict__ W, int64_t ldw, int M, int N, int K, EpiArg<MODE> epi) {
   __shared__ float As[TK][TM + 4];
   __shared__ float Ws[TK][TN + 4];
@@ -38,8 +38,7 @@ __global__ __launch_bounds__(256) void gemm_simple_kernel(const T* __restrict__ 
       const int k = k0 + kk;
       float a = 0.0f, w = 0.0f;
       if (k < K) {
-        const int rg = (m0 + row) / a_group;
-        if (m0 + row < M) a = ld_as_f32(A + rg * a_gstride + static_cast<int64_t>(m0 + row - rg * a_group) * lda + k);
+        if (m0 + row < M) a = ld_as_f32(A + static_cast<int64_t>(m0 + row) * lda + k);
         if (n0 + row < N) w = ld_as_f32(W + static_cast<int64_t>(n0 + row) * ldw + k);
       }
       As[kk][row] = a;
@@ -71,16 +70,16 @@ __global__ __launch_bounds__(256) void gemm_simple_kernel(const T* __restrict__ 
 }
 
 template <typename T>
-Error launch_simple_t(const void* A, int64_t lda, int a_group, int64_t a_gstride, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st) {
+Error launch_simple_t(const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st) {
   dim3 grid((N + TN - 1) / TN, (M + TM - 1) / TM);
   const T* a = static_cast<const T*>(A);
   const T* w = static_cast<const T*>(W);
   switch (epi.mode) {
-    case EPI_STORE: gemm_simple_kernel<T, EPI_STORE><<<grid, 256, 0, st>>>(a, lda, a_group, a_gstride, w, ldw, M, N, K, epi_arg<EPI_STORE>(epi)); break;
-    case EPI_GELU: gemm_simple_kernel<T, EPI_GELU><<<grid, 256, 0, st>>>(a, lda, a_group, a_gstride, w, ldw, M, N, K, epi_arg<EPI_GELU>(epi)); break;
-    case EPI_SILU: gemm_simple_kernel<T, EPI_SILU><<<grid, 256, 0, st>>>(a, lda, a_group, a_gstride, w, ldw, M, N, K, epi_arg<EPI_SILU>(epi)); break;
-    case EPI_F32: gemm_simple_kernel<T, EPI_F32><<<grid, 256, 0, st>>>(a, lda, a_group, a_gstride, w, ldw, M, N, K, epi_arg<EPI_F32>(epi)); break;
-    case EPI_BRANCH: gemm_simple_kernel<T, EPI_BRANCH><<<grid, 256, 0, st>>>(a, lda, a_group, a_gstride, w, ldw, M, N, K, epi_arg<EPI_BRANCH>(epi)); break;
+    case EPI_STORE: gemm_simple_kernel<T, EPI_STORE><<<grid, 256, 0, st>>>(a, lda, w, ldw, M, N, K, epi_arg<EPI_STORE>(epi)); break;
+    case EPI_GELU: gemm_simple_kernel<T, EPI_GELU><<<grid, 256, 0, st>>>(a, lda, w, ldw, M, N, K, epi_arg<EPI_GELU>(epi)); break;
+    case EPI_SILU: gemm_simple_kernel<T, EPI_SILU><<<grid, 256, 0, st>>>(a, lda, w, ldw, M, N, K, epi_arg<EPI_SILU>(epi)); break;
+    case EPI_F32: gemm_simple_kernel<T, EPI_F32><<<grid, 256, 0, st>>>(a, lda, w, ldw, M, N, K, epi_arg<EPI_F32>(epi)); break;
+    case EPI_BRANCH: gemm_simple_kernel<T, EPI_BRANCH><<<grid, 256, 0, st>>>(a, lda, w, ldw, M, N, K, epi_arg<EPI_BRANCH>(epi)); break;
     default: SPECA_FAIL(SPECA_EINVAL, "gemm: epilogue mode %d", epi.mode);
   }
   SPECA_HIP(hipGetLastError());
@@ -172,10 +171,10 @@ Error launch_attn_hd(const void* qkv, void* out, int64_t ldo, int rows, int Tn, 
 
 }  // namespace
 
-Error launch_gemm_simple(int dtype, const void* A, int64_t lda, int a_group, int64_t a_gstride, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi,
+Error launch_gemm_simple(int dtype, const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi,
                          hipStream_t st) {
-  return dtype == SPECA_BF16 ? launch_simple_t<bf16_t>(A, lda, a_group, a_gstride, W, ldw, M, N, K, epi, st)
-                             : launch_simple_t<float>(A, lda, a_group, a_gstride, W, ldw, M, N, K, epi, st);
+  return dtype == SPECA_BF16 ? launch_simple_t<bf16_t>(A, lda, W, ldw, M, N, K, epi, st)
+                             : launch_simple_t<float>(A, lda, W, ldw, M, N, K, epi, st);
 }
 
 Error launch_attention_simple(int dtype, const void* qkv, void* out, int64_t ldo, int rows, int T, int H, int hd, hipStream_t st) {

@@ -9,12 +9,9 @@ namespace speca {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-// Row m of A lies at a + (m / a_group) * a_gstride + (m % a_group) * lda (elements).
 struct Operands {
   const uint16_t* a;
   int64_t lda;
-  int a_group;
-  int64_t a_gstride;
   const uint16_t* w;
   int64_t ldw;
   int M, N, K;
