@@ -6,7 +6,7 @@ namespace speca {
 Error launch_gemm_simple(int dtype, const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K,
                          const GemmEpi& epi, hipStream_t st);
 Error launch_attention_simple(int dtype, const void* qkv, void* out, int64_t ldo, int rows, int T, int H, int hd, hipStream_t st);
-bool gemm_mfma_supported(const void* A, int64_t lda, const void* W, int64_t ldw, int N, int K);
+bool gemm_mfma_supported(const Operands& o);
 Error launch_gemm_mfma(const Operands& o, const GemmEpi& epi, hipStream_t st);
 
 bool gemm_f32_supported(const void* A, int64_t lda, const void* W, int64_t ldw, int K);
@@ -35,9 +35,10 @@ Error launch_gemm(int dtype, const void* A, int64_t lda, const void* W, int64_t 
   } else if (!epi.out || epi.ldo < N) {
     SPECA_FAIL(SPECA_EINVAL, "gemm: output missing");
   }
-  // 2^23: the matrix kernels take byte offsets of 32 bits inside a tile
-  if (dtype == SPECA_BF16 && lda <= (1 << 23) && gemm_mfma_supported(A, lda, W, ldw, N, K))
-    return launch_gemm_mfma({static_cast<const uint16_t*>(A), lda, static_cast<const uint16_t*>(W), ldw, M, N, K}, epi, st);
+  if (dtype == SPECA_BF16) {
+    const Operands o{static_cast<const uint16_t*>(A), lda, static_cast<const uint16_t*>(W), ldw, M, N, K};
+    if (gemm_mfma_supported(o)) return launch_gemm_mfma(o, epi, st);
+  }
   if (dtype == SPECA_F32 && gemm_f32_supported(A, lda, W, ldw, K))
     return launch_gemm_f32(A, lda, W, ldw, M, N, K, epi, st);
   return launch_gemm_simple(dtype, A, lda, W, ldw, M, N, K, epi, st);

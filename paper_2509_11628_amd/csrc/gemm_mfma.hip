@@ -16,6 +16,7 @@
 // ring of NS stages with one raw barrier per K-step, loads awaited with vmcnt(0) by the waves that issued them.
 // Needs K % 64 == 0.  Tiles 256x128 and 256x256 (half the L2 -> LDS bytes per FLOP of 128x128).
 
+#include <algorithm>
 #include <cmath>
 
 #include "gemm_tile.h"
@@ -364,12 +365,6 @@ Error launch_dlds(const Operands& o, const GemmEpi& epi, hipStream_t st) {
 
 }  // namespace
 
-bool gemm_mfma_supported(const void* A, int64_t lda, const void* W, int64_t ldw, int N, int K) {
-  // 2^23: offsets inside a tile are 32-bit byte counts (up to 191 rows of 2-byte elements from its first row)
-  return (K % 8 == 0) && (lda % 8 == 0) && (ldw % 8 == 0) && ldw <= (1 << 23) && (N % 4 == 0) &&
-         (reinterpret_cast<uintptr_t>(A) % 16 == 0) && (reinterpret_cast<uintptr_t>(W) % 16 == 0);
-}
-
 // ---- tile choice -------------------------------------------------------------------------------------------
 // Thirteen kernels can run a given problem; which is fastest depends on how the tile count falls on the chip's compute
 // units more than on anything else (a 270-tile launch of one-block-per-CU tiles takes two rounds, a 252-tile one
@@ -423,14 +418,22 @@ static double tile_cost(const TileKind& t, int M, int N, int K) {
   return t.a + (t.c + t.b * ((K + BK - 1) / BK)) * rounds;
 }
 
-// cheapest eligible kernel for the problem; *cost receives its modelled time
-static int pick_tile(int M, int N, int K, double* cost) {
+// Whether a kind can run the problem.  The rings hold a row's place inside the tile as a 32-bit byte offset, which bounds the
+// stride of the rows (11 million elements for the tallest tile); the large tiles hold pointers.
+static bool tile_fits(const TileKind& t, const Operands& o) {
+  if (t.whole_steps) return o.K % BK == 0 && o.K >= BK;
+  constexpr int64_t kReach = (int64_t{1} << 31) - 128;               // elements, less a row's own 256 bytes
+  return (std::min(t.bm, o.M) - 1) * o.lda < kReach && (std::min(t.bn, o.N) - 1) * o.ldw < kReach;
+}
+
+// cheapest eligible kernel for the problem (-1: none); *cost receives its modelled time
+static int pick_tile(const Operands& o, double* cost) {
   int best = -1;
   double bc = 0.0;
   for (int k = 0; k < kKinds; ++k) {
     const TileKind& t = kTileKinds[k];
-    if (t.whole_steps && (K % BK != 0 || K < BK)) continue;
-    const double c = tile_cost(t, M, N, K);
+    if (!tile_fits(t, o)) continue;
+    const double c = tile_cost(t, o.M, o.N, o.K);
     if (best < 0 || c < bc) { best = k; bc = c; }
   }
   *cost = bc;
@@ -445,9 +448,15 @@ static Error launch_kind(int kind, const Operands& o, const GemmEpi& epi, hipStr
   }
 }
 
+bool gemm_mfma_supported(const Operands& o) {
+  double cost = 0.0;
+  return (o.K % 8 == 0) && (o.lda % 8 == 0) && (o.ldw % 8 == 0) && (o.N % 4 == 0) && (reinterpret_cast<uintptr_t>(o.a) % 16 == 0) &&
+         (reinterpret_cast<uintptr_t>(o.w) % 16 == 0) && pick_tile(o, &cost) >= 0;
+}
+
 Error launch_gemm_mfma(const Operands& o, const GemmEpi& epi, hipStream_t st) {
   double whole = 0.0;
-  const int kind = pick_tile(o.M, o.N, o.K, &whole);
+  const int kind = pick_tile(o, &whole);
   // A little more than whole rounds of 256x256 tiles (the 4096 x 4608 x 1152 fc1 GEMM: 288): the columns that make whole
   // rounds go on the large tile, the remaining columns in a second launch (47 + 13 us against 61 us for the best single
   // kernel; 4096 x 9216 x 3072, 576 tiles: 236 -> 207 us).  Column ranges only shift pointers, so this is limited to the epilogues that store into `out`.
@@ -459,7 +468,9 @@ Error launch_gemm_mfma(const Operands& o, const GemmEpi& epi, hipStream_t st) {
       if (n1 >= o.N) break;
       double rest = 0.0;
       if (n1 >= 256) {
-        (void)pick_tile(o.M, o.N - n1, o.K, &rest);
+        Operands tail = o;
+        tail.N = o.N - n1;
+        (void)pick_tile(tail, &rest);
         rest += tile_cost(kTileKinds[0], o.M, n1, o.K);
         if (rest < 0.96 * whole) { head = n1; whole = rest / 0.96; }
       }
@@ -474,7 +485,7 @@ Error launch_gemm_mfma(const Operands& o, const GemmEpi& epi, hipStream_t st) {
       tail.w += static_cast<int64_t>(head) * o.ldw;
       tail.N = o.N - head;
       double cost = 0.0;
-      return launch_kind(pick_tile(tail.M, tail.N, tail.K, &cost), tail, te, st);
+      return launch_kind(pick_tile(tail, &cost), tail, te, st);
     }
   }
   return launch_kind(kind, o, epi, st);

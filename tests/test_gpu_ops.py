@@ -216,6 +216,34 @@ def test_linear_f32_of_more_row_tiles_than_a_grid_dimension():
     _check(bd.linear(_dev(a, "f32"), _dev(w, "f32")), odit.linear(a.astype(np.float64), w.astype(np.float64), None), "f32", K)
 
 
+@pytest.mark.parametrize("K", [2 ** 23 + 64, 2 ** 23 + 8])
+def test_linear_bf16_of_very_long_rows_keeps_the_matrix_kernels(K):
+    """Row strides past 2^23: offsets inside a small tile still fit into 32 bits.  The plain kernel, an order of magnitude slower
+    per column, is told apart by its time against a sixteenth of the columns."""
+    bd = _bd()
+    M, N = 3, 8
+    g = torch.Generator(device="cuda").manual_seed(1)
+    a = torch.randn((M, K), generator=g, device="cuda").to(torch.bfloat16)
+    w = torch.randn((N, K), generator=g, device="cuda").to(torch.bfloat16)
+    exp = (a.double() @ w.double().T).cpu().numpy()
+    # fp32 sums of K products in order: rounding errors of random sign, 2^-24 sqrt(K) of the magnitude; then one bf16 rounding
+    err = np.abs(bd.linear(a, w).double().cpu().numpy() - exp)
+    assert np.all(err <= 2.0 ** -8 * np.abs(exp) + 2.0 ** -24 * np.sqrt(K) * 8 * np.max(np.abs(exp)))
+
+    def ms(x, y):
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        bd.linear(x, y)
+        start.record()
+        for _ in range(3):
+            bd.linear(x, y)
+        end.record()
+        end.synchronize()
+        return start.elapsed_time(end)
+
+    k = K // 128 * 8
+    assert ms(a, w) < 16 * 4 * ms(a[:, :k].contiguous(), w[:, :k].contiguous())
+
+
 @pytest.mark.parametrize("T,hd", [(256, 72), (200, 72), (96, 64)])
 def test_attention_short_sequence_into_an_output_at_8_byte_alignment(T, hd):
     """The whole-sequence kernel (T <= 256) stores 16-byte chunks; an output that is only 8-byte aligned takes the tiled
