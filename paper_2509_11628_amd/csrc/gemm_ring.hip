@@ -32,7 +32,7 @@ __device__ __align__(16) const uint32_t kZeroChunk[4] = {0u, 0u, 0u, 0u};
 // The matrix instructions of the first loop are written as assembly: left to the compiler, the accumulators travel between
 // the vector and the accumulation registers in every step (20 to 250 moves).  Up to 6 accumulators stay in vector registers,
 // the 9 of a 96x96 wave tile in the accumulation file.  The compiler adds no wait states around assembly: mma_begin fixes the
-// zeros in their registers ahead of the loop and results are read behind it, with the states in between written out; an
+// zeros in their registers ahead of the loop and mma_end the results behind it, with the states in between written out; an
 // accumulator is used again after at least one other instruction of 8 passes, and fragments come from LDS reads that were
 // waited for (they must not pass through other registers: few enough of them are live).
 template <bool ASM, int TILES>
@@ -47,6 +47,10 @@ __device__ __forceinline__ void mma_begin(floatx16& c) {
   if constexpr (ASM && TILES > 6) asm volatile("" : "+a"(c));
   else if constexpr (ASM) asm volatile("" : "+v"(c));
 }
+
+// The accumulator as it is from here on, like mma_begin: both only pin its uses to one side (assembly keeps its order).
+template <bool ASM, int TILES>
+__device__ __forceinline__ void mma_end(floatx16& c) { mma_begin<ASM, TILES>(c); }
 
 constexpr int kWaitLds = 0xC07F;                             // s_waitcnt lgkmcnt(0)
 constexpr int wait_loads(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }       // s_waitcnt vmcnt(n)
@@ -252,7 +256,13 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(const uint16_t
 #undef SPECA_BARRIER
 #undef SPECA_PIN
   __builtin_amdgcn_s_waitcnt(wait_loads(0));                 // nothing is outstanding here; kept as a guard before LDS is reused
-  if (!STAGE_AHEAD) asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");     // matrix results to vector reads: 18 wait states at most
+  if (!STAGE_AHEAD) {
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");       // matrix results to vector reads: 18 wait states at most
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+      for (int j = 0; j < TM; ++j) mma_end<!STAGE_AHEAD, TM * TN>(acc[i][j]);      // no read of an accumulator moves ahead of the wait
+  }
   tile_epilogue<BM, BN, WGM, WGN, MODE, EH>(acc, reinterpret_cast<float*>(smem), m0, n0, M, N, epi);
 }
 
