@@ -375,26 +375,33 @@ Error launch_dlds(const Operands& o, const GemmEpi& epi, hipStream_t st) {
 // a: launch; c: prologue and epilogue; b: one 64-wide K-step; r: what a further round, or the second block, costs.  Fitted to
 // 224 problems with cold weights (the layers of 384 to 3072 features at 16 to 8192 rows, and random sizes) so that the time
 // of the kernels picked is least (0.9 % above the best kernel of each on the mean) and the times themselves fit (12 % rms).
+// The branch epilogue (residual read and written in fp32, cache planes) is two to four times as long as a plain store, the more so
+// the fewer waves a tile has for its elements, so c and r have second values for it.  Fitted to the layers of
+// 384 to 3072 features inside running models, 256 to 26624 rows, both cache layouts: the time of a block lies 0.1 % above
+// that with the best kernels on the mean where the plain constants lay 0.6 % (7 % at worst; 4096 x 1152 x 1152 without plane reads 6.8 us
+// above, with them 22.7, 9216 x 3072 x 12288 with them 152).  192x192 and 128x96 are not offered to it: leaving them out costs
+// 0.02 %.
 struct TileKind {
   int bm, bn;
   float a, c, b, r;    // three in microseconds, a ratio
+  float cb, rb;        // c and r under the branch epilogue (cb = 0: not offered to it)
   bool two;            // two blocks fit on a compute unit
   bool whole_steps;    // K % 64 == 0
 };
 constexpr TileKind kTileKinds[] = {
-    {256, 256, 2.2f, 7.52f, 1.442f, 1.02f, false, true},    // 0: large, 2 stages
-    {256, 128, 2.3f, 4.83f, 0.816f, 1.15f, false, true},    // 1: large, 3 stages
-    {128, 128, 0.8f, 6.40f, 0.535f, 1.00f, false, false},   // 2: ring of 4 stages x 64 columns
-    {128, 128, 0.9f, 3.71f, 0.771f, 0.31f, true, false},    // 3: ring of 2 x 64
-    {128, 64, 0.8f, 4.18f, 0.314f, 1.08f, false, false},    // 4: ring of 3 x 128
-    {128, 64, 2.1f, 1.41f, 0.379f, 0.66f, true, false},     // 5: ring of 3 x 64
-    {64, 64, 0.0f, 3.98f, 0.294f, 0.95f, false, false},     // 6: ring of 4 x 128
-    {32, 64, 0.0f, 3.67f, 0.266f, 0.98f, false, false},     // 7: ring of 4 x 128, two waves
-    {192, 128, 1.3f, 5.69f, 0.656f, 1.15f, false, false},   // 8: ring of 3 x 64
-    {128, 192, 1.3f, 6.75f, 0.882f, 0.42f, true, false},    // 9: ring of 2 x 64
-    {192, 192, 2.5f, 11.1f, 0.879f, 1.08f, false, false},   // 10: ring of 3 x 64
-    {96, 128, 0.0f, 4.72f, 0.435f, 1.07f, false, false},    // 11: ring of 4 x 64
-    {128, 96, 1.2f, 3.06f, 0.710f, 0.30f, true, false},     // 12: ring of 2 x 64
+    {256, 256, 2.2f, 7.52f, 1.442f, 1.02f, 13.89f, 0.83f, false, true},    // 0: large, 2 stages
+    {256, 128, 2.3f, 4.83f, 0.816f, 1.15f, 9.16f, 1.05f, false, true},     // 1: large, 3 stages
+    {128, 128, 0.8f, 6.40f, 0.535f, 1.00f, 11.39f, 0.98f, false, false},   // 2: ring of 4 stages x 64 columns
+    {128, 128, 0.9f, 3.71f, 0.771f, 0.31f, 8.66f, 0.11f, true, false},     // 3: ring of 2 x 64
+    {128, 64, 0.8f, 4.18f, 0.314f, 1.08f, 7.46f, 0.98f, false, false},     // 4: ring of 3 x 128
+    {128, 64, 2.1f, 1.41f, 0.379f, 0.66f, 5.21f, 0.50f, true, false},      // 5: ring of 3 x 64
+    {64, 64, 0.0f, 3.98f, 0.294f, 0.95f, 4.60f, 0.86f, false, false},      // 6: ring of 4 x 128
+    {32, 64, 0.0f, 3.67f, 0.266f, 0.98f, 4.61f, 0.77f, false, false},      // 7: ring of 4 x 128, two waves
+    {192, 128, 1.3f, 5.69f, 0.656f, 1.15f, 21.68f, 0.85f, false, false},   // 8: ring of 3 x 64
+    {128, 192, 1.3f, 6.75f, 0.882f, 0.42f, 13.46f, 0.19f, true, false},    // 9: ring of 2 x 64
+    {192, 192, 2.5f, 11.1f, 0.879f, 1.08f, 0.0f, 0.0f, false, false},      // 10: ring of 3 x 64
+    {96, 128, 0.0f, 4.72f, 0.435f, 1.07f, 13.07f, 0.84f, false, false},    // 11: ring of 4 x 64
+    {128, 96, 1.2f, 3.06f, 0.710f, 0.30f, 0.0f, 0.0f, true, false},        // 12: ring of 2 x 64
 };
 constexpr int kKinds = sizeof(kTileKinds) / sizeof(kTileKinds[0]);
 
@@ -410,12 +417,13 @@ static int compute_units() {
   return n;
 }
 
-static double tile_cost(const TileKind& t, int M, int N, int K) {
+static double tile_cost(const TileKind& t, bool branch, int M, int N, int K) {
   const double tiles = static_cast<double>((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
   const double depth = std::ceil(tiles / compute_units());
   const double odd = std::fmod(depth, 2.0);
-  const double rounds = t.two ? (depth - odd) / 2 * (1.0 + t.r) + odd : 1.0 + t.r * (depth - 1.0);
-  return t.a + (t.c + t.b * ((K + BK - 1) / BK)) * rounds;
+  const double c = branch ? t.cb : t.c, r = branch ? t.rb : t.r;
+  const double rounds = t.two ? (depth - odd) / 2 * (1.0 + r) + odd : 1.0 + r * (depth - 1.0);
+  return t.a + (c + t.b * ((K + BK - 1) / BK)) * rounds;
 }
 
 // Whether a kind can run the problem.  The rings hold a row's place inside the tile as a 32-bit byte offset, which bounds the
@@ -427,13 +435,13 @@ static bool tile_fits(const TileKind& t, const Operands& o) {
 }
 
 // cheapest eligible kernel for the problem (-1: none); *cost receives its modelled time
-static int pick_tile(const Operands& o, double* cost) {
+static int pick_tile(const Operands& o, bool branch, double* cost) {
   int best = -1;
   double bc = 0.0;
   for (int k = 0; k < kKinds; ++k) {
     const TileKind& t = kTileKinds[k];
-    if (!tile_fits(t, o)) continue;
-    const double c = tile_cost(t, o.M, o.N, o.K);
+    if (!tile_fits(t, o) || (branch && t.cb == 0.0f)) continue;
+    const double c = tile_cost(t, branch, o.M, o.N, o.K);
     if (best < 0 || c < bc) { best = k; bc = c; }
   }
   *cost = bc;
@@ -451,16 +459,17 @@ static Error launch_kind(int kind, const Operands& o, const GemmEpi& epi, hipStr
 bool gemm_mfma_supported(const Operands& o) {
   double cost = 0.0;
   return (o.K % 8 == 0) && (o.lda % 8 == 0) && (o.ldw % 8 == 0) && (o.N % 4 == 0) && (reinterpret_cast<uintptr_t>(o.a) % 16 == 0) &&
-         (reinterpret_cast<uintptr_t>(o.w) % 16 == 0) && pick_tile(o, &cost) >= 0;
+         (reinterpret_cast<uintptr_t>(o.w) % 16 == 0) && pick_tile(o, true, &cost) >= 0;     // the smallest tile, which fits whenever one does, serves every epilogue
 }
 
 Error launch_gemm_mfma(const Operands& o, const GemmEpi& epi, hipStream_t st) {
   double whole = 0.0;
-  const int kind = pick_tile(o, &whole);
+  const bool branch = epi.mode == EPI_BRANCH;
+  const int kind = pick_tile(o, branch, &whole);
   // A little more than whole rounds of 256x256 tiles (the 4096 x 4608 x 1152 fc1 GEMM: 288): the columns that make whole
   // rounds go on the large tile, the remaining columns in a second launch (47 + 13 us against 61 us for the best single
   // kernel; 4096 x 9216 x 3072, 576 tiles: 236 -> 207 us).  Column ranges only shift pointers, so this is limited to the epilogues that store into `out`.
-  if (epi.mode != EPI_BRANCH && o.K % BK == 0 && o.K >= BK && o.M >= 256) {
+  if (!branch && o.K % BK == 0 && o.K >= BK && o.M >= 256) {
     const int tiles_m = (o.M + 255) / 256;
     int head = 0;
     for (int rounds = 1;; ++rounds) {
@@ -470,8 +479,8 @@ Error launch_gemm_mfma(const Operands& o, const GemmEpi& epi, hipStream_t st) {
       if (n1 >= 256) {
         Operands tail = o;
         tail.N = o.N - n1;
-        (void)pick_tile(tail, &rest);
-        rest += tile_cost(kTileKinds[0], o.M, n1, o.K);
+        (void)pick_tile(tail, false, &rest);
+        rest += tile_cost(kTileKinds[0], false, o.M, n1, o.K);
         if (rest < 0.96 * whole) { head = n1; whole = rest / 0.96; }
       }
     }
@@ -485,7 +494,7 @@ Error launch_gemm_mfma(const Operands& o, const GemmEpi& epi, hipStream_t st) {
       tail.w += static_cast<int64_t>(head) * o.ldw;
       tail.N = o.N - head;
       double cost = 0.0;
-      return launch_kind(pick_tile(tail, &cost), tail, te, st);
+      return launch_kind(pick_tile(tail, false, &cost), tail, te, st);
     }
   }
   return launch_kind(kind, o, epi, st);

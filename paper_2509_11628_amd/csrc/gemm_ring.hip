@@ -285,38 +285,40 @@ Error launch_mode(const Operands& o, const GemmEpi& epi, hipStream_t st) {
   return ok();
 }
 
-template <int BM, int BN, int WGM, int WGN, int NS, int KS, bool SA>
+// BRANCH: the tile is offered to the branch epilogue (see the table in gemm_mfma.hip).
+template <int BM, int BN, int WGM, int WGN, int NS, int KS, bool SA, bool BRANCH>
 Error launch_tile(const Operands& o, const GemmEpi& epi, hipStream_t st) {
-#define SPECA_LAUNCH(MODE_)                                                                                    \
-  case MODE_:                                                                                                  \
-    return o.K % (32 * KS) ? launch_mode<BM, BN, WGM, WGN, NS, KS, SA, MODE_, true>(o, epi, st)                \
-                           : launch_mode<BM, BN, WGM, WGN, NS, KS, SA, MODE_, false>(o, epi, st);
+#define SPECA_LAUNCH(MODE_)                                                                                  \
+  return o.K % (32 * KS) ? launch_mode<BM, BN, WGM, WGN, NS, KS, SA, MODE_, true>(o, epi, st)                \
+                         : launch_mode<BM, BN, WGM, WGN, NS, KS, SA, MODE_, false>(o, epi, st);
   switch (epi.mode) {
-    SPECA_LAUNCH(EPI_STORE)
-    SPECA_LAUNCH(EPI_GELU)
-    SPECA_LAUNCH(EPI_SILU)
-    SPECA_LAUNCH(EPI_F32)
-    SPECA_LAUNCH(EPI_BRANCH)
+    case EPI_STORE: SPECA_LAUNCH(EPI_STORE)
+    case EPI_GELU: SPECA_LAUNCH(EPI_GELU)
+    case EPI_SILU: SPECA_LAUNCH(EPI_SILU)
+    case EPI_F32: SPECA_LAUNCH(EPI_F32)
+    case EPI_BRANCH:
+      if constexpr (BRANCH) { SPECA_LAUNCH(EPI_BRANCH) }
+      break;
   }
 #undef SPECA_LAUNCH
-  SPECA_FAIL(SPECA_EINVAL, "gemm: epilogue mode %d", epi.mode);
+  SPECA_FAIL(SPECA_EINVAL, "gemm: epilogue mode %d on a %d x %d tile", epi.mode, BM, BN);
 }
 
 }  // namespace
 
 Error launch_gemm_ring(int kind, const Operands& o, const GemmEpi& epi, hipStream_t st) {
   switch (kind) {
-    case 0: return launch_tile<128, 128, 2, 2, 4, 2, false>(o, epi, st);
-    case 1: return launch_tile<128, 128, 2, 2, 2, 2, false>(o, epi, st);
-    case 2: return launch_tile<128, 64, 2, 2, 3, 4, false>(o, epi, st);
-    case 3: return launch_tile<128, 64, 2, 2, 3, 2, false>(o, epi, st);
-    case 4: return launch_tile<64, 64, 2, 2, 4, 4, true>(o, epi, st);
-    case 5: return launch_tile<32, 64, 1, 2, 4, 4, true>(o, epi, st);
-    case 6: return launch_tile<192, 128, 2, 2, 3, 2, false>(o, epi, st);
-    case 7: return launch_tile<128, 192, 2, 2, 2, 2, false>(o, epi, st);
-    case 8: return launch_tile<192, 192, 2, 2, 3, 2, false>(o, epi, st);
-    case 9: return launch_tile<96, 128, 1, 4, 4, 2, false>(o, epi, st);
-    case 10: return launch_tile<128, 96, 4, 1, 2, 2, false>(o, epi, st);
+    case 0: return launch_tile<128, 128, 2, 2, 4, 2, false, true>(o, epi, st);
+    case 1: return launch_tile<128, 128, 2, 2, 2, 2, false, true>(o, epi, st);
+    case 2: return launch_tile<128, 64, 2, 2, 3, 4, false, true>(o, epi, st);
+    case 3: return launch_tile<128, 64, 2, 2, 3, 2, false, true>(o, epi, st);
+    case 4: return launch_tile<64, 64, 2, 2, 4, 4, true, true>(o, epi, st);
+    case 5: return launch_tile<32, 64, 1, 2, 4, 4, true, true>(o, epi, st);
+    case 6: return launch_tile<192, 128, 2, 2, 3, 2, false, true>(o, epi, st);
+    case 7: return launch_tile<128, 192, 2, 2, 2, 2, false, true>(o, epi, st);
+    case 8: return launch_tile<192, 192, 2, 2, 3, 2, false, false>(o, epi, st);
+    case 9: return launch_tile<96, 128, 1, 4, 4, 2, false, true>(o, epi, st);
+    case 10: return launch_tile<128, 96, 4, 1, 2, 2, false, false>(o, epi, st);
   }
   SPECA_FAIL(SPECA_EINVAL, "gemm: no such tile");
 }

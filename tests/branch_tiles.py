@@ -1,0 +1,45 @@
+"""Model shapes whose two branch layers (attention projection: rows x hidden x hidden, second MLP layer: rows x hidden x
+mlp_hidden) fall on each tile that the library runs the branch epilogue on, and the library's tile choice in Python, read
+from the table in its source, so that a refitted table does not silently move a shape to another tile."""
+import math
+import os
+import re
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+COMPUTE_UNITS = 256
+
+# rows, grid (tokens = grid^2), hidden, heads, mlp_hidden, (tile of the projection, tile of the second MLP layer)
+# tokens divide no tile height, so tiles span rows of the batch; hidden is no multiple of most tile widths
+CASES = [
+    (6, 15, 360, 5, 424, ((64, 64), (64, 64))),
+    (12, 15, 360, 5, 1288, ((128, 64), (128, 64))),
+    (7, 17, 1440, 20, 5760, ((128, 64), (128, 128))),
+    (56, 14, 360, 5, 424, ((128, 128), (128, 128))),
+    (55, 20, 360, 5, 424, ((128, 192), (128, 192))),
+    (11, 15, 792, 11, 3168, ((64, 64), (96, 128))),
+    (33, 20, 792, 11, 640, ((128, 128), (256, 256))),
+    (35, 9, 1440, 20, 5760, ((128, 128), (192, 128))),
+    (24, 15, 768, 12, 3072, ((128, 128), (256, 128))),
+]
+
+
+def tile_table():
+    src = open(os.path.join(ROOT, "paper_2509_11628_amd", "csrc", "gemm_mfma.hip")).read()
+    body = src[src.index("kTileKinds[] = {"):]
+    body = body[:body.index("};")]
+    rows = re.findall(r"\{(\d+), (\d+), ([\d.]+)f, ([\d.]+)f, ([\d.]+)f, ([\d.]+)f, ([\d.]+)f, ([\d.]+)f, (\w+), (\w+)\}", body)
+    return [tuple(int(v) for v in r[:2]) + tuple(float(v) for v in r[2:8]) + tuple(v == "true" for v in r[8:]) for r in rows]
+
+
+def branch_tile(table, M, N, K):
+    """(height, width) of the tile for a layer with the branch epilogue, and how much dearer the next best one is modelled."""
+    costs = []
+    for bm, bn, a, _, b, _, cb, rb, two, whole_steps in table:
+        if cb == 0.0 or (whole_steps and (K % 64 or K < 64)):
+            continue
+        depth = math.ceil(math.ceil(M / bm) * math.ceil(N / bn) / COMPUTE_UNITS)
+        odd = depth % 2
+        rounds = (depth - odd) / 2 * (1.0 + rb) + odd if two else 1.0 + rb * (depth - 1)
+        costs.append((a + (cb + b * math.ceil(K / 64)) * rounds, (bm, bn)))
+    costs.sort()
+    return costs[0][1], costs[1][0] / costs[0][0]

@@ -9,6 +9,7 @@ bf16 models."""
 import numpy as np
 import pytest
 
+import branch_tiles
 import speca_inputs as si
 from oracle import dit as odit, sampler as osamp, speca_core as core
 
@@ -63,6 +64,48 @@ def test_full_step_matches_oracle_forward(tiny):
     ctx.init_cache(sp.make_cfg(order=1, interval=4), B)
     ctx.full_step(xd, 0, [1], out1, labels=labels, timestep=640.0)
     assert torch.equal(out1[1], out[1]) and float(out1[0].abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("layout", ["differences", "ring"])
+@pytest.mark.parametrize("case", branch_tiles.CASES, ids=lambda c: f"{c[0]}x{c[1] ** 2}x{c[2]}x{c[4]}")
+def test_branch_epilogue_on_every_tile(case, layout):
+    """Residual update and cache refresh of the two branch layers, on every tile that carries them: ragged tiles that span rows of
+    the batch.  Three reference steps of all rows together leave the bits (output and forecast, which reads every plane) of
+    the same steps of a row alone, on the smallest tiles; the first step against the oracle's forward of that row."""
+    import paper_2509_11628_amd as sp
+    from paper_2509_11628_amd import binding as bd
+    rows, grid, D, H, Dm, _ = case
+    s = si.DiTShape(depth=1, hidden=D, heads=H, mlp_hidden=Dm, in_channels=4, latent_hw=2 * grid, patch=2, num_classes=10, freq_dim=32, dtype="bf16")
+    w = si.make_dit_weights(s, 0)
+    ctx = make_gpu(s, w)
+    cfg = sp.make_cfg(order=2, interval=100, layout=bd.CACHE_RING if layout == "ring" else bd.CACHE_DIFFERENCES)
+    x = {step: torch.from_numpy(si.make_latents(rows, 4, s.latent_hw, seed=step)).cuda() for step in (0, 3, 4)}
+    labels = [i % 11 for i in range(rows)]
+
+    def steps(which):
+        ctx.init_cache(cfg, rows)
+        out = torch.zeros((3, *x[0].shape), device="cuda")
+        first = None
+        for i, step in enumerate((0, 3, 4)):
+            ctx.full_step(x[step], step, which, out[i], labels=labels, timestep=900.0 - 100.0 * i)
+            if i == 0:
+                first = torch.empty((2, len(which), s.tokens, D), dtype=torch.bfloat16, device="cuda")
+                ctx.forecast(1, which, first)
+        f = torch.empty((2, len(which), s.tokens, D), dtype=torch.bfloat16, device="cuda")
+        ctx.forecast(6, which, f)
+        return out, first, f
+
+    out, first, f = steps(list(range(rows)))
+    for r in (0, rows // 2, rows - 1):
+        out1, first1, f1 = steps([r])
+        assert torch.equal(out1[:, r], out[:, r]), r
+        assert torch.equal(first1[:, 0], first[:, r]) and torch.equal(f1[:, 0], f[:, r]), r
+    r = rows // 2
+    exp, feats = odit.DiTOracle(s, w).forward(x[0][r:r + 1].cpu().numpy(), 900.0, [labels[r]])
+    assert max_abs_rel(out[0, r:r + 1].cpu().numpy(), exp) <= 2e-2
+    for j in range(2):
+        assert max_abs_rel(first[j, r].float().cpu().numpy(), feats[j][0]) <= 1.5e-2, j
+    ctx.close()
 
 
 def test_spec_step_matches_oracle(tiny):

@@ -168,3 +168,19 @@ def test_product_path_does_not_import_the_oracle():
         if f.endswith(".py"):
             txt = open(os.path.join(ROOT, "oracle", f)).read()
             assert "paper_2509_11628_amd" not in txt and "ctypes" not in txt
+
+
+def test_branch_tile_cases_reach_every_tile_of_the_branch_epilogue():
+    """The shapes of the GPU test of the branch epilogue fall on the tiles they are meant for, and together on all of them (the
+    32x64 tile serves the single rows they are compared with)."""
+    import branch_tiles as bt
+    table = bt.tile_table()
+    assert len(table) == 13
+    seen = {(32, 64)}
+    for rows, grid, D, H, Dm, want in bt.CASES:
+        for K, tile in zip((D, Dm), want):
+            got, margin = bt.branch_tile(table, rows * grid * grid, D, K)
+            assert got == tile and margin > 1.003, (rows, grid, D, K, got, margin)
+        seen |= set(want)
+    assert bt.branch_tile(table, 81, 360, 424)[0] == (32, 64)
+    assert seen == {t[:2] for t in table if t[6] > 0}
