@@ -362,7 +362,7 @@ def bench_mmdit(args, which):
 
 def gemm_subbatch_sweep():
     """The four block GEMMs of configuration 3 at the row counts a step can present (M = 512 k: per-sample rejection
-    sends any number of guidance pairs to the full pass; four lanes split 16 rows into groups of 4), TFLOP/s with
+    sends any number of guidance pairs to the full pass), TFLOP/s with
     weights rotating through 16 copies so that they come from HBM as inside a step."""
     import torch
     from paper_2509_11628_amd import binding as bd
@@ -407,7 +407,7 @@ def main():
     ap.add_argument("--interval", type=int, default=5)
     ap.add_argument("--layout", choices=["differences", "ring"], default="ring",
                     help="what the cache planes hold: the differences of Eq. 3, or the raw features of the last m+1 full steps")
-    ap.add_argument("--lanes", type=int, default=4, help="row groups of a step that run side by side (1 = serial)")
+    ap.add_argument("--lanes", type=int, default=4, help="1: the rows of a step run strictly serially; 2 to 4: as two groups side by side where the library expects that to be faster")
     args = ap.parse_args()
     if args.gpus != 1:
         print("bench.py: this build runs on ONE GPU only (no collectives, no sharding); use --gpus 1", file=sys.stderr)

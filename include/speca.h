@@ -272,10 +272,11 @@ typedef struct speca_profile {
 } speca_profile;
 
 /* Lanes (an execution option, not part of the method; Sec. 3.2's steps are computed per sample, so
- * the rows of a launch are independent).  A step runs its rows in up to `lanes` groups side by side
- * on library-owned streams forked from and joined to the context's stream with events, so callers
- * see the usual stream order and bit-identical results.  Default 4 (SPECA_LANES in the environment
- * at create overrides), 1 = strictly serial, at most 4.  While a profile is open steps run serially
+ * the rows of a launch are independent).  A reference step of a DiT in bf16 runs its rows as two groups side by
+ * side where the library expects that to be faster, the second on a library-owned stream forked from and joined to
+ * the context's stream with events, so callers see the usual stream order and bit-identical results.  lanes = 1:
+ * strictly serial.  2 to 4: the library decides; more than two groups are never the best, so 3 and 4 act as 2.
+ * Default 4 (SPECA_LANES in the environment at create overrides).  While a profile is open steps run serially
  * (per-kernel event times are only meaningful without overlap) unless profile_keeps_lanes != 0.
  * Returns SPECA_EINVAL for a value outside 1..4. */
 int speca_set_lanes(speca_ctx* ctx, int lanes, int profile_keeps_lanes);

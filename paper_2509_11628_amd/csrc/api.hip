@@ -1,5 +1,6 @@
 // C ABI entry points (see include/speca.h): argument validation, cache ownership,
 // per-row reference bookkeeping; all arithmetic is in the kernels.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -12,6 +13,7 @@
 using namespace speca;
 
 static thread_local std::string g_create_error;
+constexpr int kMostLanesAsked = 4;      // accepted by speca_set_lanes and SPECA_LANES; more than kMaxLanes count as kMaxLanes
 
 // ---- reduction scratch of the entry point that allocates nothing -------------------------------------------
 // speca_verify_static keeps the stage-1 partial sums of Eq. 4 in this file-scope device array instead of a
@@ -220,7 +222,7 @@ static Error create_impl(speca_ctx** out, const speca_model_desc* desc, const sp
   for (int k = 0; k < kMaxLanes; ++k) SPECA_HIP(hipEventCreateWithFlags(&ctx->lane_join[k], hipEventDisableTiming));
   if (const char* e = getenv("SPECA_LANES")) {
     const int v = atoi(e);
-    if (v >= 1 && v <= kMaxLanes) ctx->lanes = v;
+    if (v >= 1 && v <= kMostLanesAsked) ctx->lanes = std::min(v, kMaxLanes);
   }
   VerifyScratch& v = ctx->vs;
   SPECA_HIP(hipHostMalloc(reinterpret_cast<void**>(&v.verdict), kMaxVerifyRows * sizeof(uint64_t), hipHostMallocMapped | hipHostMallocCoherent));
@@ -233,12 +235,10 @@ static Error create_impl(speca_ctx** out, const speca_model_desc* desc, const sp
 }
 
 namespace speca {
-LaneSplit split_lanes(const speca_ctx* ctx, int n, int min_rows) {
+LaneSplit split_lanes(const speca_ctx* ctx, int n, int wanted) {
   LaneSplit ls;
-  int k = ctx->lanes;
-  if (ctx->prof.on && !ctx->prof.keep_lanes) k = 1;
-  if (min_rows < 1) min_rows = 1;
-  while (k > 1 && n / k < min_rows) --k;
+  const int lanes = ctx->prof.on && !ctx->prof.keep_lanes ? 1 : ctx->lanes;
+  const int k = std::max(1, std::min({wanted, lanes, n}));
   ls.n_lanes = k;
   for (int i = 0; i <= k; ++i) ls.first[i] = static_cast<int>(static_cast<int64_t>(n) * i / k);
   return ls;
@@ -490,8 +490,8 @@ const char* speca_last_error(const speca_ctx* ctx) { return ctx ? ctx->err.c_str
 
 int speca_set_lanes(speca_ctx* ctx, int lanes, int profile_keeps_lanes) {
   if (!ctx) return SPECA_EINVAL;
-  if (lanes < 1 || lanes > kMaxLanes) return finish(ctx, [&]() -> Error { SPECA_FAIL(SPECA_EINVAL, "lanes = %d (1..%d)", lanes, kMaxLanes); }());
-  ctx->lanes = lanes;
+  if (lanes < 1 || lanes > kMostLanesAsked) return finish(ctx, [&]() -> Error { SPECA_FAIL(SPECA_EINVAL, "lanes = %d (1..%d)", lanes, kMostLanesAsked); }());
+  ctx->lanes = std::min(lanes, kMaxLanes);
   ctx->prof.keep_lanes = profile_keeps_lanes != 0;
   return SPECA_OK;
 }

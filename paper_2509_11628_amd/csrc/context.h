@@ -46,7 +46,7 @@ struct speca_ctx {
   // on streams of its own (lane 0 is `stream`).  While one group sits in an HBM-bound epilogue or
   // LayerNorm the other keeps the matrix cores busy, and two half-size GEMMs together fill the CUs
   // that one tile-quantised launch leaves idle.  Fork / join with events; results do not change.
-  int lanes = 4;
+  int lanes = speca::kMaxLanes;
   hipStream_t lane_stream[speca::kMaxLanes] = {};   // [0] = stream; others library-owned
   hipEvent_t lane_fork = nullptr;
   hipEvent_t lane_join[speca::kMaxLanes] = {};
@@ -77,9 +77,9 @@ struct LaneSplit {
   int n_lanes = 1;
   int first[kMaxLanes + 1] = {};
 };
-// Split n rows over the context's lanes (at least min_rows per lane; one lane while a profile is open
+// Split n rows into `wanted` groups, as far as the context's lanes go (one while a profile is open
 // unless the caller asked for lanes explicitly: per-kernel event times are only clean when serial).
-LaneSplit split_lanes(const speca_ctx* ctx, int n, int min_rows);
+LaneSplit split_lanes(const speca_ctx* ctx, int n, int wanted);
 // main stream -> all lanes of the split (they wait for everything enqueued on the main stream so far)
 Error lanes_fork(speca_ctx* ctx, const LaneSplit& ls);
 // all lanes -> main stream

@@ -51,6 +51,7 @@ struct DiT final : Model {
   bool traj_on = false;
   // workspace for up to cap_rows rows
   int cap_rows = 0;
+  int8_t groups_for[kMaxRows + 1] = {};      // row groups of a launch of n rows, 0: not decided yet (see two_groups)
   void *emb = nullptr, *t_hid = nullptr, *sc = nullptr, *xn = nullptr, *qkv = nullptr, *att = nullptr, *f1 = nullptr;
   const float* modp = nullptr;       // modulation of the current launch's compact rows: mod, or their rows of traj_mod
   float *temb = nullptr, *mod = nullptr, *h = nullptr, *h2 = nullptr, *feat = nullptr, *tok = nullptr;
@@ -274,17 +275,35 @@ struct DiT final : Model {
     return ok();
   }
 
+  // Whether n rows run as two groups side by side.  A layer of all rows wastes what its last round of tiles leaves idle; the tiles
+  // of two half layers fill each other's partial rounds, but each half waits for a whole tile time per layer.  The cost model of
+  // the tiles weighs one against the other for the four layers of a block, and two groups are taken where it expects
+  // more than 5 % from them.  Measured over 88 sizes (384 to 1152 features, 64 to 1024 tokens, 2 to 64 rows; reference steps, one
+  // group / two groups in ms): taken 1152 features at 1024, 2048 and 8192 tokens 9.47 / 8.85, 12.8 / 12.2, 31.1 / 29.7, 768 at 3072
+  // and 12288 10.2 / 10.0, 25.0 / 24.0; not taken 1152 at 3584 and 4096 15.5 / 16.5, 18.6 / 18.6, 1024 at 4096 and 8192 15.0 / 15.6,
+  // 24.0 / 25.7.  In narrow models with many tokens the passes that are bound by memory weigh more than the rounds: 384 features
+  // at 8192, 12288 and 16384 tokens 8.45 / 8.76, 14.1 / 13.1, 13.4 / 12.3.  A single block (the verification) does not repay the
+  // fork and join (16 rows of 1152 features and 256 tokens, six steps of eight blocks 5.00 / 5.18), and fp32 layers are bound by their
+  // own latency (33 sizes of 256 to 768 features: 7 % gained at best, 22 % lost at worst).
+  bool two_groups(int n) {
+    if (n < 2 || d.dtype != SPECA_BF16 || D % 8 || Dm % 8) return false;
+    if (!groups_for[n]) {
+      const int half = (n + 1) / 2 * T;
+      double whole = 0.0, pair = 0.0;
+      const struct { bool branch; int N, K; } layers[] = {{false, 3 * D, D}, {true, D, D}, {false, Dm, D}, {true, D, Dm}};
+      for (const auto& y : layers) {
+        whole += layer_time(y.branch, n * T, y.N, y.K, false);
+        pair += layer_time(y.branch, half, y.N, y.K, true);
+      }
+      groups_for[n] = whole > 1.05 * pair || (D <= 512 && static_cast<int64_t>(n) * T >= 12288) ? 2 : 1;
+    }
+    return groups_for[n] == 2;
+  }
+
   // Blocks [l0, l1) for all n rows, the row groups of the split side by side (launches interleaved
   // block by block so the lanes stay in step).  refresh_rt / truth as in the branch functions.
   Error run_blocks(speca_ctx* ctx, int l0, int l1, float* hs, int n, const RowTable* refresh_rt, float* truth_last_mlp) {
-    // Two row groups side by side pay off where a GEMM of all rows is about one round of tiles: the epilogue of one group,
-    // which reads and writes the residual stream and the cache, then runs beside the matrix work of the other.  Measured on
-    // 20-step trajectories of the 28-block model at 256 tokens, one group / two groups in ms: 16 rows 49.5 / 47.0, 20 rows
-    // 57.4 / 55.4, 24 rows (more than one round: tiles overlap by themselves) 60.0 / 61.2, 32 rows 79.6 / 81.8; 10 rows are
-    // 6 % slower in two groups (a group fills too little of the chip), and three or four groups are never the best.
-    const int64_t tokens = static_cast<int64_t>(n) * T;
-    const int min_rows = tokens < 4096 || tokens > 5120 ? n + 1 : n / 2;
-    const LaneSplit ls = split_lanes(ctx, n, min_rows);
+    const LaneSplit ls = split_lanes(ctx, n, l1 - l0 > 1 && two_groups(n) ? 2 : 1);
     RowTable sub[kMaxLanes];
     if (refresh_rt)
       for (int k = 0; k < ls.n_lanes; ++k) sub[k] = slice_table(*refresh_rt, ls.first[k], ls.first[k + 1] - ls.first[k]);

@@ -1,7 +1,8 @@
 // Linear layers of the target model:  C[M,N] = A[M,K] * W[N,K]^T (+ bias) with a fused
 // epilogue.  A and W are row-major with K contiguous, in the model dtype; accumulation
-// is fp32.  Two kernel families implement it: bf16 MFMA with LDS-staged tiles (the dense
-// contractions of reference steps) and a plain fp32-FMA tile kernel for fp32 models.
+// is fp32.  Three kernel families implement it: bf16 MFMA with LDS-staged tiles (the dense
+// contractions of reference steps), fp32 MFMA straight from memory for fp32 models, and a plain
+// fp32-FMA tile kernel for operands whose strides or alignment neither takes.
 #pragma once
 
 #include <type_traits>
@@ -53,6 +54,9 @@ template <int MODE> inline EpiArg<MODE> epi_arg(const GemmEpi& e) {
 // M may be ragged; N % 4 == 0 is required (checked).
 Error launch_gemm(int dtype, const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi,
                   hipStream_t st);
+// Modelled time (us) of a bf16 layer on the matrix kernels (K % 8 == 0): alone on the chip, or, `paired`, as one of two such
+// layers side by side, whose tiles fill each other's partial rounds.
+double layer_time(bool branch, int M, int N, int K, bool paired);
 
 // softmax(q k^T / sqrt(hd)) v without mask.  qkv: [rows][T][3][H][hd] (model dtype),
 // out: [rows][T][ldo] with the H*hd result in the first columns (ldo >= H*hd, ldo % 4 == 0).

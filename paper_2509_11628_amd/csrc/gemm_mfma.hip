@@ -462,42 +462,60 @@ bool gemm_mfma_supported(const Operands& o) {
          (reinterpret_cast<uintptr_t>(o.w) % 16 == 0) && pick_tile(o, true, &cost) >= 0;     // the smallest tile, which fits whenever one does, serves every epilogue
 }
 
-Error launch_gemm_mfma(const Operands& o, const GemmEpi& epi, hipStream_t st) {
-  double whole = 0.0;
-  const bool branch = epi.mode == EPI_BRANCH;
-  const int kind = pick_tile(o, branch, &whole);
+// How a layer is run: all of it on one kind, or `head` columns ahead on the 256x256 tile and the rest on `kind`.
+struct Choice {
+  int kind;
+  int head;
+  double time;
+};
+static Choice choose(const Operands& o, bool branch) {
+  Choice c{-1, 0, 0.0};
+  c.kind = pick_tile(o, branch, &c.time);
   // A little more than whole rounds of 256x256 tiles (the 4096 x 4608 x 1152 fc1 GEMM: 288): the columns that make whole
   // rounds go on the large tile, the remaining columns in a second launch (47 + 13 us against 61 us for the best single
   // kernel; 4096 x 9216 x 3072, 576 tiles: 236 -> 207 us).  Column ranges only shift pointers, so this is limited to the epilogues that store into `out`.
   if (!branch && o.K % BK == 0 && o.K >= BK && o.M >= 256) {
     const int tiles_m = (o.M + 255) / 256;
-    int head = 0;
     for (int rounds = 1;; ++rounds) {
       const int n1 = static_cast<int>(static_cast<int64_t>(rounds) * compute_units() / tiles_m) * 256;
       if (n1 >= o.N) break;
+      if (n1 < 256) continue;
+      Operands tail = o;
+      tail.N = o.N - n1;
       double rest = 0.0;
-      if (n1 >= 256) {
-        Operands tail = o;
-        tail.N = o.N - n1;
-        (void)pick_tile(tail, false, &rest);
-        rest += tile_cost(kTileKinds[0], false, o.M, n1, o.K);
-        if (rest < 0.96 * whole) { head = n1; whole = rest / 0.96; }
-      }
-    }
-    if (head) {
-      Operands first = o, tail = o;
-      first.N = head;
-      SPECA_TRY(launch_kind(0, first, epi, st));
-      GemmEpi te = epi;
-      if (epi.bias) te.bias = static_cast<const uint16_t*>(epi.bias) + head;
-      te.out = epi.mode == EPI_F32 ? static_cast<void*>(static_cast<float*>(epi.out) + head) : static_cast<void*>(static_cast<uint16_t*>(epi.out) + head);
-      tail.w += static_cast<int64_t>(head) * o.ldw;
-      tail.N = o.N - head;
-      double cost = 0.0;
-      return launch_kind(pick_tile(tail, false, &cost), tail, te, st);
+      const int kind = pick_tile(tail, false, &rest);
+      rest += tile_cost(kTileKinds[0], false, o.M, n1, o.K);
+      if (rest < (c.head ? 1.0 : 0.96) * c.time) c = {kind, n1, rest};
     }
   }
-  return launch_kind(kind, o, epi, st);
+  return c;
+}
+
+double layer_time(bool branch, int M, int N, int K, bool paired) {
+  const Operands o{nullptr, K, nullptr, K, M, N, K};
+  if (!paired) return choose(o, branch).time;
+  double cost = 0.0;
+  const int kind = pick_tile(o, branch, &cost);
+  if (kind < 0) return cost;
+  const TileKind& t = kTileKinds[kind];
+  const double tiles = 2.0 * ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+  const double depth = std::max(1.0, tiles / compute_units()), c = branch ? t.cb : t.c, r = branch ? t.rb : t.r;
+  const double rounds = t.two && depth >= 2.0 ? depth / 2 * (1.0 + r) : 1.0 + r * (depth - 1.0);
+  return t.a + (c + t.b * ((K + BK - 1) / BK)) * rounds;
+}
+
+Error launch_gemm_mfma(const Operands& o, const GemmEpi& epi, hipStream_t st) {
+  const Choice c = choose(o, epi.mode == EPI_BRANCH);
+  if (!c.head) return launch_kind(c.kind, o, epi, st);
+  Operands first = o, tail = o;
+  first.N = c.head;
+  SPECA_TRY(launch_kind(0, first, epi, st));
+  GemmEpi te = epi;
+  if (epi.bias) te.bias = static_cast<const uint16_t*>(epi.bias) + c.head;
+  te.out = epi.mode == EPI_F32 ? static_cast<void*>(static_cast<float*>(epi.out) + c.head) : static_cast<void*>(static_cast<uint16_t*>(epi.out) + c.head);
+  tail.w += static_cast<int64_t>(c.head) * o.ldw;
+  tail.N = o.N - c.head;
+  return launch_kind(c.kind, tail, te, st);
 }
 
 }  // namespace speca
