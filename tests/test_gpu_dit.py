@@ -500,10 +500,10 @@ def test_lanes_do_not_change_results(rows, grid, D, H, dtype, groups):
 
 def test_config3_full_size_sampled():
     """Configuration 3 at full size, in the launch shape the benchmark times (16 rows = 8 samples x
-    guidance pair, bf16, 4 lanes): the reference step of one guidance pair (rows 0 and 8) against the
+    guidance pair, bf16): the reference step of one guidance pair (rows 0 and 8) against the
     oracle's forward of those two rows (about 10 s of CPU), model output and sampled cached features;
     then properties that hold at any size: thresholds of zero reproduce plain sampling bit for bit and
-    the lane count does not change a bit."""
+    the lane count does not change a bit (8 rows, which the library runs as two groups)."""
     import paper_2509_11628_amd as sp
     from paper_2509_11628_amd import binding as bd
     s = si.dit_xl2("bf16")
@@ -531,20 +531,25 @@ def test_config3_full_size_sampled():
         idx = (rng.integers(0, 2, 2000), rng.integers(0, s.tokens, 2000), rng.integers(0, s.hidden, 2000))
         a, b = gf[j][idx], feats[j][idx]
         assert np.max(np.abs(a - b)) <= 2e-2 * np.max(np.abs(feats[j])), j
-    # properties at full size: tau = 0 is plain sampling; lanes do not change bits (8 steps keep it short)
+    # properties at full size: tau = 0 is plain sampling; lanes do not change bits (8 steps of 4 samples keep it short)
     S = 8
     ts, ab = si.ddim_tables(S)
     res = []
-    for lanes, tau in ((4, np.zeros(S, np.float32)), (1, np.zeros(S, np.float32)), (4, bd.tau_geometric(0.5, 0.5, S)), (2, bd.tau_geometric(0.5, 0.5, S))):
+    for lanes, tau in ((4, np.zeros(S, np.float32)), (1, np.zeros(S, np.float32)), (4, bd.tau_geometric(0.5, 0.5, S)), (1, bd.tau_geometric(0.5, 0.5, S))):
         ctx.set_lanes(lanes)
-        ctx.init_cache(sp.make_cfg(order=2, interval=4), 2 * B)
-        x = torch.from_numpy(lat).cuda()
-        tr = ctx.sample(x, ts, ab, tau, cfg_scale=1.5, labels=lab)
+        ctx.init_cache(sp.make_cfg(order=2, interval=4), B)
+        x = torch.from_numpy(lat[:B // 2]).cuda()
+        tr = ctx.sample(x, ts, ab, tau, cfg_scale=1.5, labels=lab[:B // 2])
         res.append((x.cpu().numpy(), tr))
+    ctx.set_lanes(2, profile_keeps_lanes=True)
+    ctx.init_cache(sp.make_cfg(order=2, interval=4), B)
+    ctx.profile_begin()
+    ctx.full_step(xd, 0, list(range(B)), torch.zeros_like(xd), timestep=float(ts[0]), labels=labels_rows)
+    assert ctx.profile_end()["gemm"]["launches"] == 2 * 4 * s.depth          # two groups ran
     assert np.all(res[0][1]["kind"] == 0) and np.array_equal(res[0][0], res[1][0])
     assert np.array_equal(res[2][0], res[3][0]) and np.array_equal(res[2][1]["kind"], res[3][1]["kind"])
     assert np.all(np.isfinite(res[2][0]))
-    # a short trajectory in the benchmark's launch shape (8 samples, guidance, 4 lanes) with an accepted, a
+    # a short trajectory in the benchmark's launch shape (8 samples, guidance) with an accepted, a
     # rejected and another accepted attempt; sample 0 against the oracle run on that sample alone
     # (samples are independent: own cache, own schedule)
     S = 4
