@@ -438,7 +438,9 @@ Error launch_cache_warm(const CacheGeom& g, const RowTable& rt, int slot, hipStr
     mo = rt.order[i] > mo ? rt.order[i] : mo;
   }
   if (mo == 0) return ok();                            // first references: nothing old to read
-  // a cache that the 256 MB memory-side cache holds between two steps is not cold
+  // A cache that the 256 MB memory-side cache holds between two steps is not cold: reading it ahead only adds a launch per branch
+  // (six reference steps, read ahead / not, in ms: caches of 27, 94 and 108 MB 4.34 / 4.03, 8.24 / 7.93 and 5.93 / 5.66; 162 and 189 MB
+  // 6.07 / 6.16 and 9.98 / 9.70; 378, 756 and 1512 MB 13.8 / 14.1, 21.1 / 21.8 and 41.8 / 43.1).
   if (static_cast<int64_t>(g.E) * g.n_slots * (g.m + 1) * g.batch_rows * static_cast<int64_t>(dtype_size(g.dtype)) < (int64_t{128} << 20)) return ok();
   const int esz = static_cast<int>(dtype_size(g.dtype));
   const int64_t bytes = g.E * esz;
