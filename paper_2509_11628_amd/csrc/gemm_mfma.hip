@@ -21,10 +21,6 @@
 
 #include "gemm_tile.h"
 
-#ifndef SPECA_SPREAD_LOADS
-#define SPECA_SPREAD_LOADS 1
-#endif
-
 namespace speca {
 
 namespace {
@@ -160,19 +156,10 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_dlds_kernel(const uint16_t
   constexpr int LPW = AG + WG;                               // loads per loader wave and step
   // Only with the 3-stage ring: there a load has two K-steps to land; with two stages (one step of lead) issuing
   // the loads later in the step cost more at the next wait than the burst did (measured -3..-5 %).
-  constexpr bool SPREAD = NS == 3 && LPW % 4 == 0 && ((TM * TN) % (LPW / 4) == 0 || LPW / 4 == 3) && SPECA_SPREAD_LOADS;
-#ifndef SPECA_ONE_AHEAD
-#define SPECA_ONE_AHEAD 1
-#endif
-#ifndef SPECA_FINE_READS
-#define SPECA_FINE_READS 1
-#endif
-#ifndef SPECA_EARLY_LOADS
-#define SPECA_EARLY_LOADS 1
-#endif
+  constexpr bool SPREAD = NS == 3 && LPW % 4 == 0 && ((TM * TN) % (LPW / 4) == 0 || LPW / 4 == 3);
   // Two stages (one K-step of lead): the loads go one per MFMA from the start of the step, so they are all out
   // within its first slice or two instead of holding the issue of every wave up front (+6..8 % on the 256x256 tile).
-  constexpr bool EARLY = NS == 2 && LPW <= 2 * TM * TN && SPECA_EARLY_LOADS;
+  constexpr bool EARLY = NS == 2 && LPW <= 2 * TM * TN;
 #define SPECA_SLICE_GROUPS                                                                                        \
   {                                                                                                               \
     constexpr int LPS_ = LPW / 4, MM_ = TM * TN;                                                                  \
@@ -205,7 +192,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_dlds_kernel(const uint16_t
     SPECA_LDFRAG(fa1, fw1, 3);                                                                                    \
     SPECA_MFMAS(fa0, fw0);                                                                                        \
     SPECA_MFMAS(fa1, fw1);                                                                                        \
-    if (EARLY && SPECA_ONE_AHEAD && LPW <= TM * TN && TM + TN <= TM * TN) {                                       \
+    if (EARLY && LPW <= TM * TN && TM + TN <= TM * TN) {                                       \
       /* one slice of fragments ahead is enough when its reads go out one per MFMA of the current slice */        \
       __builtin_amdgcn_sched_group_barrier(0x100, TM + TN, 0);                                                    \
       _Pragma("unroll") for (int l = 0; l < TM * TN; ++l) {                                                       \
@@ -229,7 +216,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_dlds_kernel(const uint16_t
         __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                                        \
       }                                                                                                           \
       if (TM * TN - L0_ > 0) __builtin_amdgcn_sched_group_barrier(0x008, TM * TN - L0_, 0);                       \
-      if (SPECA_FINE_READS && L1_ == 0 && TM + TN <= TM * TN) {                                                   \
+      if (L1_ == 0 && TM + TN <= TM * TN) {                                                   \
         /* the next slice's fragment reads go one per MFMA too */                                                 \
         _Pragma("unroll") for (int q = 0; q < 2; ++q) {                                                           \
           _Pragma("unroll") for (int l = 0; l < TM + TN; ++l) {                                                   \
@@ -252,7 +239,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_dlds_kernel(const uint16_t
       }                                                                                                           \
     } else {                                                                                                      \
     SPECA_SLICE_GROUPS;                                                                                           \
-    if (SPECA_FINE_READS && LPW / 4 == 3 && TM * TN == 4 && TM + TN == 4) {                                       \
+    if (LPW / 4 == 3 && TM * TN == 4 && TM + TN == 4) {                                       \
       /* slices 1 and 2: the fragment reads of the slice after next go one per MFMA as well */                    \
       _Pragma("unroll") for (int q = 0; q < 2; ++q) {                                                             \
         _Pragma("unroll") for (int l = 0; l < 3; ++l) {                                                           \
