@@ -103,8 +103,8 @@ __device__ inline void vt_write_off(int d, int kb, int* lo, int* hi) {
 // the second bit of the row alone (rows r and r + 2 of one read).  head_dim 72: rows of 144 bytes spread over the banks by
 // themselves.  Its last score step covers columns 64 .. 79: the lanes of the upper half read zeros (not the next row: it
 // may hold infinities), and value dims 72 .. 95 repeat a chunk, for results that are never stored.
-// Rows beyond T are zeros (kZeroRow): their scores are masked to -inf, and the probability 0 they get must not meet an
-// infinite value (0 x inf is NaN), as it would in a copy of row T - 1.
+// Keys beyond T are read from row T - 1 (valid memory), their scores are masked to -inf.  Values beyond T are zeros (kZeroRow):
+// the probability 0 they get must not meet an infinite value (0 x inf is NaN), as it would in a copy of row T - 1.
 // Ring: two buffers; per tile the waves wait for their own loads with vmcnt(0) (all that are outstanding),
 // one barrier, loads of the next tile are issued into the buffer just freed.
 #define SPECA_ATTN_GLL(src, dst)                                                                                  \
@@ -122,7 +122,7 @@ __device__ inline int value_chunk(int c, int r) {
   return HD == 128 ? c ^ (4 * (r & 3) + ((r >> 2) & 3)) : HD == 64 ? c ^ (4 * ((r >> 1) & 1)) : c;
 }
 
-// 16 bytes of zeros: what a lane loads for keys and values past T
+// 16 bytes of zeros: what a lane loads for values past T
 __device__ __align__(16) const uint32_t kZeroRow[4] = {0u, 0u, 0u, 0u};
 
 template <int HD>
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
     koff[g] = rr * row3d + static_cast<int>(D) + (key_chunk<HD>(p, r) << 3);
     voff[g] = rr * row3d + 2 * static_cast<int>(D) + (value_chunk<HD>(p, r) << 3);
   }
-  auto issue = [&](int k0, int buf, uint16_t* dst, const int (&off)[OFFS]) {
+  auto issue = [&](int k0, int buf, uint16_t* dst, const int (&off)[OFFS], auto is_value) {
     if (k0 + 64 <= T) {
 #pragma unroll
       for (int g = 0; g < LPW; ++g) {
@@ -188,13 +188,14 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
       for (int g = 0; g < LPW; ++g) {
         const int i = wave_u + 4 * g, rr = HD == 128 ? lane >> 4 : static_cast<unsigned>(i * 64 + lane) / CH;
         const int key = k0 + RSTEP * i + rr;
-        const uint16_t* src = key < T ? base + static_cast<int64_t>(key) * row3d + (off[OFFS == 1 ? 0 : g] - rr * row3d) : reinterpret_cast<const uint16_t*>(kZeroRow);
+        const uint16_t* src = base + static_cast<int64_t>(key < T ? key : T - 1) * row3d + (off[OFFS == 1 ? 0 : g] - rr * row3d);
+        if (decltype(is_value)::value && key >= T) src = reinterpret_cast<const uint16_t*>(kZeroRow);
         if (CH % 4 == 0 || i < CH) SPECA_ATTN_GLL(src, dst + buf * TILE + i * 512);
       }
     }
   };
-  auto issue_k = [&](int k0, int buf) { issue(k0, buf, Ks, koff); };
-  auto issue_v = [&](int k0, int buf) { issue(k0, buf, Vs, voff); };
+  auto issue_k = [&](int k0, int buf) { issue(k0, buf, Ks, koff, std::false_type()); };
+  auto issue_v = [&](int k0, int buf) { issue(k0, buf, Vs, voff, std::true_type()); };
   // a wave whose queries all lie beyond T only loads (1025 tokens: three waves of every ninth block)
   const bool active = HD == 128 || q0 + wave_u * 32 < T;
   // value reader: 16-lane group g = lane / 16, j = lane % 16: key k0 + j / 4 with k0 = 16 t + 4 (g >> 1) (+ 8),
