@@ -54,8 +54,7 @@ SHAPES = [  # M, N, K
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("act", [0, 1, 2])
 def test_linear(M, N, K, dtype, act):
-    # activations: two register-staged shapes and, for the direct-to-LDS loop, one 256x128 tile (2- and 3-stage ring),
-    # one 256x256 tile and the fc1 shape of configuration 3 (one wave of 256x256 tiles plus a remainder launch)
+    # activations: two shapes on small tiles (one with a tail of K), three on middle and large ones, and the fc1 shape of configuration 3 (one wave of 256x256 tiles plus a remainder launch)
     if act and (M, N, K) not in ((200, 192, 72), (130, 1152, 1152), (4000, 1160, 256), (4000, 3400, 2048), (4096, 3456, 128),
                                  (4096, 4608, 1152)):
         return
@@ -80,8 +79,7 @@ def test_linear_row_result_independent_of_m():
     full = bd.linear(a, w)
     part = bd.linear(a[300:333].contiguous(), w)
     assert torch.equal(full[300:333], part)         # bitwise: fixed K order, no split-K
-    # the same across main loops and tile shapes: 4096 rows take the 256x128 direct-to-LDS tiles, 33 rows
-    # the register-staged 128x64 ones; K = 2048 with 4096 x 3072 outputs takes 256x256
+    # the same across main loops and tile shapes: 4096 rows take middle or large tiles, 33 rows the small ones
     a = _dev(rng.standard_normal((4096, 1152)), "bf16")
     full = bd.linear(a, w)
     assert torch.equal(full[1000:1033], bd.linear(a[1000:1033].contiguous(), w))
