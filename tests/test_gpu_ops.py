@@ -54,7 +54,8 @@ SHAPES = [  # M, N, K
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("act", [0, 1, 2])
 def test_linear(M, N, K, dtype, act):
-    # activations: two shapes on small tiles (one with a tail of K), three on middle and large ones, and the fc1 shape of configuration 3 (one wave of 256x256 tiles plus a remainder launch)
+    # activations: two shapes on small tiles (one with a tail of K), three on middle and large ones, and the fc1 shape of
+    # configuration 3 (one wave of 256x256 tiles plus a remainder launch)
     if act and (M, N, K) not in ((200, 192, 72), (130, 1152, 1152), (4000, 1160, 256), (4000, 3400, 2048), (4096, 3456, 128),
                                  (4096, 4608, 1152)):
         return
