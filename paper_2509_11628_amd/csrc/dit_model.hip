@@ -282,11 +282,12 @@ struct DiT final : Model {
   // group / two groups in ms): taken 1152 features at 1024, 2048 and 8192 tokens 9.47 / 8.85, 12.8 / 12.2, 31.1 / 29.7, 768 at 3072
   // and 12288 10.2 / 10.0, 25.0 / 24.0; not taken 1152 at 3584 and 4096 15.5 / 16.5, 18.6 / 18.6, 1024 at 4096 and 8192 15.0 / 15.6,
   // 24.0 / 25.7.  In narrow models with many tokens the passes that are bound by memory weigh more than the rounds: 384 features
-  // at 8192, 12288 and 16384 tokens 8.45 / 8.76, 14.1 / 13.1, 13.4 / 12.3.  A single block (the verification) does not repay the
+  // at 8192, 12288 and 16384 tokens 8.45 / 8.76, 14.8 / 13.8, 14.3 / 13.1, 512 at 12288 15.7 / 14.7.  Narrower still, launches bound a
+  // step: 64 to 256 features at 3072 to 16384 tokens lose up to 39 % in two groups and gain 4 % at best.  A single block (the verification) does not repay the
   // fork and join (16 rows of 1152 features and 256 tokens, six steps of eight blocks 5.00 / 5.18), and fp32 layers are bound by their
   // own latency (33 sizes of 256 to 768 features: 7 % gained at best, 22 % lost at worst).
   bool two_groups(int n) {
-    if (n < 2 || d.dtype != SPECA_BF16 || D % 8 || Dm % 8) return false;
+    if (n < 2 || d.dtype != SPECA_BF16 || D < 384 || D % 8 || Dm % 8) return false;
     if (!groups_for[n]) {
       const int half = (n + 1) / 2 * T;
       double whole = 0.0, pair = 0.0;

@@ -459,10 +459,10 @@ def test_sample_error_paths(tiny):
 
 
 # rows, grid (tokens = grid^2), hidden, heads, dtype, row groups.  12 x 256 x 384: two half layers fill rounds of tiles that one
-# leaves half empty; 13 x 1024 x 64: a narrow model with many tokens, groups of 6 and 7; 3 x 1369 x 384: never three groups;
-# 16 x 16 x 64 and fp32: one group
-@pytest.mark.parametrize("rows,grid,D,H,dtype,groups", [(12, 16, 384, 6, "bf16", 2), (13, 32, 64, 1, "bf16", 2), (3, 37, 384, 6, "bf16", None),
-                                                        (16, 4, 64, 4, "bf16", 1), (13, 32, 64, 1, "f32", 1)])
+# leaves half empty; 13 x 1024 x 384: a narrow model with many tokens, groups of 6 and 7; 3 x 1369 x 384: never three groups;
+# narrower ones and fp32: one group
+@pytest.mark.parametrize("rows,grid,D,H,dtype,groups", [(12, 16, 384, 6, "bf16", 2), (13, 32, 384, 6, "bf16", 2), (3, 37, 384, 6, "bf16", None),
+                                                        (16, 4, 64, 4, "bf16", 1), (13, 32, 64, 1, "bf16", 1), (12, 16, 384, 6, "f32", 1)])
 def test_lanes_do_not_change_results(rows, grid, D, H, dtype, groups):
     """Row groups of a step run side by side on a stream of the library; a row's result must not depend on how the rows were
     grouped: same bits for 1, 2 and 4 lanes over accepted and rejected attempts.  The launches of a profiled reference step
