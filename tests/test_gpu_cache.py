@@ -200,6 +200,25 @@ def test_verify_leaves_the_stream_idle():
     assert idle == 200
 
 
+@pytest.mark.parametrize("rows", [1023, 1024, 1025, 2100])
+def test_verify_of_more_rows_than_one_launch(rows):
+    """1024 rows share a launch; the errors of every launch arrive, and the stream is idle after the last one."""
+    sp = _sp()
+    from paper_2509_11628_amd import binding as bd
+    rng = np.random.default_rng(rows)
+    E = 24
+    truth = rng.standard_normal((rows, E)).astype(np.float32)
+    pred = (truth + rng.uniform(0.01, 0.2, (rows, 1)) * rng.standard_normal((rows, E))).astype(np.float32)
+    ctx = sp.Context(sp.cache_only_desc(1, 1, 8, bd.F32))
+    err, acc = ctx.verify(_dev(pred, "f32"), _dev(truth, "f32"), tau=0.1)
+    assert torch.cuda.current_stream().query()
+    exp = np.array([core.relative_error(pred[r], truth[r]) for r in range(rows)])
+    np.testing.assert_allclose(err, exp, rtol=2e-5)
+    clear = np.abs(exp - 0.1) > 1e-5
+    assert np.array_equal(acc[clear], (exp <= 0.1)[clear]) and 0 < acc.sum() < rows
+    ctx.close()
+
+
 def test_verify_is_bit_reproducible_and_row_independent():
     sp = _sp()
     from paper_2509_11628_amd import binding as bd
