@@ -21,6 +21,15 @@ __device__ inline float gelu_tanh_f(float a) {
 }
 __device__ inline float silu_f(float a) { return a * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950409f * a)); }
 
+// two floats -> a pair of bf16, round to nearest even (one v_cvt_pk_bf16_f32)
+__device__ inline uint32_t pack_bf16(float a, float b) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  typedef float floatx2 __attribute__((ext_vector_type(2)));
+  const floatx2 f = {a, b};
+  const bf16x2 r = __builtin_convertvector(f, bf16x2);
+  return *reinterpret_cast<const uint32_t*>(&r);
+}
+
 template <typename T> struct Store4;
 template <> struct Store4<float> {
   __device__ static void st(float* p, const float* v) { *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]); }
@@ -32,8 +41,8 @@ template <> struct Store4<float> {
 template <> struct Store4<bf16_t> {
   __device__ static void st(bf16_t* p, const float* v) {
     uint2 r;
-    r.x = static_cast<uint32_t>(f32_to_bf16(v[0])) | (static_cast<uint32_t>(f32_to_bf16(v[1])) << 16);
-    r.y = static_cast<uint32_t>(f32_to_bf16(v[2])) | (static_cast<uint32_t>(f32_to_bf16(v[3])) << 16);
+    r.x = pack_bf16(v[0], v[1]);
+    r.y = pack_bf16(v[2], v[3]);
     *reinterpret_cast<uint2*>(p) = r;
   }
   __device__ static void ld(const bf16_t* p, float* v) {
@@ -46,11 +55,12 @@ template <> struct Store4<bf16_t> {
 // Streaming forms for data that is written once and read a whole step later (the cache): no reuse to
 // keep in L2.
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 __device__ inline void st4_stream(bf16_t* p, const float* v) {
   u32x2_t r;
-  r.x = static_cast<uint32_t>(f32_to_bf16(v[0])) | (static_cast<uint32_t>(f32_to_bf16(v[1])) << 16);
-  r.y = static_cast<uint32_t>(f32_to_bf16(v[2])) | (static_cast<uint32_t>(f32_to_bf16(v[3])) << 16);
+  r.x = pack_bf16(v[0], v[1]);
+  r.y = pack_bf16(v[2], v[3]);
   __builtin_nontemporal_store(r, reinterpret_cast<u32x2_t*>(p));
 }
 __device__ inline void st4_stream(float* p, const float* v) {
@@ -199,7 +209,7 @@ struct BranchRow {
 };
 
 template <typename T>
-__device__ inline BranchRow<T> branch_row(const GemmEpi& e, int i, int m0) {
+__device__ __forceinline__ BranchRow<T> branch_row(const GemmEpi& e, int i, int m0) {
   BranchRow<T> b;
   b.refresh = e.refresh != 0;
   b.order = b.refresh ? e.rt.order[i] : 0;

@@ -17,6 +17,10 @@ struct Operands {
   int M, N, K;
 };
 
+// gemm_phase.hip: 256 x 256
+bool gemm_phase_fits(const Operands& o);
+Error launch_gemm_phase(const Operands& o, const GemmEpi& epi, hipStream_t st);
+
 // gemm_ring.hip: kinds 0 .. 10 (see its switch)
 Error launch_gemm_ring(int kind, const Operands& o, const GemmEpi& epi, hipStream_t st);
 

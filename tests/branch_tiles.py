@@ -22,6 +22,9 @@ CASES = [
     (24, 15, 768, 12, 3072, ((128, 128), (256, 128))),
 ]
 
+# the same for the largest tile with every tile inside one row of the batch (planes and residual a whole tile at a time)
+INSIDE_ROWS = [(16, 32, 1024, 16, 1024, ((256, 256), (256, 256)))]
+
 
 def tile_table():
     src = open(os.path.join(ROOT, "paper_2509_11628_amd", "csrc", "gemm_mfma.hip")).read()

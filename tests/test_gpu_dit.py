@@ -67,7 +67,7 @@ def test_full_step_matches_oracle_forward(tiny):
 
 
 @pytest.mark.parametrize("layout", ["differences", "ring"])
-@pytest.mark.parametrize("case", branch_tiles.CASES, ids=lambda c: f"{c[0]}x{c[1] ** 2}x{c[2]}x{c[4]}")
+@pytest.mark.parametrize("case", branch_tiles.CASES + branch_tiles.INSIDE_ROWS, ids=lambda c: f"{c[0]}x{c[1] ** 2}x{c[2]}x{c[4]}")
 def test_branch_epilogue_on_every_tile(case, layout):
     """Residual update and cache refresh of the two branch layers, on every tile that carries them: ragged tiles that span rows of
     the batch.  Three reference steps of all rows together leave the bits (output and forecast, which reads every plane) of

@@ -122,6 +122,24 @@ def test_linear_bf16_tiles(M, N, K):
         assert torch.equal(bd.linear(da[r:r + 1].contiguous(), dw, db)[0], out[r])
 
 
+@pytest.mark.parametrize("M,N,K,act", [(4089, 4092, 128, 0), (4089, 4088, 192, 1), (4096, 4096, 256, 2), (3841, 3844, 320, 0)])
+def test_linear_bf16_largest_tile(M, N, K, act):
+    """One round of 256x256 tiles: two to five K-steps (the loop ends with two or three of them), rows and columns that end inside
+    a tile, widths that forbid 16-byte stores (N % 8 == 4), every activation; the bits of a row alone (the smallest tile)."""
+    bd = _bd()
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    a = torch.randn((M, K), generator=g, device="cuda").to(torch.bfloat16)
+    w = (torch.randn((N, K), generator=g, device="cuda") * 0.1).to(torch.bfloat16)
+    b = (torch.randn((N,), generator=g, device="cuda") * 0.1).to(torch.bfloat16)
+    pool = torch.full((M * N + 64,), 7.0, dtype=torch.bfloat16, device="cuda")
+    out = bd.linear(a, w, b, act, out=pool[:M * N].view(M, N))
+    exp = odit.linear(a.float().cpu().numpy().astype(np.float64), w.float().cpu().numpy().astype(np.float64), b.float().cpu().numpy().astype(np.float64))
+    _check(out, odit.gelu_tanh(exp) if act == 1 else odit.silu(exp) if act == 2 else exp, "bf16", K)
+    for r in (0, 127, 128, 255, M - 1):
+        assert torch.equal(bd.linear(a[r:r + 1].contiguous(), w, b, act)[0], out[r]), r
+    assert bool((pool[M * N:] == 7.0).all())                   # nothing written past the end
+
+
 @pytest.mark.parametrize("rows,T,H,hd", [(2, 16, 4, 16), (1, 100, 2, 72), (2, 256, 3, 72), (1, 77, 2, 64), (1, 300, 2, 128), (1, 64, 1, 32),
                                           (1, 256, 2, 128), (3, 200, 2, 64), (1, 257, 2, 72), (1, 33, 1, 128),
                                           (1, 2000, 2, 128), (1, 1111, 1, 72),       # many key tiles, ragged tail

@@ -182,5 +182,7 @@ def test_branch_tile_cases_reach_every_tile_of_the_branch_epilogue():
             got, margin = bt.branch_tile(table, rows * grid * grid, D, K)
             assert got == tile and margin > 1.003, (rows, grid, D, K, got, margin)
         seen |= set(want)
+    for rows, grid, D, H, Dm, want in bt.INSIDE_ROWS:
+        assert all(bt.branch_tile(table, rows * grid * grid, D, K)[0] == tile for K, tile in zip((D, Dm), want))
     assert bt.branch_tile(table, 81, 360, 424)[0] == (32, 64)
     assert seen == {t[:2] for t in table if t[6] > 0}
