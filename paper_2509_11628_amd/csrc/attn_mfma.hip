@@ -1,22 +1,18 @@
 // bf16 MFMA attention for gfx950: softmax(q k^T / sqrt(hd)) v without mask, online softmax
 // in fp32 (no T x T matrix is ever written).
 //
-// One block = 128 queries of one (row, head): 4 waves x 32 queries.  Keys/values stream
-// through LDS in tiles of 64 keys, double buffered, one barrier per tile.
-// Both contractions run on v_mfma_f32_32x32x16_bf16 producing TRANSPOSED tiles:
+// Both contractions run on the bf16 matrix instructions and produce TRANSPOSED tiles:
 //   S^T[key][query] = K q^T   (A operand = key rows from LDS, B operand = the wave's query
 //                              rows, held in registers for the whole kernel)
 //   O^T[d][query]  += V^T P^T (A operand = V^T from LDS, B operand = P^T)
-// In both results a lane's 16 values belong to ONE query (column lane % 32), so the softmax
-// statistics and the rescaling of O are lane-local; only the max/sum over the lane pair
-// (lane, lane ^ 32) needs a shuffle.  The P^T operand is taken straight from the S^T
-// accumulators: the MFMA reduction index is a dummy, so the keys are simply fed to the second
-// MFMA in the order the first one left them in the lane (keys 16t+4h+0..3, 16t+8+4h+0..3 for
-// half-wave h), and V^T is read from LDS in that same order.
+// In both results a lane's values belong to ONE query (its column), so the softmax statistics and the rescaling of O are
+// lane-local; only the maximum and the sum over the lanes that share a column cross lanes.  The P^T operand is taken straight
+// from the S^T accumulators: the reduction index is a dummy, so the keys are simply fed to the second contraction in the order
+// the first one left them in the lane, and V^T is read from LDS in that same order.
 // Two kernels: a tiled one (keys/values in 64-key tiles that go global -> LDS directly, V^T fragments from the transposing
-// LDS read, the next tile's scores issued under the current tile's online softmax) and, for T <= 256, one that holds the
-// whole sequence of a head in LDS (V transposed on its way there, in registers) and takes the softmax in one pass.
-// head_dim is padded with zeros to a multiple of 16 for q k^T and to a multiple of 32 for P V (results that are not stored).
+// LDS read, the next tile's scores issued under the current tile's online softmax; 16x16x32 instructions) and, for T <= 256, one
+// that holds the whole sequence of a head in LDS (V transposed on its way there, in registers) and takes the softmax in one pass
+// (32x32x16).  head_dim is padded with zeros to whole instructions (results that are not stored).
 #include <type_traits>
 
 #include "gemm.h"
@@ -27,6 +23,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 union Frag {
   uint4 u;
@@ -78,38 +75,34 @@ __device__ inline void vt_write_off(int d, int kb, int* lo, int* hi) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Tiled kernel whose key and value tiles go global -> LDS directly
-// (global_load_lds_dwordx4: lane l's 16 bytes land at the wave-uniform LDS address + 16 l) and whose
-// V^T operand is formed by the transposing LDS read, so nothing is staged or transposed in registers.
-// Bound by the vector unit (exponentials, maxima and conversions of the softmax) beside the matrix cores at long
-// sequences, by the latency of one block's chain of tiles at short ones.  Narrow heads took a kernel before that staged
-// keys and values in registers and transposed V there, with neither a tile's scores nor its loads under the softmax
-// (us, before -> now): 4 rows x 1025 tokens x 16 heads of 72 73.5 -> 64.3, 16 x 1024 174 -> 155, 1 x 4096 137 -> 122;
-// heads of 64: 2 x 2048 x 6 50.4 -> 42.4, 1 x 8000 x 24 549 -> 547.  The old kernel at three blocks per compute unit (168
-// registers) was slower than at two: 1 x 4096 x 16 heads of 72 188.
+// Tiled kernel: one block = 128 queries of one (row, head), 4 waves x 32 queries; keys and values stream through LDS in tiles of
+// 64 keys, double buffered, one barrier per tile.  The tiles go global -> LDS directly (a wave fills 64 chunks of 16 bytes at a
+// wave-uniform address) and V^T is formed by the transposing LDS read, so nothing is staged or transposed in registers.
 //
-// Both tiles are stored row-major as they are in memory: 64 keys x 2 HD bytes, one load instruction per 64 chunks of 16
-// bytes.  For head_dim 128 (rows of 16 chunks; the narrower ones follow):
-// Keys:   S^T = K q^T reads, per lane, chunk 2 ks + h of row l32 (ds_read_b128); chunk c of row r sits at
-//         position c ^ (r & 15), so the 16 lanes of a read phase touch all 64 banks once.
-// Values: ds_read_b64_tr_b16, per group of 16 lanes: lane j points at 4 consecutive dims
-//         d0 + 4 (j % 4) of key k0 + j / 4, and lane i of the group receives dim d0 + i of the keys
-//         k0 .. k0 + 3 (measured lane layout).  Two such reads (keys 16 t + 4 h + 0..3 and
-//         16 t + 8 + 4 h + 0..3) are one A fragment of V^T in exactly the key order the S^T
-//         accumulators hand P^T to the second MFMA.  The four rows a half-wave reads are moved to
-//         different 64-byte bank groups: chunk c of row r sits at position
-//         c ^ (4 (r & 3) + ((r >> 2) & 3)).
-// head_dim 64: rows of 128 bytes share the banks in pairs, so keys are swizzled by (r & 7) ^ ((r >> 3) & 1) and values by
-// the second bit of the row alone (rows r and r + 2 of one read).  head_dim 72: rows of 144 bytes spread over the banks by
-// themselves.  Its last score step covers columns 64 .. 79: the lanes of the upper half read zeros (not the next row: it
-// may hold infinities), and value dims 72 .. 95 repeat a chunk, for results that are never stored.
-// Keys beyond T are read from row T - 1 (valid memory), their scores are masked to -inf.  Values beyond T are zeros (kZeroRow):
-// the probability 0 they get must not meet an infinite value (0 x inf is NaN), as it would in a copy of row T - 1.
-// Ring: two buffers; per tile the waves wait for their own loads with vmcnt(0) (all that are outstanding),
-// one barrier, loads of the next tile are issued into the buffer just freed.
-#define SPECA_ATTN_GLL(src, dst)                                                                                  \
-  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src),                         \
-                                   (__attribute__((address_space(3))) void*)(dst), 16, 0, 0)
+// Both tiles are stored row-major as they are in memory, the 16-byte chunks of a row permuted so that the lanes which read
+// together touch all banks once:
+// Keys:   a fragment is 16 rows x 32 columns, lane l reads chunk 4 ks + l / 16 of row l % 16; chunk c of row r sits at position
+//         c ^ (r & 15) (head_dim 128) or c ^ (r & 7) ^ ((r >> 3) & 1) (64: two rows share the 64 banks).
+// Values: ds_read_b64_tr_b16, per group of 16 lanes: lane j points at 4 consecutive dims d0 + 4 (j % 4) of key k0 + j / 4, and
+//         lane i of the group receives dim d0 + i of the keys k0 .. k0 + 3 (measured lane layout).  With k0 = 32 u + 4 g and
+//         32 u + 16 + 4 g for group g two such reads are one A fragment of V^T in exactly the key order in which the S^T
+//         accumulators hand P^T on.  Two groups read 8 rows x 32 bytes at a time: chunk c of row r sits at position
+//         c ^ (2 (r & 7)) (head_dim 128) or c ^ (2 ((r >> 1) & 3)) (64).
+// head_dim 72: rows of 144 bytes spread over the banks by themselves.  Its last score step covers columns 64 .. 95: beyond 71
+// the lanes read zeros (not the next row: it may hold infinities), and value dims 72 .. 79 repeat a chunk, for results that are
+// never stored.
+// Keys and values beyond T read as zeros (the buffer ends there); their scores are masked to -inf, and the probability 0 meets no
+// infinite value (0 x inf is NaN).
+//
+// What bounds it: power (zeros instead of random data: 1210 to 1260 TFLOP/s against 1055 to 1150 at 24 heads of 128; without the
+// loads into LDS 1315), then the vector unit.  Before, the loads of the next tile were waited for ahead of the key reads of the
+// current one (the compiler takes global_load_lds for a store that LDS reads may alias), every key fragment was waited for
+// in front of its own matrix instruction, O was rescaled whenever a maximum moved, and 32x32x16 instructions drew more power.
+// us, before -> now: 1 row x 27 286 tokens x 24 heads of 128 9533 -> 8510, 1 x 4608 x 24 307 -> 275, 2 x 845 x 24 42.8 -> 36.2,
+// 4 x 1025 x 16 heads of 72 61.6 -> 50.7, 16 x 1024 x 16 142 -> 122, 2 x 2048 x 6 heads of 64 41.7 -> 33.9.  32x32x16 in the same
+// schedule is faster on zeros (1490 TFLOP/s) and slower on data where rounds end ragged (13 632 tokens 2306 -> 2160 us); 8 waves
+// on one pair of tiles gain 6 % at 4608 tokens and lose 4 % at 27 286 and 13 % at 4096; the loads as inline assembly, without
+// the wait that the compiler puts ahead of a tile's value reads: 0.5 %.
 typedef short short4v __attribute__((ext_vector_type(4)));
 
 // element offset inside a row of the stored chunk c of row r (involutions: the loader uses them the other way round)
@@ -119,240 +112,287 @@ __device__ inline int key_chunk(int c, int r) {
 }
 template <int HD>
 __device__ inline int value_chunk(int c, int r) {
-  return HD == 128 ? c ^ (4 * (r & 3) + ((r >> 2) & 3)) : HD == 64 ? c ^ (4 * ((r >> 1) & 1)) : c;
+  return HD == 128 ? c ^ (2 * (r & 7)) : HD == 64 ? c ^ (2 * ((r >> 1) & 3)) : c;
 }
 
-// 16 bytes of zeros: what a lane loads for values past T
-__device__ __align__(16) const uint32_t kZeroRow[4] = {0u, 0u, 0u, 0u};
+// The reference of a query's exponentials follows its running maximum only when that has grown by more than a factor of 2^8:
+// probabilities reach 2^8 and are as precise relative to their sum, and the sums and O are scaled rarely instead of whenever one
+// of the lanes' maxima moves (every tile of a sequence of a few thousand keys).
+constexpr float kRescale = 8.0f;
+
+// 16 bytes per lane from byte offset off[lane] of a buffer into LDS at the wave-uniform dst + 16 lane; zeros past the buffer's end
+__device__ __forceinline__ void buffer_to_lds(const uint16_t* buffer, int bytes, uint32_t off, uint16_t* dst) {
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(buffer), 0, bytes, 0x00020000);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)dst, 16, off, 0, 0, 0);
+}
+
+// maximum and sum over the lanes l % 16 + {0, 16, 32, 48}, which hold one query
+__device__ __forceinline__ float max_of_groups(float x) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float sum_of_groups(float x) {
+  x += __shfl_xor(x, 16, 64);
+  return x + __shfl_xor(x, 32, 64);
+}
 
 template <int HD>
 __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* __restrict__ qkv, uint16_t* __restrict__ out, int64_t ldo,
                                                             int T, int H, float scale_log2e) {
   constexpr int CH = HD / 8;                  // 16-byte chunks of a row, and load instructions of a tile
-  constexpr int KS = (HD + 15) / 16, DT = (HD + 31) / 32;
+  constexpr int KS = (HD + 31) / 32;          // steps of 32 columns of q k^T
+  constexpr int DT = (HD + 15) / 16;          // tiles of 16 dims of O^T
   constexpr int LPW = (CH + 3) / 4;           // load instructions per wave and tile
   constexpr int TILE = 64 * HD;               // elements of one key or value tile
-  extern __shared__ __align__(16) uint16_t smem[];
+  __shared__ __align__(16) uint16_t smem[4 * TILE + 8];
   uint16_t* Ks = smem;                        // [2][64][HD]
   uint16_t* Vs = smem + 2 * TILE;             // [2][64][HD]
-  uint16_t* zero = smem + 4 * TILE;           // head_dim 72: the key columns 72 .. 79 of the last step
+  uint16_t* zero = smem + 4 * TILE;           // head_dim 72: the key columns 72 .. 95 of the last step
 
   const int row = blockIdx.z, head = blockIdx.y, q0 = blockIdx.x * 128;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l32 = lane & 31, lhi = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g4 = lane >> 4;
   const int64_t D = static_cast<int64_t>(H) * HD;
   const uint16_t* base = qkv + static_cast<int64_t>(row) * T * 3 * D + head * HD;
 
-  Frag qf[KS];
-  {
-    const int q = q0 + wave * 32 + l32;
+  bf16x8 qf[KS][2];                           // queries 16 n + l16, columns 32 ks + 8 g4 ..
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-      qf[ks].u = q < T && (2 * ks + 1 < CH || lhi == 0) ? *reinterpret_cast<const uint4*>(base + static_cast<int64_t>(q) * 3 * D + ks * 16 + lhi * 8)
-                                                        : make_uint4(0, 0, 0, 0);
-    if (2 * KS > CH && tid < 8) zero[tid] = 0;
+  for (int n = 0; n < 2; ++n) {
+    const int q = q0 + wave * 32 + n * 16 + l16;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      Frag f;
+      f.u = q < T && 4 * ks + g4 < CH ? *reinterpret_cast<const uint4*>(base + static_cast<int64_t>(q) * 3 * D + ks * 32 + g4 * 8) : make_uint4(0, 0, 0, 0);
+      qf[ks][n] = f.v;
+    }
   }
-  floatx16 o[DT];
+  if (4 * KS > CH && tid < 8) zero[tid] = 0;
+  floatx4 o[DT][2];
 #pragma unroll
   for (int i = 0; i < DT; ++i)
 #pragma unroll
-    for (int q = 0; q < 16; ++q) o[i][q] = 0.0f;
-  float mrun = -INFINITY, lrun = 0.0f;
+    for (int n = 0; n < 2; ++n) o[i][n] = floatx4{};
 
-  // Loader: wave w issues instructions i = w, w + 4, ... of a tile's CH; lane -> chunk slot 64 i + lane, row slot / CH.
-  // With whole rows per lane group (head_dim 128: rows 4 i + lane / 16) the source chunk does not depend on the
-  // instruction (r & 15 and the value swizzle only see 4 wave + lane / 16), so a tile's addresses are one per-lane 32-bit
-  // offset on top of a wave-uniform row pointer; else there is one offset per instruction.  Only a ragged last tile looks at
-  // rows per lane.
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  const int row3d = static_cast<int>(3 * D);
-  constexpr int OFFS = HD == 128 ? 1 : LPW, RSTEP = HD == 128 ? 4 : 0;
-  int koff[OFFS], voff[OFFS];
+  // Loader: wave w issues instructions i = w, w + 4, ... of a tile's CH; lane -> chunk slot 64 i + lane, row slot / CH.  Through
+  // buffer descriptors that begin at the tile and end behind key T - 1: what lies beyond reads as zeros, and the compiler does not
+  // take the loads for LDS reads that every later key fragment would have to wait for.
+  const int64_t row_bytes = 6 * D;
+  uint32_t koff[LPW], voff[LPW];
 #pragma unroll
-  for (int g = 0; g < OFFS; ++g) {
-    const int slot = (wave_u + 4 * g) * 64 + lane, r = HD == 128 ? 4 * wave_u + (lane >> 4) : static_cast<unsigned>(slot) / CH, p = slot - r * CH;
-    const int rr = HD == 128 ? lane >> 4 : r;
-    koff[g] = rr * row3d + static_cast<int>(D) + (key_chunk<HD>(p, r) << 3);
-    voff[g] = rr * row3d + 2 * static_cast<int>(D) + (value_chunk<HD>(p, r) << 3);
+  for (int u = 0; u < LPW; ++u) {
+    const int slot = (wave + 4 * u) * 64 + lane, r = static_cast<unsigned>(slot) / CH, p = slot - r * CH;
+    koff[u] = static_cast<uint32_t>(r * row_bytes + 2 * D + (key_chunk<HD>(p, r) << 4));
+    voff[u] = static_cast<uint32_t>(r * row_bytes + 4 * D + (value_chunk<HD>(p, r) << 4));
   }
-  auto issue = [&](int k0, int buf, uint16_t* dst, const int (&off)[OFFS], auto is_value) {
-    if (k0 + 64 <= T) {
+  auto issue = [&](int kt, uint16_t* dst, const uint32_t (&off)[LPW]) {
+    const int keys = T - kt * 64 < 64 ? T - kt * 64 : 64;
+    const uint16_t* from = base + kt * (32 * row_bytes);
 #pragma unroll
-      for (int g = 0; g < LPW; ++g) {
-        const int i = wave_u + 4 * g;
-        const uint16_t* ub = base + static_cast<int64_t>(k0 + RSTEP * i) * row3d;      // wave-uniform
-        if (CH % 4 == 0 || i < CH) SPECA_ATTN_GLL(ub + off[OFFS == 1 ? 0 : g], dst + buf * TILE + i * 512);
+    for (int u = 0; u < LPW; ++u)
+      if (CH % 4 == 0 || wave + 4 * u < CH) buffer_to_lds(from, static_cast<int>(keys * row_bytes), off[u], dst + (kt & 1) * TILE + (wave + 4 * u) * 512);
+  };
+  // a wave whose queries all lie beyond T only loads (1025 tokens: three waves of every ninth block)
+  const bool active = q0 + wave * 32 < T;
+
+  // Key fragment: keys 16 m + l16, chunk 4 ks + g4 of the tile in buffer kb (rows 16 apart are swizzled alike).
+  int krd[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) krd[ks] = l16 * HD + (key_chunk<HD>(4 * ks + g4, l16) << 3);
+  auto key_frag = [&](int kb, int ks, int m) {
+    const uint16_t* kc = Ks + kb * TILE + m * 16 * HD + krd[ks];
+    if (4 * ks + 3 >= CH && 4 * ks + g4 >= CH) kc = zero;
+    return *reinterpret_cast<const bf16x8*>(kc);
+  };
+  // Value fragment: dims 16 dt + l16 of the keys 32 u + 4 g4 .. + 3 and 32 u + 16 + 4 g4 .. + 3, in two transposing reads: lane j
+  // of a group of 16 points at dims 16 dt + 4 (j % 4) of key k0 + j / 4 (chunk 2 dt + (j % 4) / 2, half j % 2).
+  const int vrow = 4 * g4 + (l16 >> 2);
+  auto value_frag = [&](int vb, int u, int dt) {
+    const int c0 = 2 * dt + ((l16 & 3) >> 1), c = CH % 2 == 0 || c0 < CH ? c0 : CH - 1;        // dims beyond HD: any, never stored
+    const uint16_t* va = Vs + vb * TILE + (32 * u + vrow) * HD + (l16 & 1) * 4 + (value_chunk<HD>(c, vrow) << 3);      // rows + 16 are swizzled alike
+    union { short4v h[2]; bf16x8 v; } vf;
+    vf.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)va);
+    vf.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(va + 16 * HD));
+    return vf.v;
+  };
+
+  // Online softmax.  A lane's scores of a tile: s[m][n][i], key 16 m + 4 g4 + i, query 16 n + l16.
+  float mref[2] = {-INFINITY, -INFINITY}, moff[2] = {}, lrun[2] = {}, psum[2] = {}, corr[2] = {1.0f, 1.0f}, tmax[2];
+  bool moved = false;
+  // one score of 32, in the order in which the second contraction needs them
+  auto maximum = [&](const floatx4 (&s)[4][2], int from, int to) {
+#pragma unroll
+    for (int i = from; i < to; ++i) tmax[(i >> 2) & 1] = fmaxf(tmax[(i >> 2) & 1], s[i >> 3][(i >> 2) & 1][i & 3]);
+  };
+  auto reference = [&]() {
+    moved = false;
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      const float t = max_of_groups(tmax[n]);
+      const bool mv = (t - mref[n]) * scale_log2e > kRescale;      // true in the first tile
+      const float mnew = mv ? t : mref[n];
+      moff[n] = mnew * scale_log2e;
+      corr[n] = mv ? fast_exp2(mref[n] * scale_log2e - moff[n]) : 1.0f;
+      mref[n] = mnew;
+      moved |= mv;
+    }
+  };
+  auto probabilities = [&](floatx4 (&s)[4][2], int from, int to) {
+#pragma unroll
+    for (int i = from; i < to; ++i) {
+      const int m = i >> 3, n = (i >> 2) & 1;
+      const float p = fast_exp2(fmaf(s[m][n][i & 3], scale_log2e, -moff[n]));
+      s[m][n][i & 3] = p;
+      psum[n] += p;
+    }
+  };
+  auto pack = [&](const floatx4 (&s)[4][2], int u, int n) {        // P^T of keys 32 u .. 32 u + 31
+    Frag pf;
+    pf.u = make_uint4(cvt_pk_bf16(s[2 * u][n][0], s[2 * u][n][1]), cvt_pk_bf16(s[2 * u][n][2], s[2 * u][n][3]),
+                      cvt_pk_bf16(s[2 * u + 1][n][0], s[2 * u + 1][n][1]), cvt_pk_bf16(s[2 * u + 1][n][2], s[2 * u + 1][n][3]));
+    return pf.v;
+  };
+  auto mask = [&](floatx4 (&s)[4][2], int kt) {                    // keys past T
+#pragma unroll
+    for (int i = 0; i < 32; ++i)
+      if (kt * 64 + (i >> 3) * 16 + 4 * g4 + (i & 3) >= T) s[i >> 3][(i >> 2) & 1][i & 3] = -INFINITY;
+  };
+
+  // Tile kt, whose scores lie in sc with their reference known.  A wave issues in order, so what runs side by side is written side by
+  // side, pinned around every pair of matrix instructions: first the scores of tile kt + 1 with the first NP probabilities of tile
+  // kt, then O^T += V^T P^T with the other probabilities in its first half and the maximum of tile kt + 1 in its second.  Fragments
+  // are read RA steps ahead.  NEXT: there is a tile kt + 1; the last one is masked.
+#define SPECA_PIN() __builtin_amdgcn_sched_barrier(0)
+  constexpr int NS = 4 * KS, NV = 2 * DT, RA = 4, NP = 20;
+  auto tile = [&](floatx4 (&sc)[4][2], floatx4 (&sn)[4][2], int kt, int buf, auto next_tag) {
+    constexpr bool NEXT = decltype(next_tag)::value;
+    bf16x8 kf[NS], vf[NV], pf[2][2];
+    if constexpr (NEXT) {
+#pragma unroll
+      for (int i = 0; i < RA; ++i) kf[i] = key_frag(1 - buf, i >> 2, i & 3);
+      SPECA_PIN();
+    }
+    if (__any(moved)) {
+#pragma unroll
+      for (int n = 0; n < 2; ++n) {
+        lrun[n] *= corr[n];
+#pragma unroll
+        for (int i = 0; i < DT; ++i) o[i][n] *= corr[n];
+      }
+    }
+    psum[0] = psum[1] = 0.0f;
+    if constexpr (NEXT) {
+#pragma unroll
+      for (int i = 0; i < NS; ++i) {
+        if (i + RA < NS) kf[i + RA] = key_frag(1 - buf, (i + RA) >> 2, (i + RA) & 3);
+        else vf[i + RA - NS] = value_frag(buf, (i + RA - NS) / DT, (i + RA - NS) % DT);
+        if (i >= NS - 2) pf[0][i - NS + 2] = pack(sc, 0, i - NS + 2);
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+          probabilities(sc, (2 * i + n) * NP / (2 * NS), (2 * i + n + 1) * NP / (2 * NS));
+          SPECA_PIN();
+          sn[i & 3][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[i], qf[i >> 2][n], i < 4 ? floatx4{} : sn[i & 3][n], 0, 0, 0);
+          SPECA_PIN();
+        }
       }
     } else {
 #pragma unroll
-      for (int g = 0; g < LPW; ++g) {
-        const int i = wave_u + 4 * g, rr = HD == 128 ? lane >> 4 : static_cast<unsigned>(i * 64 + lane) / CH;
-        const int key = k0 + RSTEP * i + rr;
-        const uint16_t* src = base + static_cast<int64_t>(key < T ? key : T - 1) * row3d + (off[OFFS == 1 ? 0 : g] - rr * row3d);
-        if (decltype(is_value)::value && key >= T) src = reinterpret_cast<const uint16_t*>(kZeroRow);
-        if (CH % 4 == 0 || i < CH) SPECA_ATTN_GLL(src, dst + buf * TILE + i * 512);
+      for (int i = 0; i < RA; ++i) vf[i] = value_frag(buf, i / DT, i % DT);
+      probabilities(sc, 0, NP);
+#pragma unroll
+      for (int n = 0; n < 2; ++n) pf[0][n] = pack(sc, 0, n);
+    }
+    tmax[0] = tmax[1] = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      if (i + RA < NV) vf[i + RA] = value_frag(buf, (i + RA) / DT, (i + RA) % DT);
+      if (i >= DT - 1 && i <= DT) pf[1][i - DT + 1] = pack(sc, 1, i - DT + 1);
+      if constexpr (NEXT) {
+        if (i == DT && kt * 64 + 128 > T) mask(sn, kt + 1);
+      }
+#pragma unroll
+      for (int n = 0; n < 2; ++n) {
+        if (i < DT) probabilities(sc, NP + (2 * i + n) * (32 - NP) / (2 * DT - 1), i + 1 == DT && n ? 32 : NP + (2 * i + n + 1) * (32 - NP) / (2 * DT - 1));
+        else if constexpr (NEXT) maximum(sn, (2 * (i - DT) + n) * 32 / (2 * DT), (2 * (i - DT) + n + 1) * 32 / (2 * DT));
+        SPECA_PIN();
+        o[i % DT][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[i], pf[i / DT][n], o[i % DT][n], 0, 0, 0);
+        SPECA_PIN();
       }
     }
+#pragma unroll
+    for (int n = 0; n < 2; ++n) lrun[n] += psum[n];
+    if constexpr (NEXT) reference();
   };
-  auto issue_k = [&](int k0, int buf) { issue(k0, buf, Ks, koff, std::false_type()); };
-  auto issue_v = [&](int k0, int buf) { issue(k0, buf, Vs, voff, std::true_type()); };
-  // a wave whose queries all lie beyond T only loads (1025 tokens: three waves of every ninth block)
-  const bool active = HD == 128 || q0 + wave_u * 32 < T;
-  // value reader: 16-lane group g = lane / 16, j = lane % 16: key k0 + j / 4 with k0 = 16 t + 4 (g >> 1) (+ 8),
-  // dims dt * 32 + 16 (g & 1) + 4 (j % 4) .. + 3: chunk dt * 4 + 2 (g & 1) + (j % 4) / 2, half (j % 2)
-  const int vg = lane >> 4, vj = lane & 15;
-  const int vkey0 = 4 * (vg >> 1) + (vj >> 2);                     // key inside the 16-key step, first read (second: + 8)
-  const int vchunk0 = 2 * (vg & 1) + ((vj & 3) >> 1);              // chunk inside the 32-dim block
-  const int vhalf = (vj & 1) * 4;                                  // element offset inside the chunk
-
-  // S^T of the 64 keys in key buffer kb
-  auto scores = [&](floatx16 (&s)[2], int kb) {
-#pragma unroll
-    for (int st = 0; st < 2; ++st) {
-#pragma unroll
-      for (int q = 0; q < 16; ++q) s[st][q] = 0.0f;
-      const uint16_t* kp = Ks + kb * TILE + (st * 32 + l32) * HD;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        Frag kf;
-        const uint16_t* kc = kp + (key_chunk<HD>(2 * ks + lhi, l32) << 3);       // rows + 32 are swizzled alike
-        if (2 * ks + 1 >= CH && lhi) kc = zero;
-        kf.u = *reinterpret_cast<const uint4*>(kc);
-        s[st] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf.v, qf[ks].v, s[st], 0, 0, 0);
-      }
-    }
-  };
-  // online softmax of tile kt (scores in s, replaced by probabilities), then O^T += V^T P^T from value buffer vb
-  auto softmax_pv = [&](floatx16 (&s)[2], int kt, int vb, auto masked) {
-    const int kbase = kt * 64;
-    if (decltype(masked)::value && kbase + 64 > T) {
-#pragma unroll
-      for (int st = 0; st < 2; ++st)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-          const int key = kbase + st * 32 + 8 * (q >> 2) + 4 * lhi + (q & 3);
-          if (key >= T) s[st][q] = -INFINITY;
-        }
-    }
-    float tmax = -INFINITY;
-#pragma unroll
-    for (int st = 0; st < 2; ++st)
-#pragma unroll
-      for (int q = 0; q < 16; ++q) tmax = fmaxf(tmax, s[st][q]);
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-    const float mnew = fmaxf(mrun, tmax);
-    const float moff = mnew * scale_log2e;
-    float psum = 0.0f;
-#pragma unroll
-    for (int st = 0; st < 2; ++st)
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const float p = fast_exp2(fmaf(s[st][q], scale_log2e, -moff));
-        s[st][q] = p;
-        psum += p;
-      }
-    if (!decltype(masked)::value) {
-#pragma unroll
-      for (int i = 0; i < 2 * KS; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);     // one key fragment read
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);     // one MFMA of the next tile's scores
-        __builtin_amdgcn_sched_group_barrier(0x400, HD == 128 ? 2 : HD == 72 ? 3 : 4, 0);     // two (three, four) exponentials of this tile's softmax
-        __builtin_amdgcn_sched_group_barrier(0x002, HD == 128 ? 7 : HD == 72 ? 11 : 14, 0);   // seven (eleven, fourteen) of its other vector instructions
-      }
-    }
-    if (__any(mnew != mrun)) {
-      const float corr = fast_exp2(mrun * scale_log2e - moff);
-      lrun *= corr;
-#pragma unroll
-      for (int i = 0; i < DT; ++i)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) o[i][q] *= corr;
-      mrun = mnew;
-    }
-    lrun += psum;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int st = t >> 1, j0 = (t & 1) * 8;
-      Frag pf;
-      pf.u = make_uint4(cvt_pk_bf16(s[st][j0], s[st][j0 + 1]), cvt_pk_bf16(s[st][j0 + 2], s[st][j0 + 3]),
-                        cvt_pk_bf16(s[st][j0 + 4], s[st][j0 + 5]), cvt_pk_bf16(s[st][j0 + 6], s[st][j0 + 7]));
-      const int ka = 16 * t + vkey0, kb = ka + 8;                  // rows of the two transposing reads
-      const uint16_t* va = Vs + vb * TILE + ka * HD + vhalf;
-      const uint16_t* vbp = Vs + vb * TILE + kb * HD + vhalf;
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
-        const int c = CH % 4 == 0 || dt * 4 + vchunk0 < CH ? dt * 4 + vchunk0 : CH - 1;      // dims beyond HD: any, never stored
-        const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(va + (value_chunk<HD>(c, ka) << 3)));
-        const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(vbp + (value_chunk<HD>(c, kb) << 3)));
-        union { short4v h[2]; bf16x8 v; } vf;
-        vf.h[0] = lo; vf.h[1] = hi;
-        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.v, pf.v, o[dt], 0, 0, 0);
-      }
-    }
-  };
-
+  // Ring: keys are fetched two tiles ahead, values one.  At the top of tile kt the wave's outstanding loads are K(kt + 1) and V(kt);
+  // behind the barrier K(kt + 2) overwrites K(kt) (read in tile kt - 1) and V(kt + 1) overwrites V(kt - 1).  A wave's own fragment
+  // reads are complete before the barrier, and no memory access moves across it.
+#define SPECA_TURN()                                        \
+  {                                                         \
+    __builtin_amdgcn_s_waitcnt(0x0070);                     \
+    asm volatile("" ::: "memory");                          \
+    __builtin_amdgcn_s_barrier();                           \
+    asm volatile("" ::: "memory");                          \
+    SPECA_PIN();                                            \
+  }
+  // tile kt, not the last one, in buffer PAR = kt % 2, its scores in SC
+#define SPECA_ATTN_TILE(PAR, SC, SN)                                      \
+  {                                                                       \
+    SPECA_TURN()                                                          \
+    if (kt + 2 < ntiles) issue(kt + 2, Ks, koff);                         \
+    issue(kt + 1, Vs, voff);                                              \
+    if (active) tile(SC, SN, kt, PAR, std::true_type());                  \
+  }
   const int ntiles = (T + 63) / 64;
-  {
-    // The scores of tile kt + 1 are issued before the softmax of tile kt: their MFMAs run while the vector
-    // unit takes exponentials.  Keys are therefore fetched two tiles ahead, values one: at the top of
-    // iteration kt the wave's outstanding loads are K(kt + 1) and V(kt), both awaited with vmcnt(0);
-    // K(kt + 2) then overwrites K(kt) (consumed in iteration kt - 1), V(kt + 1) overwrites V(kt - 1).
-    floatx16 sa[2], sb[2];
-    issue_k(0, 0);
-    __builtin_amdgcn_s_waitcnt(0x0F70);
-    __syncthreads();
-    if (1 < ntiles) issue_k(64, 1);
-    issue_v(0, 0);
-    if (active) scores(sa, 0);
-    // All tiles but the last: no tail mask and no condition between the score MFMAs of tile kt + 1 and the
-    // softmax of tile kt, so both sit in one scheduling region; the group barriers ask for one key-fragment
-    // read and one MFMA per two exponentials and seven other vector instructions (the wave issues in order:
-    // without the interleave the sixteen dependent MFMAs would all be issued before the first exponential).
-#define SPECA_ATTN_ITER(kt_, SC, SN)                                                                              \
-  {                                                                                                               \
-    __builtin_amdgcn_s_waitcnt(0x0F70);                                                                           \
-    __syncthreads();                                                                                              \
-    if ((kt_) + 2 < ntiles) issue_k(((kt_) + 2) * 64, (kt_) & 1);                                                 \
-    issue_v(((kt_) + 1) * 64, ((kt_) + 1) & 1);                                                                   \
-    if (active) {                                                                                                 \
-      scores(SN, ((kt_) + 1) & 1);                                                                                \
-      softmax_pv(SC, (kt_), (kt_) & 1, std::false_type());                                                        \
-    }                                                                                                             \
-  }
-    int kt = 0;
-    for (; kt + 2 < ntiles; kt += 2) {
-      SPECA_ATTN_ITER(kt, sa, sb);
-      SPECA_ATTN_ITER(kt + 1, sb, sa);
+  floatx4 sa[4][2], sb[4][2];
+  issue(0, Ks, koff);
+  SPECA_TURN()
+  if (1 < ntiles) issue(1, Ks, koff);
+  issue(0, Vs, voff);
+  if (active) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      const bf16x8 kf = key_frag(0, i >> 2, i & 3);
+#pragma unroll
+      for (int n = 0; n < 2; ++n) sa[i & 3][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[i >> 2][n], i < 4 ? floatx4{} : sa[i & 3][n], 0, 0, 0);
     }
-    if (kt + 1 < ntiles) {                     // two tiles left: kt (scores in sa) and the last one
-      SPECA_ATTN_ITER(kt, sa, sb);
-      __builtin_amdgcn_s_waitcnt(0x0F70);
-      __syncthreads();
-      if (active) softmax_pv(sb, kt + 1, (kt + 1) & 1, std::true_type());
-    } else {                                   // one tile left, its scores are in sa
-      __builtin_amdgcn_s_waitcnt(0x0F70);
-      __syncthreads();
-      if (active) softmax_pv(sa, kt, kt & 1, std::true_type());
-    }
-#undef SPECA_ATTN_ITER
+    if (ntiles == 1) mask(sa, 0);
+    tmax[0] = tmax[1] = -INFINITY;
+    maximum(sa, 0, 32);
+    reference();
   }
+  int kt = 0;
+  for (; kt + 2 < ntiles; ++kt) {
+    SPECA_ATTN_TILE(0, sa, sb)
+    ++kt;
+    SPECA_ATTN_TILE(1, sb, sa)
+  }
+  if (kt + 1 < ntiles) {
+    SPECA_ATTN_TILE(0, sa, sb)
+    ++kt;
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+      for (int n = 0; n < 2; ++n) sa[m][n] = sb[m][n];
+  }
+  SPECA_TURN()
+  if (active) tile(sa, sb, kt, kt & 1, std::false_type());
+#undef SPECA_ATTN_TILE
+#undef SPECA_TURN
+#undef SPECA_PIN
 
-  const float ltot = lrun + __shfl_xor(lrun, 32, 64);
-  const float inv = 1.0f / ltot;
-  const int q = q0 + wave * 32 + l32;
-  if (q < T) {
-    uint16_t* op = out + (static_cast<int64_t>(row) * T + q) * ldo + head * HD;
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+  for (int n = 0; n < 2; ++n) {
+    const float inv = 1.0f / sum_of_groups(lrun[n]);
+    const int q = q0 + wave * 32 + n * 16 + l16;
+    if (q < T) {
+      uint16_t* op = out + (static_cast<int64_t>(row) * T + q) * ldo + head * HD + 4 * g4;
 #pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        const int d = dt * 32 + 8 * jj + 4 * lhi;
-        if (dt * 32 + 8 * jj >= HD) continue;
-        uint2 r;
-        r.x = cvt_pk_bf16(o[dt][4 * jj] * inv, o[dt][4 * jj + 1] * inv);
-        r.y = cvt_pk_bf16(o[dt][4 * jj + 2] * inv, o[dt][4 * jj + 3] * inv);
-        *reinterpret_cast<uint2*>(op + d) = r;
-      }
+      for (int dt = 0; dt < DT; ++dt)
+        if (dt * 16 + 4 * g4 < HD)
+          *reinterpret_cast<uint2*>(op + dt * 16) =
+              make_uint2(cvt_pk_bf16(o[dt][n][0] * inv, o[dt][n][1] * inv), cvt_pk_bf16(o[dt][n][2] * inv, o[dt][n][3] * inv));
+    }
   }
 }
 
@@ -602,14 +642,8 @@ Error launch_hd(const void* qkv, void* out, int64_t ldo, int rows, int T, int H,
     SPECA_HIP(hipGetLastError());
     return ok();
   }
-  constexpr size_t smem = static_cast<size_t>(4) * 64 * HD * sizeof(uint16_t) + (HD % 16 ? 16 : 0);
-  static bool attr_set = false;
-  if (smem > 64 * 1024 && !attr_set) {
-    SPECA_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(attention_dma_kernel<HD>), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem)));
-    attr_set = true;
-  }
   const float sl2 = 1.4426950408889634f / sqrtf(static_cast<float>(HD));
-  attention_dma_kernel<HD><<<dim3((T + 127) / 128, H, rows), 256, smem, st>>>(static_cast<const uint16_t*>(qkv), static_cast<uint16_t*>(out), ldo, T, H, sl2);
+  attention_dma_kernel<HD><<<dim3((T + 127) / 128, H, rows), 256, 0, st>>>(static_cast<const uint16_t*>(qkv), static_cast<uint16_t*>(out), ldo, T, H, sl2);
   SPECA_HIP(hipGetLastError());
   return ok();
 }
