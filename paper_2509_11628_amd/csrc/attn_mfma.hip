@@ -120,6 +120,11 @@ __device__ inline int value_chunk(int c, int r) {
 // of the lanes' maxima moves (every tile of a sequence of a few thousand keys).
 constexpr float kRescale = 8.0f;
 
+// A last block of at most this many queries has its waves share them and split the keys instead of leaving three of four idle.
+// 4 rows x 1025 tokens x 16 heads of 72, 64 blocks of one query behind one round of whole ones: 50.0 -> 45.2 us; nothing to gain
+// where rounds are many (27 286 tokens, 24 blocks of 22 queries among 5112: 8449 -> 8431).
+constexpr int kFewQueries = 32;
+
 // 16 bytes per lane from byte offset off[lane] of a buffer into LDS at the wave-uniform dst + 16 lane; zeros past the buffer's end
 __device__ __forceinline__ void buffer_to_lds(const uint16_t* buffer, int bytes, uint32_t off, uint16_t* dst) {
   const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(buffer), 0, bytes, 0x00020000);
@@ -151,7 +156,13 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
   uint16_t* Vs = smem + 2 * TILE;             // [2][64][HD]
   uint16_t* zero = smem + 4 * TILE;           // head_dim 72: the key columns 72 .. 95 of the last step
 
-  const int row = blockIdx.z, head = blockIdx.y, q0 = blockIdx.x * 128;
+  // Blocks of a few queries (the last one of a (row, head) whose T ends shortly past a multiple of 128) come last: they are
+  // short and fill what the rounds of whole blocks leave.
+  const int nq = gridDim.x, pairs = gridDim.y * gridDim.z, lin = blockIdx.x + nq * (blockIdx.y + gridDim.y * blockIdx.z);
+  const int whole = T - (nq - 1) * 128 <= kFewQueries ? nq - 1 : nq;          // whole blocks per pair
+  const bool few = lin >= whole * pairs;
+  const int pair = few ? lin - whole * pairs : lin / whole, q0 = (few ? whole : lin - pair * whole) * 128;
+  const int row = pair / H, head = pair - row * H;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g4 = lane >> 4;
   const int64_t D = static_cast<int64_t>(H) * HD;
@@ -160,7 +171,7 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
   bf16x8 qf[KS][2];                           // queries 16 n + l16, columns 32 ks + 8 g4 ..
 #pragma unroll
   for (int n = 0; n < 2; ++n) {
-    const int q = q0 + wave * 32 + n * 16 + l16;
+    const int q = q0 + (few ? 0 : wave * 32) + n * 16 + l16;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       Frag f;
@@ -193,7 +204,7 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
     for (int u = 0; u < LPW; ++u)
       if (CH % 4 == 0 || wave + 4 * u < CH) buffer_to_lds(from, static_cast<int>(keys * row_bytes), off[u], dst + (kt & 1) * TILE + (wave + 4 * u) * 512);
   };
-  // a wave whose queries all lie beyond T only loads (1025 tokens: three waves of every ninth block)
+  // a wave whose queries all lie beyond T only loads
   const bool active = q0 + wave * 32 < T;
 
   // Key fragment: keys 16 m + l16, chunk 4 ks + g4 of the tile in buffer kb (rows 16 apart are swizzled alike).
@@ -208,13 +219,31 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
   // Value fragment: dims 16 dt + l16 of the keys 32 u + 4 g4 .. + 3 and 32 u + 16 + 4 g4 .. + 3, in two transposing reads: lane j
   // of a group of 16 points at dims 16 dt + 4 (j % 4) of key k0 + j / 4 (chunk 2 dt + (j % 4) / 2, half j % 2).
   const int vrow = 4 * g4 + (l16 >> 2);
-  auto value_frag = [&](int vb, int u, int dt) {
+  auto value_half = [&](int vb, int k0, int dt) {                  // keys k0 + 4 g4 .. + 3 (rows 16 apart are swizzled alike)
     const int c0 = 2 * dt + ((l16 & 3) >> 1), c = CH % 2 == 0 || c0 < CH ? c0 : CH - 1;        // dims beyond HD: any, never stored
-    const uint16_t* va = Vs + vb * TILE + (32 * u + vrow) * HD + (l16 & 1) * 4 + (value_chunk<HD>(c, vrow) << 3);      // rows + 16 are swizzled alike
+    const uint16_t* va = Vs + vb * TILE + (k0 + vrow) * HD + (l16 & 1) * 4 + (value_chunk<HD>(c, vrow) << 3);
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)va);
+  };
+  auto value_frag = [&](int vb, int u, int dt) {
     union { short4v h[2]; bf16x8 v; } vf;
-    vf.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)va);
-    vf.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(va + 16 * HD));
+    vf.h[0] = value_half(vb, 32 * u, dt);
+    vf.h[1] = value_half(vb, 32 * u + 16, dt);
     return vf.v;
+  };
+  auto store = [&](const float (&sum)[2]) {
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      const float inv = 1.0f / sum[n];
+      const int q = q0 + (few ? 0 : wave * 32) + n * 16 + l16;
+      if (q < T) {
+        uint16_t* op = out + (static_cast<int64_t>(row) * T + q) * ldo + head * HD + 4 * g4;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+          if (dt * 16 + 4 * g4 < HD)
+            *reinterpret_cast<uint2*>(op + dt * 16) =
+                make_uint2(cvt_pk_bf16(o[dt][n][0] * inv, o[dt][n][1] * inv), cvt_pk_bf16(o[dt][n][2] * inv, o[dt][n][3] * inv));
+      }
+    }
   };
 
   // Online softmax.  A lane's scores of a tile: s[m][n][i], key 16 m + 4 g4 + i, query 16 n + l16.
@@ -259,11 +288,119 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
       if (kt * 64 + (i >> 3) * 16 + 4 * g4 + (i & 3) >= T) s[i >> 3][(i >> 2) & 1][i & 3] = -INFINITY;
   };
 
+  // Ring: keys are fetched two tiles ahead, values one.  At the top of tile kt the wave's outstanding loads are K(kt + 1) and V(kt);
+  // behind the barrier K(kt + 2) overwrites K(kt) (read in tile kt - 1) and V(kt + 1) overwrites V(kt - 1).  A wave's own fragment
+  // reads are complete before the barrier, and no memory access moves across it.
+#define SPECA_PIN() __builtin_amdgcn_sched_barrier(0)
+#define SPECA_TURN()                                        \
+  {                                                         \
+    __builtin_amdgcn_s_waitcnt(0x0070);                     \
+    asm volatile("" ::: "memory");                          \
+    __builtin_amdgcn_s_barrier();                           \
+    asm volatile("" ::: "memory");                          \
+    SPECA_PIN();                                            \
+  }
+  const int ntiles = (T + 63) / 64;
+  if (few) {
+    // At most 32 queries: the waves share them and split every tile's keys, 16 each, with statistics of their own (one after the
+    // other in a single wave, the block would take half as long as a whole one).  Second contraction by 16x16x16 instructions.
+    floatx4 s[2];
+    float m[2] = {-INFINITY, -INFINITY}, l[2] = {};
+    issue(0, Ks, koff);
+    issue(0, Vs, voff);
+    for (int kt = 0; kt < ntiles; ++kt) {
+      SPECA_TURN()
+      if (kt + 1 < ntiles) {
+        issue(kt + 1, Ks, koff);
+        issue(kt + 1, Vs, voff);
+      }
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const bf16x8 kf = key_frag(kt & 1, ks, wave);
+#pragma unroll
+        for (int n = 0; n < 2; ++n) s[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[ks][n], ks ? s[n] : floatx4{}, 0, 0, 0);
+      }
+      short4v pf[2];
+#pragma unroll
+      for (int n = 0; n < 2; ++n) {
+        float t = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (kt * 64 + wave * 16 + 4 * g4 + i >= T) s[n][i] = -INFINITY;
+          t = fmaxf(t, s[n][i]);
+        }
+        const float mnew = fmaxf(m[n], max_of_groups(t)), off = mnew == -INFINITY ? 0.0f : mnew * scale_log2e;      // no finite score yet: weights 0
+        const float c = fast_exp2(m[n] * scale_log2e - off);
+        m[n] = mnew;
+        l[n] *= c;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          s[n][i] = fast_exp2(fmaf(s[n][i], scale_log2e, -off));
+          l[n] += s[n][i];
+        }
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) o[dt][n] *= c;
+        union { uint32_t u[2]; short4v v; } pk;
+        pk.u[0] = cvt_pk_bf16(s[n][0], s[n][1]);
+        pk.u[1] = cvt_pk_bf16(s[n][2], s[n][3]);
+        pf[n] = pk.v;
+      }
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) {
+        const short4v vf = value_half(kt & 1, 16 * wave, dt);
+#pragma unroll
+        for (int n = 0; n < 2; ++n) o[dt][n] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf, pf[n], o[dt][n], 0, 0, 0);
+      }
+    }
+    // together: everything relative to the largest maximum, then waves 1 .. 3 hand their sums to wave 0 through LDS
+    float* stat = reinterpret_cast<float*>(smem);
+    SPECA_TURN()
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+      if (g4 == 0) stat[wave * 32 + n * 16 + l16] = m[n];
+    SPECA_TURN()
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      float top = -INFINITY;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) top = fmaxf(top, stat[w * 32 + n * 16 + l16]);
+      const float c = fast_exp2(m[n] * scale_log2e - top * scale_log2e);
+      l[n] = sum_of_groups(l[n]) * c;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) o[dt][n] *= c;
+    }
+    SPECA_TURN()
+    constexpr int PART = DT * 2 * 256 + 128;                       // floats of a wave: O, then the sums of every lane
+    static_assert(3 * PART * 4 <= 4 * TILE * 2, "three waves' sums in the operand buffers");
+    if (wave) {
+      float* part = stat + (wave - 1) * PART;
+#pragma unroll
+      for (int n = 0; n < 2; ++n) {
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<floatx4*>(part + ((dt * 2 + n) * 64 + lane) * 4) = o[dt][n];
+        part[DT * 512 + n * 64 + lane] = l[n];
+      }
+    }
+    SPECA_TURN()
+    if (wave) return;
+#pragma unroll
+    for (int w = 0; w < 3; ++w) {
+      const float* part = stat + w * PART;
+#pragma unroll
+      for (int n = 0; n < 2; ++n) {
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) o[dt][n] += *reinterpret_cast<const floatx4*>(part + ((dt * 2 + n) * 64 + lane) * 4);
+        l[n] += part[DT * 512 + n * 64 + lane];
+      }
+    }
+    store(l);
+    return;
+  }
+
   // Tile kt, whose scores lie in sc with their reference known.  A wave issues in order, so what runs side by side is written side by
   // side, pinned around every pair of matrix instructions: first the scores of tile kt + 1 with the first NP probabilities of tile
   // kt, then O^T += V^T P^T with the other probabilities in its first half and the maximum of tile kt + 1 in its second.  Fragments
   // are read RA steps ahead.  NEXT: there is a tile kt + 1; the last one is masked.
-#define SPECA_PIN() __builtin_amdgcn_sched_barrier(0)
   constexpr int NS = 4 * KS, NV = 2 * DT, RA = 4, NP = 20;
   auto tile = [&](floatx4 (&sc)[4][2], floatx4 (&sn)[4][2], int kt, int buf, auto next_tag) {
     constexpr bool NEXT = decltype(next_tag)::value;
@@ -324,17 +461,6 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
     for (int n = 0; n < 2; ++n) lrun[n] += psum[n];
     if constexpr (NEXT) reference();
   };
-  // Ring: keys are fetched two tiles ahead, values one.  At the top of tile kt the wave's outstanding loads are K(kt + 1) and V(kt);
-  // behind the barrier K(kt + 2) overwrites K(kt) (read in tile kt - 1) and V(kt + 1) overwrites V(kt - 1).  A wave's own fragment
-  // reads are complete before the barrier, and no memory access moves across it.
-#define SPECA_TURN()                                        \
-  {                                                         \
-    __builtin_amdgcn_s_waitcnt(0x0070);                     \
-    asm volatile("" ::: "memory");                          \
-    __builtin_amdgcn_s_barrier();                           \
-    asm volatile("" ::: "memory");                          \
-    SPECA_PIN();                                            \
-  }
   // tile kt, not the last one, in buffer PAR = kt % 2, its scores in SC
 #define SPECA_ATTN_TILE(PAR, SC, SN)                                      \
   {                                                                       \
@@ -343,7 +469,6 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
     issue(kt + 1, Vs, voff);                                              \
     if (active) tile(SC, SN, kt, PAR, std::true_type());                  \
   }
-  const int ntiles = (T + 63) / 64;
   floatx4 sa[4][2], sb[4][2];
   issue(0, Ks, koff);
   SPECA_TURN()
@@ -382,18 +507,8 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
 #undef SPECA_PIN
 
 #pragma unroll
-  for (int n = 0; n < 2; ++n) {
-    const float inv = 1.0f / sum_of_groups(lrun[n]);
-    const int q = q0 + wave * 32 + n * 16 + l16;
-    if (q < T) {
-      uint16_t* op = out + (static_cast<int64_t>(row) * T + q) * ldo + head * HD + 4 * g4;
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-        if (dt * 16 + 4 * g4 < HD)
-          *reinterpret_cast<uint2*>(op + dt * 16) =
-              make_uint2(cvt_pk_bf16(o[dt][n][0] * inv, o[dt][n][1] * inv), cvt_pk_bf16(o[dt][n][2] * inv, o[dt][n][3] * inv));
-    }
-  }
+  for (int n = 0; n < 2; ++n) lrun[n] = sum_of_groups(lrun[n]);
+  store(lrun);
 }
 
 // Whole-sequence form for T <= 256: one block of 8 waves per (row, head).  Every key and value of the

@@ -195,10 +195,10 @@ def test_attention_infinite_value_in_the_last_row(T, hd, dtype):
 
 
 @pytest.mark.parametrize("T,hd,dtype,first,last", [(17, 64, "f32", 16, 17), (40, 16, "f32", 32, 40), (17, 16, "bf16", 16, 17), (300, 72, "f32", 288, 300),
-                                                   (70, 128, "f32", 16, 32), (70, 32, "bf16", 48, 70)])
+                                                   (70, 128, "f32", 16, 32), (70, 32, "bf16", 48, 70), (257, 64, "bf16", 0, 16)])
 def test_attention_keys_of_minus_infinity(T, hd, dtype, first, last):
-    """Scores of -inf over whole 16-key tiles, so that a wave of the fp32 kernel sees no finite score: those keys have weight 0
-    and the result is the attention over the others (fp32 rounding; bf16 rounds the result once)."""
+    """Scores of -inf over whole 16-key tiles, so that a wave of the fp32 kernel, or one that shares the last query with others and
+    takes 16 keys of every tile, sees no finite score: those keys have weight 0 and the result is the attention over the others (fp32 rounding; bf16 rounds the result once)."""
     bd = _bd()
     rng = np.random.default_rng(T + hd)
     qkv = si._store(rng.standard_normal((1, T, 3, 1, hd)).astype(np.float32), dtype)
