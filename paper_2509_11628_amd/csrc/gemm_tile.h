@@ -48,6 +48,83 @@ __device__ __forceinline__ bool tile_coords(int tiles_m, int tiles_n, int group_
   return true;
 }
 
+// Which quads of a tile are a thread's in the epilogue: row qr + p RPP of a half, column quad part QPR + tid % QPR.
+template <int BM, int BN, int NT, int EH>
+struct TileQuads {
+  static constexpr int PARTS = NT % (BN / 4) ? 3 : 1;       // a tile of 192 columns is written 64 columns at a time
+  static constexpr int QPR = BN / 4 / PARTS;                // quads per row
+  static constexpr int RPP = NT / QPR;                      // rows per pass
+  static constexpr int PASSES = EH / RPP;
+  static constexpr int HALVES = BM / EH;
+  static_assert(BM % EH == 0 && NT % QPR == 0 && EH % RPP == 0, "epilogue shape");
+};
+
+// Branch epilogue without planes to read back (ring layout, order 0, no refresh) of a tile inside one batch row.  What bounds an
+// epilogue is its chain of memory round trips: a load behind a store is waited for together with that store.  So the residual
+// of the whole tile and the gate are requested at once, ahead of the staging through LDS, and only stores follow (before, 4 batches of
+// 4 rows on 256x128 tiles, 16 single rows on 128x128).  16 rows x 256 tokens x 1152 features, 28 blocks, 50 steps 105.4 -> 103.2 ms;
+// 2 rows 37.94 -> 37.82, two rows of 845 tokens x 3072 features, 6 blocks, 8 steps 14.60 -> 14.48.  The same loads ahead of the
+// K loop on the small tiles hold the first operands back: 2 rows 37.8 -> 41.6.
+template <int BM, int BN, int NT, int EH>
+struct BranchAhead {
+  using Q = TileQuads<BM, BN, NT, EH>;
+  BranchRow<bf16_t> br;
+  float gate[Q::PARTS][4], hv[Q::HALVES][Q::PARTS][Q::PASSES][4];
+
+  __device__ __forceinline__ bool load(const GemmEpi& epi, int m0, int n0, int M, int N) {
+    const int i_first = m0 / epi.tokens;
+    if (i_first != ((m0 + BM < M ? m0 + BM : M) - 1) / epi.tokens) return false;
+    br = branch_row<bf16_t>(epi, i_first, m0);
+    if (br.order) return false;
+    const int tid = threadIdx.x, qr = tid / Q::QPR;
+#pragma unroll
+    for (int part = 0; part < Q::PARTS; ++part) {
+      const int n = n0 + (part * Q::QPR + tid % Q::QPR) * 4;
+      if (n < N) Store4<float>::ld(br.gate + n, gate[part]);
+    }
+#pragma unroll
+    for (int h = 0; h < Q::HALVES; ++h)
+#pragma unroll
+      for (int part = 0; part < Q::PARTS; ++part)
+#pragma unroll
+        for (int p = 0; p < Q::PASSES; ++p) {
+          const int r = h * EH + qr + p * Q::RPP, n = n0 + (part * Q::QPR + tid % Q::QPR) * 4;
+          if (n < N && m0 + r < M) Store4<float>::ld(br.h + static_cast<int64_t>(br.t0 + r) * epi.ldh + n, hv[h][part][p]);
+        }
+    return true;
+  }
+
+  // the quad's result v (bias added)
+  __device__ __forceinline__ void store(const GemmEpi& epi, int h, int part, int p, int n, const float (&v)[4]) const {
+    const int64_t pos = static_cast<int64_t>(br.t0 + h * EH + static_cast<int>(threadIdx.x) / Q::QPR + p * Q::RPP) * epi.ldh + n;
+    if (br.refresh) st4_stream(br.d[0] + pos, v);
+    float x[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x[q] = fmaf(gate[part][q], v[q], hv[h][part][p][q]);
+    Store4<float>::st(br.h + pos, x);
+  }
+};
+
+// the tile's rows h EH .. on their way through LDS, by the waves that hold them
+template <int BM, int BN, int WGM, int WGN, int EH>
+__device__ __forceinline__ void stage_rows(const floatx16 (&acc)[BN / WGN / 32][BM / WGM / 32], float* Cs, int h) {
+  constexpr int WM = BM / WGM, WN = BN / WGN;
+  static_assert(EH % WM == 0, "epilogue shape");
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wm = wave / WGN, wn = wave % WGN, l32 = lane & 31, lhi = lane >> 5;
+  if (wm * WM / EH != h) return;
+#pragma unroll
+  for (int j = 0; j < WM / 32; ++j)
+#pragma unroll
+    for (int i = 0; i < WN / 32; ++i)
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) {
+        const int r = wm * WM - h * EH + j * 32 + l32, c = wn * WN + i * 32 + 8 * jj + 4 * lhi;
+        *reinterpret_cast<float4*>(Cs + r * (BN + 4) + c) =
+            make_float4(acc[i][j][4 * jj], acc[i][j][4 * jj + 1], acc[i][j][4 * jj + 2], acc[i][j][4 * jj + 3]);
+      }
+}
+
 // Epilogue of one block tile.  acc[i][j][4*jj + ii] = C[m][n] with m = wm*WM + j*32 + l32,
 // n = wn*WN + i*32 + 8*jj + 4*lhi + ii inside the tile.  The tile goes through LDS (fp32, rows padded
 // by 16 bytes: conflict-free for the 16-byte writes of 16 consecutive lanes), EH rows at a time, so
@@ -58,24 +135,49 @@ template <int BM, int BN, int WGM, int WGN, int MODE, int EH>
 __device__ __forceinline__ void tile_epilogue(floatx16 (&acc)[BN / WGN / 32][BM / WGM / 32], float* Cs, int m0, int n0, int M, int N,
                                               const EpiArg<MODE>& epi) {
   constexpr int NT = WGM * WGN * 64;
-  constexpr int WM = BM / WGM, WN = BN / WGN;
-  constexpr int TM = WM / 32, TN = WN / 32;
+  using Q = TileQuads<BM, BN, NT, EH>;
   constexpr int CST = BN + 4;                        // floats per staged row
-  constexpr int PARTS = NT % (BN / 4) ? 3 : 1;       // a tile of 192 columns is written 64 columns at a time
-  constexpr int QPR = BN / 4 / PARTS;                // quads per row
-  constexpr int RPP = NT / QPR;                      // rows per pass
-  constexpr int PASSES = EH / RPP;
-  static_assert(BM % EH == 0 && EH % WM == 0 && NT % QPR == 0 && EH % RPP == 0, "epilogue shape");
+  constexpr int PARTS = Q::PARTS, QPR = Q::QPR, RPP = Q::RPP, PASSES = Q::PASSES;
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WGN, wn = wave % WGN;
-  const int l32 = lane & 31, lhi = lane >> 5;
   const int qr = tid / QPR;
   float bias_p[PARTS][4] = {};                       // on its way while the tile goes through LDS
 #pragma unroll
   for (int part = 0; part < PARTS; ++part) {
     const int n = n0 + (part * QPR + tid % QPR) * 4;
     if (epi.bias && n < N) Store4<bf16_t>::ld(static_cast<const bf16_t*>(epi.bias) + n, bias_p[part]);
+  }
+  if constexpr (MODE == EPI_BRANCH) {
+    BranchAhead<BM, BN, NT, EH> ahead;
+    if (ahead.load(epi, m0, n0, M, N)) {
+      // own LDS accesses done, then a barrier; the loads above stay in flight
+      auto turn = [] {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+      };
+#pragma unroll
+      for (int h = 0; h < Q::HALVES; ++h) {
+        turn();
+        stage_rows<BM, BN, WGM, WGN, EH>(acc, Cs, h);
+        turn();
+#pragma unroll
+        for (int part = 0; part < PARTS; ++part) {
+          const int qc = (part * QPR + tid % QPR) * 4;
+#pragma unroll
+          for (int p = 0; p < PASSES; ++p) {
+            const int r = qr + p * RPP;
+            if (n0 + qc < N && m0 + h * EH + r < M) {
+              const float4 t = *reinterpret_cast<const float4*>(Cs + r * CST + qc);
+              const float* bias = bias_p[part];
+              const float v[4] = {t.x + bias[0], t.y + bias[1], t.z + bias[2], t.w + bias[3]};
+              ahead.store(epi, h, part, p, n0 + qc, v);
+            }
+          }
+        }
+      }
+      return;
+    }
   }
   // block-uniform row table when the whole tile lies inside one batch row: scalar loads
   const int m_last = (m0 + BM < M ? m0 + BM : M) - 1;
@@ -90,18 +192,7 @@ __device__ __forceinline__ void tile_epilogue(floatx16 (&acc)[BN / WGN / 32][BM 
 #pragma unroll 1
   for (int h = 0; h < BM / EH; ++h) {
     __syncthreads();                                 // operand buffers / previous part consumed
-    if (wm * WM / EH == h) {
-#pragma unroll
-      for (int j = 0; j < TM; ++j)
-#pragma unroll
-        for (int i = 0; i < TN; ++i)
-#pragma unroll
-          for (int jj = 0; jj < 4; ++jj) {
-            const int r = wm * WM - h * EH + j * 32 + l32, c = wn * WN + i * 32 + 8 * jj + 4 * lhi;
-            *reinterpret_cast<float4*>(Cs + r * CST + c) =
-                make_float4(acc[i][j][4 * jj], acc[i][j][4 * jj + 1], acc[i][j][4 * jj + 2], acc[i][j][4 * jj + 3]);
-          }
-    }
+    stage_rows<BM, BN, WGM, WGN, EH>(acc, Cs, h);
     __syncthreads();
     const int mh = m0 + h * EH;                      // first global row of this part
 #pragma unroll
@@ -111,7 +202,8 @@ __device__ __forceinline__ void tile_epilogue(floatx16 (&acc)[BN / WGN / 32][BM 
       const float* bias = bias_p[part];
       if constexpr (MODE == EPI_BRANCH) {
         // batches of EB rows: all loads of the batch are issued before its first store
-        // (fewer when the accumulators of a later part are still live: 128 registers for a 64x128 wave tile)
+        // (single rows when the accumulators of a later part are still live: pairs take more than the 256 registers that two
+        // waves per SIMD have)
         constexpr int EBMAX = (BM / EH > 1) ? 1 : 4;
         constexpr int EB = PASSES % EBMAX == 0 ? EBMAX : (PASSES % 2 == 0 ? 2 : 1);
         if (uniform) {

@@ -22,8 +22,11 @@ CASES = [
     (24, 15, 768, 12, 3072, ((128, 128), (256, 128))),
 ]
 
-# the same for the largest tile with every tile inside one row of the batch (planes and residual a whole tile at a time)
-INSIDE_ROWS = [(16, 32, 1024, 16, 1024, ((256, 256), (256, 256)))]
+# the same with tiles inside one row of the batch: every tile of the largest kind (planes and residual a whole tile at a time), and
+# some of the 256- and 192-row tiles that find the residual a whole tile ahead (row heights up to 128 have such tiles above)
+INSIDE_ROWS = [(16, 32, 1024, 16, 1024, ((256, 256), (256, 256))),
+               (14, 17, 1440, 20, 5760, ((128, 128), (256, 128))),
+               (5, 24, 1440, 20, 5760, ((128, 128), (192, 128)))]
 
 
 def tile_table():
