@@ -175,6 +175,28 @@ def test_attention_tiles_of_narrow_heads(T, hd):
     assert torch.equal(bd.attention(dq[1:].contiguous(), H)[0], got[1])
 
 
+@pytest.mark.parametrize("T,hd", [(257, 64), (300, 72), (1025, 128), (200, 72)])
+def test_attention_is_exact_at_the_largest_weight(T, hd):
+    """Two keys share the weight, the second, in a later tile, d = 0 .. 8 doublings above the first, and all values are alike: the result is
+    that value, bit for bit.  The largest probability is 1 without rounding; the other one, w0 <= 1/2 of the sum, is rounded by
+    2^-9 (just under 1) to 2^-8 (just over 1/2, w0 = 1/3) of itself, so the sums differ by less than 2^-9, half a step of the result at
+    the least.  A probability above 1 at the maximum would be off by up to 2^-8 of the whole."""
+    bd = _bd()
+    rng = np.random.default_rng(T + hd)
+    qkv = np.zeros((1, T, 3, 2, hd), np.float32)
+    d = np.linspace(0.0, 7.9, T)
+    rng.shuffle(d)
+    qkv[0, :, 0, :, 0] = (d * np.sqrt(hd) / np.log2(np.e))[:, None]
+    qkv[0, :, 0, :, 1] = 64.0
+    qkv[0, :, 1, :, 1] = -64.0                                 # weight 2^-500 and less for all keys but two
+    qkv[0, [3, T - 30], 1, :, 1] = 0.0
+    qkv[0, T - 30, 1, :, 0] = 1.0
+    value = si._store(rng.uniform(1.0, 2.0, (2, hd)).astype(np.float32), "bf16")
+    qkv[0, :, 2] = value
+    got = bd.attention(_dev(qkv.reshape(1, T, -1), "bf16"), 2).float().cpu().numpy().reshape(T, 2, hd)
+    assert np.array_equal(got, np.broadcast_to(value, got.shape)), int((got != value).any(axis=(1, 2)).sum())
+
+
 @pytest.mark.parametrize("T,hd,dtype", [(257, 64, "bf16"), (300, 72, "bf16"), (1025, 72, "bf16"), (300, 128, "bf16"), (200, 72, "bf16"), (33, 16, "bf16"),
                                         (17, 32, "f32"), (33, 64, "f32"), (300, 72, "f32"), (77, 128, "f32")])
 def test_attention_infinite_value_in_the_last_row(T, hd, dtype):
