@@ -259,7 +259,7 @@ __global__ __launch_bounds__(256, 2) void attention_dma_kernel(const uint16_t* _
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
       const float mnew = fmaxf(mref[n], max_of_groups(tmax[n]));
-      moff[n] = mnew * scale_log2e;
+      moff[n] = mnew == -INFINITY ? 0.0f : mnew * scale_log2e;     // no finite score yet: weights 0
       corr[n] = fast_exp2(mref[n] * scale_log2e - moff[n]);
       moved |= mnew != mref[n];
       mref[n] = mnew;

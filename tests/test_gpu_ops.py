@@ -235,6 +235,24 @@ def test_attention_keys_of_minus_infinity(T, hd, dtype, first, last):
     assert np.isnan(bd.attention(_dev(qkv.reshape(1, T, -1), dtype), 1).float().cpu().numpy()).all()
 
 
+@pytest.mark.parametrize("T,hd,first,last", [(257, 64, 0, 64), (300, 72, 0, 128), (1025, 128, 0, 64), (300, 128, 64, 256)])
+def test_attention_key_tiles_of_minus_infinity(T, hd, first, last):
+    """The same over whole tiles of 64 keys, the first ones among them: an online softmax has no finite maximum to start from.  Every
+    probability and the result are rounded by at most 2^-8 of themselves, sums are fp32."""
+    bd = _bd()
+    rng = np.random.default_rng(T + hd)
+    qkv = si._store(rng.standard_normal((1, T, 3, 1, hd)).astype(np.float32), "bf16")
+    qkv[:, :, :2] = np.abs(qkv[:, :, :2])                      # positive queries: every score against a key of -inf is -inf
+    rest = np.r_[0:first, last:T]
+    q, k, v = (qkv[:, :, i].transpose(0, 2, 1, 3).astype(np.float64) for i in range(3))
+    exp, size = (odit.attention(q, k[:, :, rest], x[:, :, rest]).transpose(0, 2, 1, 3).reshape(1, T, hd) for x in (v, np.abs(v)))
+    qkv[0, first:last, 1] = -np.inf
+    got = bd.attention(_dev(qkv.reshape(1, T, -1), "bf16"), 1).float().cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(got - exp) <= 2.0 ** -8 * (np.abs(exp) + size) + 1e-5)
+    qkv[0, :, 1] = -np.inf                                     # no finite score at all: no softmax
+    assert np.isnan(bd.attention(_dev(qkv.reshape(1, T, -1), "bf16"), 1).float().cpu().numpy()).all()
+
+
 @pytest.mark.parametrize("rows,H,dtype", [(65541, 1, "f32"), (65541, 1, "bf16"), (1, 65541, "f32")])
 def test_attention_of_more_rows_or_heads_than_a_grid_dimension(rows, H, dtype):
     bd = _bd()
