@@ -29,9 +29,14 @@
 // accumulators in the accumulation file (a quarter less LDS traffic): the same K-step, 2 us more in prologue and epilogue.
 //
 // Epilogue from registers, without LDS: the weight rows of a pair of 16-row tiles are interleaved in fours, so that a lane
-// ends up with eight consecutive features of one token (16 bytes of bf16, 64 bytes per token and instruction).
-// 4096 x 3456 x 1152 31.7 (through LDS) -> 30.7 us.
+// ends up with eight consecutive features of one token (16 bytes of bf16, 64 bytes per token and instruction).  The two pairs of a
+// token are stored one behind the other, so that whole lines of 128 bytes leave together.  All tokens of one pair ahead of the other
+// pair's, and 8 bytes per lane where N % 8 == 4, cost up to a third of a short layer (us with cold weights, half lines / whole lines;
+// the in-phase loop with its epilogue through LDS): 4096 x 4096 x 128 17.0 / 13.3 (16.0), 4096 x 3456 x 1152 36.2 / 32.6 (36.6),
+// 8192 x 8192 x 256 87 / 66 (70), 24808 x 12288 x 448 438 / 347 (370), 4089 x 4092 x 256 24.6 / 17.4 (17.9).
 // Needs K % 64 == 0, K >= 128 and the tile's operand rows within 4 GB.
+
+#include <type_traits>
 
 #include "gemm_tile.h"
 
@@ -50,19 +55,23 @@ static_assert(TM == 8 && TN == 4, "two halves of tokens, two pairs of feature ti
 constexpr int kWaitLds = 0xC07F;               // s_waitcnt lgkmcnt(0)
 template <int N> __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70); }
 
-// Eight consecutive features, n .. n + 7; `two`: the second four exist; `wide`: 16-byte accesses are aligned.
-__device__ __forceinline__ void st8(bf16_t* p, const float* v, bool two, bool wide) {
-  if (wide && two) {
-    *reinterpret_cast<uint4*>(p) = make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7]));
-  } else {
-    Store4<bf16_t>::st(p, v);
-    if (two) Store4<bf16_t>::st(p + 4, v + 4);
-  }
+// Eight consecutive features of a token (`two`: only the first four exist otherwise).  Rows start at multiples of four features, so
+// 16 bytes may lie at 8-byte alignment, which global stores allow.
+typedef u32x4_t __attribute__((aligned(8))) u32x4_a8;
+__device__ __forceinline__ u32x4_t pack8(const float* v) {
+  return u32x4_t{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7])};
+}
+__device__ __forceinline__ void st8(bf16_t* p, const float* v, bool two) {
+  if (two) *reinterpret_cast<u32x4_a8*>(p) = pack8(v);
+  else Store4<bf16_t>::st(p, v);
+}
+__device__ __forceinline__ void st8(float* p, const float* v, bool two) {
+  Store4<float>::st(p, v);
+  if (two) Store4<float>::st(p + 4, v + 4);
 }
 __device__ __forceinline__ void st8_stream(bf16_t* p, const float* v, bool two, bool wide) {
   if (wide && two) {
-    const u32x4_t r = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7])};
-    __builtin_nontemporal_store(r, reinterpret_cast<u32x4_t*>(p));
+    __builtin_nontemporal_store(pack8(v), reinterpret_cast<u32x4_t*>(p));
   } else {
     st4_stream(p, v);
     if (two) st4_stream(p + 4, v + 4);
@@ -146,45 +155,59 @@ __device__ __forceinline__ void branch_each(const floatx4 (&acc)[TN][TM], Branch
   if constexpr (J + 1 < TM) branch_each<P, J + 1>(acc, br, gate, epi, spans, m0, rows, row0, n, two, wide, bias);
 }
 
-// The epilogue of a lane for pair P of the tiles: tokens m0 + row0, + 16, ... (TM of them), features n .. n + 7.
-template <int MODE, int P>
-__device__ __forceinline__ void lane_epilogue(const floatx4 (&acc)[TN][TM], int m0, int row0, int n, int M, int N, const EpiArg<MODE>& epi) {
+__device__ __forceinline__ void load_bias(const void* bias, int n, int N, float (&b)[8]) {
+  if (!bias) return;
+  if (n < N) Store4<bf16_t>::ld(static_cast<const bf16_t*>(bias) + n, b);
+  if (n + 4 < N) Store4<bf16_t>::ld(static_cast<const bf16_t*>(bias) + n + 4, b + 4);
+}
+
+// The branch epilogue of a lane for pair P of the tiles: tokens m0 + row0, + 16, ... (TM of them), features n .. n + 7.
+template <int P>
+__device__ __forceinline__ void lane_branch(const floatx4 (&acc)[TN][TM], int m0, int row0, int n, int M, int N, const GemmEpi& epi) {
   if (n >= N) return;
   const bool two = n + 4 < N;
   const int rows = M - m0 < BM ? M - m0 : BM;
   float bias[8] = {};
-  if (epi.bias) {
-    Store4<bf16_t>::ld(static_cast<const bf16_t*>(epi.bias) + n, bias);
-    if (two) Store4<bf16_t>::ld(static_cast<const bf16_t*>(epi.bias) + n + 4, bias + 4);
+  load_bias(epi.bias, n, N, bias);
+  const bool wide = ((reinterpret_cast<uintptr_t>(epi.g.base) & 15) | ((epi.g.E | epi.cache_elem_offset | epi.ldh) & 7)) == 0;
+  const int i_first = m0 / epi.tokens;
+  float gate[8];
+  // a tile inside one batch row needs its table once for the whole block (scalar loads)
+  const bool spans = i_first != (m0 + rows - 1) / epi.tokens;
+  BranchRow<bf16_t> br = branch_row<bf16_t>(epi, i_first, m0);
+  load_gate(br.gate, n, two, gate);
+  if (!spans && br.order == 0) branch_tokens<P, 0, TM, false>(acc, br, gate, epi.ldh, rows, row0, n, two, wide, bias);
+  else branch_each<P, 0>(acc, br, gate, epi, spans, m0, rows, row0, n, two, wide, bias);
+}
+
+// The eight features of pair P for the lane's token j, into `out`.
+template <int MODE, int P, typename T>
+__device__ __forceinline__ void store_pair(const floatx4 (&acc)[TN][TM], int j, const float (&bias)[8], T* out, int n, int N) {
+  if (n >= N) return;
+  float v[8];
+  lane_values<P>(acc, j, bias, v);
+  if constexpr (MODE == EPI_GELU || MODE == EPI_SILU) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = MODE == EPI_GELU ? gelu_tanh_f(v[q]) : silu_f(v[q]);
   }
-  if constexpr (MODE == EPI_BRANCH) {
-    const bool wide = ((reinterpret_cast<uintptr_t>(epi.g.base) & 15) | ((epi.g.E | epi.cache_elem_offset | epi.ldh) & 7)) == 0;
-    const int i_first = m0 / epi.tokens;
-    float gate[8];
-    // a tile inside one batch row needs its table once for the whole block (scalar loads)
-    const bool spans = i_first != (m0 + rows - 1) / epi.tokens;
-    BranchRow<bf16_t> br = branch_row<bf16_t>(epi, i_first, m0);
-    load_gate(br.gate, n, two, gate);
-    if (!spans && br.order == 0) branch_tokens<P, 0, TM, false>(acc, br, gate, epi.ldh, rows, row0, n, two, wide, bias);
-    else branch_each<P, 0>(acc, br, gate, epi, spans, m0, rows, row0, n, two, wide, bias);
-  } else {
-    const bool wide = ((reinterpret_cast<uintptr_t>(epi.out) & 15) | (epi.ldo & 7)) == 0;
+  st8(out + n, v, n + 4 < N);
+}
+
+// Epilogues that store into `out`: a lane's tokens m0 + row0, + 16, ... (TM of them), features n .. n + 7 and n + 32 .. n + 39.
+template <int MODE>
+__device__ __forceinline__ void lane_store(const floatx4 (&acc)[TN][TM], int m0, int row0, int n, int M, int N, const EpiArg<MODE>& epi) {
+  using T = std::conditional_t<MODE == EPI_F32, float, bf16_t>;
+  float bias[2][8] = {};
+  load_bias(epi.bias, n, N, bias[0]);
+  load_bias(epi.bias, n + 32, N, bias[1]);
+  const int rows = M - m0 < BM ? M - m0 : BM;
 #pragma unroll
-    for (int j = 0; j < TM; ++j) {
-      const int r = row0 + j * 16;
-      if (r < rows) {
-        float v[8];
-        lane_values<P>(acc, j, bias, v);
-        const int64_t pos = static_cast<int64_t>(m0 + r) * epi.ldo + n;
-        if constexpr (MODE == EPI_F32) {
-          Store4<float>::st(static_cast<float*>(epi.out) + pos, v);
-          if (two) Store4<float>::st(static_cast<float*>(epi.out) + pos + 4, v + 4);
-        } else {
-#pragma unroll
-          for (int q = 0; q < 8; ++q) v[q] = MODE == EPI_GELU ? gelu_tanh_f(v[q]) : MODE == EPI_SILU ? silu_f(v[q]) : v[q];
-          st8(static_cast<bf16_t*>(epi.out) + pos, v, two, wide);
-        }
-      }
+  for (int j = 0; j < TM; ++j) {
+    const int r = row0 + j * 16;
+    if (r < rows) {
+      T* out = static_cast<T*>(epi.out) + static_cast<int64_t>(m0 + r) * epi.ldo;
+      store_pair<MODE, 0>(acc, j, bias[0], out, n, N);
+      store_pair<MODE, 1>(acc, j, bias[1], out, n + 32, N);
     }
   }
 }
@@ -347,8 +370,13 @@ __global__ __launch_bounds__(512, 2) void gemm_phase_kernel(const uint16_t* __re
 #undef SPECA_LOAD_W
 #undef SPECA_LOAD_A
 #undef SPECA_BUFFER_TO_LDS
-  lane_epilogue<MODE, 0>(acc, m0, wm * WM + l16, n0 + wn * WN + g4 * 8, M, N, epi);
-  lane_epilogue<MODE, 1>(acc, m0, wm * WM + l16, n0 + wn * WN + 32 + g4 * 8, M, N, epi);
+  const int row0 = wm * WM + l16, n = n0 + wn * WN + g4 * 8;
+  if constexpr (MODE == EPI_BRANCH) {
+    lane_branch<0>(acc, m0, row0, n, M, N, epi);
+    lane_branch<1>(acc, m0, row0, n + 32, M, N, epi);
+  } else {
+    lane_store<MODE>(acc, m0, row0, n, M, N, epi);
+  }
 }
 
 template <int MODE>
