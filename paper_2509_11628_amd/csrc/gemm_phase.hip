@@ -33,7 +33,10 @@
 // token are stored one behind the other, so that whole lines of 128 bytes leave together.  All tokens of one pair ahead of the other
 // pair's, and 8 bytes per lane where N % 8 == 4, cost up to a third of a short layer (us with cold weights, half lines / whole lines;
 // the in-phase loop with its epilogue through LDS): 4096 x 4096 x 128 17.0 / 13.3 (16.0), 4096 x 3456 x 1152 36.2 / 32.6 (36.6),
-// 8192 x 8192 x 256 87 / 66 (70), 24808 x 12288 x 448 438 / 347 (370), 4089 x 4092 x 256 24.6 / 17.4 (17.9).
+// 8192 x 8192 x 256 87 / 66 (70), 24808 x 12288 x 448 438 / 347 (370), 4089 x 4092 x 256 24.6 / 17.4 (17.9).  The branch epilogue takes both
+// pairs of a token together for the same reason, and needs half as many round trips where it goes token by token (us of a reference
+// step of 4 blocks in one row group, planes of differences, one pair at a time / both; in-phase loop): 30 rows x 784 tokens x 1152 features
+// 5538 / 5318 (6633), 28 x 1024 x 768 4078 / 4002 (4039), 57 x 256 x 1152 3496 / 3478 (3544); without planes 45 x 400 x 1152 3554 / 3442 (3748).
 // Needs K % 64 == 0, K >= 128 and the tile's operand rows within 4 GB.
 
 #include <type_traits>
@@ -78,136 +81,148 @@ __device__ __forceinline__ void st8_stream(bf16_t* p, const float* v, bool two, 
   }
 }
 
-// Results and bias of the lane's token j and its features of pair P of the tiles.
-template <int P>
-__device__ __forceinline__ void lane_values(const floatx4 (&acc)[TN][TM], int j, const float (&bias)[8], float (&v)[8]) {
+// The lane's token j, its eight features of pair P of the tiles (bias added)
+__device__ __forceinline__ void lane_values(const floatx4 (&acc)[TN][TM], int j, int P, float (&v)[8]) {
 #pragma unroll
-  for (int q = 0; q < 8; ++q) v[q] = acc[2 * P + q / 4][j][q % 4] + bias[q];
+  for (int q = 0; q < 8; ++q) v[q] = acc[2 * P + q / 4][j][q % 4];
 }
 
-// Branch epilogue of the lane's tokens J .. J + EB - 1, features n .. n + 7, all loads ahead of the first store; PLANES: planes
-// are read back (order >= 1).
-template <int P, int J, int EB, bool PLANES>
-__device__ __forceinline__ void branch_tokens(const floatx4 (&acc)[TN][TM], const BranchRow<bf16_t>& br, const float (&gate)[8], int64_t ldh, int rows,
-                                              int row0, int n, bool two, bool wide, const float (&bias)[8]) {
-  float hv[EB][8], old[PLANES ? EB : 1][SPECA_MAX_ORDER][8];
+// Eight values of features n .. n + 7; past N, a multiple of 4, the last four again (never stored), so that no branch parts the loads
+template <typename T>
+__device__ __forceinline__ void ld8(const T* p, int n, int N, float (&v)[8]) {
+  Store4<T>::ld(p + min(n, N - 4), v);
+  Store4<T>::ld(p + min(n + 4, N - 4), v + 4);
+}
+__device__ __forceinline__ void load_gate(const float* gate, int n, int N, float (&g)[2][8]) {
+  ld8(gate, n, N, g[0]);
+  ld8(gate, n + 32, N, g[1]);
+}
+
+// Branch epilogue of the lane's tokens J .. J + EB - 1, features n .. n + 7 and n + 32 .. n + 39, all loads ahead of the first store;
+// PLANES: planes are read back (order >= 1).
+template <int J, int EB, bool PLANES>
+__device__ __forceinline__ void branch_tokens(const floatx4 (&acc)[TN][TM], const BranchRow<bf16_t>& br, const float (&gate)[2][8], int64_t ldh, int rows,
+                                              int row0, int n, int N, bool wide) {
+  float hv[EB][2][8], old[PLANES ? EB : 1][SPECA_MAX_ORDER][2][8];
 #pragma unroll
   for (int u = 0; u < EB; ++u) {
-    const int r = row0 + (J + u) * 16;
-    if (r < rows) {
-      const int64_t pos = (br.t0 + r) * ldh + n;
-      Store4<float>::ld(br.h + pos, hv[u]);
-      if (two) Store4<float>::ld(br.h + pos + 4, hv[u] + 4);
-      if constexpr (PLANES) {
+    const int64_t at = (br.t0 + min(row0 + (J + u) * 16, rows - 1)) * ldh;       // rows past the end: the last one again
 #pragma unroll
-        for (int o = 0; o < SPECA_MAX_ORDER; ++o)
-          if (o < br.order) {
-            ld4_stream(br.d[o] + pos, old[u][o]);
-            if (two) ld4_stream(br.d[o] + pos + 4, old[u][o] + 4);
+    for (int P = 0; P < 2; ++P) ld8(br.h + at, n + 32 * P, N, hv[u][P]);
+    if constexpr (PLANES) {
+#pragma unroll
+      for (int o = 0; o < SPECA_MAX_ORDER; ++o)
+        if (o < br.order) {
+#pragma unroll
+          for (int P = 0; P < 2; ++P) {
+            ld4_stream(br.d[o] + at + min(n + 32 * P, N - 4), old[u][o][P]);
+            ld4_stream(br.d[o] + at + min(n + 32 * P + 4, N - 4), old[u][o][P] + 4);
           }
-      }
+        }
     }
   }
 #pragma unroll
   for (int u = 0; u < EB; ++u) {
     const int r = row0 + (J + u) * 16;
     if (r < rows) {
-      const int64_t pos = (br.t0 + r) * ldh + n;
-      float v[8];
-      lane_values<P>(acc, J + u, bias, v);
-      if (br.refresh) {
-        st8_stream(br.d[0] + pos, v, two, wide);
-        if constexpr (PLANES) {
-          float cur[8];
+      const int64_t at = (br.t0 + r) * ldh;
+      float v[2][8];
 #pragma unroll
-          for (int q = 0; q < 8; ++q) cur[q] = v[q];
+      for (int P = 0; P < 2; ++P) lane_values(acc, J + u, P, v[P]);
+      if (br.refresh) {
+        float cur[2][8];
+#pragma unroll
+        for (int P = 0; P < 2; ++P) {
+          const int np = n + 32 * P;
+          if (np < N) st8_stream(br.d[0] + at + np, v[P], np + 4 < N, wide);
+#pragma unroll
+          for (int q = 0; q < 8; ++q) cur[P][q] = v[P][q];
+        }
+        if constexpr (PLANES) {
 #pragma unroll
           for (int o = 1; o <= SPECA_MAX_ORDER; ++o)
             if (o <= br.order) {
 #pragma unroll
-              for (int q = 0; q < 8; ++q) cur[q] = (cur[q] - old[u][o - 1][q]) * br.inv[o - 1];
-              st8_stream(br.d[o] + pos, cur, two, wide);
+              for (int P = 0; P < 2; ++P) {
+                const int np = n + 32 * P;
+#pragma unroll
+                for (int q = 0; q < 8; ++q) cur[P][q] = (cur[P][q] - old[u][o - 1][P][q]) * br.inv[o - 1];
+                if (np < N) st8_stream(br.d[o] + at + np, cur[P], np + 4 < N, wide);
+              }
             }
         }
       }
 #pragma unroll
-      for (int q = 0; q < 8; ++q) v[q] = fmaf(gate[q], v[q], hv[u][q]);
-      Store4<float>::st(br.h + pos, v);
-      if (two) Store4<float>::st(br.h + pos + 4, v + 4);
+      for (int P = 0; P < 2; ++P) {
+        const int np = n + 32 * P;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[P][q] = fmaf(gate[P][q], v[P][q], hv[u][P][q]);
+        if (np < N) st8(br.h + at + np, v[P], np + 4 < N);
+      }
     }
   }
 }
 
-__device__ __forceinline__ void load_gate(const float* gate, int n, bool two, float (&g)[8]) {
-  Store4<float>::ld(gate + n, g);
-  if (two) Store4<float>::ld(gate + n + 4, g + 4);
-}
-
 // Token by token from J on, planes read back; where the tile spans rows of the batch every token looks its row up.
-template <int P, int J>
-__device__ __forceinline__ void branch_each(const floatx4 (&acc)[TN][TM], BranchRow<bf16_t>& br, float (&gate)[8], const GemmEpi& epi, bool spans, int m0,
-                                            int rows, int row0, int n, bool two, bool wide, const float (&bias)[8]) {
-  if (spans && row0 + J * 16 < rows) {
-    br = branch_row<bf16_t>(epi, (m0 + row0 + J * 16) / epi.tokens, m0);
-    load_gate(br.gate, n, two, gate);
+template <int J>
+__device__ __forceinline__ void branch_each(const floatx4 (&acc)[TN][TM], BranchRow<bf16_t>& br, float (&gate)[2][8], const GemmEpi& epi, bool spans, int m0,
+                                            int rows, int row0, int n, int N, bool wide) {
+  if (spans) {
+    br = branch_row<bf16_t>(epi, (m0 + min(row0 + J * 16, rows - 1)) / epi.tokens, m0);
+    load_gate(br.gate, n, N, gate);
   }
-  branch_tokens<P, J, 1, true>(acc, br, gate, epi.ldh, rows, row0, n, two, wide, bias);
-  if constexpr (J + 1 < TM) branch_each<P, J + 1>(acc, br, gate, epi, spans, m0, rows, row0, n, two, wide, bias);
+  branch_tokens<J, 1, true>(acc, br, gate, epi.ldh, rows, row0, n, N, wide);
+  if constexpr (J + 1 < TM) branch_each<J + 1>(acc, br, gate, epi, spans, m0, rows, row0, n, N, wide);
 }
 
-__device__ __forceinline__ void load_bias(const void* bias, int n, int N, float (&b)[8]) {
-  if (!bias) return;
-  if (n < N) Store4<bf16_t>::ld(static_cast<const bf16_t*>(bias) + n, b);
-  if (n + 4 < N) Store4<bf16_t>::ld(static_cast<const bf16_t*>(bias) + n + 4, b + 4);
-}
-
-// The branch epilogue of a lane for pair P of the tiles: tokens m0 + row0, + 16, ... (TM of them), features n .. n + 7.
-template <int P>
-__device__ __forceinline__ void lane_branch(const floatx4 (&acc)[TN][TM], int m0, int row0, int n, int M, int N, const GemmEpi& epi) {
-  if (n >= N) return;
-  const bool two = n + 4 < N;
-  const int rows = M - m0 < BM ? M - m0 : BM;
-  float bias[8] = {};
-  load_bias(epi.bias, n, N, bias);
-  const bool wide = ((reinterpret_cast<uintptr_t>(epi.g.base) & 15) | ((epi.g.E | epi.cache_elem_offset | epi.ldh) & 7)) == 0;
-  const int i_first = m0 / epi.tokens;
-  float gate[8];
-  // a tile inside one batch row needs its table once for the whole block (scalar loads)
-  const bool spans = i_first != (m0 + rows - 1) / epi.tokens;
-  BranchRow<bf16_t> br = branch_row<bf16_t>(epi, i_first, m0);
-  load_gate(br.gate, n, two, gate);
-  if (!spans && br.order == 0) branch_tokens<P, 0, TM, false>(acc, br, gate, epi.ldh, rows, row0, n, two, wide, bias);
-  else branch_each<P, 0>(acc, br, gate, epi, spans, m0, rows, row0, n, two, wide, bias);
-}
-
-// The eight features of pair P for the lane's token j, into `out`.
-template <int MODE, int P, typename T>
-__device__ __forceinline__ void store_pair(const floatx4 (&acc)[TN][TM], int j, const float (&bias)[8], T* out, int n, int N) {
-  if (n >= N) return;
-  float v[8];
-  lane_values<P>(acc, j, bias, v);
-  if constexpr (MODE == EPI_GELU || MODE == EPI_SILU) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] = MODE == EPI_GELU ? gelu_tanh_f(v[q]) : silu_f(v[q]);
-  }
-  st8(out + n, v, n + 4 < N);
-}
-
-// Epilogues that store into `out`: a lane's tokens m0 + row0, + 16, ... (TM of them), features n .. n + 7 and n + 32 .. n + 39.
+// The epilogue of a lane: tokens m0 + row0, + 16, ... (TM of them), features n .. n + 7 and n + 32 .. n + 39.
 template <int MODE>
-__device__ __forceinline__ void lane_store(const floatx4 (&acc)[TN][TM], int m0, int row0, int n, int M, int N, const EpiArg<MODE>& epi) {
-  using T = std::conditional_t<MODE == EPI_F32, float, bf16_t>;
-  float bias[2][8] = {};
-  load_bias(epi.bias, n, N, bias[0]);
-  load_bias(epi.bias, n + 32, N, bias[1]);
+__device__ __forceinline__ void lane_epilogue(floatx4 (&acc)[TN][TM], int m0, int row0, int n, int M, int N, const EpiArg<MODE>& epi) {
   const int rows = M - m0 < BM ? M - m0 : BM;
+  if (epi.bias) {
+    float bias[2][8] = {};
+    ld8(static_cast<const bf16_t*>(epi.bias), n, N, bias[0]);
+    ld8(static_cast<const bf16_t*>(epi.bias), n + 32, N, bias[1]);
 #pragma unroll
-  for (int j = 0; j < TM; ++j) {
-    const int r = row0 + j * 16;
-    if (r < rows) {
-      T* out = static_cast<T*>(epi.out) + static_cast<int64_t>(m0 + r) * epi.ldo;
-      store_pair<MODE, 0>(acc, j, bias[0], out, n, N);
-      store_pair<MODE, 1>(acc, j, bias[1], out, n + 32, N);
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+      for (int j = 0; j < TM; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[i][j][q] += bias[i / 2][i % 2 * 4 + q];
+  }
+  if constexpr (MODE == EPI_BRANCH) {
+    const bool wide = ((reinterpret_cast<uintptr_t>(epi.g.base) & 15) | ((epi.g.E | epi.cache_elem_offset | epi.ldh) & 7)) == 0;
+    const int i_first = m0 / epi.tokens;
+    float gate[2][8];
+    // a tile inside one batch row needs its table once for the whole block (scalar loads)
+    const bool spans = i_first != (m0 + rows - 1) / epi.tokens;
+    BranchRow<bf16_t> br = branch_row<bf16_t>(epi, i_first, m0);
+    load_gate(br.gate, n, N, gate);
+    if (!spans && br.order == 0) {
+      branch_tokens<0, TM / 2, false>(acc, br, gate, epi.ldh, rows, row0, n, N, wide);
+      branch_tokens<TM / 2, TM / 2, false>(acc, br, gate, epi.ldh, rows, row0, n, N, wide);
+    } else {
+      branch_each<0>(acc, br, gate, epi, spans, m0, rows, row0, n, N, wide);
+    }
+  } else {
+    using T = std::conditional_t<MODE == EPI_F32, float, bf16_t>;
+#pragma unroll
+    for (int j = 0; j < TM; ++j) {
+      const int r = row0 + j * 16;
+      if (r < rows) {
+        T* out = static_cast<T*>(epi.out) + static_cast<int64_t>(m0 + r) * epi.ldo;
+#pragma unroll
+        for (int P = 0; P < 2; ++P) {
+          const int np = n + 32 * P;
+          float v[8];
+          lane_values(acc, j, P, v);
+          if constexpr (MODE == EPI_GELU || MODE == EPI_SILU) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = MODE == EPI_GELU ? gelu_tanh_f(v[q]) : silu_f(v[q]);
+          }
+          if (np < N) st8(out + np, v, np + 4 < N);
+        }
+      }
     }
   }
 }
@@ -370,13 +385,7 @@ __global__ __launch_bounds__(512, 2) void gemm_phase_kernel(const uint16_t* __re
 #undef SPECA_LOAD_W
 #undef SPECA_LOAD_A
 #undef SPECA_BUFFER_TO_LDS
-  const int row0 = wm * WM + l16, n = n0 + wn * WN + g4 * 8;
-  if constexpr (MODE == EPI_BRANCH) {
-    lane_branch<0>(acc, m0, row0, n, M, N, epi);
-    lane_branch<1>(acc, m0, row0, n + 32, M, N, epi);
-  } else {
-    lane_store<MODE>(acc, m0, row0, n, M, N, epi);
-  }
+  lane_epilogue<MODE>(acc, m0, wm * WM + l16, n0 + wn * WN + g4 * 8, M, N, epi);
 }
 
 template <int MODE>
