@@ -278,11 +278,14 @@ struct DiT final : Model {
   // Whether n rows run as two groups side by side.  A layer of all rows wastes what its last round of tiles leaves idle; the tiles
   // of two half layers fill each other's partial rounds, but each half waits for a whole tile time per layer.  The cost model of
   // the tiles weighs one against the other for the four layers of a block, and two groups are taken where it expects
-  // more than 5 % from them.  Measured over 88 sizes (384 to 1152 features, 64 to 1024 tokens, 2 to 64 rows; reference steps, one
-  // group / two groups in ms): taken 1152 features at 1024, 2048 and 8192 tokens 9.47 / 8.85, 12.8 / 12.2, 31.1 / 29.7, 768 at 3072
-  // and 12288 10.2 / 10.0, 25.0 / 24.0; not taken 1152 at 3584 and 4096 15.5 / 16.5, 18.6 / 18.6, 1024 at 4096 and 8192 15.0 / 15.6,
-  // 24.0 / 25.7.  In narrow models with many tokens the passes that are bound by memory weigh more than the rounds: 384 features
-  // at 8192, 12288 and 16384 tokens 8.45 / 8.76, 14.8 / 13.8, 14.3 / 13.1, 512 at 12288 15.7 / 14.7.  Narrower still, launches bound a
+  // more than 5 % from them.  Measured over 550 random sizes (384 to 1440 features, 64 to 1024 tokens, 2 to 64 rows, both layouts;
+  // reference steps of 4 blocks): the 119 taken gain 4.3 % on the mean (-10 to +16 %), the 431 others would lose 8.5 % (gains of up to 16 % left
+  // where 256x256 tiles fill a round in part and planes of differences are read: 10 rows x 576 tokens x 768).  One group / two groups in us: taken 28 rows x
+  // 576 tokens x 1152 features 3253 / 2954, 62 x 576 x 1024 6438 / 5824, 59 x 256 x 1152 2738 / 2496, 14 x 784 x 384 692 / 635; not taken
+  // 16 x 256 x 1152 917 / 919, 5 x 256 x 1152 549 / 595, 26 x 144 x 768 580 / 645, 28 x 196 x 512 620 / 680.  The choice moves with the tiles' constants:
+  // with ones that overrated a round of 256x256 it took one group at 28 x 1024 x 768 (4127 instead of 3533).
+  // In narrow models with many tokens the passes that are bound by memory weigh more than the rounds: 384 features
+  // at 8192, 12288 and 16384 tokens 8.45 / 8.76, 14.8 / 13.8, 14.3 / 13.1 ms of 28 blocks, 512 at 12288 15.7 / 14.7.  Narrower still, launches bound a
   // step: 64 to 256 features at 3072 to 16384 tokens lose up to 39 % in two groups and gain 4 % at best.  A single block (the verification) does not repay the
   // fork and join (16 rows of 1152 features and 256 tokens, six steps of eight blocks 5.00 / 5.18), and fp32 layers are bound by their
   // own latency (33 sizes of 256 to 768 features: 7 % gained at best, 22 % lost at worst).

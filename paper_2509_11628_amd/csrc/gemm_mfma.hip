@@ -286,10 +286,13 @@ Error launch_dlds(const Operands& o, const GemmEpi& epi, hipStream_t st) {
 // that with the best kernels on the mean where the plain constants lay 0.6 % (7 % at worst; 4096 x 1152 x 1152 without plane reads 6.8 us
 // above, with them 22.7, 9216 x 3072 x 12288 with them 152).  192x192 and 128x96 are not offered to it: leaving them out costs
 // 0.02 %.
-// The constants of 256x256, 256x128 and 128x192, which compete with each other, were fitted again when 256x256 moved to
-// gemm_phase.hip: on 110 layers that only store (512 to 8192 rows, 768 to 3072 features) and 44 branch layers inside models the
-// picks lie 0.20 % above the best kernels on the mean (layers that only store) and of half a block (branch layers), 0.54 % with
-// the constants before.
+// Fitted again since, each time on the kernels that ran then: 256x128 and 128x192 when 256x256 moved to gemm_phase.hip, 256x256
+// and the r of 128x192 when its epilogue stored whole lines.  Cold weights, 256 to 27 286 rows: picks among single kernels lie 0.7 % above the
+// best one on the mean over 260 layers with K % 64 == 0 (0.9 % before) and 0.8 % over 160 with tails of K (1.1 % before; r = 0.45 had sent
+// 8568 x 2304 x 1448 to 128x128 tiles, 83 -> 87.5 us).  The times of long layers on 256x256 come out low (4096 x 3456 x 3072 69 us, modelled 62),
+// where no other kind is near.  The branch values of the kinds other than 256x256 are older than the residual requested ahead of the staging
+// (gemm_tile.h), which shortens all of them: over 223 branch layers of models with 384 to 1152 features, 1000 to 43 000 rows and both
+// layouts the picks cost 0.7 % of a reference step on the mean and 8 % at worst (fc2 of 3840 x 768 x 3072 on 96x128 where 128x64 is best).
 struct TileKind {
   int bm, bn;
   float a, c, b, r;    // three in microseconds, a ratio
@@ -298,7 +301,7 @@ struct TileKind {
   bool whole_steps;    // K % 64 == 0
 };
 constexpr TileKind kTileKinds[] = {
-    {256, 256, 6.3f, 8.7f, 1.067f, 1.19f, 15.4f, 0.80f, false, true},      // 0: phases (gemm_phase.hip)
+    {256, 256, 2.4f, 7.8f, 1.07f, 1.15f, 16.5f, 0.95f, false, true},       // 0: phases (gemm_phase.hip)
     {256, 128, 2.4f, 5.66f, 0.791f, 1.17f, 9.5f, 1.00f, false, true},      // 1: large, 3 stages
     {128, 128, 0.8f, 6.40f, 0.535f, 1.00f, 11.39f, 0.98f, false, false},   // 2: ring of 4 stages x 64 columns
     {128, 128, 0.9f, 3.71f, 0.771f, 0.31f, 8.66f, 0.11f, true, false},     // 3: ring of 2 x 64
@@ -307,7 +310,7 @@ constexpr TileKind kTileKinds[] = {
     {64, 64, 0.0f, 3.98f, 0.294f, 0.95f, 4.60f, 0.86f, false, false},      // 6: ring of 4 x 128
     {32, 64, 0.0f, 3.67f, 0.266f, 0.98f, 4.61f, 0.77f, false, false},      // 7: ring of 4 x 128, two waves
     {192, 128, 1.3f, 5.69f, 0.656f, 1.15f, 21.68f, 0.85f, false, false},   // 8: ring of 3 x 64
-    {128, 192, 0.5f, 5.27f, 0.945f, 0.45f, 14.96f, 0.155f, true, false},    // 9: ring of 2 x 64
+    {128, 192, 0.5f, 5.27f, 0.945f, 0.40f, 14.96f, 0.155f, true, false},    // 9: ring of 2 x 64
     {192, 192, 2.5f, 11.1f, 0.879f, 1.08f, 0.0f, 0.0f, false, false},      // 10: ring of 3 x 64
     {96, 128, 0.0f, 4.72f, 0.435f, 1.07f, 13.07f, 0.84f, false, false},    // 11: ring of 4 x 64
     {128, 96, 1.2f, 3.06f, 0.710f, 0.30f, 0.0f, 0.0f, true, false},        // 12: ring of 2 x 64

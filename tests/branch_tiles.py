@@ -1,12 +1,13 @@
-"""Model shapes whose two branch layers (attention projection: rows x hidden x hidden, second MLP layer: rows x hidden x
-mlp_hidden) fall on each tile that the library runs the branch epilogue on, and the library's tile choice in Python, read
-from the table in its source, so that a refitted table does not silently move a shape to another tile."""
+"""The library's tile choice in Python, read from the table in its source, so that a refitted table does not silently move a shape to
+another tile; and model shapes whose two branch layers (attention projection: rows x hidden x hidden, second MLP layer: rows x hidden x
+mlp_hidden) fall on each tile that the library runs the branch epilogue on."""
 import math
 import os
 import re
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 COMPUTE_UNITS = 256
+SHORTEST_K = {(256, 256): 128}
 
 # rows, grid (tokens = grid^2), hidden, heads, mlp_hidden, (tile of the projection, tile of the second MLP layer)
 # tokens divide no tile height, so tiles span rows of the batch; hidden is no multiple of most tile widths
@@ -41,7 +42,7 @@ def branch_tile(table, M, N, K):
     """(height, width) of the tile for a layer with the branch epilogue, and how much dearer the next best one is modelled."""
     costs = []
     for bm, bn, a, _, b, _, cb, rb, two, whole_steps in table:
-        if cb == 0.0 or (whole_steps and (K % 64 or K < 64)):
+        if cb == 0.0 or (whole_steps and (K % 64 or K < SHORTEST_K.get((bm, bn), 64))):
             continue
         depth = math.ceil(math.ceil(M / bm) * math.ceil(N / bn) / COMPUTE_UNITS)
         odd = depth % 2
@@ -49,3 +50,34 @@ def branch_tile(table, M, N, K):
         costs.append((a + (cb + b * math.ceil(K / 64)) * rounds, (bm, bn)))
     costs.sort()
     return costs[0][1], costs[1][0] / costs[0][0]
+
+
+def _store_cost(kind, M, N, K):
+    bm, bn, a, c, b, r, _, _, two, _ = kind
+    depth = math.ceil(math.ceil(M / bm) * math.ceil(N / bn) / COMPUTE_UNITS)
+    odd = depth % 2
+    return a + (c + b * math.ceil(K / 64)) * ((depth - odd) / 2 * (1.0 + r) + odd if two else 1.0 + r * (depth - 1))
+
+
+def _store_kind(table, M, N, K):
+    kinds = [k for k in table if not k[9] or (K % 64 == 0 and K >= SHORTEST_K.get(k[:2], 64))]
+    costs = sorted((_store_cost(k, M, N, K), k[:2]) for k in kinds)
+    return costs[0][1], costs[0][0], costs[1][0]
+
+
+def store_tile(table, M, N, K):
+    """(height, width) of the tile for a layer that only stores, the columns that run on the largest tile ahead of it in a launch of
+    their own, and how much dearer the next best single tile is modelled."""
+    tile, cost, runner_up = _store_kind(table, M, N, K)
+    head, margin = 0, runner_up / cost
+    if M >= 256 and K % 64 == 0 and K >= SHORTEST_K[(256, 256)]:
+        rounds = 1
+        while (n1 := rounds * COMPUTE_UNITS // math.ceil(M / 256) * 256) < N:
+            rounds += 1
+            if n1 < 256:
+                continue
+            kind, rest, _ = _store_kind(table, M, N - n1, K)
+            rest += _store_cost(next(k for k in table if k[:2] == (256, 256)), M, n1, K)
+            if rest < (1.0 if head else 0.96) * cost:
+                tile, head, cost = kind, n1, rest
+    return tile, head, margin
