@@ -37,7 +37,7 @@
 // pairs of a token together for the same reason, and needs half as many round trips where it goes token by token (us of a reference
 // step of 4 blocks in one row group, planes of differences, one pair at a time / both; in-phase loop): 30 rows x 784 tokens x 1152 features
 // 5538 / 5318 (6633), 28 x 1024 x 768 4078 / 4002 (4039), 57 x 256 x 1152 3496 / 3478 (3544); without planes 45 x 400 x 1152 3554 / 3442 (3748).
-// Needs K % 64 == 0, K >= 128 and the tile's operand rows within 4 GB.
+// Needs K % 64 == 0 and the tile's operand rows within 4 GB.
 
 #include <type_traits>
 
@@ -347,19 +347,24 @@ __global__ __launch_bounds__(512, 2) void gemm_phase_kernel(const uint16_t* __re
     SPECA_BARRIER()                                                      \
     col += ROW;                                                          \
   }
-  const int nk = K / BK;                       // >= 2
+  const int nk = K / BK;
   SPECA_LOAD_W(0, 0, 0)
   SPECA_LOAD_A(0, 0, 0)
   SPECA_LOAD_W(1, 0, 0)
   SPECA_LOAD_A(1, 0, 0)
-  SPECA_LOAD_W(0, 1, ROW)
-  SPECA_LOAD_A(0, 1, ROW)
-  SPECA_LOAD_W(1, 1, ROW)
-  wait_loads<12>();
+  if (nk > 1) {
+    SPECA_LOAD_W(0, 1, ROW)
+    SPECA_LOAD_A(0, 1, ROW)
+    SPECA_LOAD_W(1, 1, ROW)
+    wait_loads<12>();                          // W0 has landed
+  } else {
+    wait_loads<6>();
+  }
   SPECA_BARRIER()
   SPECA_READ_W(0, 0, 0)
   __builtin_amdgcn_s_waitcnt(kWaitLds);
-  wait_loads<10>();
+  if (nk > 1) wait_loads<10>();                // A0 has landed
+  else wait_loads<4>();
   SPECA_BARRIER()
   if (wm) SPECA_BARRIER()                      // half a phase behind from here on
   int col = 0, left = nk - 1;                  // byte column of the K-step, K-steps to come after it
@@ -409,7 +414,7 @@ Error launch_mode(const Operands& o, const GemmEpi& epi, hipStream_t st) {
 
 bool gemm_phase_fits(const Operands& o) {
   const int64_t stride = o.lda > o.ldw ? o.lda : o.ldw;
-  return o.K % BK == 0 && o.K >= 2 * BK && stride < (int64_t{1} << 31) / 256 - o.K;      // 255 rows and a row's own bytes below 2^32
+  return o.K % BK == 0 && o.K >= BK && stride < (int64_t{1} << 31) / 256 - o.K;      // 255 rows and a row's own bytes below 2^32
 }
 
 Error launch_gemm_phase(const Operands& o, const GemmEpi& epi, hipStream_t st) {

@@ -7,7 +7,6 @@ import re
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 COMPUTE_UNITS = 256
-SHORTEST_K = {(256, 256): 128}
 
 # rows, grid (tokens = grid^2), hidden, heads, mlp_hidden, (tile of the projection, tile of the second MLP layer)
 # tokens divide no tile height, so tiles span rows of the batch; hidden is no multiple of most tile widths
@@ -29,6 +28,9 @@ INSIDE_ROWS = [(16, 32, 1024, 16, 1024, ((256, 256), (256, 256))),
                (14, 17, 1440, 20, 5760, ((128, 128), (256, 128))),
                (5, 24, 1440, 20, 5760, ((128, 128), (192, 128)))]
 
+# rows, features, K and activation of layers that only store, all of them on the largest tile
+LARGEST = [(4089, 4092, 64, 1), (4089, 4092, 128, 0), (4089, 4088, 192, 1), (4096, 4096, 256, 2), (3841, 3844, 320, 0)]
+
 
 def tile_table():
     src = open(os.path.join(ROOT, "paper_2509_11628_amd", "csrc", "gemm_mfma.hip")).read()
@@ -42,7 +44,7 @@ def branch_tile(table, M, N, K):
     """(height, width) of the tile for a layer with the branch epilogue, and how much dearer the next best one is modelled."""
     costs = []
     for bm, bn, a, _, b, _, cb, rb, two, whole_steps in table:
-        if cb == 0.0 or (whole_steps and (K % 64 or K < SHORTEST_K.get((bm, bn), 64))):
+        if cb == 0.0 or (whole_steps and (K % 64 or K < 64)):
             continue
         depth = math.ceil(math.ceil(M / bm) * math.ceil(N / bn) / COMPUTE_UNITS)
         odd = depth % 2
@@ -60,7 +62,7 @@ def _store_cost(kind, M, N, K):
 
 
 def _store_kind(table, M, N, K):
-    kinds = [k for k in table if not k[9] or (K % 64 == 0 and K >= SHORTEST_K.get(k[:2], 64))]
+    kinds = [k for k in table if not k[9] or K % 64 == 0]
     costs = sorted((_store_cost(k, M, N, K), k[:2]) for k in kinds)
     return costs[0][1], costs[0][0], costs[1][0]
 
@@ -70,7 +72,7 @@ def store_tile(table, M, N, K):
     their own, and how much dearer the next best single tile is modelled."""
     tile, cost, runner_up = _store_kind(table, M, N, K)
     head, margin = 0, runner_up / cost
-    if M >= 256 and K % 64 == 0 and K >= SHORTEST_K[(256, 256)]:
+    if M >= 256 and K % 64 == 0:
         rounds = 1
         while (n1 := rounds * COMPUTE_UNITS // math.ceil(M / 256) * 256) < N:
             rounds += 1

@@ -8,6 +8,7 @@ oracle's value rounded to bf16, plus that fp32 noise."""
 import numpy as np
 import pytest
 
+import branch_tiles
 import speca_inputs as si
 from oracle import dit as odit, speca_core as core
 
@@ -122,10 +123,10 @@ def test_linear_bf16_tiles(M, N, K):
         assert torch.equal(bd.linear(da[r:r + 1].contiguous(), dw, db)[0], out[r])
 
 
-@pytest.mark.parametrize("M,N,K,act", [(4089, 4092, 128, 0), (4089, 4088, 192, 1), (4096, 4096, 256, 2), (3841, 3844, 320, 0)])
+@pytest.mark.parametrize("M,N,K,act", branch_tiles.LARGEST)
 def test_linear_bf16_largest_tile(M, N, K, act):
-    """One round of 256x256 tiles: two to five K-steps (the loop ends with two or three of them), rows and columns that end inside
-    a tile, widths that forbid 16-byte stores (N % 8 == 4), every activation; the bits of a row alone (the smallest tile)."""
+    """One round of 256x256 tiles: one to five K-steps (the loop ends with two or three of them), rows and columns that end inside
+    a tile, widths that put every other row at 8-byte alignment (N % 8 == 4), every activation; the bits of a row alone (the smallest tile)."""
     bd = _bd()
     g = torch.Generator(device="cuda").manual_seed(M + N + K)
     a = torch.randn((M, K), generator=g, device="cuda").to(torch.bfloat16)

@@ -191,8 +191,16 @@ def test_branch_tile_cases_reach_every_tile_of_the_branch_epilogue():
 
 
 @pytest.mark.parametrize("M,N,K,tile", [(8568, 2304, 1448, (128, 192)), (9500, 3456, 4016, (128, 192)), (15082, 11936, 5464, (128, 192)),
-                                        (1349, 9216, 256, (256, 256)), (2693, 9216, 192, (256, 256)), (3377, 4608, 256, (256, 256))])
+                                        (1349, 9216, 256, (256, 256)), (2693, 9216, 192, (256, 256)), (3377, 4608, 256, (256, 256)),
+                                        (7662, 12288, 64, (256, 256))])
 def test_store_layers_run_on_the_tile_that_was_measured_fastest(M, N, K, tile):
     """Sizes where constants fitted to an older kernel had picked a tile that is 3 to 8 % slower."""
     import branch_tiles as bt
     assert bt.store_tile(bt.tile_table(), M, N, K)[:2] == (tile, 0)
+
+
+def test_largest_tile_cases_run_on_the_largest_tile():
+    import branch_tiles as bt
+    for M, N, K, _ in bt.LARGEST:
+        tile, head, margin = bt.store_tile(bt.tile_table(), M, N, K)
+        assert tile == (256, 256) and head == 0 and margin > 1.003, (M, N, K, tile, head, margin)
