@@ -31,6 +31,12 @@ INSIDE_ROWS = [(16, 32, 1024, 16, 1024, ((256, 256), (256, 256))),
 # rows, features, K and activation of layers that only store, all of them on the largest tile
 LARGEST = [(4089, 4092, 64, 1), (4089, 4092, 128, 0), (4089, 4088, 192, 1), (4096, 4096, 256, 2), (3841, 3844, 320, 0)]
 
+# rows, features and K of layers that only store: every tile, ragged rows and columns, tails of K where the tile takes them, and
+# 256x128 (three stages, two groups of loaders) at 3 n, 3 n + 1 and 3 n + 2 K-steps
+STORES = [(1, 16, 8), (33, 4, 128), (65, 140, 200), (3401, 264, 8), (257, 3304, 136), (771, 2500, 136), (1034, 3592, 384), (132, 3408, 328), (1715, 3524, 248),
+          (3839, 3224, 456), (2461, 3280, 456), (2348, 2528, 512), (3588, 4000, 64), (3437, 3460, 520), (845, 3076, 6152), (500, 3076, 3080), (3603, 796, 1912),
+          (7359, 772, 768), (7177, 784, 832), (7277, 772, 896), (3209, 2520, 880), (741, 3424, 40)]
+
 
 def tile_table():
     src = open(os.path.join(ROOT, "paper_2509_11628_amd", "csrc", "gemm_mfma.hip")).read()
@@ -61,16 +67,16 @@ def _store_cost(kind, M, N, K):
     return a + (c + b * math.ceil(K / 64)) * ((depth - odd) / 2 * (1.0 + r) + odd if two else 1.0 + r * (depth - 1))
 
 
-def _store_kind(table, M, N, K):
-    kinds = [k for k in table if not k[9] or K % 64 == 0]
-    costs = sorted((_store_cost(k, M, N, K), k[:2]) for k in kinds)
+def store_kind(table, M, N, K):
+    """Place in the table of the cheapest tile for a layer that only stores, its modelled time and that of the next one."""
+    costs = sorted((_store_cost(k, M, N, K), i) for i, k in enumerate(table) if not k[9] or K % 64 == 0)
     return costs[0][1], costs[0][0], costs[1][0]
 
 
 def store_tile(table, M, N, K):
     """(height, width) of the tile for a layer that only stores, the columns that run on the largest tile ahead of it in a launch of
     their own, and how much dearer the next best single tile is modelled."""
-    tile, cost, runner_up = _store_kind(table, M, N, K)
+    kind, cost, runner_up = store_kind(table, M, N, K)
     head, margin = 0, runner_up / cost
     if M >= 256 and K % 64 == 0:
         rounds = 1
@@ -78,8 +84,8 @@ def store_tile(table, M, N, K):
             rounds += 1
             if n1 < 256:
                 continue
-            kind, rest, _ = _store_kind(table, M, N - n1, K)
-            rest += _store_cost(next(k for k in table if k[:2] == (256, 256)), M, n1, K)
+            tail, rest, _ = store_kind(table, M, N - n1, K)
+            rest += _store_cost(table[0], M, n1, K)
             if rest < (1.0 if head else 0.96) * cost:
-                tile, head, cost = kind, n1, rest
-    return tile, head, margin
+                kind, head, cost = tail, n1, rest
+    return table[kind][:2], head, margin

@@ -41,10 +41,9 @@ def _check(got, exp, dtype, K):
 SHAPES = [  # M, N, K
     (128, 128, 64), (256, 64, 128), (200, 192, 72), (1, 64, 64), (130, 1152, 1152), (515, 256, 4608), (16, 2304, 1152),
     (300, 16, 64),
-    # the direct-to-LDS tiles, each with ragged M and N: 128x128, 256x128 (3-stage ring, K-steps 3n+1 and 3n+2), 256x256
+    # middle and large bf16 tiles with ragged M and N (every tile by name: test_linear_bf16_tiles)
     (1000, 3304, 128), (4000, 1160, 256), (4000, 1160, 320), (4000, 3400, 2048),
-    # one and two K-steps (the rings re-read the last tile into a free stage past the end of K): 3-stage and 2-stage
-    # 256x128, and the shortest K the 256x256 tile takes
+    # one and two K-steps on middle tiles and on 256x256, and many
     (4096, 3456, 64), (4000, 1160, 64), (4096, 3456, 128), (4608, 3072, 2048),
     # the MLP GEMMs of configuration 3 at full size
     (4096, 4608, 1152), (4096, 1152, 4608),
@@ -56,7 +55,7 @@ SHAPES = [  # M, N, K
 @pytest.mark.parametrize("act", [0, 1, 2])
 def test_linear(M, N, K, dtype, act):
     # activations: two shapes on small tiles (one with a tail of K), three on middle and large ones, and the fc1 shape of
-    # configuration 3 (one wave of 256x256 tiles plus a remainder launch)
+    # configuration 3 (one round of 256x256 tiles plus a remainder launch)
     if act and (M, N, K) not in ((200, 192, 72), (130, 1152, 1152), (4000, 1160, 256), (4000, 3400, 2048), (4096, 3456, 128),
                                  (4096, 4608, 1152)):
         return
@@ -104,9 +103,7 @@ def test_linear_f32_tiles(M, N, K):
     assert torch.equal(bd.linear(da[r:r + 1].contiguous(), dw, db)[0], out[r])
 
 
-@pytest.mark.parametrize("M,N,K", [(1, 16, 8), (33, 4, 128), (65, 140, 200), (3401, 264, 8), (257, 3304, 136), (771, 2500, 136), (1034, 3592, 384),
-                                   (132, 3408, 328), (1715, 3524, 248), (3839, 3224, 456), (2461, 3280, 456), (2348, 2528, 512), (3588, 4000, 64), (3437, 3460, 520),
-                                   (845, 3076, 6152), (500, 3076, 3080), (3603, 796, 1912)])
+@pytest.mark.parametrize("M,N,K", branch_tiles.STORES)
 def test_linear_bf16_tiles(M, N, K):
     """bf16 layers at the edges of the tiles of 32x64 to 256x256 (ragged rows and columns, K tails of 8): sampled rows against
     the oracle, and the same bits for a row computed alone (the smallest tile)."""

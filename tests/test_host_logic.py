@@ -204,3 +204,13 @@ def test_largest_tile_cases_run_on_the_largest_tile():
     for M, N, K, _ in bt.LARGEST:
         tile, head, margin = bt.store_tile(bt.tile_table(), M, N, K)
         assert tile == (256, 256) and head == 0 and margin > 1.003, (M, N, K, tile, head, margin)
+
+
+def test_store_cases_reach_every_tile():
+    import branch_tiles as bt
+    table = bt.tile_table()
+    assert table[0][:2] == (256, 256)
+    got = [(bt.store_kind(table, M, N, K)[0], K % 64 != 0) for M, N, K in bt.STORES if bt.store_tile(table, M, N, K)[1] == 0]
+    assert {k for k, _ in got} == set(range(len(table)))
+    assert {k for k, tail in got if tail} == {k for k, t in enumerate(table) if not t[9]}
+    assert {K // 64 % 3 for M, N, K in bt.STORES if bt.store_tile(table, M, N, K)[:2] == ((256, 128), 0)} == {0, 1, 2}
