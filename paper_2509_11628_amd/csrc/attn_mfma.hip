@@ -94,13 +94,14 @@ __device__ inline void vt_write_off(int d, int kb, int* lo, int* hi) {
 // Keys and values beyond T read as zeros (the buffer ends there); their scores are masked to -inf, and the probability 0 meets no
 // infinite value (0 x inf is NaN).
 //
-// What bounds it: power (zeros instead of random data: 1210 to 1260 TFLOP/s against 1055 to 1150 at 24 heads of 128; without the
-// loads into LDS 1315), then the vector unit.  Before, the loads of the next tile were waited for ahead of the key reads of the
+// What bounds it: power (1059 TFLOP/s at 27 286 tokens x 24 heads of 128, 1327 on zeros, whose maxima never move), then the vector
+// unit.  Before, the loads of the next tile were waited for ahead of the key reads of the
 // current one (the compiler takes global_load_lds for a store that LDS reads may alias), every key fragment was waited for
-// in front of its own matrix instruction, O was rescaled whenever a maximum moved, and 32x32x16 instructions drew more power.
-// us, before -> now: 1 row x 27 286 tokens x 24 heads of 128 9533 -> 8510, 1 x 4608 x 24 307 -> 275, 2 x 845 x 24 42.8 -> 36.2,
-// 4 x 1025 x 16 heads of 72 61.6 -> 50.7, 16 x 1024 x 16 142 -> 122, 2 x 2048 x 6 heads of 64 41.7 -> 33.9.  32x32x16 in the same
-// schedule is faster on zeros (1490 TFLOP/s) and slower on data where rounds end ragged (13 632 tokens 2306 -> 2160 us); 8 waves
+// in front of its own matrix instruction, and 32x32x16 instructions drew more power.
+// us, before -> now: 1 row x 27 286 tokens x 24 heads of 128 9765 -> 8639, 1 x 4608 x 24 308 -> 296, 2 x 845 x 24 40.7 -> 38.1,
+// 4 x 1025 x 16 heads of 72 60.2 -> 45.6, 16 x 1024 x 16 142 -> 127, 2 x 2048 x 6 heads of 64 41.7 -> 34.6.  Variants, measured with
+// a reference of the exponentials that lagged (below; 1055 to 1150 TFLOP/s, 1210 to 1260 on zeros): without the loads into LDS 1315; 32x32x16 in
+// the same schedule faster on zeros (1490) and slower on data where rounds end ragged (13 632 tokens 2306 -> 2160 us); 8 waves
 // on one pair of tiles gain 6 % at 4608 tokens and lose 4 % at 27 286 and 13 % at 4096; the loads as inline assembly, without
 // the wait that the compiler puts ahead of a tile's value reads: 0.5 %.
 typedef short short4v __attribute__((ext_vector_type(4)));
@@ -116,7 +117,7 @@ __device__ inline int value_chunk(int c, int r) {
 }
 
 // The reference of a query's exponentials is its running maximum, so the largest probability is 1 exactly, also as bf16.  A reference
-// that follows only past a factor of 2^8 saves most of the rescaling (us, lagging / following: 1 row x 4608 tokens x 24 heads of 128
+// that follows only past a factor of 2^8, a published way to rescale rarely, saves time (us, lagging / following: 1 row x 4608 tokens x 24 heads of 128
 // 270 / 284, 1 x 27 286 x 24 8502 / 8618, 4 x 1025 x 16 heads of 72 45.0 / 45.3), but rounds the largest probability too: error against
 // 64 bits 2.33e-3 instead of 2.22e-3 for scores of deviation 1 over 1025 keys, 2.26e-3 instead of 1.80e-3 for deviation 2.5.
 

@@ -385,8 +385,8 @@ static Choice choose(const Operands& o, bool branch) {
   Choice c{-1, 0, 0.0};
   c.kind = pick_tile(o, branch, &c.time);
   // A little more than whole rounds of 256x256 tiles (the 4096 x 4608 x 1152 fc1 GEMM: 288): the columns that make whole
-  // rounds go on the large tile, the remaining columns in a second launch (47 + 13 us against 61 us for the best single
-  // kernel; 4096 x 9216 x 3072, 576 tiles: 236 -> 207 us).  Column ranges only shift pointers, so this is limited to the epilogues that store into `out`.
+  // rounds go on the large tile, the remaining columns in a second launch (together 47.6 us against 61.8 for the best single
+  // kernel, 128x192; 4096 x 9216 x 3072, 576 tiles: 207 -> 181 us).  Column ranges only shift pointers, so this is limited to the epilogues that store into `out`.
   if (!branch && o.M >= 256 && gemm_phase_fits(o)) {
     const int tiles_m = (o.M + 255) / 256;
     for (int rounds = 1;; ++rounds) {

@@ -9,7 +9,7 @@
 // 64 x 32 quadrant of every wave (16 matrix instructions): (A0,W0) (A0,W1) (A1,W1) (A1,W0).  In front of its matrix part a
 // phase reads the one half that is new to it, in the order W0(0) A0(0) W1(0) A1(0) W0(1) A0(1) ... (W0(0) ahead of the loop),
 // so every phase reads at most eight fragments and issues the two direct-to-LDS loads (per wave) of one later half.
-// Waves 4..7 run half a phase behind waves 0..3 (one barrier more ahead of the loop): while one wave of a SIMD issues its reads
+// Waves 4..7 run half a phase behind waves 0..3 (one barrier more ahead of the loop; known as ping-pong): while one wave of a SIMD issues its reads
 // and loads the other has the matrix cores.  Two barriers per phase keep the groups in step:  reads, loads | matrix part |.
 //
 // With c the position of a half in that order, phase p = 1, 2, ... reads c = p and loads c = p + 6, which takes the LDS of
@@ -20,12 +20,12 @@
 //   - free: c = p - 2 was read in phase p - 2.  The fragments of a phase are used by its own matrix part, so the reads are
 //     complete before the barrier behind it; W0, read in a K-step's last phase and used in the next one, is waited for there.
 //     The group behind passes that barrier two barriers before any wave issues the loads of phase p.
-// Every load has six phases, over 2000 clocks, to land, and no wait empties the queue.
+// Every load has five phases, 1.6 us, to land, and no wait empties the queue.
 // What bounds it: LDS traffic (192 KB read and 64 KB written per K-step, 1.13 us alone) beside the matrix instructions
 // (1.02 us alone at the power limit): 1.28 us a K-step where the in-phase loop with one barrier and an empty load queue per
-// K-step and 32x32x16 took 1.46.  4608 x 3072 x 12288 289 -> 246 us, 4608 x 9216 x 3072 232 -> 202, 4096 x 3456 x 1152
-// 34.6 -> 30.7, 27286 x 9216 x 3072 1299 -> 1128, 8192^3 837 -> 718 (1533 TFLOP/s; the vendor library 691).  Without the
-// half-phase offset between the groups: 1012 instead of 1339 TFLOP/s at 4608 x 3072 x 12288.  Four waves of 128 x 128 with
+// K-step and 32x32x16 took 1.46.  us with warm weights, that loop -> this one with the epilogue below: 4608 x 3072 x 12288 287 -> 245,
+// 4608 x 9216 x 3072 238 -> 206, 4096 x 3456 x 1152 36.2 -> 32.1, 27286 x 9216 x 3072 1327 -> 1138, 8192^3 860 -> 744 (1478 TFLOP/s).
+// Without the half-phase offset between the groups: 1012 instead of 1339 TFLOP/s at 4608 x 3072 x 12288.  Four waves of 128 x 128 with
 // accumulators in the accumulation file (a quarter less LDS traffic): the same K-step, 2 us more in prologue and epilogue.
 //
 // Epilogue from registers, without LDS: the weight rows of a pair of 16-row tiles are interleaved in fours, so that a lane

@@ -1,4 +1,4 @@
-// What the two bf16 GEMM kernels share: types, operand description, tile numbering, the epilogue of a block tile.
+// What the three bf16 GEMM kernels share: types, operand description, tile numbering, the epilogue of a block tile.
 #pragma once
 
 #include "epilogue.h"
@@ -63,8 +63,9 @@ struct TileQuads {
 // epilogue is its chain of memory round trips: a load behind a store is waited for together with that store.  So the residual
 // of the whole tile and the gate are requested at once, ahead of the staging through LDS, and only stores follow (before, 4 batches of
 // 4 rows on 256x128 tiles, 16 single rows on 128x128).  16 rows x 256 tokens x 1152 features, 28 blocks, 50 steps 105.4 -> 103.2 ms;
-// 2 rows 37.94 -> 37.82, two rows of 845 tokens x 3072 features, 6 blocks, 8 steps 14.60 -> 14.48.  The same loads ahead of the
-// K loop on the small tiles hold the first operands back: 2 rows 37.8 -> 41.6.
+// 2 rows 37.94 -> 37.82, two rows of 845 tokens x 3072 features, 6 blocks, 8 steps 14.60 -> 14.48.  Every tile gains (us per layer inside
+// reference steps, 2 to 24 rows): 64x64 0.6 to 3.7, 32x64 1.3 to 2.8, 128x64 2.1 to 10, 96x128 1.3 to 14, 128x128 3.4 to 19, 128x192 6.6 to 21,
+// 192x128 1.5 to 17, 256x128 5.8 to 29.  The same loads ahead of the K loop on the small tiles hold the first operands back: 2 rows 37.8 -> 41.6.
 template <int BM, int BN, int NT, int EH>
 struct BranchAhead {
   using Q = TileQuads<BM, BN, NT, EH>;

@@ -22,7 +22,7 @@ CASES = [
     (24, 15, 768, 12, 3072, ((128, 128), (256, 128))),
 ]
 
-# the same with tiles inside one row of the batch: every tile of the largest kind (planes and residual a whole tile at a time), and
+# the same with tiles inside one row of the batch: every tile of the largest kind (residual half a tile at a time, planes token by token), and
 # some of the 256- and 192-row tiles that find the residual a whole tile ahead (row heights up to 128 have such tiles above)
 INSIDE_ROWS = [(16, 32, 1024, 16, 1024, ((256, 256), (256, 256))),
                (14, 17, 1440, 20, 5760, ((128, 128), (256, 128))),
