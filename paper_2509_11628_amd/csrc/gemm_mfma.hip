@@ -381,6 +381,10 @@ struct Choice {
   int head;
   double time;
 };
+// What a second launch costs beyond the two modelled times, in microseconds.  Over 220 layers that the model would split without it, splits of
+// layers under 40 us lost 5 % on the mean (7000 x 3072 x 192 21.2 -> 23.1 us); with it 156 are split, 6 % faster on the mean and one of them
+// slower by more than 2 %, and the choice lies 0.1 % above the better form of each on the mean (0.9 % without).
+constexpr double kSecondLaunch = 4.0;
 static Choice choose(const Operands& o, bool branch) {
   Choice c{-1, 0, 0.0};
   c.kind = pick_tile(o, branch, &c.time);
@@ -398,7 +402,7 @@ static Choice choose(const Operands& o, bool branch) {
       double rest = 0.0;
       const int kind = pick_tile(tail, false, &rest);
       rest += tile_cost(kTileKinds[0], false, o.M, n1, o.K);
-      if (rest < (c.head ? 1.0 : 0.96) * c.time) c = {kind, n1, rest};
+      if (c.head ? rest < c.time : rest + kSecondLaunch < 0.96 * c.time) c = {kind, n1, rest};
     }
   }
   return c;

@@ -87,7 +87,8 @@ __device__ __forceinline__ void lane_values(const floatx4 (&acc)[TN][TM], int j,
   for (int q = 0; q < 8; ++q) v[q] = acc[2 * P + q / 4][j][q % 4];
 }
 
-// Eight values of features n .. n + 7; past N, a multiple of 4, the last four again (never stored), so that no branch parts the loads
+// Eight values of features n .. n + 7; past N, a multiple of 4, the last four again (never used, whatever the lane they belong to has
+// stored by then), so that no branch parts the loads
 template <typename T>
 __device__ __forceinline__ void ld8(const T* p, int n, int N, float (&v)[8]) {
   Store4<T>::ld(p + min(n, N - 4), v);

@@ -38,8 +38,12 @@ STORES = [(1, 16, 8), (33, 4, 128), (65, 140, 200), (3401, 264, 8), (257, 3304, 
           (7359, 772, 768), (7177, 784, 832), (7277, 772, 896), (3209, 2520, 880), (741, 3424, 40)]
 
 
+def _source():
+    return open(os.path.join(ROOT, "paper_2509_11628_amd", "csrc", "gemm_mfma.hip")).read()
+
+
 def tile_table():
-    src = open(os.path.join(ROOT, "paper_2509_11628_amd", "csrc", "gemm_mfma.hip")).read()
+    src = _source()
     body = src[src.index("kTileKinds[] = {"):]
     body = body[:body.index("};")]
     rows = re.findall(r"\{(\d+), (\d+), ([\d.]+)f, ([\d.]+)f, ([\d.]+)f, ([\d.]+)f, ([\d.]+)f, ([\d.]+)f, (\w+), (\w+)\}", body)
@@ -76,6 +80,7 @@ def store_kind(table, M, N, K):
 def store_tile(table, M, N, K):
     """(height, width) of the tile for a layer that only stores, the columns that run on the largest tile ahead of it in a launch of
     their own, and how much dearer the next best single tile is modelled."""
+    second = float(re.search(r"kSecondLaunch = ([\d.]+);", _source()).group(1))
     kind, cost, runner_up = store_kind(table, M, N, K)
     head, margin = 0, runner_up / cost
     if M >= 256 and K % 64 == 0:
@@ -86,6 +91,6 @@ def store_tile(table, M, N, K):
                 continue
             tail, rest, _ = store_kind(table, M, N - n1, K)
             rest += _store_cost(table[0], M, n1, K)
-            if rest < (1.0 if head else 0.96) * cost:
+            if rest < cost if head else rest + second < 0.96 * cost:
                 kind, head, cost = tail, n1, rest
     return table[kind][:2], head, margin

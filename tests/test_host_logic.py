@@ -192,11 +192,19 @@ def test_branch_tile_cases_reach_every_tile_of_the_branch_epilogue():
 
 @pytest.mark.parametrize("M,N,K,tile", [(8568, 2304, 1448, (128, 192)), (9500, 3456, 4016, (128, 192)), (15082, 11936, 5464, (128, 192)),
                                         (1349, 9216, 256, (256, 256)), (2693, 9216, 192, (256, 256)), (3377, 4608, 256, (256, 256)),
-                                        (7662, 12288, 64, (256, 256))])
+                                        (7662, 12288, 64, (256, 256)), (7000, 3072, 192, (128, 192)), (6947, 3456, 256, (128, 192)),
+                                        (2833, 7588, 320, (128, 192))])
 def test_store_layers_run_on_the_tile_that_was_measured_fastest(M, N, K, tile):
-    """Sizes where constants fitted to an older kernel had picked a tile that is 3 to 8 % slower."""
+    """Sizes where constants fitted to an older kernel had picked a tile that is 3 to 8 % slower, and short layers that lose 6 to 9 %
+    where they are split into whole rounds of the largest tile and a rest."""
     import branch_tiles as bt
     assert bt.store_tile(bt.tile_table(), M, N, K)[:2] == (tile, 0)
+
+
+@pytest.mark.parametrize("M,N,K,head", [(4096, 4608, 1152, 4096), (4096, 9216, 3072, 8192), (27286, 3072, 3072, 2816)])
+def test_layers_a_little_over_whole_rounds_are_split(M, N, K, head):
+    import branch_tiles as bt
+    assert bt.store_tile(bt.tile_table(), M, N, K)[1] == head
 
 
 def test_largest_tile_cases_run_on_the_largest_tile():
