@@ -193,6 +193,7 @@ struct DiT final : Model {
   struct Lane {
     hipStream_t st;
     int o;
+    bool beside;      // another group runs beside this one
   };
   const float* mod_at(int l, int which, int o = 0) const {
     return modp + static_cast<int64_t>(o) * mod_n + static_cast<int64_t>(l) * 6 * D + static_cast<int64_t>(which) * D;
@@ -217,6 +218,7 @@ struct DiT final : Model {
       SPECA_TRY(launch_ln_modulate(d.dtype, hl, mod_at(l, 0, ln.o), mod_at(l, 1, ln.o), mod_n, xn_l, M, T, D, st));
     }
     GemmEpi e;
+    e.beside = ln.beside;
     e.mode = EPI_STORE; e.bias = blk[l].qkv_b; e.out = qkv_l; e.ldo = 3 * D;
     {
       ProfScope ps(ctx, st, SPECA_PROF_GEMM, 2.0 * Md * 3 * D * D, (Md * 4 * D + 3.0 * D * D) * esz);
@@ -231,6 +233,7 @@ struct DiT final : Model {
       SPECA_TRY(launch_attention(d.dtype, qkv_l, att_l, D, n, T, H, hd, st));
     }
     GemmEpi b;
+    b.beside = ln.beside;
     b.mode = EPI_BRANCH; b.bias = blk[l].proj_b; b.h = hl; b.ldh = D; b.gate = mod_at(l, 2, ln.o); b.gate_stride = mod_n; b.tokens = T;
     if (refresh_rt) { b.refresh = 1; b.slot = 2 * l; b.g = ctx->geom; b.rt = *refresh_rt; }
     ProfScope ps(ctx, st, SPECA_PROF_GEMM, 2.0 * Md * D * D, (Md * D + 1.0 * D * D) * esz + Md * D * 8);
@@ -257,12 +260,14 @@ struct DiT final : Model {
       SPECA_TRY(launch_cache_warm(ctx->geom, *refresh_rt, 2 * l + 1, st));
     }
     GemmEpi e;
+    e.beside = ln.beside;
     e.mode = EPI_GELU; e.bias = blk[l].fc1_b; e.out = f1_l; e.ldo = Dm;
     {
       ProfScope ps(ctx, st, SPECA_PROF_GEMM, 2.0 * Md * Dm * D, (Md * (D + Dm) + 1.0 * D * Dm) * esz);
       SPECA_TRY(launch_gemm(d.dtype, xn_l, D, blk[l].fc1_w, D, static_cast<int>(M), Dm, D, e, st));
     }
     GemmEpi b;
+    b.beside = ln.beside;
     b.bias = blk[l].fc2_b;
     if (truth_out) {
       b.mode = EPI_F32; b.out = truth_out + ln.o * TD; b.ldo = D;
@@ -278,12 +283,11 @@ struct DiT final : Model {
   // Whether n rows run as two groups side by side.  A layer of all rows wastes what its last round of tiles leaves idle; the tiles
   // of two half layers fill each other's partial rounds, but each half waits for a whole tile time per layer.  The cost model of
   // the tiles weighs one against the other for the four layers of a block, and two groups are taken where it expects
-  // more than 5 % from them.  Measured over 550 random sizes (384 to 1440 features, 64 to 1024 tokens, 2 to 64 rows, both layouts;
-  // reference steps of 4 blocks): the 119 taken gain 4.3 % on the mean (-10 to +16 %), the 431 others would lose 8.5 % (gains of up to 16 % left
-  // where 256x256 tiles fill a round in part and planes of differences are read: 10 rows x 576 tokens x 768).  One group / two groups in us: taken 28 rows x
-  // 576 tokens x 1152 features 3253 / 2954, 62 x 576 x 1024 6438 / 5824, 59 x 256 x 1152 2738 / 2496, 14 x 784 x 384 692 / 635; not taken
-  // 16 x 256 x 1152 917 / 919, 5 x 256 x 1152 549 / 595, 26 x 144 x 768 580 / 645, 28 x 196 x 512 620 / 680.  The choice moves with the tiles' constants:
-  // with ones that overrated a round of 256x256 it took one group at 28 x 1024 x 768 (4127 instead of 3533).
+  // more than 1 % and 20 us per block from them.  In two groups the tiles are those whose rounds, filled by both, take least.  Measured over 174 sizes
+  // (384 to 3072 features, 64 to 1024 tokens, 2 to 64 rows, both layouts; reference steps of 4 blocks): the choice lies 0.5 % above the better
+  // form on the mean and 9 % at worst (21 rows x 1024 tokens x 1152: 4097 us in one group, 3743 in two); one group throughout would lose 2.3 %.
+  // One group / two groups in us: 24 x 1024 x 1024 3685 / 3407, 16 x 576 x 1152 with planes of differences 2459 / 2092, 42 x 576 x 1024
+  // 3490 / 3232; not taken 10 x 256 x 1152 625 / 703, 8 x 256 x 3072 2115 / 2255, 17 x 256 x 384 316 / 354.
   // In narrow models with many tokens the passes that are bound by memory weigh more than the rounds: 384 features
   // at 8192, 12288 and 16384 tokens 8.45 / 8.76, 14.8 / 13.8, 14.3 / 13.1 ms of 28 blocks, 512 at 12288 15.7 / 14.7.  Narrower still, launches bound a
   // step: 64 to 256 features at 3072 to 16384 tokens lose up to 39 % in two groups and gain 4 % at best.  A single block (the verification) does not repay the
@@ -299,7 +303,7 @@ struct DiT final : Model {
         whole += layer_time(y.branch, n * T, y.N, y.K, false);
         pair += layer_time(y.branch, half, y.N, y.K, true);
       }
-      groups_for[n] = whole > 1.05 * pair || (D <= 512 && static_cast<int64_t>(n) * T >= 12288) ? 2 : 1;
+      groups_for[n] = whole > 1.01 * pair + 20.0 || (D <= 512 && static_cast<int64_t>(n) * T >= 12288) ? 2 : 1;
     }
     return groups_for[n] == 2;
   }
@@ -315,11 +319,11 @@ struct DiT final : Model {
     Error body = [&]() -> Error {
       for (int l = l0; l < l1; ++l) {
         for (int k = 0; k < ls.n_lanes; ++k) {
-          const Lane ln{ctx->lane_stream[k], ls.first[k]};
+          const Lane ln{ctx->lane_stream[k], ls.first[k], ls.n_lanes > 1};
           SPECA_TRY(attn_branch(ctx, ln, l, hs, ls.first[k + 1] - ls.first[k], refresh_rt ? &sub[k] : nullptr));
         }
         for (int k = 0; k < ls.n_lanes; ++k) {
-          const Lane ln{ctx->lane_stream[k], ls.first[k]};
+          const Lane ln{ctx->lane_stream[k], ls.first[k], ls.n_lanes > 1};
           SPECA_TRY(mlp_branch(ctx, ln, l, hs, ls.first[k + 1] - ls.first[k], refresh_rt ? &sub[k] : nullptr,
                                l == l1 - 1 ? truth_last_mlp : nullptr));
         }

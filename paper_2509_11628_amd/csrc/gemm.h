@@ -25,6 +25,7 @@ struct GemmEpi {
   const void* bias = nullptr;     // [N] model dtype
   void* out = nullptr;            // STORE/GELU/SILU/F32 destination
   int64_t ldo = 0;
+  bool beside = false;            // another launch shares the chip (a row group of two): no unit counts as idle
   // EPI_BRANCH
   float* h = nullptr;             // [M][N] fp32 residual stream
   int64_t ldh = 0;

@@ -39,15 +39,11 @@
 // 5538 / 5318 (6633), 28 x 1024 x 768 4078 / 4002 (4039), 57 x 256 x 1152 3496 / 3478 (3544); without planes 45 x 400 x 1152 3554 / 3442 (3748).
 // Needs K % 64 == 0 and the tile's operand rows within 4 GB.
 
-#include <type_traits>
-
-#include "gemm_tile.h"
+#include "lane_epilogue.h"
 
 namespace speca {
 
 namespace {
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int BM = 256, BN = 256, WM = 128, WN = 64, BK = 64;
 constexpr int ROW = BK * 2;                    // bytes of a staged row
@@ -57,176 +53,6 @@ static_assert(TM == 8 && TN == 4, "two halves of tokens, two pairs of feature ti
 
 constexpr int kWaitLds = 0xC07F;               // s_waitcnt lgkmcnt(0)
 template <int N> __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70); }
-
-// Eight consecutive features of a token (`two`: only the first four exist otherwise).  Rows start at multiples of four features, so
-// 16 bytes may lie at 8-byte alignment, which global stores allow.
-typedef u32x4_t __attribute__((aligned(8))) u32x4_a8;
-__device__ __forceinline__ u32x4_t pack8(const float* v) {
-  return u32x4_t{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7])};
-}
-__device__ __forceinline__ void st8(bf16_t* p, const float* v, bool two) {
-  if (two) *reinterpret_cast<u32x4_a8*>(p) = pack8(v);
-  else Store4<bf16_t>::st(p, v);
-}
-__device__ __forceinline__ void st8(float* p, const float* v, bool two) {
-  Store4<float>::st(p, v);
-  if (two) Store4<float>::st(p + 4, v + 4);
-}
-__device__ __forceinline__ void st8_stream(bf16_t* p, const float* v, bool two, bool wide) {
-  if (wide && two) {
-    __builtin_nontemporal_store(pack8(v), reinterpret_cast<u32x4_t*>(p));
-  } else {
-    st4_stream(p, v);
-    if (two) st4_stream(p + 4, v + 4);
-  }
-}
-
-// The lane's token j, its eight features of pair P of the tiles (bias added)
-__device__ __forceinline__ void lane_values(const floatx4 (&acc)[TN][TM], int j, int P, float (&v)[8]) {
-#pragma unroll
-  for (int q = 0; q < 8; ++q) v[q] = acc[2 * P + q / 4][j][q % 4];
-}
-
-// Eight values of features n .. n + 7; past N, a multiple of 4, the last four again (never used, whatever the lane they belong to has
-// stored by then), so that no branch parts the loads
-template <typename T>
-__device__ __forceinline__ void ld8(const T* p, int n, int N, float (&v)[8]) {
-  Store4<T>::ld(p + min(n, N - 4), v);
-  Store4<T>::ld(p + min(n + 4, N - 4), v + 4);
-}
-__device__ __forceinline__ void load_gate(const float* gate, int n, int N, float (&g)[2][8]) {
-  ld8(gate, n, N, g[0]);
-  ld8(gate, n + 32, N, g[1]);
-}
-
-// Branch epilogue of the lane's tokens J .. J + EB - 1, features n .. n + 7 and n + 32 .. n + 39, all loads ahead of the first store;
-// PLANES: planes are read back (order >= 1).
-template <int J, int EB, bool PLANES>
-__device__ __forceinline__ void branch_tokens(const floatx4 (&acc)[TN][TM], const BranchRow<bf16_t>& br, const float (&gate)[2][8], int64_t ldh, int rows,
-                                              int row0, int n, int N, bool wide) {
-  float hv[EB][2][8], old[PLANES ? EB : 1][SPECA_MAX_ORDER][2][8];
-#pragma unroll
-  for (int u = 0; u < EB; ++u) {
-    const int64_t at = (br.t0 + min(row0 + (J + u) * 16, rows - 1)) * ldh;       // rows past the end: the last one again
-#pragma unroll
-    for (int P = 0; P < 2; ++P) ld8(br.h + at, n + 32 * P, N, hv[u][P]);
-    if constexpr (PLANES) {
-#pragma unroll
-      for (int o = 0; o < SPECA_MAX_ORDER; ++o)
-        if (o < br.order) {
-#pragma unroll
-          for (int P = 0; P < 2; ++P) {
-            ld4_stream(br.d[o] + at + min(n + 32 * P, N - 4), old[u][o][P]);
-            ld4_stream(br.d[o] + at + min(n + 32 * P + 4, N - 4), old[u][o][P] + 4);
-          }
-        }
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < EB; ++u) {
-    const int r = row0 + (J + u) * 16;
-    if (r < rows) {
-      const int64_t at = (br.t0 + r) * ldh;
-      float v[2][8];
-#pragma unroll
-      for (int P = 0; P < 2; ++P) lane_values(acc, J + u, P, v[P]);
-      if (br.refresh) {
-        float cur[2][8];
-#pragma unroll
-        for (int P = 0; P < 2; ++P) {
-          const int np = n + 32 * P;
-          if (np < N) st8_stream(br.d[0] + at + np, v[P], np + 4 < N, wide);
-#pragma unroll
-          for (int q = 0; q < 8; ++q) cur[P][q] = v[P][q];
-        }
-        if constexpr (PLANES) {
-#pragma unroll
-          for (int o = 1; o <= SPECA_MAX_ORDER; ++o)
-            if (o <= br.order) {
-#pragma unroll
-              for (int P = 0; P < 2; ++P) {
-                const int np = n + 32 * P;
-#pragma unroll
-                for (int q = 0; q < 8; ++q) cur[P][q] = (cur[P][q] - old[u][o - 1][P][q]) * br.inv[o - 1];
-                if (np < N) st8_stream(br.d[o] + at + np, cur[P], np + 4 < N, wide);
-              }
-            }
-        }
-      }
-#pragma unroll
-      for (int P = 0; P < 2; ++P) {
-        const int np = n + 32 * P;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) v[P][q] = fmaf(gate[P][q], v[P][q], hv[u][P][q]);
-        if (np < N) st8(br.h + at + np, v[P], np + 4 < N);
-      }
-    }
-  }
-}
-
-// Token by token from J on, planes read back; where the tile spans rows of the batch every token looks its row up.
-template <int J>
-__device__ __forceinline__ void branch_each(const floatx4 (&acc)[TN][TM], BranchRow<bf16_t>& br, float (&gate)[2][8], const GemmEpi& epi, bool spans, int m0,
-                                            int rows, int row0, int n, int N, bool wide) {
-  if (spans) {
-    br = branch_row<bf16_t>(epi, (m0 + min(row0 + J * 16, rows - 1)) / epi.tokens, m0);
-    load_gate(br.gate, n, N, gate);
-  }
-  branch_tokens<J, 1, true>(acc, br, gate, epi.ldh, rows, row0, n, N, wide);
-  if constexpr (J + 1 < TM) branch_each<J + 1>(acc, br, gate, epi, spans, m0, rows, row0, n, N, wide);
-}
-
-// The epilogue of a lane: tokens m0 + row0, + 16, ... (TM of them), features n .. n + 7 and n + 32 .. n + 39.
-template <int MODE>
-__device__ __forceinline__ void lane_epilogue(floatx4 (&acc)[TN][TM], int m0, int row0, int n, int M, int N, const EpiArg<MODE>& epi) {
-  const int rows = M - m0 < BM ? M - m0 : BM;
-  if (epi.bias) {
-    float bias[2][8] = {};
-    ld8(static_cast<const bf16_t*>(epi.bias), n, N, bias[0]);
-    ld8(static_cast<const bf16_t*>(epi.bias), n + 32, N, bias[1]);
-#pragma unroll
-    for (int i = 0; i < TN; ++i)
-#pragma unroll
-      for (int j = 0; j < TM; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) acc[i][j][q] += bias[i / 2][i % 2 * 4 + q];
-  }
-  if constexpr (MODE == EPI_BRANCH) {
-    const bool wide = ((reinterpret_cast<uintptr_t>(epi.g.base) & 15) | ((epi.g.E | epi.cache_elem_offset | epi.ldh) & 7)) == 0;
-    const int i_first = m0 / epi.tokens;
-    float gate[2][8];
-    // a tile inside one batch row needs its table once for the whole block (scalar loads)
-    const bool spans = i_first != (m0 + rows - 1) / epi.tokens;
-    BranchRow<bf16_t> br = branch_row<bf16_t>(epi, i_first, m0);
-    load_gate(br.gate, n, N, gate);
-    if (!spans && br.order == 0) {
-      branch_tokens<0, TM / 2, false>(acc, br, gate, epi.ldh, rows, row0, n, N, wide);
-      branch_tokens<TM / 2, TM / 2, false>(acc, br, gate, epi.ldh, rows, row0, n, N, wide);
-    } else {
-      branch_each<0>(acc, br, gate, epi, spans, m0, rows, row0, n, N, wide);
-    }
-  } else {
-    using T = std::conditional_t<MODE == EPI_F32, float, bf16_t>;
-#pragma unroll
-    for (int j = 0; j < TM; ++j) {
-      const int r = row0 + j * 16;
-      if (r < rows) {
-        T* out = static_cast<T*>(epi.out) + static_cast<int64_t>(m0 + r) * epi.ldo;
-#pragma unroll
-        for (int P = 0; P < 2; ++P) {
-          const int np = n + 32 * P;
-          float v[8];
-          lane_values(acc, j, P, v);
-          if constexpr (MODE == EPI_GELU || MODE == EPI_SILU) {
-#pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] = MODE == EPI_GELU ? gelu_tanh_f(v[q]) : silu_f(v[q]);
-          }
-          if (np < N) st8(out + np, v, np + 4 < N);
-        }
-      }
-    }
-  }
-}
 
 template <int MODE>
 __global__ __launch_bounds__(512, 2) void gemm_phase_kernel(const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ W,
@@ -393,7 +219,7 @@ __global__ __launch_bounds__(512, 2) void gemm_phase_kernel(const uint16_t* __re
 #undef SPECA_LOAD_W
 #undef SPECA_LOAD_A
 #undef SPECA_BUFFER_TO_LDS
-  lane_epilogue<MODE>(acc, m0, wm * WM + l16, n0 + wn * WN + g4 * 8, M, N, epi);
+  lane_epilogue<BM, MODE>(acc, m0, wm * WM + l16, n0 + wn * WN + g4 * 8, M, N, epi);
 }
 
 template <int MODE>
@@ -407,7 +233,7 @@ Error launch_mode(const Operands& o, const GemmEpi& epi, hipStream_t st) {
     SPECA_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 2 * STAGE));
     attr_set = true;
   }
-  kern<<<static_cast<unsigned>((nblk + 7) / 8 * 8), 512, 2 * STAGE, st>>>(o.a, o.lda, o.w, o.ldw, o.M, o.N, o.K, tiles_m, tiles_n, tiles_m < 4 ? tiles_m : 4,
+  kern<<<tile_blocks(tiles_m, tiles_n), 512, 2 * STAGE, st>>>(o.a, o.lda, o.w, o.ldw, o.M, o.N, o.K, tiles_m, tiles_n, tiles_m < 4 ? tiles_m : 4,
                                                                    epi_arg<MODE>(epi));
   SPECA_HIP(hipGetLastError());
   return ok();

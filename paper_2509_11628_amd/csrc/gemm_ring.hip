@@ -1,24 +1,27 @@
 // bf16 MFMA GEMM for gfx950, small and middle tiles:  C[M,N] = A[M,K] * W[N,K]^T with fused epilogues.
 //
-// For problems that do not fill the chip with 256-row tiles: a block is bound there by what its compute unit can draw
-// (about 41 bytes per clock through the direct-to-LDS path) and by its own chain of waits, so the loop keeps several stages
-// of loads in flight and passes few barriers.  Wave64, v_mfma_f32_32x32x16_bf16, the same operand roles and the same order of
-// K as the large tiles, hence the same bits.  Operands go global -> LDS directly into a ring of NS stages of 64 or 128
-// columns, every wave loading its share of every stage; rows are unpadded with an XOR swizzle of the chunk position, so that
-// the 16 lanes which read one chunk index of 16 consecutive rows touch all banks once.  Two loops:
+// For problems that do not fill the chip with larger tiles, and for tails of K: a block is bound there by what its compute unit can draw
+// through the direct-to-LDS path and by its own chain of waits, so the loop keeps several stages of loads in flight and passes few
+// barriers.  Wave64, v_mfma_f32_32x32x16_bf16, the same operand roles and the same order of K as the large tiles, hence the same
+// bits.  Operands go global -> LDS directly into a ring of NS stages of 64 or 128 columns; rows are unpadded with an XOR swizzle of
+// the chunk position, so that the 16 lanes which read one chunk index of 16 rows touch all banks once.  Two loops:
 //   several tiles per wave  fragments are read one 32-wide slice ahead of the matrix instructions that use them.  The stage's
 //                           only barrier sits before its last slice: by then all its slices are in registers (the stage is
 //                           free, the loads of a later one go there) and the next stage has landed.
 //   one tile per wave       (STAGE_AHEAD) a slice is too little matrix work to hide an LDS read behind, so the fragments of
 //                           the whole next stage are read under the matrix work of the current one; one barrier per stage.
+// LW > 0: loads are issued by LW waves of their own.  A wave issues in order, and the direct-to-LDS path takes 1 KB per 10 ns, so a wave that
+// loads and computes has its matrix instructions wait for its loads to be taken: 64x64 tiles at 512 x 1152 x 4608 took 0.58 us per
+// stage where the loads alone take 0.34 (0.17 the fragments and matrix instructions).  They pass the same barriers and leave after the
+// last one.  Tiles of which two blocks share a unit load from the waves that compute (LW = 0): each block covers the other's waits.
 // What keeps a stage intact between its readers and its next loads: a wave waits for its own fragment reads (lgkmcnt(0))
-// BEFORE the barrier that hands the stage on, and nothing may move across that barrier (see gemm_mfma.hip).  What lands is
-// awaited by count: loads into LDS complete in the order in which a wave issued them, like all its vector loads, and a wave
-// lets those of later stages be.
-// Measured with cold weights against register-staged tiles of 128x64 to 256x128 (us, before -> now): 512 x 1152 x 4608
-// 32.6 -> 23.2, 512 x 1152 x 1152 10.9 -> 8.9, 512 x 4608 x 1152 16.6 -> 13.0, 77 x 3072 x 12288 80 -> 46, 4096 x 1152 x 4608
-// 59.6 -> 53.0, 64 x 768 x 3072 22.0 -> 14.2.  At 512 x 1152 x 4608 the loads alone take 21 us (15 from L2), the LDS reads and
-// matrix instructions alone 17: what is left is what they disturb each other at the LDS.
+// BEFORE the barrier that hands the stage on, and nothing may move across that barrier.  The barrier builtin alone does not give that:
+// matrix instructions, and with them the waits for the fragments they use, are free to sink below it, and a load that hits in L2
+// then overtakes reads still queued at the LDS.  What lands is awaited by count: loads into LDS complete in the order in which a wave
+// issued them, like all its vector loads, and a wave lets those of later stages be.
+// us, register-staged tiles of 128x64 to 256x128 -> all waves load and compute -> loader waves (cold weights, read ahead by the idle units,
+// gemm_tile.h; warm weights in brackets): 512 x 1152 x 4608 32.6 -> 23.2 -> 18.1 (16.0), 77 x 3072 x 12288 80 -> 46 -> 33 (31), 1536 x 1152 x 4608
+// 29 -> 25 (24), 124 x 768 x 3072 14.2 -> 10.5, 16 x 1152 x 3736 23.4 -> 14.8.
 
 #include "gemm_tile.h"
 
@@ -79,9 +82,9 @@ constexpr size_t lds_bytes(int BM, int BN, int NS, int KS) {
   return ring > epi ? ring : epi;
 }
 
-// KTAIL: K is no multiple of a stage.
-template <int BM, int BN, int WGM, int WGN, int NS, int KS, bool STAGE_AHEAD, int MODE, bool KTAIL>
-__global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(const uint16_t* __restrict__ A, int64_t lda,
+// LW: waves that only load (0: all waves load and compute).  KTAIL: K is no multiple of a stage.
+template <int BM, int BN, int WGM, int WGN, int NS, int KS, bool STAGE_AHEAD, int LW, int MODE, bool KTAIL>
+__global__ __launch_bounds__((WGM* WGN + LW) * 64) void gemm_ring_kernel(const uint16_t* __restrict__ A, int64_t lda,
                                                         const uint16_t* __restrict__ W, int64_t ldw, int M, int N, int K, int tiles_m, int tiles_n,
                                                         int group_m, EpiArg<MODE> epi) {
   constexpr int NW = WGM * WGN;
@@ -93,17 +96,24 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(const uint16_t
   constexpr int ROW = COLS * 2;                              // bytes of a stage row
   constexpr int CPR = 4 * KS;                                // 16-byte chunks per row
   constexpr int GR = 64 / CPR;                               // rows per load instruction (1 KiB)
-  constexpr int AL = BM / GR / NW, WL = BN / GR / NW, LPW = AL + WL;                 // loads of a wave per stage
-  static_assert(BM % (NW * GR) == 0 && BN % (NW * GR) == 0, "row groups must divide among the waves");
+  constexpr int LD = LW ? LW : NW;                           // waves that load
+  constexpr int AL = BM / GR / LD, WL = BN / GR / LD, LPW = AL + WL;                 // their loads per stage
+  static_assert(BM % (LD * GR) == 0 && BN % (LD * GR) == 0, "row groups must divide among the waves");
   static_assert((NS - 1) * LPW < 64, "outstanding loads of a wave");
   constexpr int STAGE = (BM + BN) * ROW;                     // bytes
   constexpr int EH = epilogue_rows(BM, BN, NS * STAGE);
   extern __shared__ __align__(16) char smem[];
 
   int tm, tn;
+  const int held = tile_blocks(tiles_m, tiles_n);
+  if (static_cast<int>(blockIdx.x) >= held) {
+    read_ahead(W, ldw, N, K, blockIdx.x - held, gridDim.x - held);
+    return;
+  }
   if (!tile_coords(tiles_m, tiles_n, group_m, &tm, &tn)) return;
   const int m0 = tm * BM, n0 = tn * BN;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lwave = LW ? wave - NW : wave;                   // loader (negative: none)
   const int wm = wave / WGN, wn = wave % WGN;
   const int l32 = lane & 31, lhi = lane >> 5;
 
@@ -131,16 +141,16 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(const uint16_t
 #pragma unroll
   for (int u = 0; u < LPW; ++u) {
     if (u < AL) {
-      const int g = wave + NW * u, r = g * GR + lrow;
+      const int g = lwave + LD * u, r = g * GR + lrow;
       voff[u] = static_cast<uint32_t>(static_cast<int64_t>(m0 + r < M ? r : M - 1 - m0) * lda * 2 + chunk(g) * 16);
     } else {
-      const int g = wave + NW * (u - AL), r = g * GR + lrow;
+      const int g = lwave + LD * (u - AL), r = g * GR + lrow;
       voff[u] = static_cast<uint32_t>(static_cast<int64_t>(n0 + r < N ? r : N - 1 - n0) * ldw * 2 + chunk(g) * 16);
     }
   }
   auto load_one = [&](int s, int slot, int u) {              // load u of this wave's share of stage s
     const bool is_a = u < AL;
-    const int g = wave + NW * (is_a ? u : u - AL);
+    const int g = lwave + LD * (is_a ? u : u - AL);
     const char* src = (is_a ? ba : bw) + static_cast<int64_t>(s) * ROW + voff[u];
     if (KTAIL && s == nk - 1) src = s * COLS + chunk(g) * 8 < K ? src : reinterpret_cast<const char*>(kZeroChunk);
     SPECA_GLL(src, smem + slot * STAGE + (is_a ? 0 : BM * ROW) + g * 1024);
@@ -177,21 +187,60 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(const uint16_t
     asm volatile("" ::: "memory");  \
     SPECA_PIN();                    \
   }
+  if constexpr (LW > 0) {
+    if (wave >= NW) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+        if (s < nk) {
+#pragma unroll
+          for (int u = 0; u < LPW; ++u) load_one(s, s, u);
+        }
+      wait_stage<LPW, NS - 1>((nk < NS ? nk : NS) - 1);
+      SPECA_BARRIER();
+      int slot = 0;
+      if constexpr (STAGE_AHEAD) {
+        wait_stage<LPW, NS - 2>((nk < NS ? nk : NS) - 2);
+        SPECA_BARRIER();
+        for (int s = 0; s < nk; ++s) {
+          if (s + NS < nk) {
+#pragma unroll
+            for (int u = 0; u < LPW; ++u) load_one(s + NS, slot, u);
+          }
+          SPECA_PIN();
+          wait_stage<LPW, NS - 2>((nk - 1 < s + NS ? nk - 1 : s + NS) - (s + 2));
+          SPECA_BARRIER();
+          slot = slot + 1 == NS ? 0 : slot + 1;
+        }
+      } else {
+        for (int s = 0; s < nk; ++s) {
+          wait_stage<LPW, NS - 2>((nk < s + NS ? nk : s + NS) - (s + 2));
+          SPECA_BARRIER();
+          if (s + NS < nk) {
+#pragma unroll
+            for (int u = 0; u < LPW; ++u) load_one(s + NS, slot, u);
+          }
+          SPECA_PIN();
+          slot = slot + 1 == NS ? 0 : slot + 1;
+        }
+      }
+      return;
+    }
+  }
   // prologue: stages 0 .. NS-1, the first one awaited
 #pragma unroll
   for (int s = 0; s < NS; ++s)
-    if (s < nk) {
+    if (!LW && s < nk) {
 #pragma unroll
       for (int u = 0; u < LPW; ++u) load_one(s, s, u);
     }
-  wait_stage<LPW, NS - 1>((nk < NS ? nk : NS) - 1);
+  if (!LW) wait_stage<LPW, NS - 1>((nk < NS ? nk : NS) - 1);
   SPECA_BARRIER();
   int slot = 0;
   if constexpr (STAGE_AHEAD) {
 #pragma unroll
     for (int q = 0; q < KS; ++q) read_slice(q, 0, q);
     __builtin_amdgcn_s_waitcnt(kWaitLds);                    // stage 0 is in registers
-    wait_stage<LPW, NS - 2>((nk < NS ? nk : NS) - 2);  // stage 1 has landed
+    if (!LW) wait_stage<LPW, NS - 2>((nk < NS ? nk : NS) - 2);  // stage 1 has landed
     SPECA_BARRIER();
     // Iteration s: stage s is in registers (set `cur`), its slot is free, stage s + 1 has landed
 #define SPECA_STAGE(s, cur)                                                                                       \
@@ -200,7 +249,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(const uint16_t
     if ((s) + 1 < nk) {                                                                                           \
       _Pragma("unroll") for (int q = 0; q < KS; ++q) read_slice((1 - (cur)) * KS + q, next, q);                   \
     }                                                                                                             \
-    if ((s) + NS < nk) {                                                                                          \
+    if (!LW && (s) + NS < nk) {                                                                                   \
       _Pragma("unroll") for (int u = 0; u < LPW; ++u) load_one((s) + NS, slot, u);                                \
     }                                                                                                             \
     SPECA_PIN();                                                                                                  \
@@ -210,7 +259,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(const uint16_t
           mma<!STAGE_AHEAD, TM * TN>(acc[i][j], fw[(cur) * KS + q / 2][q & 1][i], fa[(cur) * KS + q / 2][q & 1][j]);            \
     SPECA_PIN();                                                                                                  \
     __builtin_amdgcn_s_waitcnt(kWaitLds);                     /* stage s + 1 is in registers: its slot is free */   \
-    wait_stage<LPW, NS - 2>((nk - 1 < (s) + NS ? nk - 1 : (s) + NS) - ((s) + 2));         /* stage s + 2 has landed */ \
+    if (!LW) wait_stage<LPW, NS - 2>((nk - 1 < (s) + NS ? nk - 1 : (s) + NS) - ((s) + 2));         /* stage s + 2 has landed */ \
     SPECA_BARRIER();                                                                                              \
     slot = next;                                                                                                  \
   }
@@ -246,9 +295,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(const uint16_t
         SPECA_SLICE(q & 1, true, slot, q + 1, false, 0, 0)
       }
       __builtin_amdgcn_s_waitcnt(kWaitLds);                  // the last slice too: the stage's LDS is free
-      wait_stage<LPW, NS - 2>((nk < s + NS ? nk : s + NS) - (s + 2));       // stage s + 1 has landed (later ones: up to s + NS - 1)
+      if (!LW) wait_stage<LPW, NS - 2>((nk < s + NS ? nk : s + NS) - (s + 2));       // stage s + 1 has landed (later ones: up to s + NS - 1)
       SPECA_BARRIER();
-      SPECA_SLICE((KS - 1) & 1, s + 1 < nk, next, 0, s + NS < nk, s + NS, slot)
+      SPECA_SLICE((KS - 1) & 1, s + 1 < nk, next, 0, !LW && s + NS < nk, s + NS, slot)
       slot = next;
     }
 #undef SPECA_SLICE
@@ -266,31 +315,31 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(const uint16_t
   tile_epilogue<BM, BN, WGM, WGN, MODE, EH>(acc, reinterpret_cast<float*>(smem), m0, n0, M, N, epi);
 }
 
-template <int BM, int BN, int WGM, int WGN, int NS, int KS, bool SA, int MODE, bool KTAIL>
+template <int BM, int BN, int WGM, int WGN, int NS, int KS, bool SA, int LW, int MODE, bool KTAIL>
 Error launch_mode(const Operands& o, const GemmEpi& epi, hipStream_t st) {
   const int tiles_m = (o.M + BM - 1) / BM, tiles_n = (o.N + BN - 1) / BN;
   const int64_t nblk = static_cast<int64_t>(tiles_m) * tiles_n;
   if (nblk > 0x7FFFFFF0) SPECA_FAIL(SPECA_EINVAL, "gemm: too many tiles");
   constexpr size_t smem = lds_bytes(BM, BN, NS, KS);
-  auto kern = gemm_ring_kernel<BM, BN, WGM, WGN, NS, KS, SA, MODE, KTAIL>;
+  auto kern = gemm_ring_kernel<BM, BN, WGM, WGN, NS, KS, SA, LW, MODE, KTAIL>;
   static bool attr_set = false;   // more than 64 KB of dynamic LDS must be requested once per kernel
   if (smem > 64 * 1024 && !attr_set) {
     SPECA_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem)));
     attr_set = true;
   }
   const int group_m = tiles_m < 4 ? tiles_m : 4;
-  kern<<<static_cast<unsigned>((nblk + 7) / 8 * 8), WGM * WGN * 64, smem, st>>>(o.a, o.lda, o.w, o.ldw, o.M, o.N, o.K, tiles_m, tiles_n, group_m,
+  kern<<<LW ? launch_blocks(tiles_m, tiles_n, o, epi) : tile_blocks(tiles_m, tiles_n), (WGM * WGN + LW) * 64, smem, st>>>(o.a, o.lda, o.w, o.ldw, o.M, o.N, o.K, tiles_m, tiles_n, group_m,
                                                                     epi_arg<MODE>(epi));
   SPECA_HIP(hipGetLastError());
   return ok();
 }
 
 // BRANCH: the tile is offered to the branch epilogue (see the table in gemm_mfma.hip).
-template <int BM, int BN, int WGM, int WGN, int NS, int KS, bool SA, bool BRANCH>
+template <int BM, int BN, int WGM, int WGN, int NS, int KS, bool SA, bool BRANCH, int LW>
 Error launch_tile(const Operands& o, const GemmEpi& epi, hipStream_t st) {
 #define SPECA_LAUNCH(MODE_)                                                                                  \
-  return o.K % (32 * KS) ? launch_mode<BM, BN, WGM, WGN, NS, KS, SA, MODE_, true>(o, epi, st)                \
-                         : launch_mode<BM, BN, WGM, WGN, NS, KS, SA, MODE_, false>(o, epi, st);
+  return o.K % (32 * KS) ? launch_mode<BM, BN, WGM, WGN, NS, KS, SA, LW, MODE_, true>(o, epi, st)                \
+                         : launch_mode<BM, BN, WGM, WGN, NS, KS, SA, LW, MODE_, false>(o, epi, st);
   switch (epi.mode) {
     case EPI_STORE: SPECA_LAUNCH(EPI_STORE)
     case EPI_GELU: SPECA_LAUNCH(EPI_GELU)
@@ -308,17 +357,15 @@ Error launch_tile(const Operands& o, const GemmEpi& epi, hipStream_t st) {
 
 Error launch_gemm_ring(int kind, const Operands& o, const GemmEpi& epi, hipStream_t st) {
   switch (kind) {
-    case 0: return launch_tile<128, 128, 2, 2, 4, 2, false, true>(o, epi, st);
-    case 1: return launch_tile<128, 128, 2, 2, 2, 2, false, true>(o, epi, st);
-    case 2: return launch_tile<128, 64, 2, 2, 3, 4, false, true>(o, epi, st);
-    case 3: return launch_tile<128, 64, 2, 2, 3, 2, false, true>(o, epi, st);
-    case 4: return launch_tile<64, 64, 2, 2, 4, 4, true, true>(o, epi, st);
-    case 5: return launch_tile<32, 64, 1, 2, 4, 4, true, true>(o, epi, st);
-    case 6: return launch_tile<192, 128, 2, 2, 3, 2, false, true>(o, epi, st);
-    case 7: return launch_tile<128, 192, 2, 2, 2, 2, false, true>(o, epi, st);
-    case 8: return launch_tile<192, 192, 2, 2, 3, 2, false, false>(o, epi, st);
-    case 9: return launch_tile<96, 128, 1, 4, 4, 2, false, true>(o, epi, st);
-    case 10: return launch_tile<128, 96, 4, 1, 2, 2, false, false>(o, epi, st);
+    case 0: return launch_tile<128, 128, 2, 2, 4, 2, false, true, 4>(o, epi, st);
+    case 1: return launch_tile<128, 128, 2, 2, 2, 2, false, true, 0>(o, epi, st);
+    case 2: return launch_tile<128, 64, 2, 2, 3, 4, false, true, 4>(o, epi, st);
+    case 3: return launch_tile<64, 64, 2, 2, 3, 4, true, true, 4>(o, epi, st);
+    case 4: return launch_tile<32, 64, 1, 2, 4, 4, true, true, 2>(o, epi, st);
+    case 5: return launch_tile<192, 128, 2, 2, 3, 2, false, true, 4>(o, epi, st);
+    case 6: return launch_tile<128, 192, 2, 2, 2, 2, false, true, 0>(o, epi, st);
+    case 7: return launch_tile<192, 192, 2, 2, 3, 2, false, false, 0>(o, epi, st);
+    case 8: return launch_tile<96, 128, 1, 4, 4, 2, false, true, 4>(o, epi, st);
   }
   SPECA_FAIL(SPECA_EINVAL, "gemm: no such tile");
 }

@@ -1,4 +1,4 @@
-// What the three bf16 GEMM kernels share: types, operand description, tile numbering, the epilogue of a block tile.
+// What the bf16 GEMM kernels share: types, operand description, tile numbering, the epilogue of a block tile.
 #pragma once
 
 #include "epilogue.h"
@@ -17,9 +17,16 @@ struct Operands {
   int M, N, K;
 };
 
+// Blocks of a launch of one block per compute unit: those of the tiles and, if they leave units idle, one for each of these
+// (read_ahead).
+unsigned launch_blocks(int tiles_m, int tiles_n, const Operands& o, const GemmEpi& epi);
+
 // gemm_phase.hip: 256 x 256
-bool gemm_phase_fits(const Operands& o);
+bool gemm_phase_fits(const Operands& o);      // the tiles of gemm_duo.hip, too
 Error launch_gemm_phase(const Operands& o, const GemmEpi& epi, hipStream_t st);
+
+// gemm_duo.hip: bm x 128, bm = 64, 128, 192, 256 (what gemm_phase_fits)
+Error launch_gemm_duo(int bm, const Operands& o, const GemmEpi& epi, hipStream_t st);
 
 // gemm_ring.hip: kinds 0 .. 10 (see its switch)
 Error launch_gemm_ring(int kind, const Operands& o, const GemmEpi& epi, hipStream_t st);
@@ -28,14 +35,39 @@ Error launch_gemm_ring(int kind, const Operands& o, const GemmEpi& epi, hipStrea
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src),                         \
                                    (__attribute__((address_space(3))) void*)(dst), 16, 0, 0)
 
+// Blocks of a launch that hold tiles: a multiple of the 8 XCDs.
+__host__ __device__ __forceinline__ int tile_blocks(int tiles_m, int tiles_n) { return (tiles_m * tiles_n + 7) / 8 * 8; }
+
+// Reads of a layer that leaves compute units idle wait for weights: a unit keeps about 50 KB on their way, 94 bytes per ns from the
+// memory-side cache and 56 from HBM.  So the idle units read the weights ahead into that cache: blocks behind those of the tiles
+// walk W in the order of K, 128 columns of all rows at a time, which they finish long before the tiles reach the last of them.
+// Operands alone, 64x64 tiles at 512 x 1152 x 4608: 22.0 us cold, 16.0 with the weights and activations read ahead, 14.5 warm.
+__device__ __forceinline__ void read_ahead(const uint16_t* W, int64_t ldw, int N, int K, int part, int parts) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6, lane = threadIdx.x & 63;
+  const int groups = (N + 3) / 4;                            // 4 rows x 256 bytes per instruction
+  const int total = groups * ((K + 127) / 128), step = parts * waves;
+  constexpr int U = 8;                                       // instructions of a wave on their way
+  for (int i = part * waves + wave; i < total; i += U * step) {
+    u32x4_t v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int at = i + u * step < total ? i + u * step : total - 1, slab = at / groups, g = at - slab * groups;
+      const int row = g * 4 + (lane >> 4) < N ? g * 4 + (lane >> 4) : N - 1, col = slab * 128 + (lane & 15) * 8 < K ? slab * 128 + (lane & 15) * 8 : 0;
+      v[u] = *reinterpret_cast<const u32x4_t*>(W + row * ldw + col);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) asm volatile("" : : "v"(v[u]));        // the values are of no use, only their being read
+  }
+}
+
 // XCD-aware tile id: blocks b, b+8, b+16, ... run on the same XCD; give them neighbouring tiles
-// (the grid is rounded up to a multiple of 8; surplus blocks leave at once).  Inside an XCD's
+// (surplus blocks leave at once).  Inside an XCD's
 // range tiles are walked in groups of group_m M-panels, N fastest across the group's panels,
 // so that the tiles in flight at one time form a compact rectangle and share operand panels
 // in that XCD's L2.
 __device__ __forceinline__ bool tile_coords(int tiles_m, int tiles_n, int group_m, int* tm, int* tn) {
   const int bid = blockIdx.x;
-  const int per_xcd = gridDim.x / 8;
+  const int per_xcd = tile_blocks(tiles_m, tiles_n) / 8;
   const int tile = (bid % 8) * per_xcd + bid / 8;
   if (tile >= tiles_m * tiles_n) return false;
   const int per_group = group_m * tiles_n;

@@ -8,34 +8,43 @@ import re
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 COMPUTE_UNITS = 256
 
-# rows, grid (tokens = grid^2), hidden, heads, mlp_hidden, (tile of the projection, tile of the second MLP layer)
+# rows, grid (tokens = grid^2), hidden, heads, mlp_hidden, (kind of the projection, kind of the second MLP layer: places in the table)
 # tokens divide no tile height, so tiles span rows of the batch; hidden is no multiple of most tile widths
 CASES = [
-    (6, 15, 360, 5, 424, ((64, 64), (64, 64))),
-    (12, 15, 360, 5, 1288, ((128, 64), (128, 64))),
-    (7, 17, 1440, 20, 5760, ((128, 64), (128, 128))),
-    (56, 14, 360, 5, 424, ((128, 128), (128, 128))),
-    (55, 20, 360, 5, 424, ((128, 192), (128, 192))),
-    (11, 15, 792, 11, 3168, ((64, 64), (96, 128))),
-    (33, 20, 792, 11, 640, ((128, 128), (256, 256))),
-    (35, 9, 1440, 20, 5760, ((128, 128), (192, 128))),
-    (24, 15, 768, 12, 3072, ((128, 128), (256, 128))),
+    (6, 15, 360, 5, 424, (5, 5)),
+    (12, 15, 360, 5, 1288, (4, 4)),
+    (7, 17, 1440, 20, 5760, (2, 12)),
+    (56, 14, 360, 5, 424, (8, 8)),
+    (55, 20, 360, 5, 424, (8, 8)),
+    (11, 15, 792, 11, 3168, (5, 5)),
+    (33, 20, 792, 11, 640, (3, 13)),
+    (35, 9, 1440, 20, 5760, (3, 13)),
+    (24, 15, 768, 12, 3072, (11, 13)),
+    (12, 15, 360, 5, 640, (4, 11)),
+    (17, 12, 792, 11, 640, (5, 12)),
+    (28, 14, 360, 5, 3168, (2, 10)),
+    (38, 17, 360, 5, 3168, (8, 7)),
+    (24, 17, 792, 11, 640, (3, 1)),
+    (49, 17, 792, 11, 640, (3, 0)),
 ]
 
 # the same with tiles inside one row of the batch: every tile of the largest kind (residual half a tile at a time, planes token by token), and
 # some of the 256- and 192-row tiles that find the residual a whole tile ahead (row heights up to 128 have such tiles above)
-INSIDE_ROWS = [(16, 32, 1024, 16, 1024, ((256, 256), (256, 256))),
-               (14, 17, 1440, 20, 5760, ((128, 128), (256, 128))),
-               (5, 24, 1440, 20, 5760, ((128, 128), (192, 128)))]
+INSIDE_ROWS = [(16, 32, 1024, 16, 1024, (0, 0)),
+               (14, 17, 1440, 20, 5760, (3, 1)),
+               (5, 24, 1440, 20, 5760, (3, 13))]
 
 # rows, features, K and activation of layers that only store, all of them on the largest tile
 LARGEST = [(4089, 4092, 64, 1), (4089, 4092, 128, 0), (4089, 4088, 192, 1), (4096, 4096, 256, 2), (3841, 3844, 320, 0)]
 
-# rows, features and K of layers that only store: every tile, ragged rows and columns, tails of K where the tile takes them, and
-# 256x128 (three stages, two groups of loaders) at 3 n, 3 n + 1 and 3 n + 2 K-steps
+# rows, features and K of layers that only store: every kind, ragged rows and columns, tails of K where the kind takes them, and the tiles of
+# two wave groups (places 1, 11, 12, 13) at one to six and at 3 n, 3 n + 1 and 3 n + 2 K-steps, fewer and more than the ring has stages
 STORES = [(1, 16, 8), (33, 4, 128), (65, 140, 200), (3401, 264, 8), (257, 3304, 136), (771, 2500, 136), (1034, 3592, 384), (132, 3408, 328), (1715, 3524, 248),
           (3839, 3224, 456), (2461, 3280, 456), (2348, 2528, 512), (3588, 4000, 64), (3437, 3460, 520), (845, 3076, 6152), (500, 3076, 3080), (3603, 796, 1912),
-          (7359, 772, 768), (7177, 784, 832), (7277, 772, 896), (3209, 2520, 880), (741, 3424, 40)]
+          (7359, 772, 768), (7177, 784, 832), (7277, 772, 896), (3209, 2520, 880), (741, 3424, 40),
+          (4889, 3100, 320), (4916, 3180, 256), (5889, 2620, 384), (31, 4, 64), (5506, 132, 128), (5444, 136, 192), (5567, 132, 256), (5713, 136, 320),
+          (5647, 284, 64), (5468, 280, 128), (5460, 336, 192), (518, 3604, 256), (513, 3636, 320), (6055, 648, 192), (1697, 2308, 256), (5525, 652, 320),
+          (5498, 652, 384), (5398, 1096, 40), (5941, 2564, 64), (4995, 1540, 384)]
 
 
 def _source():
@@ -51,15 +60,15 @@ def tile_table():
 
 
 def branch_tile(table, M, N, K):
-    """(height, width) of the tile for a layer with the branch epilogue, and how much dearer the next best one is modelled."""
+    """Place in the table of the tile for a layer with the branch epilogue, and how much dearer the next best one is modelled."""
     costs = []
-    for bm, bn, a, _, b, _, cb, rb, two, whole_steps in table:
+    for place, (bm, bn, a, _, b, _, cb, rb, two, whole_steps) in enumerate(table):
         if cb == 0.0 or (whole_steps and (K % 64 or K < 64)):
             continue
         depth = math.ceil(math.ceil(M / bm) * math.ceil(N / bn) / COMPUTE_UNITS)
         odd = depth % 2
         rounds = (depth - odd) / 2 * (1.0 + rb) + odd if two else 1.0 + rb * (depth - 1)
-        costs.append((a + (cb + b * math.ceil(K / 64)) * rounds, (bm, bn)))
+        costs.append((a + (cb + b * math.ceil(K / 64)) * rounds, place))
     costs.sort()
     return costs[0][1], costs[1][0] / costs[0][0]
 

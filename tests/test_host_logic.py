@@ -171,12 +171,13 @@ def test_product_path_does_not_import_the_oracle():
 
 
 def test_branch_tile_cases_reach_every_tile_of_the_branch_epilogue():
-    """The shapes of the GPU test of the branch epilogue fall on the tiles they are meant for, and together on all of them (the
+    """The shapes of the GPU test of the branch epilogue fall on the kinds they are meant for, and together on all of them (the
     32x64 tile serves the single rows they are compared with)."""
     import branch_tiles as bt
     table = bt.tile_table()
-    assert len(table) == 13
-    seen = {(32, 64)}
+    assert len(table) == 14
+    single = [t[:2] for t in table].index((32, 64))
+    seen = {single}
     for rows, grid, D, H, Dm, want in bt.CASES:
         for K, tile in zip((D, Dm), want):
             got, margin = bt.branch_tile(table, rows * grid * grid, D, K)
@@ -186,8 +187,8 @@ def test_branch_tile_cases_reach_every_tile_of_the_branch_epilogue():
         for K, tile in zip((D, Dm), want):
             got, margin = bt.branch_tile(table, rows * grid * grid, D, K)
             assert got == tile and margin > 1.003, (rows, grid, D, K, got, margin)
-    assert bt.branch_tile(table, 81, 360, 424)[0] == (32, 64)
-    assert seen == {t[:2] for t in table if t[6] > 0}
+    assert bt.branch_tile(table, 81, 360, 424)[0] == single
+    assert seen == {k for k, t in enumerate(table) if t[6] > 0}
 
 
 @pytest.mark.parametrize("M,N,K,tile", [(8568, 2304, 1448, (128, 192)), (9500, 3456, 4016, (128, 192)), (15082, 11936, 5464, (128, 192)),
@@ -222,3 +223,5 @@ def test_store_cases_reach_every_tile():
     assert {k for k, _ in got} == set(range(len(table)))
     assert {k for k, tail in got if tail} == {k for k, t in enumerate(table) if not t[9]}
     assert {K // 64 % 3 for M, N, K in bt.STORES if bt.store_tile(table, M, N, K)[:2] == ((256, 128), 0)} == {0, 1, 2}
+    steps = {k: {K // 64 for M, N, K in bt.STORES if bt.store_tile(table, M, N, K)[1] == 0 and bt.store_kind(table, M, N, K)[0] == k} for k in (1, 11, 12, 13)}
+    assert steps[11] >= {2, 3, 4, 5} and steps[12] >= {1, 2, 3, 4, 5} and steps[13] >= {3, 4, 5, 6} and steps[1] >= {4, 5, 6}, steps
