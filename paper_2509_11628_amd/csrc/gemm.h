@@ -55,6 +55,19 @@ template <int MODE> inline EpiArg<MODE> epi_arg(const GemmEpi& e) {
 // M may be ragged; N % 4 == 0 is required (checked).
 Error launch_gemm(int dtype, const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi,
                   hipStream_t st);
+// One layer of two token ranges ("streams") of every batch row, with weights, bias and gate of their own; A, output, residual and cache
+// are those of all tokens of all rows.
+struct StreamLayer {
+  int rows, tokens;                  // batch rows; tokens of each
+  int len[2], off[2];                // tokens of a stream in a row, and the first of them
+  const uint16_t* w[2];
+  const void* bias[2];
+  const float* gate[2];              // EPI_BRANCH: of batch row 0, epi.gate_stride apart
+};
+// The tile kind with which one launch for both streams of all rows is expected to take less than a launch per row and stream (the weights are
+// read once, a short stream's tiles run beside the long one's, and both fill one set of rounds); negative: go row by row and stream by stream.
+int streams_kind(int dtype, const void* A, int64_t lda, int64_t ldw, int N, int K, const StreamLayer& y, int mode);
+Error launch_gemm_streams(int kind, const void* A, int64_t lda, int64_t ldw, int N, int K, const StreamLayer& y, const GemmEpi& epi, hipStream_t st);
 // Modelled time (us) of a bf16 layer on the matrix kernels (K % 8 == 0): alone on the chip, or, `paired`, as one of two such
 // layers side by side, whose tiles fill each other's partial rounds.
 double layer_time(bool branch, int M, int N, int K, bool paired);

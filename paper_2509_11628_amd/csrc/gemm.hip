@@ -8,6 +8,8 @@ Error launch_gemm_simple(int dtype, const void* A, int64_t lda, const void* W, i
 Error launch_attention_simple(int dtype, const void* qkv, void* out, int64_t ldo, int rows, int T, int H, int hd, hipStream_t st);
 bool gemm_mfma_supported(const Operands& o);
 Error launch_gemm_mfma(const Operands& o, const GemmEpi& epi, hipStream_t st);
+int pick_streams(const Operands& o, const StreamLayer& y, bool branch);
+Error launch_gemm_mfma_streams(int kind, const Operands& o, const StreamLayer& y, const GemmEpi& epi, hipStream_t st);
 
 bool gemm_f32_supported(const void* A, int64_t lda, const void* W, int64_t ldw, int K);
 Error launch_gemm_f32(const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st);
@@ -16,11 +18,7 @@ Error launch_attention_f32(int dtype, const void* qkv, void* out, int64_t ldo, i
 bool attention_mfma_supported(const void* qkv, const void* out, int64_t ldo, int H, int hd);
 Error launch_attention_mfma(const void* qkv, void* out, int64_t ldo, int rows, int T, int H, int hd, hipStream_t st);
 
-Error launch_gemm(int dtype, const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi,
-                  hipStream_t st) {
-  if (!A || !W) SPECA_FAIL(SPECA_EINVAL, "gemm: NULL operand");
-  if (M < 1 || N < 4 || K < 1 || N % 4) SPECA_FAIL(SPECA_EINVAL, "gemm: M=%d N=%d K=%d (N must be a multiple of 4)", M, N, K);
-  if (lda < K || ldw < K) SPECA_FAIL(SPECA_EINVAL, "gemm: leading dimensions smaller than K");
+static Error check_epilogue(int M, int N, const GemmEpi& epi) {
   if (epi.mode == EPI_BRANCH) {
     if (!epi.h || !epi.gate || epi.tokens < 1 || epi.ldh != N) SPECA_FAIL(SPECA_EINVAL, "gemm: branch epilogue arguments");
     if (M % epi.tokens) SPECA_FAIL(SPECA_EINVAL, "gemm: M=%d is not a multiple of tokens=%d", M, epi.tokens);
@@ -35,6 +33,15 @@ Error launch_gemm(int dtype, const void* A, int64_t lda, const void* W, int64_t 
   } else if (!epi.out || epi.ldo < N) {
     SPECA_FAIL(SPECA_EINVAL, "gemm: output missing");
   }
+  return ok();
+}
+
+Error launch_gemm(int dtype, const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi,
+                  hipStream_t st) {
+  if (!A || !W) SPECA_FAIL(SPECA_EINVAL, "gemm: NULL operand");
+  if (M < 1 || N < 4 || K < 1 || N % 4) SPECA_FAIL(SPECA_EINVAL, "gemm: M=%d N=%d K=%d (N must be a multiple of 4)", M, N, K);
+  if (lda < K || ldw < K) SPECA_FAIL(SPECA_EINVAL, "gemm: leading dimensions smaller than K");
+  SPECA_TRY(check_epilogue(M, N, epi));
   if (dtype == SPECA_BF16) {
     const Operands o{static_cast<const uint16_t*>(A), lda, static_cast<const uint16_t*>(W), ldw, M, N, K};
     if (gemm_mfma_supported(o)) return launch_gemm_mfma(o, epi, st);
@@ -42,6 +49,22 @@ Error launch_gemm(int dtype, const void* A, int64_t lda, const void* W, int64_t 
   if (dtype == SPECA_F32 && gemm_f32_supported(A, lda, W, ldw, K))
     return launch_gemm_f32(A, lda, W, ldw, M, N, K, epi, st);
   return launch_gemm_simple(dtype, A, lda, W, ldw, M, N, K, epi, st);
+}
+
+static Operands stream_operands(const void* A, int64_t lda, int64_t ldw, int N, int K, const StreamLayer& y) {
+  return {static_cast<const uint16_t*>(A), lda, y.w[0], ldw, y.rows * y.tokens, N, K};
+}
+
+int streams_kind(int dtype, const void* A, int64_t lda, int64_t ldw, int N, int K, const StreamLayer& y, int mode) {
+  if (dtype != SPECA_BF16 || mode == EPI_SILU || lda < K || ldw < K) return -1;
+  return pick_streams(stream_operands(A, lda, ldw, N, K, y), y, mode == EPI_BRANCH);
+}
+
+Error launch_gemm_streams(int kind, const void* A, int64_t lda, int64_t ldw, int N, int K, const StreamLayer& y, const GemmEpi& epi, hipStream_t st) {
+  GemmEpi e = epi;
+  e.gate = y.gate[0];
+  SPECA_TRY(check_epilogue(y.rows * y.tokens, N, e));
+  return launch_gemm_mfma_streams(kind, stream_operands(A, lda, ldw, N, K, y), y, e, st);
 }
 
 Error launch_attention(int dtype, const void* qkv, void* out, int64_t ldo, int rows, int T, int H, int hd, hipStream_t st) {

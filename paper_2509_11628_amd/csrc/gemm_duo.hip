@@ -43,9 +43,10 @@ __device__ __forceinline__ void wait_steps(int later) {
   }
 }
 
-template <int BM, int MODE>
+template <int BM, int MODE, bool STREAMS>
 __global__ __launch_bounds__(512, 2) void gemm_duo_kernel(const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ W,
-                                                          int64_t ldw, int M, int N, int K, int tiles_m, int tiles_n, int group_m, EpiArg<MODE> epi) {
+                                                          int64_t ldw, int M, int N, int K, int tiles_m, int tiles_n, int group_m, EpiArg<MODE> epi,
+                                                          StreamArg<STREAMS> streams) {
   constexpr int WM = BM / 4, TM = WM / 16, TN = 4;
   constexpr int NS = stages(BM), STAGE = stage_bytes(BM);
   constexpr int AL = BM / 64, L = AL + BN / 64;              // loads of a wave per K-step: activations, all
@@ -54,11 +55,15 @@ __global__ __launch_bounds__(512, 2) void gemm_duo_kernel(const uint16_t* __rest
   int tm, tn;
   const int held = tile_blocks(tiles_m, tiles_n);
   if (static_cast<int>(blockIdx.x) >= held) {
-    read_ahead(W, ldw, N, K, blockIdx.x - held, gridDim.x - held);
+    const int part = blockIdx.x - held, parts = gridDim.x - held;
+    if constexpr (STREAMS) read_ahead(part & 1 ? streams.w2 : W, ldw, N, K, part / 2, (parts + 1 - (part & 1)) / 2);
+    else read_ahead(W, ldw, N, K, part, parts);
     return;
   }
   if (!tile_coords(tiles_m, tiles_n, group_m, &tm, &tn)) return;
-  const int m0 = tm * BM, n0 = tn * BN;
+  const BlockRows<STREAMS> block(streams, W, M, tm, BM);
+  const int m0 = block.m0, n0 = tn * BN;
+  const int64_t first = block.map.at(m0);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, g4 = lane >> 4;
   const bool second = wave >= 4;               // G1
@@ -75,11 +80,11 @@ __global__ __launch_bounds__(512, 2) void gemm_duo_kernel(const uint16_t* __rest
 #pragma unroll
   for (int u = 0; u < L; ++u) {
     const int g = wave + 8 * (u < AL ? u : u - AL), r = g * 8 + lrow;
-    if (u < AL) off[u] = static_cast<uint32_t>(m0 + r < M ? r : M - 1 - m0) * static_cast<uint32_t>(lda) * 2 + ((lane & 7) ^ ((r >> 1) & 7)) * 16;
+    if (u < AL) off[u] = static_cast<uint32_t>(block.map.at(min(m0 + r, block.map.M - 1)) - first) * static_cast<uint32_t>(lda) * 2 + ((lane & 7) ^ ((r >> 1) & 7)) * 16;
     else off[u] = static_cast<uint32_t>(n0 + r < N ? r : N - 1 - n0) * static_cast<uint32_t>(ldw) * 2 + ((lane & 7) ^ (((r >> 1) & 1) | (((r >> 3) & 3) << 1))) * 16;
   }
-  const auto abuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(A) + static_cast<int64_t>(m0) * lda, 0, -1, 0x00020000);
-  const auto wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(W) + static_cast<int64_t>(n0) * ldw, 0, -1, 0x00020000);
+  const auto abuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(A) + first * lda, 0, -1, 0x00020000);
+  const auto wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(block.w) + static_cast<int64_t>(n0) * ldw, 0, -1, 0x00020000);
   // this wave's share of K-step s, to the stage at byte `at` (plain variables: the host pass drops the kernel where arguments of the
   // builtin depend on its template parameters)
 #define SPECA_LOAD_STEP(s, at)                                                                                     \
@@ -142,15 +147,21 @@ __global__ __launch_bounds__(512, 2) void gemm_duo_kernel(const uint16_t* __rest
   if (!second) SPECA_BARRIER()
 #undef SPECA_BARRIER
 #undef SPECA_LOAD_STEP
-  lane_epilogue<BM, MODE>(acc, m0, wm * WM + l16, n0 + wn * 64 + g4 * 8, M, N, epi);
+  const void* bias = epi.bias;
+  const float* gate = nullptr;
+  if constexpr (MODE == EPI_BRANCH) gate = epi.gate;
+  if constexpr (STREAMS) {
+    if (block.second) { bias = streams.bias2; gate = streams.gate2; }
+  }
+  lane_epilogue<BM, MODE>(acc, block.map, bias, gate, m0, wm * WM + l16, n0 + wn * 64 + g4 * 8, N, epi);
 }
 
-template <int BM, int MODE>
-Error launch_mode(const Operands& o, const GemmEpi& epi, hipStream_t st) {
-  const int tiles_m = (o.M + BM - 1) / BM, tiles_n = (o.N + BN - 1) / BN;
+template <int BM, int MODE, bool STREAMS>
+Error launch_mode(const Operands& o, const GemmEpi& epi, const StreamArg<STREAMS>& streams, hipStream_t st) {
+  const int tiles_m = stream_tiles(streams, o.M, BM), tiles_n = (o.N + BN - 1) / BN;
   const int64_t nblk = static_cast<int64_t>(tiles_m) * tiles_n;
   if (nblk > 0x7FFFFFF0) SPECA_FAIL(SPECA_EINVAL, "gemm: too many tiles");
-  auto kern = gemm_duo_kernel<BM, MODE>;
+  auto kern = gemm_duo_kernel<BM, MODE, STREAMS>;
   constexpr int smem = stages(BM) * stage_bytes(BM);
   static bool attr_set = false;   // more than 64 KB of dynamic LDS must be requested once per kernel
   if (!attr_set) {
@@ -158,21 +169,36 @@ Error launch_mode(const Operands& o, const GemmEpi& epi, hipStream_t st) {
     attr_set = true;
   }
   kern<<<launch_blocks(tiles_m, tiles_n, o, epi), 512, smem, st>>>(o.a, o.lda, o.w, o.ldw, o.M, o.N, o.K, tiles_m, tiles_n, tiles_m < 4 ? tiles_m : 4,
-                                                                     epi_arg<MODE>(epi));
+                                                                     epi_arg<MODE>(epi), streams);
   SPECA_HIP(hipGetLastError());
   return ok();
 }
 
 template <int BM>
 Error launch_tile(const Operands& o, const GemmEpi& epi, hipStream_t st) {
+#define SPECA_LAUNCH(MODE) \
+  case MODE: return launch_mode<BM, MODE, false>(o, epi, {}, st);
   switch (epi.mode) {
-    case EPI_STORE: return launch_mode<BM, EPI_STORE>(o, epi, st);
-    case EPI_GELU: return launch_mode<BM, EPI_GELU>(o, epi, st);
-    case EPI_SILU: return launch_mode<BM, EPI_SILU>(o, epi, st);
-    case EPI_F32: return launch_mode<BM, EPI_F32>(o, epi, st);
-    case EPI_BRANCH: return launch_mode<BM, EPI_BRANCH>(o, epi, st);
+    SPECA_LAUNCH(EPI_STORE)
+    SPECA_LAUNCH(EPI_GELU)
+    SPECA_LAUNCH(EPI_SILU)
+    SPECA_LAUNCH(EPI_F32)
+    SPECA_LAUNCH(EPI_BRANCH)
   }
+#undef SPECA_LAUNCH
   SPECA_FAIL(SPECA_EINVAL, "gemm: epilogue mode %d", epi.mode);
+}
+
+template <int BM>
+Error launch_streams(const Operands& o, const GemmEpi& epi, TwoStreams streams, hipStream_t st) {
+  streams.tiles1 = (streams.rows * streams.len1 + BM - 1) / BM;
+  switch (epi.mode) {
+    case EPI_STORE: return launch_mode<BM, EPI_STORE, true>(o, epi, streams, st);
+    case EPI_GELU: return launch_mode<BM, EPI_GELU, true>(o, epi, streams, st);
+    case EPI_F32: return launch_mode<BM, EPI_F32, true>(o, epi, streams, st);
+    case EPI_BRANCH: return launch_mode<BM, EPI_BRANCH, true>(o, epi, streams, st);
+  }
+  SPECA_FAIL(SPECA_EINVAL, "gemm: epilogue mode %d of two streams", epi.mode);
 }
 
 }  // namespace
@@ -184,6 +210,16 @@ Error launch_gemm_duo(int bm, const Operands& o, const GemmEpi& epi, hipStream_t
     case 128: return launch_tile<128>(o, epi, st);
     case 192: return launch_tile<192>(o, epi, st);
     case 256: return launch_tile<256>(o, epi, st);
+  }
+  SPECA_FAIL(SPECA_EINVAL, "gemm: no such tile");
+}
+
+Error launch_gemm_duo_streams(int bm, const Operands& o, const GemmEpi& epi, const TwoStreams& streams, hipStream_t st) {
+  switch (bm) {
+    case 64: return launch_streams<64>(o, epi, streams, st);
+    case 128: return launch_streams<128>(o, epi, streams, st);
+    case 192: return launch_streams<192>(o, epi, streams, st);
+    case 256: return launch_streams<256>(o, epi, streams, st);
   }
   SPECA_FAIL(SPECA_EINVAL, "gemm: no such tile");
 }

@@ -9,7 +9,7 @@
 #include <algorithm>
 #include <cmath>
 
-#include "gemm_tile.h"
+#include "lane_epilogue.h"
 
 namespace speca {
 
@@ -83,8 +83,7 @@ unsigned launch_blocks(int tiles_m, int tiles_n, const Operands& o, const GemmEp
 }
 
 // `paired`: two such layers run side by side, so their tiles fill each other's partial rounds
-static double tile_cost(const TileKind& t, bool branch, int M, int N, int K, bool paired) {
-  const double tiles = static_cast<double>((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+static double tile_cost(const TileKind& t, bool branch, double tiles, int K, bool paired) {
   if (paired) {
     const double depth = std::max(1.0, 2.0 * tiles / compute_units()), c = branch ? t.cb : t.c, r = branch ? t.rb : t.r;
     const double rounds = t.two && depth >= 2.0 ? depth / 2 * (1.0 + r) : 1.0 + r * (depth - 1.0);
@@ -96,6 +95,8 @@ static double tile_cost(const TileKind& t, bool branch, int M, int N, int K, boo
   const double rounds = t.two ? (depth - odd) / 2 * (1.0 + r) + odd : 1.0 + r * (depth - 1.0);
   return t.a + (c + t.b * ((K + BK - 1) / BK)) * rounds;
 }
+
+static double tiles_of(const TileKind& t, int M, int N) { return static_cast<double>((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn); }
 
 // Whether a kind can run the problem.  The rings hold a row's place inside the tile as a 32-bit byte offset, which bounds the
 // stride of the rows (11 million elements for the tallest tile); the others hold it in 32 bits from a buffer's base.
@@ -112,7 +113,7 @@ static int pick_tile(const Operands& o, bool branch, bool paired, double* cost) 
   for (int k = 0; k < kKinds; ++k) {
     const TileKind& t = kTileKinds[k];
     if (!tile_fits(t, o) || (branch && t.cb == 0.0f)) continue;
-    const double c = tile_cost(t, branch, o.M, o.N, o.K, paired);
+    const double c = tile_cost(t, branch, tiles_of(t, o.M, o.N), o.K, paired);
     if (best < 0 || c < bc) { best = k; bc = c; }
   }
   *cost = bc;
@@ -161,7 +162,7 @@ static Choice choose(const Operands& o, bool branch, bool paired) {
       tail.N = o.N - n1;
       double rest = 0.0;
       const int kind = pick_tile(tail, false, false, &rest);
-      rest += tile_cost(kTileKinds[0], false, o.M, n1, o.K, false);
+      rest += tile_cost(kTileKinds[0], false, tiles_of(kTileKinds[0], o.M, n1), o.K, false);
       if (c.head ? rest < c.time : rest + kSecondLaunch < 0.96 * c.time) c = {kind, n1, rest};
     }
   }
@@ -185,6 +186,41 @@ Error launch_gemm_mfma(const Operands& o, const GemmEpi& epi, hipStream_t st) {
   tail.w += static_cast<int64_t>(c.head) * o.ldw;
   tail.N = o.N - c.head;
   return launch_kind(c.kind, tail, te, st);
+}
+
+// One launch for both streams against a launch per row and stream, us per pass: 2 rows x (768 + 77 tokens) x 3072 features, 6 blocks of which 2
+// are dual, 8 steps 12 860 -> 11 330; 3 rows x (256 + 40) x 1024, 5 blocks, 3 dual, 6 steps 2962 -> 1939; 2 x (750 + 333) x 1536, 5 blocks, 4 dual,
+// 6 steps 4751 -> 3597; 1 row x (4096 + 512) x 3072, 57 blocks, 19 dual, 10 steps 216.6 -> 212.6 ms; 1 x (27 030 + 256) x 3072 221.1 -> 221.6 ms.
+int pick_streams(const Operands& o, const StreamLayer& y, bool branch) {
+  const auto side_ok = [](const void* w) { return w && reinterpret_cast<uintptr_t>(w) % 16 == 0; };
+  if (o.N % 4 || o.lda % 8 || o.ldw % 8 || reinterpret_cast<uintptr_t>(o.a) % 16 || !side_ok(y.w[0]) || !side_ok(y.w[1]) || !gemm_phase_fits(o) ||
+      static_cast<int64_t>(y.rows) * y.tokens >= (int64_t{1} << 31) / o.lda)                 // byte offsets inside a tile: 32 bits
+    return -1;
+  double separate = 0.0, best = 0.0;
+  for (int s = 0; s < 2; ++s) {
+    Operands one = o;
+    one.M = y.len[s];
+    separate += y.rows * choose(one, branch, false).time;
+  }
+  int kind = -1;
+  for (int k = 0; k < kKinds; ++k) {
+    const TileKind& t = kTileKinds[k];
+    if (!t.whole_steps) continue;
+    const double c = tile_cost(t, branch, tiles_of(t, y.rows * y.len[0], o.N) + tiles_of(t, y.rows * y.len[1], o.N), o.K, false);
+    if (kind < 0 || c < best) { kind = k; best = c; }
+  }
+  return best < separate ? kind : -1;
+}
+
+Error launch_gemm_mfma_streams(int kind, const Operands& o, const StreamLayer& y, const GemmEpi& epi, hipStream_t st) {
+  Operands first = o;
+  first.w = y.w[0];
+  GemmEpi e = epi;
+  e.bias = y.bias[0];
+  e.gate = y.gate[0];
+  const TwoStreams streams{y.w[1], y.bias[1], y.gate[1], 0, y.rows, y.tokens, y.len[0], y.off[0], y.len[1], y.off[1]};
+  const TileKind& t = kTileKinds[kind];
+  return t.bn == 256 ? launch_gemm_phase_streams(first, e, streams, st) : launch_gemm_duo_streams(t.bm, first, e, streams, st);
 }
 
 }  // namespace speca

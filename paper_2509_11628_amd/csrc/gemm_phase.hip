@@ -54,13 +54,16 @@ static_assert(TM == 8 && TN == 4, "two halves of tokens, two pairs of feature ti
 constexpr int kWaitLds = 0xC07F;               // s_waitcnt lgkmcnt(0)
 template <int N> __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70); }
 
-template <int MODE>
+template <int MODE, bool STREAMS>
 __global__ __launch_bounds__(512, 2) void gemm_phase_kernel(const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ W,
-                                                            int64_t ldw, int M, int N, int K, int tiles_m, int tiles_n, int group_m, EpiArg<MODE> epi) {
+                                                            int64_t ldw, int M, int N, int K, int tiles_m, int tiles_n, int group_m, EpiArg<MODE> epi,
+                                                            StreamArg<STREAMS> streams) {
   extern __shared__ __align__(16) char smem[];               // [2][A: 256 rows, W: 256 rows][64 columns]
   int tm, tn;
   if (!tile_coords(tiles_m, tiles_n, group_m, &tm, &tn)) return;
-  const int m0 = tm * BM, n0 = tn * BN;
+  const BlockRows<STREAMS> block(streams, W, M, tm, BM);
+  const int m0 = block.m0, n0 = tn * BN;
+  const int64_t first = block.map.at(m0);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 2, wn = wave & 3, l16 = lane & 15, g4 = lane >> 4;
 
@@ -86,7 +89,7 @@ __global__ __launch_bounds__(512, 2) void gemm_phase_kernel(const uint16_t* __re
     for (int u = 0; u < 2; ++u) {
       const int ga = u * 16 + h * 8 + wave, gw = u * 16 + (wave >> 2) * 8 + h * 4 + (wave & 3);
       const int ra = ga * 8 + lrow, rw = gw * 8 + lrow;
-      aoff[h][u] = static_cast<uint32_t>(m0 + ra < M ? ra : M - 1 - m0) * static_cast<uint32_t>(lda) * 2 + ((lane & 7) ^ ((ra >> 1) & 7)) * 16;
+      aoff[h][u] = static_cast<uint32_t>(block.map.at(min(m0 + ra, block.map.M - 1)) - first) * static_cast<uint32_t>(lda) * 2 + ((lane & 7) ^ ((ra >> 1) & 7)) * 16;
       woff[h][u] = static_cast<uint32_t>(n0 + rw < N ? rw : N - 1 - n0) * static_cast<uint32_t>(ldw) * 2 +
                    ((lane & 7) ^ (((rw >> 1) & 1) | (((rw >> 3) & 3) << 1))) * 16;
       adst[h][u] = ga * 1024;
@@ -94,8 +97,8 @@ __global__ __launch_bounds__(512, 2) void gemm_phase_kernel(const uint16_t* __re
     }
   // Loads through buffer descriptors: the K-step is a scalar offset, and the compiler does not take them for LDS reads that every
   // later fragment would have to wait for.
-  const auto abuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(A) + static_cast<int64_t>(m0) * lda, 0, -1, 0x00020000);
-  const auto wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(W) + static_cast<int64_t>(n0) * ldw, 0, -1, 0x00020000);
+  const auto abuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(A) + first * lda, 0, -1, 0x00020000);
+  const auto wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(block.w) + static_cast<int64_t>(n0) * ldw, 0, -1, 0x00020000);
 #define SPECA_BUFFER_TO_LDS(buf, dst, off, col) \
   __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (__attribute__((address_space(3))) void*)(dst), 16, off, col, 0, 0)
 #define SPECA_LOAD_A(h, st, col)                                                     \
@@ -219,22 +222,28 @@ __global__ __launch_bounds__(512, 2) void gemm_phase_kernel(const uint16_t* __re
 #undef SPECA_LOAD_W
 #undef SPECA_LOAD_A
 #undef SPECA_BUFFER_TO_LDS
-  lane_epilogue<BM, MODE>(acc, m0, wm * WM + l16, n0 + wn * WN + g4 * 8, M, N, epi);
+  const void* bias = epi.bias;
+  const float* gate = nullptr;
+  if constexpr (MODE == EPI_BRANCH) gate = epi.gate;
+  if constexpr (STREAMS) {
+    if (block.second) { bias = streams.bias2; gate = streams.gate2; }
+  }
+  lane_epilogue<BM, MODE>(acc, block.map, bias, gate, m0, wm * WM + l16, n0 + wn * WN + g4 * 8, N, epi);
 }
 
-template <int MODE>
-Error launch_mode(const Operands& o, const GemmEpi& epi, hipStream_t st) {
-  const int tiles_m = (o.M + BM - 1) / BM, tiles_n = (o.N + BN - 1) / BN;
+template <int MODE, bool STREAMS>
+Error launch_mode(const Operands& o, const GemmEpi& epi, const StreamArg<STREAMS>& streams, hipStream_t st) {
+  const int tiles_m = stream_tiles(streams, o.M, BM), tiles_n = (o.N + BN - 1) / BN;
   const int64_t nblk = static_cast<int64_t>(tiles_m) * tiles_n;
   if (nblk > 0x7FFFFFF0) SPECA_FAIL(SPECA_EINVAL, "gemm: too many tiles");
-  auto kern = gemm_phase_kernel<MODE>;
+  auto kern = gemm_phase_kernel<MODE, STREAMS>;
   static bool attr_set = false;   // more than 64 KB of dynamic LDS must be requested once per kernel
   if (!attr_set) {
     SPECA_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 2 * STAGE));
     attr_set = true;
   }
   kern<<<tile_blocks(tiles_m, tiles_n), 512, 2 * STAGE, st>>>(o.a, o.lda, o.w, o.ldw, o.M, o.N, o.K, tiles_m, tiles_n, tiles_m < 4 ? tiles_m : 4,
-                                                                   epi_arg<MODE>(epi));
+                                                                   epi_arg<MODE>(epi), streams);
   SPECA_HIP(hipGetLastError());
   return ok();
 }
@@ -249,13 +258,24 @@ bool gemm_phase_fits(const Operands& o) {
 Error launch_gemm_phase(const Operands& o, const GemmEpi& epi, hipStream_t st) {
   if (!gemm_phase_fits(o)) SPECA_FAIL(SPECA_EINVAL, "gemm: K=%d or the row strides do not fit the 256x256 tile", o.K);
   switch (epi.mode) {
-    case EPI_STORE: return launch_mode<EPI_STORE>(o, epi, st);
-    case EPI_GELU: return launch_mode<EPI_GELU>(o, epi, st);
-    case EPI_SILU: return launch_mode<EPI_SILU>(o, epi, st);
-    case EPI_F32: return launch_mode<EPI_F32>(o, epi, st);
-    case EPI_BRANCH: return launch_mode<EPI_BRANCH>(o, epi, st);
+    case EPI_STORE: return launch_mode<EPI_STORE, false>(o, epi, {}, st);
+    case EPI_GELU: return launch_mode<EPI_GELU, false>(o, epi, {}, st);
+    case EPI_SILU: return launch_mode<EPI_SILU, false>(o, epi, {}, st);
+    case EPI_F32: return launch_mode<EPI_F32, false>(o, epi, {}, st);
+    case EPI_BRANCH: return launch_mode<EPI_BRANCH, false>(o, epi, {}, st);
   }
   SPECA_FAIL(SPECA_EINVAL, "gemm: epilogue mode %d", epi.mode);
+}
+
+Error launch_gemm_phase_streams(const Operands& o, const GemmEpi& epi, TwoStreams streams, hipStream_t st) {
+  streams.tiles1 = (streams.rows * streams.len1 + BM - 1) / BM;
+  switch (epi.mode) {
+    case EPI_STORE: return launch_mode<EPI_STORE, true>(o, epi, streams, st);
+    case EPI_GELU: return launch_mode<EPI_GELU, true>(o, epi, streams, st);
+    case EPI_F32: return launch_mode<EPI_F32, true>(o, epi, streams, st);
+    case EPI_BRANCH: return launch_mode<EPI_BRANCH, true>(o, epi, streams, st);
+  }
+  SPECA_FAIL(SPECA_EINVAL, "gemm: epilogue mode %d of two streams", epi.mode);
 }
 
 }  // namespace speca

@@ -1,6 +1,6 @@
-// Epilogue from registers of the tiles that compute with 16x16x32 matrix instructions (gemm_phase.hip, gemm_duo.hip): a wave owns 64
-// features, whose weight rows are interleaved in fours per pair of 16-row tiles, so that a lane holds eight consecutive features of one
-// token in each of two pairs, 32 features apart.
+// What the tiles that compute with 16x16x32 matrix instructions share (gemm_phase.hip, gemm_duo.hip): the rows of a launch, and the epilogue from
+// registers.  A wave owns 64 features, whose weight rows are interleaved in fours per pair of 16-row tiles, so that a lane holds eight
+// consecutive features of one token in each of two pairs, 32 features apart.
 #pragma once
 
 #include <type_traits>
@@ -10,6 +10,61 @@
 namespace speca {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// The rows of a launch.  Plain: M of them, one behind the other.  Streams: the tokens of every batch row are split into two ranges with weights
+// of their own (image and text of a dual-stream block); a tile holds rows of one of them, numbered over the batch, and row v of a
+// stream lies at (v / len) tokens + off + v % len.
+template <bool STREAMS> struct RowMap;
+template <> struct RowMap<false> {
+  int M;
+  __device__ __forceinline__ int64_t at(int v) const { return v; }
+};
+template <> struct RowMap<true> {
+  int M, len, off, tokens;
+  __device__ __forceinline__ int64_t at(int v) const {
+    const int i = v / len;
+    return static_cast<int64_t>(i) * tokens + off + (v - i * len);
+  }
+};
+
+// The two streams of a launch: tiles [0, tiles1) of the M direction are rows of the first one.
+struct TwoStreams {
+  const uint16_t* w2;
+  const void* bias2;
+  const float* gate2;
+  int tiles1, rows, tokens;      // batch rows; tokens of each
+  int len1, off1, len2, off2;
+};
+struct OneStream {};
+template <bool STREAMS> using StreamArg = std::conditional_t<STREAMS, TwoStreams, OneStream>;
+
+// tiles of a launch in the M direction
+inline int stream_tiles(const OneStream&, int M, int bm) { return (M + bm - 1) / bm; }
+inline int stream_tiles(const TwoStreams& s, int, int bm) { return (s.rows * s.len1 + bm - 1) / bm + (s.rows * s.len2 + bm - 1) / bm; }
+
+// What a block works on: its rows, its first one among them, its weights.
+template <bool STREAMS>
+struct BlockRows {
+  RowMap<STREAMS> map;
+  int m0;
+  const uint16_t* w;
+  bool second;
+
+  __device__ __forceinline__ BlockRows(const StreamArg<STREAMS>& s, const uint16_t* W, int M, int tm, int bm) {
+    if constexpr (STREAMS) {
+      second = tm >= s.tiles1;
+      m0 = (second ? tm - s.tiles1 : tm) * bm;
+      w = second ? s.w2 : W;
+      const int len = second ? s.len2 : s.len1;
+      map = {s.rows * len, len, second ? s.off2 : s.off1, s.tokens};
+    } else {
+      second = false;
+      m0 = tm * bm;
+      w = W;
+      map = {M};
+    }
+  }
+};
 
 // Eight consecutive features of a token (`two`: only the first four exist otherwise).  Rows start at multiples of four features, so
 // 16 bytes may lie at 8-byte alignment, which global stores allow.
@@ -118,26 +173,44 @@ __device__ __forceinline__ void branch_tokens(const floatx4 (&acc)[4][TM], const
   }
 }
 
+// The batch row of row v of a stream or launch, for a tile that begins at its row m0
+template <bool STREAMS>
+__device__ __forceinline__ int batch_row(const GemmEpi& epi, const RowMap<STREAMS>& map, int v) {
+  if constexpr (STREAMS) return v / map.len;
+  else return v / epi.tokens;
+}
+template <bool STREAMS>
+__device__ __forceinline__ BranchRow<bf16_t> tile_row(const GemmEpi& epi, const RowMap<STREAMS>& map, const float* gates, int m0, int v) {
+  const int i = batch_row(epi, map, v);
+  BranchRow<bf16_t> br = branch_row<bf16_t>(epi, i, m0);
+  if constexpr (STREAMS) {
+    br.gate = gates + static_cast<int64_t>(i) * epi.gate_stride;
+    br.t0 = map.off + m0 - i * map.len;
+  }
+  return br;
+}
+
 // Token by token from J on, planes read back; where the tile spans rows of the batch every token looks its row up.
-template <int J, int TM>
-__device__ __forceinline__ void branch_each(const floatx4 (&acc)[4][TM], BranchRow<bf16_t>& br, float (&gate)[2][8], const GemmEpi& epi, bool spans, int m0,
-                                            int rows, int row0, int n, int N, bool wide) {
+template <int J, int TM, bool STREAMS>
+__device__ __forceinline__ void branch_each(const floatx4 (&acc)[4][TM], BranchRow<bf16_t>& br, float (&gate)[2][8], const GemmEpi& epi,
+                                            const RowMap<STREAMS>& map, const float* gates, bool spans, int m0, int rows, int row0, int n, int N, bool wide) {
   if (spans) {
-    br = branch_row<bf16_t>(epi, (m0 + min(row0 + J * 16, rows - 1)) / epi.tokens, m0);
+    br = tile_row(epi, map, gates, m0, m0 + min(row0 + J * 16, rows - 1));
     load_gate(br.gate, n, N, gate);
   }
   branch_tokens<J, 1, true>(acc, br, gate, epi.ldh, rows, row0, n, N, wide);
-  if constexpr (J + 1 < TM) branch_each<J + 1>(acc, br, gate, epi, spans, m0, rows, row0, n, N, wide);
+  if constexpr (J + 1 < TM) branch_each<J + 1>(acc, br, gate, epi, map, gates, spans, m0, rows, row0, n, N, wide);
 }
 
-// The epilogue of a lane: tokens m0 + row0, + 16, ... (TM of them), features n .. n + 7 and n + 32 .. n + 39.
-template <int BM, int MODE, int TM>
-__device__ __forceinline__ void lane_epilogue(floatx4 (&acc)[4][TM], int m0, int row0, int n, int M, int N, const EpiArg<MODE>& epi) {
-  const int rows = M - m0 < BM ? M - m0 : BM;
-  if (epi.bias) {
+// The epilogue of a lane (bias and gates: of its stream): rows m0 + row0, + 16, ... (TM of them), features n .. n + 7 and n + 32 .. n + 39.
+template <int BM, int MODE, int TM, bool STREAMS>
+__device__ __forceinline__ void lane_epilogue(floatx4 (&acc)[4][TM], const RowMap<STREAMS>& map, const void* biases, const float* gates, int m0, int row0,
+                                              int n, int N, const EpiArg<MODE>& epi) {
+  const int rows = map.M - m0 < BM ? map.M - m0 : BM;
+  if (biases) {
     float bias[2][8] = {};
-    ld8(static_cast<const bf16_t*>(epi.bias), n, N, bias[0]);
-    ld8(static_cast<const bf16_t*>(epi.bias), n + 32, N, bias[1]);
+    ld8(static_cast<const bf16_t*>(biases), n, N, bias[0]);
+    ld8(static_cast<const bf16_t*>(biases), n + 32, N, bias[1]);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -147,18 +220,18 @@ __device__ __forceinline__ void lane_epilogue(floatx4 (&acc)[4][TM], int m0, int
   }
   if constexpr (MODE == EPI_BRANCH) {
     const bool wide = ((reinterpret_cast<uintptr_t>(epi.g.base) & 15) | ((epi.g.E | epi.cache_elem_offset | epi.ldh) & 7)) == 0;
-    const int i_first = m0 / epi.tokens;
+    const int i_first = batch_row(epi, map, m0);
     float gate[2][8];
     // a tile inside one batch row needs its table once for the whole block (scalar loads)
-    const bool spans = i_first != (m0 + rows - 1) / epi.tokens;
-    BranchRow<bf16_t> br = branch_row<bf16_t>(epi, i_first, m0);
+    const bool spans = i_first != batch_row(epi, map, m0 + rows - 1);
+    BranchRow<bf16_t> br = tile_row(epi, map, gates, m0, m0);
     load_gate(br.gate, n, N, gate);
     if (!spans && br.order == 0) {
       constexpr int EB = TM > 4 ? TM / 2 : TM;
       branch_tokens<0, EB, false>(acc, br, gate, epi.ldh, rows, row0, n, N, wide);
       if constexpr (EB < TM) branch_tokens<EB, TM - EB, false>(acc, br, gate, epi.ldh, rows, row0, n, N, wide);
     } else {
-      branch_each<0>(acc, br, gate, epi, spans, m0, rows, row0, n, N, wide);
+      branch_each<0>(acc, br, gate, epi, map, gates, spans, m0, rows, row0, n, N, wide);
     }
   } else {
     using T = std::conditional_t<MODE == EPI_F32, float, bf16_t>;
@@ -166,7 +239,7 @@ __device__ __forceinline__ void lane_epilogue(floatx4 (&acc)[4][TM], int m0, int
     for (int j = 0; j < TM; ++j) {
       const int r = row0 + j * 16;
       if (r < rows) {
-        T* out = static_cast<T*>(epi.out) + static_cast<int64_t>(m0 + r) * epi.ldo;
+        T* out = static_cast<T*>(epi.out) + map.at(m0 + r) * epi.ldo;
 #pragma unroll
         for (int P = 0; P < 2; ++P) {
           const int np = n + 32 * P;
@@ -182,5 +255,8 @@ __device__ __forceinline__ void lane_epilogue(floatx4 (&acc)[4][TM], int m0, int
     }
   }
 }
+
+Error launch_gemm_phase_streams(const Operands& o, const GemmEpi& epi, TwoStreams streams, hipStream_t st);
+Error launch_gemm_duo_streams(int bm, const Operands& o, const GemmEpi& epi, const TwoStreams& streams, hipStream_t st);
 
 }  // namespace speca

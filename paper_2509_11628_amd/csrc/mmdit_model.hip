@@ -255,44 +255,54 @@ struct MMDiT final : Model {
       ProfScope ps(ctx, SPECA_PROF_OTHER, 0.0, static_cast<double>(NT) * D * (4 + esz));
       SPECA_TRY(launch_ln_modulate2(d.dtype, hs, mt, mt + D, mi, mi + D, Tt, mod_n, xn, NT, T, D, st));
     }
-    for (int i = 0; i < n; ++i)
+    // both streams of all rows in one launch, or row by row and stream by stream
+    auto layer = [&](const void* a, int K, const void* const (&w)[2], const void* const (&bias)[2], int N, int gate_at, const GemmEpi& joint) -> Error {
+      StreamLayer y{n, T, {Ti, Tt}, {Tt, 0}, {}, {}, {}};            // the long stream first
       for (int s = 0; s < 2; ++s) {
-        const int64_t t0 = static_cast<int64_t>(i) * T + off[s];
-        GemmEpi e;
-        e.mode = EPI_STORE; e.bias = sw[s]->qkv_b; e.out = at(qkv, t0 * 3 * D); e.ldo = 3 * D;
-        SPECA_TRY(gemm(ctx, SPECA_PROF_GEMM, at(xn, t0 * D), D, sw[s]->qkv_w, D, len[s], 3 * D, D, e));
+        y.w[s] = static_cast<const uint16_t*>(w[1 - s]);
+        y.bias[s] = bias[1 - s];
+        y.gate[s] = sm[1 - s] + gate_at;
       }
+      const int kind = streams_kind(d.dtype, a, K, K, N, K, y, joint.mode);
+      if (kind >= 0) {
+        ProfScope ps(ctx, SPECA_PROF_GEMM, 2.0 * NT * N * K, (static_cast<double>(NT) * (K + N) + 2.0 * N * K) * esz);
+        return launch_gemm_streams(kind, a, K, K, N, K, y, joint, st);
+      }
+      for (int i = 0; i < n; ++i)
+        for (int s = 0; s < 2; ++s) {
+          const int64_t t0 = static_cast<int64_t>(i) * T + off[s];
+          GemmEpi e = joint;
+          e.bias = bias[s];
+          if (joint.mode == EPI_BRANCH) {
+            e.h = joint.h + t0 * D; e.gate = sm[s] + gate_at + static_cast<int64_t>(i) * mod_n; e.gate_stride = 0; e.tokens = len[s];
+            if (joint.refresh) { e.rt = one_row(joint.rt, i); e.cache_elem_offset = static_cast<int64_t>(off[s]) * D; }
+          } else {
+            e.out = joint.mode == EPI_F32 ? static_cast<void*>(static_cast<float*>(joint.out) + t0 * N) : static_cast<void*>(at(joint.out, t0 * N));
+          }
+          SPECA_TRY(gemm(ctx, SPECA_PROF_GEMM, at(a, t0 * K), K, w[s], K, len[s], N, K, e));
+        }
+      return ok();
+    };
+    auto branch = [&](int slot) {
+      GemmEpi b;
+      b.mode = EPI_BRANCH; b.h = hs; b.ldh = D; b.gate_stride = mod_n; b.tokens = T;
+      if (refresh_rt) { b.refresh = 1; b.slot = slot; b.g = ctx->geom; b.rt = *refresh_rt; }
+      return b;
+    };
+    GemmEpi e;
+    e.mode = EPI_STORE; e.out = qkv; e.ldo = 3 * D;
+    SPECA_TRY(layer(xn, D, {sw[0]->qkv_w, sw[1]->qkv_w}, {sw[0]->qkv_b, sw[1]->qkv_b}, 3 * D, 0, e));
     SPECA_TRY(attention_part(ctx, n, txt[l].qnorm, txt[l].knorm, img[l].qnorm, img[l].knorm, att, D));
-    for (int i = 0; i < n; ++i)
-      for (int s = 0; s < 2; ++s) {
-        const int64_t t0 = static_cast<int64_t>(i) * T + off[s];
-        GemmEpi b;
-        b.mode = EPI_BRANCH; b.bias = sw[s]->proj_b; b.h = hs + t0 * D; b.ldh = D; b.gate = sm[s] + 2 * D + static_cast<int64_t>(i) * mod_n;
-        b.gate_stride = 0; b.tokens = len[s];
-        if (refresh_rt) { b.refresh = 1; b.slot = 2 * l; b.g = ctx->geom; b.rt = one_row(*refresh_rt, i); b.cache_elem_offset = static_cast<int64_t>(off[s]) * D; }
-        SPECA_TRY(gemm(ctx, SPECA_PROF_GEMM, at(att, t0 * D), D, sw[s]->proj_w, D, len[s], D, D, b));
-      }
+    SPECA_TRY(layer(att, D, {sw[0]->proj_w, sw[1]->proj_w}, {sw[0]->proj_b, sw[1]->proj_b}, D, 2 * D, branch(2 * l)));
     {
       ProfScope ps(ctx, SPECA_PROF_OTHER, 0.0, static_cast<double>(NT) * D * (4 + esz));
       SPECA_TRY(launch_ln_modulate2(d.dtype, hs, mt + 3 * D, mt + 4 * D, mi + 3 * D, mi + 4 * D, Tt, mod_n, xn, NT, T, D, st));
     }
-    for (int i = 0; i < n; ++i)
-      for (int s = 0; s < 2; ++s) {
-        const int64_t t0 = static_cast<int64_t>(i) * T + off[s];
-        GemmEpi e;
-        e.mode = EPI_GELU; e.bias = sw[s]->fc1_b; e.out = at(f1, t0 * Dm); e.ldo = Dm;
-        SPECA_TRY(gemm(ctx, SPECA_PROF_GEMM, at(xn, t0 * D), D, sw[s]->fc1_w, D, len[s], Dm, D, e));
-        GemmEpi b;
-        b.bias = sw[s]->fc2_b;
-        if (truth_out) {
-          b.mode = EPI_F32; b.out = truth_out + t0 * D; b.ldo = D;
-        } else {
-          b.mode = EPI_BRANCH; b.h = hs + t0 * D; b.ldh = D; b.gate = sm[s] + 5 * D + static_cast<int64_t>(i) * mod_n; b.gate_stride = 0;
-          b.tokens = len[s];
-          if (refresh_rt) { b.refresh = 1; b.slot = 2 * l + 1; b.g = ctx->geom; b.rt = one_row(*refresh_rt, i); b.cache_elem_offset = static_cast<int64_t>(off[s]) * D; }
-        }
-        SPECA_TRY(gemm(ctx, SPECA_PROF_GEMM, at(f1, t0 * Dm), Dm, sw[s]->fc2_w, Dm, len[s], D, Dm, b));
-      }
+    e = GemmEpi(); e.mode = EPI_GELU; e.out = f1; e.ldo = Dm;
+    SPECA_TRY(layer(xn, D, {sw[0]->fc1_w, sw[1]->fc1_w}, {sw[0]->fc1_b, sw[1]->fc1_b}, Dm, 0, e));
+    GemmEpi f = branch(2 * l + 1);
+    if (truth_out) { f = GemmEpi(); f.mode = EPI_F32; f.out = truth_out; f.ldo = D; }
+    SPECA_TRY(layer(f1, Dm, {sw[0]->fc2_w, sw[1]->fc2_w}, {sw[0]->fc2_b, sw[1]->fc2_b}, D, 5 * D, f));
     return ok();
   }
 

@@ -124,9 +124,48 @@ def test_mmdit_error_paths(tiny):
     assert e.value.code == bd.EINVAL and "single0.lin2_w" in e.value.msg
 
 
+# rows, text tokens, latent height and width (patch 2), hidden, heads, mlp_hidden: streams of one token, shorter than a tile, that end inside tiles and
+# tiles that span rows of the batch; large enough for 256x256 tiles; an MLP of 136 features, whose second layer goes row by row and stream by stream
+@pytest.mark.parametrize("layout", ["differences", "ring"])
+@pytest.mark.parametrize("rows,txt,h,w,D,H,Dm", [(2, 1, 16, 16, 128, 2, 512), (3, 77, 20, 22, 128, 2, 512), (3, 129, 34, 30, 512, 8, 2048),
+                                                 (1, 300, 66, 62, 768, 12, 3072), (2, 40, 18, 22, 128, 2, 136), (5, 65, 128, 128, 512, 8, 2048)])
+def test_dual_blocks_of_all_rows_in_one_launch(rows, txt, h, w, D, H, Dm, layout):
+    """Three reference steps of all rows together leave the bits (output and every cached plane) of the same steps of a row alone, and the
+    first one agrees with the oracle's forward of a row (smaller shapes)."""
+    import dataclasses
+    import paper_2509_11628_amd as sp
+    from paper_2509_11628_amd import binding as bd
+    s = dataclasses.replace(si.mmdit_tiny("bf16"), depth_dual=2, depth_single=1, hidden=D, heads=H, mlp_hidden=Dm, txt_tokens=txt, latent_h=h, latent_w=w)
+    weights = si.make_mmdit_weights(s, 0)
+    ctx = make_gpu(s, weights)
+    text, vec = si.make_text(rows, s, 3)
+    td, vd = torch.from_numpy(text).cuda().bfloat16(), torch.from_numpy(vec).cuda().bfloat16()
+    x = {i: torch.from_numpy(si.make_video_latents(rows, s, i)).cuda() for i in range(3)}
+    cfg = sp.make_cfg(order=2, interval=100, layout=bd.CACHE_RING if layout == "ring" else bd.CACHE_DIFFERENCES)
+
+    def steps(which):
+        ctx.init_cache(cfg, rows)
+        out = torch.zeros((3, *x[0].shape), device="cuda")
+        for i, step in enumerate((0, 3, 4)):
+            ctx.full_step(x[i], step, which, out[i], timestep=900.0 - 100.0 * i, txt=td, pooled=vd)
+        f = torch.empty((s.n_slots, len(which), s.tokens, D), dtype=torch.bfloat16, device="cuda")
+        ctx.forecast(6, which, f)
+        return out, f
+
+    out, f = steps(list(range(rows)))
+    for r in {0, rows - 1}:
+        out1, f1 = steps([r])
+        assert torch.equal(out1[:, r], out[:, r]) and torch.equal(f1[:, 0], f[:, r]), r
+    if s.tokens <= 1400:
+        r = rows - 1
+        exp, _ = ommdit.MMDiTOracle(s, weights).forward(x[0][r:r + 1].cpu().numpy(), 900.0, (text[r:r + 1], vec[r:r + 1]))
+        assert max_abs_rel(out[0, r:r + 1].cpu().numpy(), exp) <= 2e-2
+    ctx.close()
+
+
 def test_flux_width_slice_matches_oracle():
     """One dual-stream and one single-stream block at the full FLUX width (D 3072, 24 heads of 128,
-    MLP 12288) on 128 + 1280 tokens: the 256x256 and 256x128 GEMM tiles, the K lengths of
+    MLP 12288) on 128 + 1280 tokens: the large GEMM tiles, the K lengths of
     configuration 4 (3072, 12288, 15360) and the tiled attention over 22 key tiles, against the
     oracle's forward (about a minute of CPU).  The benchmark's model differs in depth and token count."""
     import dataclasses
