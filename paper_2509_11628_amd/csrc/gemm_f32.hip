@@ -2,8 +2,8 @@
 // unpacked vector FMAs reach, and exact fp32 products and sums).
 //
 // The models that run in fp32 are small, so their launches are bound by latency, not by rate: a 512 x 384 x 1536 layer is
-// 4 us of matrix work, and a vector-FMA block walking K behind a barrier per 16 columns took 97 us (now 14; attention over
-// 256 keys of two rows x 6 heads 340 us with one query per thread, now 8; 4096^3 runs at 98 TFLOP/s).  Hence
+// 4 us of matrix work, and a vector-FMA block walking K behind a barrier per 16 columns took 97 us (now 11; attention over
+// 256 keys of two rows x 6 heads 340 us with one query per thread, now 8).  Hence, but for the larger tiles of whole 64-column stages,
 //   - no LDS and no barrier in the loops: a lane's operands come from memory as 16-byte pieces that are fragments as they
 //     stand.  The reduction index is a dummy, so lane l of a wave simply takes columns 4 (l / 16) .. + 3 of its row, and
 //     instruction c of the step consumes component c of both operands: one load feeds four instructions;
@@ -11,6 +11,7 @@
 //   - the four waves of a block share one output tile and split K (GEMM: steps of 16 dealt round robin) or the keys
 //     (attention: tiles of 16 keys), and their partial results meet once, in LDS, in wave order.  The split depends on K
 //     (on the number of keys) alone, so a row's bits depend neither on M nor on the tile.
+#include <algorithm>
 #include <type_traits>
 
 #include "epilogue.h"
@@ -29,7 +30,7 @@ __device__ __forceinline__ floatx4 mfma4(float a, float b, floatx4 c) { return _
 // PF = steps of loads in flight per wave.
 // KTAIL: K is no multiple of 16.
 template <int TM, int TN, int PF, int MODE, bool KTAIL>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int64_t lda, const float* __restrict__ W, int64_t ldw, int M, int N,
+__global__ __launch_bounds__(256) void gemm_f32_small_kernel(const float* __restrict__ A, int64_t lda, const float* __restrict__ W, int64_t ldw, int M, int N,
                                                        int K, EpiArg<MODE> epi) {
   constexpr int BM = 16 * TM, BN = 16 * TN;
   constexpr int CST = BN + 4;                     // floats per staged row
@@ -117,6 +118,136 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
   }
 }
 
+// The same for tiles that leave every unit enough to do: operands come through LDS.  Fragments straight from memory are 16 rows x 64 bytes per
+// instruction, of which a unit takes 33 bytes per ns; loads that go to LDS directly take 256 bytes of each of 4 rows, 94.  A stage is 64 columns, the
+// four steps of 16 that the four waves deal among themselves, so every wave adds up the same products in the same order as above.
+// Chunk c (16 bytes) of row r sits at position c ^ (r % 16): the rows of a fragment touch all banks once.  A ring of NS stages; a wave
+// waits for its own loads (in issue order) and for its fragments ahead of the barrier behind which the stage before is loaded over.
+// Needs K % 64 == 0: with the zeros of a last stage selected in the loop, 512 x 1152 x 384 took 10.4 us and 1000 x 772 x 260 was slower than above.
+// us, above -> here: 512 x 1152 x 384 11.6 -> 9.1, 512 x 384 x 1536 14.5 -> 11.3, 2048 x 1152 x 384 37.3 -> 27.8, 33 x 4608 x 1152 16.7 -> 14.5,
+// 8192 x 1152 x 1152 247 -> 191, 4096^3 1392 -> 1133 (121 TFLOP/s).
+
+constexpr int f32_stage_bytes(int TM, int TN) { return 16 * (TM + TN) * 256; }
+constexpr int f32_lds_bytes(int TM, int TN, int NS) {
+  const int ring = NS * f32_stage_bytes(TM, TN), part = 4 * 16 * TM * (16 * TN + 4) * 4;
+  return ring > part ? ring : part;
+}
+
+template <int TM, int TN, int NS, int MODE>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int64_t lda, const float* __restrict__ W, int64_t ldw, int M, int N,
+                                                       int K, EpiArg<MODE> epi) {
+  constexpr int BM = 16 * TM, BN = 16 * TN, CST = BN + 4, STAGE = f32_stage_bytes(TM, TN);
+  constexpr int L = (BM + BN) / 16;               // loads of a wave per stage
+  static_assert((BM + BN) % 16 == 0 && BM % 16 == 0 && NS >= 2 && (NS - 1) * L < 64, "4 rows per load, four waves");
+  extern __shared__ __align__(16) char lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g4 = lane >> 4;
+  const int64_t mt = static_cast<int64_t>(blockIdx.z) * gridDim.y + blockIdx.y;
+  if (mt * BM >= M) return;
+  const int m0 = static_cast<int>(mt) * BM, n0 = blockIdx.x * BN;
+  // load u of a wave: rows 4 g .. + 3 of the tile's BM + BN, g = wave + 4 u; lane l supplies what lies at position l % 16 of row 4 g + l / 16
+  const float* from[L];
+#pragma unroll
+  for (int u = 0; u < L; ++u) {
+    const int r = (wave + 4 * u) * 4 + (lane >> 4), rw = r - BM;
+    from[u] = (r < BM ? A + static_cast<int64_t>(m0 + r < M ? m0 + r : M - 1) * lda : W + static_cast<int64_t>(n0 + rw < N ? n0 + rw : N - 1) * ldw) + ((lane & 15) ^ (r & 15)) * 4;
+  }
+  auto load = [&](int s, int slot) {
+#pragma unroll
+    for (int u = 0; u < L; ++u) {
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(from[u] + static_cast<int64_t>(s) * 64), (__attribute__((address_space(3))) void*)(lds + slot * STAGE + (wave + 4 * u) * 1024), 16, 0, 0);
+    }
+  };
+  floatx4 acc[TN][TM];
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int i = 0; i < TM; ++i) acc[j][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const int nk = K / 64;
+#pragma unroll
+  for (int s = 0; s < NS - 1; ++s)
+    if (s < nk) load(s, s);
+  constexpr auto loads_left = [](int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; };          // s_waitcnt vmcnt(n)
+  const int at = l16 * 256 + ((4 * wave + g4) ^ l16) * 16;
+  int slot = 0, next = NS - 1;                    // of stage s and of stage s + NS - 1
+  for (int s = 0; s < nk; ++s) {
+    if (s + NS - 2 < nk) __builtin_amdgcn_s_waitcnt(loads_left((NS - 2) * L));
+    else __builtin_amdgcn_s_waitcnt(loads_left(0));
+    __builtin_amdgcn_s_waitcnt(0xC07F);           // fragments of the stage before
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if (s + NS - 1 < nk) load(s + NS - 1, next);
+    floatx4 a[TM], w[TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) a[i] = *reinterpret_cast<const floatx4*>(lds + slot * STAGE + at + i * 16 * 256);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) w[j] = *reinterpret_cast<const floatx4*>(lds + slot * STAGE + at + (BM + j * 16) * 256);
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int i = 0; i < TM; ++i) acc[j][i] = mfma4(w[j][c], a[i][c], acc[j][i]);
+    slot = slot + 1 == NS ? 0 : slot + 1;
+    next = next + 1 == NS ? 0 : next + 1;
+  }
+  __syncthreads();
+  float* part = reinterpret_cast<float*>(lds);
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int i = 0; i < TM; ++i) *reinterpret_cast<floatx4*>(part + wave * (BM * CST) + (i * 16 + l16) * CST + j * 16 + 4 * g4) = acc[j][i];
+  __syncthreads();
+  constexpr int QPR = BN / 4;
+#pragma unroll
+  for (int q = tid; q < BM * QPR; q += 256) {
+    const int r = q / QPR, c = (q % QPR) * 4;
+    const int m = m0 + r, n = n0 + c;
+    if (m < M && n < N) {
+      float v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float* x = part + r * CST + c + e;
+        v[e] = ((x[0] + x[BM * CST]) + x[2 * BM * CST]) + x[3 * BM * CST];
+      }
+      epilogue_quad<float, MODE>(epi, m, n, v);
+    }
+  }
+}
+
+template <int TM, int TN, int NS, int MODE>
+Error launch_f32_mode(dim3 grid, const float* A, int64_t lda, const float* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st) {
+  auto kern = gemm_f32_kernel<TM, TN, NS, MODE>;
+  constexpr int smem = f32_lds_bytes(TM, TN, NS);
+  static bool attr_set = false;   // more than 64 KB of dynamic LDS must be requested once per kernel
+  if (smem > 64 * 1024 && !attr_set) {
+    SPECA_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem));
+    attr_set = true;
+  }
+  kern<<<grid, 256, smem, st>>>(A, lda, W, ldw, M, N, K, epi_arg<MODE>(epi));
+  SPECA_HIP(hipGetLastError());
+  return ok();
+}
+
+template <int TM, int TN, int NS>
+Error launch_f32_lds(const float* A, int64_t lda, const float* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st) {
+  const unsigned row_tiles = (M + 16 * TM - 1) / (16 * TM), grid_y = row_tiles < 32768 ? row_tiles : 32768;
+  const dim3 grid((N + 16 * TN - 1) / (16 * TN), grid_y, (row_tiles + grid_y - 1) / grid_y);
+#define SPECA_LAUNCH(MODE_) \
+  case MODE_: return launch_f32_mode<TM, TN, NS, MODE_>(grid, A, lda, W, ldw, M, N, K, epi, st);
+  switch (epi.mode) {
+    SPECA_LAUNCH(EPI_STORE)
+    SPECA_LAUNCH(EPI_GELU)
+    SPECA_LAUNCH(EPI_SILU)
+    SPECA_LAUNCH(EPI_F32)
+    SPECA_LAUNCH(EPI_BRANCH)
+  }
+#undef SPECA_LAUNCH
+  SPECA_FAIL(SPECA_EINVAL, "gemm: epilogue mode %d", epi.mode);
+}
+
 template <int TM, int TN, int PF>
 Error launch_f32_tile(const float* A, int64_t lda, const float* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi,
                       hipStream_t st) {
@@ -124,8 +255,8 @@ Error launch_f32_tile(const float* A, int64_t lda, const float* W, int64_t ldw, 
   const dim3 grid((N + 16 * TN - 1) / (16 * TN), grid_y, (row_tiles + grid_y - 1) / grid_y);
 #define SPECA_LAUNCH(MODE_)                                                                                                  \
   {                                                                                                                          \
-    if (K % 16) gemm_f32_kernel<TM, TN, PF, MODE_, true><<<grid, 256, 0, st>>>(A, lda, W, ldw, M, N, K, epi_arg<MODE_>(epi)); \
-    else gemm_f32_kernel<TM, TN, PF, MODE_, false><<<grid, 256, 0, st>>>(A, lda, W, ldw, M, N, K, epi_arg<MODE_>(epi));        \
+    if (K % 16) gemm_f32_small_kernel<TM, TN, PF, MODE_, true><<<grid, 256, 0, st>>>(A, lda, W, ldw, M, N, K, epi_arg<MODE_>(epi)); \
+    else gemm_f32_small_kernel<TM, TN, PF, MODE_, false><<<grid, 256, 0, st>>>(A, lda, W, ldw, M, N, K, epi_arg<MODE_>(epi));        \
   }
   switch (epi.mode) {
     case EPI_STORE: SPECA_LAUNCH(EPI_STORE) break;
@@ -370,14 +501,35 @@ static Error launch_f32_kind(int kind, const float* a, int64_t lda, const float*
 }
 
 Error launch_gemm_f32(const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st) {
-  // The largest tile that still makes 128 blocks (one on every second compute unit): a block's waves read every operand
+  const float *a = static_cast<const float*>(A), *w = static_cast<const float*>(W);
+  const auto blocks = [&](int bm, int bn) { return static_cast<int64_t>((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  const int rows = (M + 15) / 16 * 16;
+  // Straight from memory, the largest tile that still makes 128 blocks (one on every second compute unit): a block's waves read every operand
   // piece once per tile, and that traffic costs more than idle units do down to there (512 x 1152 x 384: 144 blocks of 64 x 64
   // 11.4 us, 576 of 32 x 32 12.8, 2304 of 16 x 16 18.1; 512 x 384 x 384 with 48 / 192 / 768 blocks: 11.1 / 5.6 / 7.6 us).
   // Tiles more than twice as high as the problem only read rows again.
   constexpr int bm[5] = {64, 32, 32, 16, 16}, bn[5] = {64, 64, 32, 32, 16};
   int kind = 0;
-  while (kind < 4 && (bm[kind] > 2 * ((M + 15) / 16 * 16) || static_cast<int64_t>((M + bm[kind] - 1) / bm[kind]) * ((N + bn[kind] - 1) / bn[kind]) < 128)) ++kind;
-  return launch_f32_kind(kind, static_cast<const float*>(A), lda, static_cast<const float*>(W), ldw, M, N, K, epi, st);
+  while (kind < 4 && (bm[kind] > 2 * rows || blocks(bm[kind], bn[kind]) < 128)) ++kind;
+  if (K % 64 || rows < 32 || kind > 2) return launch_f32_kind(kind, a, lda, w, ldw, M, N, K, epi, st);
+  // Through LDS, the tile that takes least: its rounds over 256 units times its stages, each the longer of 4 TM TN matrix instructions per wave
+  // (32 clocks) and of its loads at 94 bytes per ns, and 0.4 us a round.  Fewer than 128 blocks of 32 x 32, or 16 rows: a step's latency
+  // binds, not the loads.
+  constexpr int tm[4] = {4, 4, 2, 2}, tn[4] = {4, 3, 4, 2};
+  int best = 0;
+  double least = 0.0;
+  for (int k = 0; k < 4; ++k) {
+    const double rounds = static_cast<double>((blocks(16 * tm[k], 16 * tn[k]) + 255) / 256);
+    const double stage = std::max(tm[k] * tn[k] * 0.0533, (tm[k] + tn[k]) * 16 * 256 / 94e3);
+    const double time = rounds * (stage * (K / 64) + 0.4);
+    if (k == 0 || time < least) { best = k; least = time; }
+  }
+  switch (best) {
+    case 0: return launch_f32_lds<4, 4, 2>(a, lda, w, ldw, M, N, K, epi, st);
+    case 1: return launch_f32_lds<4, 3, 2>(a, lda, w, ldw, M, N, K, epi, st);
+    case 2: return launch_f32_lds<2, 4, 3>(a, lda, w, ldw, M, N, K, epi, st);
+    default: return launch_f32_lds<2, 2, 4>(a, lda, w, ldw, M, N, K, epi, st);
+  }
 }
 
 Error launch_attention_f32(int dtype, const void* qkv, void* out, int64_t ldo, int rows, int T, int H, int hd, hipStream_t st) {
