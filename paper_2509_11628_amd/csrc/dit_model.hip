@@ -21,6 +21,31 @@
 
 namespace speca {
 
+// In how many groups side by side n rows of T tokens run (bf16 models of 384 features and more).  A layer of all rows wastes what its last round
+// of tiles leaves idle; the tiles of two half layers fill each other's partial rounds, and what one group does outside the matrix cores
+// runs beside the other's layers, but each half waits for a whole tile time per layer.  The cost model of the tiles weighs `whole` against
+// `pair` for the four layers of a block (us).  In two groups the tiles are those whose rounds, filled by both, take least.
+//   - up to 512 features: whole > 1.1 pair, or 12288 tokens and more, where the passes that are bound by memory weigh more than the rounds;
+//   - wider: whole > 1.17 pair, or whole > 1.01 pair + 18, or 8192 tokens and more, where the model misses what runs beside the other's layers.
+// Measured in both forms at 540 sizes (384 to 3072 features, 16 to 1024 tokens, 2 to 64 rows, both layouts, reference steps of 4 to 28
+// blocks).  One group / two groups in us per block: 10 rows x 784 tokens x 1152 with planes of differences 554 / 461, 21 x 1024 x 1152 988 / 908,
+// 18 x 1024 x 1152 866 / 765, 14 x 784 x 768 with planes 433 / 344; near the line 8 x 256 x 1152 135.4 / 137.6 (with planes 162.3 / 163.7), 12 x 256 x 384
+// 59.7 / 63.0 (with planes 75.5 / 72.5); not taken 16 x 256 x 1152 199 / 204, 10 x 256 x 1152 156 / 176, 12 x 121 x 384 60 / 80.
+// Narrower models are bound by launches: 64 to 256 features at 3072 to 16384 tokens lose up to 39 % in two groups and gain 4 % at best.  A single
+// block (the verification) does not repay the fork and join (16 rows of 1152 features and 256 tokens, six steps of eight blocks 5.00 / 5.18 ms), and
+// fp32 layers are bound by their own latency (33 sizes of 256 to 768 features: 7 % gained at best, 22 % lost at worst).
+int dit_row_groups(int n, int T, int D, int Dm) {
+  double whole = 0.0, pair = 0.0;
+  const struct { bool branch; int N, K; } layers[] = {{false, 3 * D, D}, {true, D, D}, {false, Dm, D}, {true, D, Dm}};
+  for (const auto& y : layers) {
+    whole += layer_time(y.branch, n * T, y.N, y.K, false);
+    pair += layer_time(y.branch, (n + 1) / 2 * T, y.N, y.K, true);
+  }
+  const int64_t rows = static_cast<int64_t>(n) * T;
+  if (D <= 512) return whole > 1.1 * pair || rows >= 12288 ? 2 : 1;
+  return whole > 1.17 * pair || whole > 1.01 * pair + 18.0 || rows >= 8192 ? 2 : 1;
+}
+
 namespace {
 
 struct BlockW {
@@ -280,31 +305,9 @@ struct DiT final : Model {
     return ok();
   }
 
-  // Whether n rows run as two groups side by side.  A layer of all rows wastes what its last round of tiles leaves idle; the tiles
-  // of two half layers fill each other's partial rounds, but each half waits for a whole tile time per layer.  The cost model of
-  // the tiles weighs one against the other for the four layers of a block, and two groups are taken where it expects
-  // more than 1 % and 20 us per block from them.  In two groups the tiles are those whose rounds, filled by both, take least.  Measured over 174 sizes
-  // (384 to 3072 features, 64 to 1024 tokens, 2 to 64 rows, both layouts; reference steps of 4 blocks): the choice lies 0.5 % above the better
-  // form on the mean and 9 % at worst (21 rows x 1024 tokens x 1152: 4097 us in one group, 3743 in two); one group throughout would lose 2.3 %.
-  // One group / two groups in us: 24 x 1024 x 1024 3685 / 3407, 16 x 576 x 1152 with planes of differences 2459 / 2092, 42 x 576 x 1024
-  // 3490 / 3232; not taken 10 x 256 x 1152 625 / 703, 8 x 256 x 3072 2115 / 2255, 17 x 256 x 384 316 / 354.
-  // In narrow models with many tokens the passes that are bound by memory weigh more than the rounds: 384 features
-  // at 8192, 12288 and 16384 tokens 8.45 / 8.76, 14.8 / 13.8, 14.3 / 13.1 ms of 28 blocks, 512 at 12288 15.7 / 14.7.  Narrower still, launches bound a
-  // step: 64 to 256 features at 3072 to 16384 tokens lose up to 39 % in two groups and gain 4 % at best.  A single block (the verification) does not repay the
-  // fork and join (16 rows of 1152 features and 256 tokens, six steps of eight blocks 5.00 / 5.18), and fp32 layers are bound by their
-  // own latency (33 sizes of 256 to 768 features: 7 % gained at best, 22 % lost at worst).
   bool two_groups(int n) {
     if (n < 2 || d.dtype != SPECA_BF16 || D < 384 || D % 8 || Dm % 8) return false;
-    if (!groups_for[n]) {
-      const int half = (n + 1) / 2 * T;
-      double whole = 0.0, pair = 0.0;
-      const struct { bool branch; int N, K; } layers[] = {{false, 3 * D, D}, {true, D, D}, {false, Dm, D}, {true, D, Dm}};
-      for (const auto& y : layers) {
-        whole += layer_time(y.branch, n * T, y.N, y.K, false);
-        pair += layer_time(y.branch, half, y.N, y.K, true);
-      }
-      groups_for[n] = whole > 1.01 * pair + 20.0 || (D <= 512 && static_cast<int64_t>(n) * T >= 12288) ? 2 : 1;
-    }
+    if (!groups_for[n]) groups_for[n] = static_cast<int8_t>(dit_row_groups(n, T, D, Dm));
     return groups_for[n] == 2;
   }
 

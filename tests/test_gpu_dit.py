@@ -458,11 +458,11 @@ def test_sample_error_paths(tiny):
     assert e.value.code == bd.EINVAL
 
 
-# rows, grid (tokens = grid^2), hidden, heads, dtype, row groups.  28 x 400 x 768: two half layers fill rounds of tiles that one
-# leaves half empty; 12 x 256 x 384: they would not; 13 x 1024 x 384: a narrow model with many tokens, groups of 6 and 7; 3 x 1369 x 384: never three groups;
+# rows, grid (tokens = grid^2), hidden, heads, dtype, row groups.  12 x 256 x 384: two half layers fill rounds of tiles that one
+# leaves half empty; 13 x 1024 x 384: a narrow model with many tokens, groups of 6 and 7; 3 x 1369 x 384: never three groups;
 # narrower ones and fp32: one group
-@pytest.mark.parametrize("rows,grid,D,H,dtype,groups", [(28, 20, 768, 12, "bf16", 2), (12, 16, 384, 6, "bf16", 1), (13, 32, 384, 6, "bf16", 2), (3, 37, 384, 6, "bf16", None),
-                                                        (16, 4, 64, 4, "bf16", 1), (13, 32, 64, 1, "bf16", 1), (12, 16, 384, 6, "f32", 1)])
+@pytest.mark.parametrize("rows,grid,D,H,dtype,groups", [(12, 16, 384, 6, "bf16", 2), (13, 32, 384, 6, "bf16", 2), (3, 37, 384, 6, "bf16", None),
+                                                        (16, 4, 64, 4, "bf16", 1), (13, 32, 64, 1, "bf16", 1), (12, 16, 384, 6, "f32", 1), (28, 20, 768, 12, "bf16", 2)])
 def test_lanes_do_not_change_results(rows, grid, D, H, dtype, groups):
     """Row groups of a step run side by side on a stream of the library; a row's result must not depend on how the rows were
     grouped: same bits for 1, 2 and 4 lanes over accepted and rejected attempts.  The launches of a profiled reference step
@@ -503,7 +503,7 @@ def test_config3_full_size_sampled():
     guidance pair, bf16): the reference step of one guidance pair (rows 0 and 8) against the
     oracle's forward of those two rows (about 10 s of CPU), model output and sampled cached features;
     then properties that hold at any size: thresholds of zero reproduce plain sampling bit for bit and
-    the lane count does not change a bit (30 rows, which the library runs as two groups)."""
+    the lane count does not change a bit (8 rows, which the library runs as two groups)."""
     import paper_2509_11628_amd as sp
     from paper_2509_11628_amd import binding as bd
     s = si.dit_xl2("bf16")
@@ -531,23 +531,20 @@ def test_config3_full_size_sampled():
         idx = (rng.integers(0, 2, 2000), rng.integers(0, s.tokens, 2000), rng.integers(0, s.hidden, 2000))
         a, b = gf[j][idx], feats[j][idx]
         assert np.max(np.abs(a - b)) <= 2e-2 * np.max(np.abs(feats[j])), j
-    # properties at full size: tau = 0 is plain sampling; lanes do not change bits (8 steps of 15 samples)
+    # properties at full size: tau = 0 is plain sampling; lanes do not change bits (8 steps of 4 samples keep it short)
     S = 8
-    n = 15
-    many, many_lab = np.concatenate([lat, 0.5 * lat])[:n], np.concatenate([lab, lab])[:n]
     ts, ab = si.ddim_tables(S)
     res = []
     for lanes, tau in ((4, np.zeros(S, np.float32)), (1, np.zeros(S, np.float32)), (4, bd.tau_geometric(0.5, 0.5, S)), (1, bd.tau_geometric(0.5, 0.5, S))):
         ctx.set_lanes(lanes)
-        ctx.init_cache(sp.make_cfg(order=2, interval=4), 2 * n)
-        x = torch.from_numpy(many).cuda()
-        tr = ctx.sample(x, ts, ab, tau, cfg_scale=1.5, labels=many_lab)
+        ctx.init_cache(sp.make_cfg(order=2, interval=4), B)
+        x = torch.from_numpy(lat[:B // 2]).cuda()
+        tr = ctx.sample(x, ts, ab, tau, cfg_scale=1.5, labels=lab[:B // 2])
         res.append((x.cpu().numpy(), tr))
     ctx.set_lanes(2, profile_keeps_lanes=True)
-    ctx.init_cache(sp.make_cfg(order=2, interval=4), 2 * n)
-    xm = torch.from_numpy(np.concatenate([many, many])).cuda()
+    ctx.init_cache(sp.make_cfg(order=2, interval=4), B)
     ctx.profile_begin()
-    ctx.full_step(xm, 0, list(range(2 * n)), torch.zeros_like(xm), timestep=float(ts[0]), labels=list(many_lab) + [s.num_classes] * n)
+    ctx.full_step(xd, 0, list(range(B)), torch.zeros_like(xd), timestep=float(ts[0]), labels=labels_rows)
     assert ctx.profile_end()["gemm"]["launches"] == 2 * 4 * s.depth          # two groups ran
     assert np.all(res[0][1]["kind"] == 0) and np.array_equal(res[0][0], res[1][0])
     assert np.array_equal(res[2][0], res[3][0]) and np.array_equal(res[2][1]["kind"], res[3][1]["kind"])

@@ -225,3 +225,14 @@ def test_store_cases_reach_every_tile():
     assert {K // 64 % 3 for M, N, K in bt.STORES if bt.store_tile(table, M, N, K)[:2] == ((256, 128), 0)} == {0, 1, 2}
     steps = {k: {K // 64 for M, N, K in bt.STORES if bt.store_tile(table, M, N, K)[1] == 0 and bt.store_kind(table, M, N, K)[0] == k} for k in (1, 11, 12, 13)}
     assert steps[11] >= {2, 3, 4, 5} and steps[12] >= {1, 2, 3, 4, 5} and steps[13] >= {3, 4, 5, 6} and steps[1] >= {4, 5, 6}, steps
+
+
+@pytest.mark.parametrize("rows,tokens,D,groups", [(12, 256, 384, 2), (8, 256, 1152, 2), (28, 400, 768, 2), (30, 256, 1152, 2), (10, 784, 1152, 2),
+                                                  (19, 529, 1152, 2), (21, 1024, 1152, 2), (13, 729, 1024, 2), (14, 961, 768, 2),
+                                                  (10, 256, 1152, 1), (16, 256, 1152, 1), (6, 256, 1152, 1), (12, 121, 384, 1), (13, 1024, 384, 2)])
+def test_row_groups_are_those_that_were_measured_faster(bd, rows, tokens, D, groups):
+    """Rows of a reference step in one group or two: within 6 % of the faster form at each of these, which differ by up to 28 %."""
+    from ctypes import c_int
+    f = bd.load_library()._ZN5speca14dit_row_groupsEiiii
+    f.argtypes, f.restype = [c_int] * 4, c_int
+    assert f(rows, tokens, D, 4 * D) == groups
