@@ -168,7 +168,7 @@ Error launch_mode(const Operands& o, const GemmEpi& epi, const StreamArg<STREAMS
     SPECA_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem));
     attr_set = true;
   }
-  kern<<<launch_blocks(tiles_m, tiles_n, o, epi), 512, smem, st>>>(o.a, o.lda, o.w, o.ldw, o.M, o.N, o.K, tiles_m, tiles_n, tiles_m < 4 ? tiles_m : 4,
+  kern<<<launch_blocks(BM, BN, tiles_m, tiles_n, o, epi), 512, smem, st>>>(o.a, o.lda, o.w, o.ldw, o.M, o.N, o.K, tiles_m, tiles_n, tiles_m < 4 ? tiles_m : 4,
                                                                      epi_arg<MODE>(epi), streams);
   SPECA_HIP(hipGetLastError());
   return ok();

@@ -328,7 +328,7 @@ Error launch_mode(const Operands& o, const GemmEpi& epi, hipStream_t st) {
     attr_set = true;
   }
   const int group_m = tiles_m < 4 ? tiles_m : 4;
-  kern<<<LW ? launch_blocks(tiles_m, tiles_n, o, epi) : tile_blocks(tiles_m, tiles_n), (WGM * WGN + LW) * 64, smem, st>>>(o.a, o.lda, o.w, o.ldw, o.M, o.N, o.K, tiles_m, tiles_n, group_m,
+  kern<<<LW ? launch_blocks(BM, BN, tiles_m, tiles_n, o, epi) : tile_blocks(tiles_m, tiles_n), (WGM * WGN + LW) * 64, smem, st>>>(o.a, o.lda, o.w, o.ldw, o.M, o.N, o.K, tiles_m, tiles_n, group_m,
                                                                     epi_arg<MODE>(epi));
   SPECA_HIP(hipGetLastError());
   return ok();

@@ -17,9 +17,9 @@ struct Operands {
   int M, N, K;
 };
 
-// Blocks of a launch of one block per compute unit: those of the tiles and, if they leave units idle, one for each of these
+// Blocks of a launch of one block (a tile of bm x bn) per compute unit: those of the tiles and, if they leave units idle, one for each of these
 // (read_ahead).
-unsigned launch_blocks(int tiles_m, int tiles_n, const Operands& o, const GemmEpi& epi);
+unsigned launch_blocks(int bm, int bn, int tiles_m, int tiles_n, const Operands& o, const GemmEpi& epi);
 
 // gemm_phase.hip: 256 x 256
 bool gemm_phase_fits(const Operands& o);      // the tiles of gemm_duo.hip, too
