@@ -151,7 +151,9 @@ struct Choice {
 };
 // What a second launch costs beyond the two modelled times, in microseconds.  Over 220 layers that the model would split without it, splits of
 // layers under 40 us lost 5 % on the mean (7000 x 3072 x 192 21.2 -> 23.1 us); with it 156 are split, 6 % faster on the mean and one of them
-// slower by more than 2 %, and the choice lies 0.1 % above the better form of each on the mean (0.9 % without).
+// slower by more than 2 %, and the choice lies 0.1 % above the better form of each on the mean (0.9 % without).  It is part of the layer's time, which
+// the choices of row groups and of streams weigh: dual blocks of 34 sizes where that decides 0.5 % faster on the mean (4 % to -2.6 %; 2 rows x (1312 + 40)
+// tokens x 3072 features, 4 blocks, 4440 -> 4267 us).
 constexpr double kSecondLaunch = 4.0;
 static Choice choose(const Operands& o, bool branch, bool paired) {
   Choice c{-1, 0, 0.0};
@@ -170,8 +172,8 @@ static Choice choose(const Operands& o, bool branch, bool paired) {
       tail.N = o.N - n1;
       double rest = 0.0;
       const int kind = pick_tile(tail, false, false, &rest);
-      rest += tile_cost(kTileKinds[0], false, tiles_of(kTileKinds[0], o.M, n1), o.K, false);
-      if (c.head ? rest < c.time : rest + kSecondLaunch < 0.96 * c.time) c = {kind, n1, rest};
+      rest += tile_cost(kTileKinds[0], false, tiles_of(kTileKinds[0], o.M, n1), o.K, false) + kSecondLaunch;
+      if (rest < (c.head ? 1.0 : 0.96) * c.time) c = {kind, n1, rest};
     }
   }
   return c;

@@ -261,3 +261,41 @@ def test_idle_units_read_ahead_only_where_they_stay_ahead(bd, bm, bn, M, N, K, a
     assert f(bm, bn, tm, tn, C.byref(o), epi) == held + ahead
     epi[32] = 1                                        # beside another launch: no unit counts as idle
     assert f(bm, bn, tm, tn, C.byref(o), epi) == held
+
+
+@pytest.mark.parametrize("M,N,K", [(4096, 4608, 1152), (4096, 9216, 3072), (27286, 3072, 3072), (512, 3456, 1152)])
+def test_a_layers_time_counts_its_second_launch(bd, M, N, K):
+    """The time that row groups and streams are weighed by is that of both parts of a split layer and of the launch between them."""
+    from ctypes import c_bool, c_double, c_int
+    import branch_tiles as bt
+    f = bd.load_library()._ZN5speca10layer_timeEbiiib
+    f.argtypes, f.restype = [c_bool, c_int, c_int, c_int, c_bool], c_double
+    table, head = bt.tile_table(), bt.store_tile(bt.tile_table(), M, N, K)[1]
+    want = bt.store_kind(table, M, N - head, K)[1]
+    if head:
+        second = float(re.search(r"kSecondLaunch = ([\d.]+);", bt._source()).group(1))
+        want += bt._store_cost(table[0], M, head, K) + second
+    assert f(False, M, N, K, False) == pytest.approx(want, rel=1e-5)
+
+
+@pytest.mark.parametrize("D,rows,img,txt,N", [(3072, 2, 1312, 40, 12288), (1536, 2, 2736, 8, 6144), (3072, 1, 1950, 244, 12288)])
+def test_both_streams_in_one_launch_where_separate_layers_are_split(bd, D, rows, img, txt, N):
+    """Layers that are split into two launches when a stream runs alone: 2 to 4 % of a reference step were lost by leaving these launches uncounted."""
+    assert streams_kind(bd, rows, img, txt, N, D, branch=False) >= 0
+
+
+def streams_kind(bd, rows, img, txt, N, K, branch):
+    """Place in the tile table of the launch for both streams of a dual block's layer (negative: row by row and stream by stream)."""
+    import ctypes as C
+
+    class Operands(C.Structure):
+        _fields_ = [("a", C.c_void_p), ("lda", C.c_int64), ("w", C.c_void_p), ("ldw", C.c_int64), ("M", C.c_int), ("N", C.c_int), ("K", C.c_int)]
+
+    class StreamLayer(C.Structure):
+        _fields_ = [("rows", C.c_int), ("tokens", C.c_int), ("len", C.c_int * 2), ("off", C.c_int * 2), ("w", C.c_void_p * 2), ("bias", C.c_void_p * 2),
+                    ("gate", C.c_void_p * 2)]
+
+    f = bd.load_library()._ZN5speca12pick_streamsERKNS_8OperandsERKNS_11StreamLayerEb
+    f.argtypes, f.restype = [C.c_void_p, C.c_void_p, C.c_bool], C.c_int
+    y = StreamLayer(rows, img + txt, (img, txt), (txt, 0), (4096, 8192))          # addresses that are only looked at for their alignment
+    return f(C.byref(Operands(4096, K, 4096, K, rows * (img + txt), N, K)), C.byref(y), branch)
