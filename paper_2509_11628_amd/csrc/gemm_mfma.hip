@@ -29,6 +29,11 @@ constexpr int BK = 64;
 // 800 problems with cold weights (16 to 27 286 rows, the layers of 384 to 3072 features and random sizes, K from 64 on, tails of K; layers below 10 us
 // inside captured graphs, where the host's launch does not count), so that the time of the kernels picked is least (1.0 % above the best kernel of
 // each on the mean) and the times themselves fit (7 to 13 % rms).
+// c and r of the plain stores were then corrected on 1300 layers above 9.5 us, half of them with K below 800, for which that fit's picks had been
+// up to 22 % slower than the kinds and table before it.  On 412 other layers 0.993 of the time on the mean (0.55 to 1.07, read-ahead's limits
+// included), and those more than 5 % slower than before that fit are 7 instead of 14.  us, its pick / now:
+// 1781 x 3456 x 384 13.7 / 11.1 (128x128 / 256x128), 5649 x 3456 x 256 30.1 / 24.9 (128x192 / split), 21616 x 3456 x 64 53.9 / 48.5 (128x192 / 256x256),
+// 628 x 9216 x 384 13.8 / 11.3 (128x128 / 256x128), 6578 x 3072 x 96 23.7 / 22.2 (128x192 / 128x128).
 // The branch epilogue (residual read and written in fp32, cache planes) is two to four times as long as a plain store, so c and r have
 // second values for it, fitted to 170 reference steps of 4 blocks (384 to 3072 features, 200 to 51 200 rows, both cache layouts), each of
 // them with its branch layers on every kind: the picks cost 0.4 % of a step on the mean (13 % at worst: planes of differences).
@@ -43,20 +48,20 @@ struct TileKind {
   bool whole_steps;    // K % 64 == 0
 };
 constexpr TileKind kTileKinds[] = {
-    {256, 256, 3.5f, 6.45f, 1.096f, 1.12f, 16.4f, 0.76f, false, true},       // 0: phases (gemm_phase.hip)
-    {256, 128, 5.3f, 3.47f, 0.597f, 1.23f, 7.6f, 1.05f, false, true},        // 1: two groups (gemm_duo.hip)
+    {256, 256, 3.5f, 5.86f, 1.096f, 1.12f, 16.4f, 0.76f, false, true},       // 0: phases (gemm_phase.hip)
+    {256, 128, 5.3f, 3.34f, 0.597f, 1.23f, 7.6f, 1.05f, false, true},        // 1: two groups (gemm_duo.hip)
     {128, 128, 3.2f, 2.55f, 0.504f, 1.24f, 7.7f, 0.96f, false, false},       // 2: ring of 4 stages x 64 columns
     {128, 128, 3.8f, 2.54f, 0.760f, 0.36f, 8.5f, 0.11f, true, false},        // 3: ring of 2 x 64
     {128, 64, 0.6f, 2.88f, 0.348f, 1.02f, 5.5f, 0.92f, false, false},        // 4: ring of 3 x 128
     {64, 64, 1.0f, 2.12f, 0.216f, 1.03f, 4.4f, 0.88f, false, false},         // 5: ring of 3 x 128
     {32, 64, 0.6f, 2.54f, 0.208f, 0.91f, 4.4f, 0.77f, false, false},         // 6: ring of 4 x 128, two waves
     {192, 128, 2.7f, 4.12f, 0.669f, 1.11f, 17.7f, 0.95f, false, false},      // 7: ring of 3 x 64
-    {128, 192, 2.3f, 3.99f, 1.025f, 0.33f, 9.4f, 0.11f, true, false},        // 8: ring of 2 x 64
-    {192, 192, 4.6f, 5.76f, 0.900f, 1.12f, 0.0f, 0.00f, false, false},       // 9: ring of 3 x 64
-    {96, 128, 0.4f, 3.05f, 0.476f, 1.03f, 11.4f, 0.78f, false, false},       // 10: ring of 4 x 64
-    {64, 128, 0.5f, 2.37f, 0.361f, 1.00f, 3.5f, 0.90f, false, true},         // 11: two groups
-    {128, 128, 0.0f, 3.15f, 0.455f, 1.08f, 6.9f, 0.96f, false, true},        // 12: two groups
-    {192, 128, 3.2f, 4.00f, 0.522f, 1.20f, 8.2f, 1.04f, false, true},        // 13: two groups
+    {128, 192, 2.3f, 4.20f, 1.025f, 0.33f, 9.4f, 0.11f, true, false},        // 8: ring of 2 x 64
+    {192, 192, 4.6f, 7.16f, 0.900f, 1.12f, 0.0f, 0.00f, false, false},       // 9: ring of 3 x 64
+    {96, 128, 0.4f, 4.40f, 0.476f, 1.03f, 11.4f, 0.78f, false, false},       // 10: ring of 4 x 64
+    {64, 128, 0.5f, 2.46f, 0.361f, 1.00f, 3.5f, 0.90f, false, true},         // 11: two groups
+    {128, 128, 0.0f, 3.15f, 0.455f, 1.30f, 6.9f, 0.96f, false, true},        // 12: two groups
+    {192, 128, 3.2f, 3.82f, 0.522f, 1.20f, 8.2f, 1.04f, false, true},        // 13: two groups
 };
 constexpr int kKinds = sizeof(kTileKinds) / sizeof(kTileKinds[0]);
 

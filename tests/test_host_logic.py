@@ -202,6 +202,17 @@ def test_store_layers_run_on_the_tile_that_was_measured_fastest(M, N, K, tile):
     assert bt.store_tile(bt.tile_table(), M, N, K)[:2] == (tile, 0)
 
 
+@pytest.mark.parametrize("M,N,K,place,head", [(1781, 3456, 384, 1, 0), (2097, 3456, 256, 1, 0), (628, 9216, 384, 1, 0), (4830, 1212, 320, 1, 0),
+                                              (21616, 3456, 64, 0, 0), (3888, 2304, 768, 0, 0), (6578, 3072, 96, 3, 0), (608, 9216, 72, 8, 0),
+                                              (5649, 3456, 256, 12, 2816)])
+def test_short_layers_run_on_a_kind_that_was_measured_fast(M, N, K, place, head):
+    """Short layers (place of the kind in the table, columns on the largest tile ahead of it) that constants fitted mostly to long ones had made 5 to
+    22 % slower than they had been."""
+    import branch_tiles as bt
+    table = bt.tile_table()
+    assert bt.store_tile(table, M, N, K)[1] == head and bt.store_kind(table, M, N - head, K)[0] == place
+
+
 @pytest.mark.parametrize("M,N,K,head", [(4096, 4608, 1152, 4096), (4096, 9216, 3072, 8192), (27286, 3072, 3072, 2816)])
 def test_layers_a_little_over_whole_rounds_are_split(M, N, K, head):
     import branch_tiles as bt
