@@ -310,3 +310,18 @@ def streams_kind(bd, rows, img, txt, N, K, branch):
     f.argtypes, f.restype = [C.c_void_p, C.c_void_p, C.c_bool], C.c_int
     y = StreamLayer(rows, img + txt, (img, txt), (txt, 0), (4096, 8192))          # addresses that are only looked at for their alignment
     return f(C.byref(Operands(4096, K, 4096, K, rows * (img + txt), N, K)), C.byref(y), branch)
+
+
+@pytest.mark.parametrize("tokens,n,D", [(256, 2, 1152), (256, 16, 1152), (1, 1, 8), (5, 64, 384), (1 << 21, 1, 4096), ((1 << 21) + 3, 1, 4096), (7456541, 1, 1152), (2 ** 31 - 1, 1, 16)])
+def test_patch_embedding_reaches_every_token(bd, tokens, n, D):
+    """Threads of a row number tokens x features / 4, or a quarter where a thread takes four tokens; rows of 34 GB and more of hidden state
+    are still numbered in 32 bits."""
+    import ctypes as C
+    f = bd.load_library()._ZN5speca17patch_embed_splitEliiPl
+    f.argtypes, f.restype = [C.c_int64, C.c_int, C.c_int, C.POINTER(C.c_int64)], C.c_int
+    threads = C.c_int64()
+    per = f(tokens, n, D, C.byref(threads))
+    assert per == (4 if tokens * n * D >= 4 * 4 * 256 * 512 else 1)
+    last = threads.value - 1                          # the kernel's thread -> (group of tokens, features)
+    assert last < 2 ** 32 - 256
+    assert last // (D // 4) * per < tokens <= (last // (D // 4) + 1) * per and last % (D // 4) == D // 4 - 1
