@@ -2,6 +2,7 @@
 // conditioning sum, patch embedding, LayerNorm + adaLN modulation, the fused
 // forecast-and-fold of speculative steps, un-patchify.
 #include "dit_kernels.h"
+#include "gemm.h"
 
 namespace speca {
 
@@ -364,7 +365,7 @@ Error launch_cond_sum(int dtype, const float* temb, int n_steps, const void* y_t
 // Tokens per thread of the patch embedding of n rows, and its threads for a row, whose number a thread holds in 32 bits.  Several tokens where
 // two blocks are left for every unit of the chip (2 rows x 256 tokens x 1152 features with one 7.1 us, 16 rows 29 with one and 17 with four).
 int patch_embed_split(int64_t tokens, int n, int D, int64_t* threads) {
-  const int per_thread = tokens * n * (D / 4) >= int64_t{4} * 256 * 512 ? 4 : 1;
+  const int per_thread = tokens * n * (D / 4) >= int64_t{4} * 256 * 2 * compute_units() ? 4 : 1;
   *threads = (tokens + per_thread - 1) / per_thread * (D / 4);
   return per_thread;
 }

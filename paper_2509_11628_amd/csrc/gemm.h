@@ -1,8 +1,9 @@
 // Linear layers of the target model:  C[M,N] = A[M,K] * W[N,K]^T (+ bias) with a fused
 // epilogue.  A and W are row-major with K contiguous, in the model dtype; accumulation
 // is fp32.  Three kernel families implement it: bf16 MFMA with LDS-staged tiles (the dense
-// contractions of reference steps), fp32 MFMA straight from memory for fp32 models, and a plain
-// fp32-FMA tile kernel for operands whose strides or alignment neither takes.
+// contractions of reference steps), fp32 MFMA for fp32 models, with tiles through LDS where K is a
+// multiple of 64 and straight from memory elsewhere, and a plain fp32-FMA tile kernel for operands whose
+// strides or alignment neither takes.
 #pragma once
 
 #include <type_traits>
@@ -10,6 +11,8 @@
 #include "common.h"
 
 namespace speca {
+
+int compute_units();               // of the device (256 where there is none)
 
 enum EpiMode {
   EPI_STORE = 0,   // out[m][n] = T(acc + bias)

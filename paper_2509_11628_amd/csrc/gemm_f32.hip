@@ -490,44 +490,44 @@ bool gemm_f32_supported(const void* A, int64_t lda, const void* W, int64_t ldw, 
   return K % 4 == 0 && lda % 4 == 0 && ldw % 4 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0;
 }
 
-static Error launch_f32_kind(int kind, const float* a, int64_t lda, const float* w, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st) {
-  switch (kind) {
-    case 0: return launch_f32_tile<4, 4, 2>(a, lda, w, ldw, M, N, K, epi, st);
-    case 1: return launch_f32_tile<2, 4, 3>(a, lda, w, ldw, M, N, K, epi, st);
-    case 2: return launch_f32_tile<2, 2, 4>(a, lda, w, ldw, M, N, K, epi, st);
-    case 3: return launch_f32_tile<1, 2, 6>(a, lda, w, ldw, M, N, K, epi, st);
-    default: return launch_f32_tile<1, 1, 8>(a, lda, w, ldw, M, N, K, epi, st);
-  }
-}
-
-Error launch_gemm_f32(const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st) {
-  const float *a = static_cast<const float*>(A), *w = static_cast<const float*>(W);
+// Which kernel runs a layer: 0 .. 4 straight from memory, 5 .. 8 through LDS.
+int gemm_f32_kind(int M, int N, int K) {
   const auto blocks = [&](int bm, int bn) { return static_cast<int64_t>((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-  const int rows = (M + 15) / 16 * 16;
+  const int rows = (M + 15) / 16 * 16, units = compute_units();
   // Straight from memory, the largest tile that still makes 128 blocks (one on every second compute unit): a block's waves read every operand
   // piece once per tile, and that traffic costs more than idle units do down to there (512 x 1152 x 384: 144 blocks of 64 x 64
   // 11.4 us, 576 of 32 x 32 12.8, 2304 of 16 x 16 18.1; 512 x 384 x 384 with 48 / 192 / 768 blocks: 11.1 / 5.6 / 7.6 us).
   // Tiles more than twice as high as the problem only read rows again.
   constexpr int bm[5] = {64, 32, 32, 16, 16}, bn[5] = {64, 64, 32, 32, 16};
   int kind = 0;
-  while (kind < 4 && (bm[kind] > 2 * rows || blocks(bm[kind], bn[kind]) < 128)) ++kind;
-  if (K % 64 || rows < 32 || kind > 2) return launch_f32_kind(kind, a, lda, w, ldw, M, N, K, epi, st);
-  // Through LDS, the tile that takes least: its rounds over 256 units times its stages, each the longer of 4 TM TN matrix instructions per wave
+  while (kind < 4 && (bm[kind] > 2 * rows || blocks(bm[kind], bn[kind]) < units / 2)) ++kind;
+  if (K % 64 || rows < 32 || kind > 2) return kind;
+  // Through LDS, the tile that takes least: its rounds over the units times its stages, each the longer of 4 TM TN matrix instructions per wave
   // (32 clocks) and of its loads at 94 bytes per ns, and 0.4 us a round.  Fewer than 128 blocks of 32 x 32, or 16 rows: a step's latency
   // binds, not the loads.
   constexpr int tm[4] = {4, 4, 2, 2}, tn[4] = {4, 3, 4, 2};
   int best = 0;
   double least = 0.0;
   for (int k = 0; k < 4; ++k) {
-    const double rounds = static_cast<double>((blocks(16 * tm[k], 16 * tn[k]) + 255) / 256);
+    const double rounds = static_cast<double>((blocks(16 * tm[k], 16 * tn[k]) + units - 1) / units);
     const double stage = std::max(tm[k] * tn[k] * 0.0533, (tm[k] + tn[k]) * 16 * 256 / 94e3);
     const double time = rounds * (stage * (K / 64) + 0.4);
     if (k == 0 || time < least) { best = k; least = time; }
   }
-  switch (best) {
-    case 0: return launch_f32_lds<4, 4, 2>(a, lda, w, ldw, M, N, K, epi, st);
-    case 1: return launch_f32_lds<4, 3, 2>(a, lda, w, ldw, M, N, K, epi, st);
-    case 2: return launch_f32_lds<2, 4, 3>(a, lda, w, ldw, M, N, K, epi, st);
+  return 5 + best;
+}
+
+Error launch_gemm_f32(const void* A, int64_t lda, const void* W, int64_t ldw, int M, int N, int K, const GemmEpi& epi, hipStream_t st) {
+  const float *a = static_cast<const float*>(A), *w = static_cast<const float*>(W);
+  switch (gemm_f32_kind(M, N, K)) {
+    case 0: return launch_f32_tile<4, 4, 2>(a, lda, w, ldw, M, N, K, epi, st);
+    case 1: return launch_f32_tile<2, 4, 3>(a, lda, w, ldw, M, N, K, epi, st);
+    case 2: return launch_f32_tile<2, 2, 4>(a, lda, w, ldw, M, N, K, epi, st);
+    case 3: return launch_f32_tile<1, 2, 6>(a, lda, w, ldw, M, N, K, epi, st);
+    case 4: return launch_f32_tile<1, 1, 8>(a, lda, w, ldw, M, N, K, epi, st);
+    case 5: return launch_f32_lds<4, 4, 2>(a, lda, w, ldw, M, N, K, epi, st);
+    case 6: return launch_f32_lds<4, 3, 2>(a, lda, w, ldw, M, N, K, epi, st);
+    case 7: return launch_f32_lds<2, 4, 3>(a, lda, w, ldw, M, N, K, epi, st);
     default: return launch_f32_lds<2, 2, 4>(a, lda, w, ldw, M, N, K, epi, st);
   }
 }

@@ -65,7 +65,7 @@ constexpr TileKind kTileKinds[] = {
 };
 constexpr int kKinds = sizeof(kTileKinds) / sizeof(kTileKinds[0]);
 
-static int compute_units() {
+int compute_units() {
   static const int n = [] {
     int dev = 0, cu = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cu < 1) {

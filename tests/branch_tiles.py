@@ -46,6 +46,10 @@ STORES = [(1, 16, 8), (33, 4, 128), (65, 140, 200), (3401, 264, 8), (257, 3304, 
           (5647, 284, 64), (5468, 280, 128), (5460, 336, 192), (518, 3604, 256), (513, 3636, 320), (6055, 648, 192), (1697, 2308, 256), (5525, 652, 320),
           (5498, 652, 384), (5398, 1096, 40), (5941, 2564, 64), (4995, 1540, 384)]
 
+# fp32 models: rows, grid, hidden, heads, mlp_hidden, (kernels of the two branch layers, as launch_gemm_f32 counts them: 5 .. 8 are the tiles
+# through LDS).  A row alone runs straight from memory.
+F32_CASES = [(30, 13, 192, 3, 576, (5, 5)), (12, 13, 320, 5, 640, (6, 6)), (9, 11, 384, 6, 1536, (7, 7)), (7, 9, 384, 6, 1536, (8, 8)), (25, 9, 64, 4, 128, (8, 8))]
+
 
 def _source():
     return open(os.path.join(ROOT, "paper_2509_11628_amd", "csrc", "gemm_mfma.hip")).read()

@@ -108,6 +108,43 @@ def test_branch_epilogue_on_every_tile(case, layout):
     ctx.close()
 
 
+@pytest.mark.parametrize("layout", ["differences", "ring"])
+@pytest.mark.parametrize("case", branch_tiles.F32_CASES, ids=lambda c: f"{c[0]}x{c[1] ** 2}x{c[2]}x{c[4]}")
+def test_branch_epilogue_f32_through_lds(case, layout):
+    """The branch layers of fp32 models on the tiles whose operands come through LDS: three reference steps of all rows together leave the bits
+    of the same steps of a row alone, straight from memory, and the first one agrees with the oracle's forward of that row."""
+    import paper_2509_11628_amd as sp
+    from paper_2509_11628_amd import binding as bd
+    rows, grid, D, H, Dm, _ = case
+    s = si.DiTShape(depth=1, hidden=D, heads=H, mlp_hidden=Dm, in_channels=4, latent_hw=2 * grid, patch=2, num_classes=10, freq_dim=32, dtype="f32")
+    w = si.make_dit_weights(s, 0)
+    ctx = make_gpu(s, w)
+    cfg = sp.make_cfg(order=2, interval=100, layout=bd.CACHE_RING if layout == "ring" else bd.CACHE_DIFFERENCES)
+    x = {step: torch.from_numpy(si.make_latents(rows, 4, s.latent_hw, seed=step)).cuda() for step in (0, 3, 4)}
+    labels = [i % 11 for i in range(rows)]
+
+    def steps(which):
+        ctx.init_cache(cfg, rows)
+        out = torch.zeros((3, *x[0].shape), device="cuda")
+        f = torch.empty((2, 2, len(which), s.tokens, D), device="cuda")
+        for i, step in enumerate((0, 3, 4)):
+            ctx.full_step(x[step], step, which, out[i], labels=labels, timestep=900.0 - 100.0 * i)
+            if i != 1:
+                ctx.forecast(step + 2, which, f[i // 2])
+        return out, f
+
+    out, f = steps(list(range(rows)))
+    for r in (0, rows // 2, rows - 1):
+        out1, f1 = steps([r])
+        assert torch.equal(out1[:, r], out[:, r]) and torch.equal(f1[:, :, 0], f[:, :, r]), r
+    r = rows // 2
+    exp, feats = odit.DiTOracle(s, w).forward(x[0][r:r + 1].cpu().numpy(), 900.0, [labels[r]])
+    assert max_abs_rel(out[0, r:r + 1].cpu().numpy(), exp) <= 1e-5
+    for j in range(2):
+        assert max_abs_rel(f[0, j, r].cpu().numpy(), feats[j][0]) <= 1e-5, j
+    ctx.close()
+
+
 def test_spec_step_matches_oracle(tiny):
     import paper_2509_11628_amd as sp
     s, w, om, ctx = tiny

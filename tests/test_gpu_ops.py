@@ -90,8 +90,9 @@ def test_linear_row_result_independent_of_m():
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 4, 4), (15, 20, 12), (17, 516, 260), (33, 1028, 20), (129, 1100, 16), (300, 2052, 100), (2100, 132, 72), (40, 64, 7),
-                                   # through LDS: 64x64, 64x48, 32x64 and 32x32 tiles, one to nine stages, ragged rows and columns
-                                   (4100, 516, 64), (513, 1148, 384), (2047, 1156, 128), (515, 388, 192), (130, 2300, 576), (33, 4612, 320)])
+                                   # through LDS: 64x48 (two), 32x64, 32x32, 32x64 (two) and 64x64 (two) tiles, one to nine stages, ragged rows and columns
+                                   (4100, 516, 64), (513, 1148, 384), (2047, 1156, 128), (515, 388, 192), (130, 2300, 576), (33, 4612, 320),
+                                   (5001, 516, 128), (4999, 516, 192)])
 def test_linear_f32_tiles(M, N, K):
     """fp32 layers at the edges of every tile of the fp32 matrix kernel (16 to 64 rows and columns, K in four interleaved
     parts of 16, tails of 4) and a K that only the plain kernel takes; a row's bits do not depend on M or on the tile."""

@@ -325,3 +325,17 @@ def test_patch_embedding_reaches_every_token(bd, tokens, n, D):
     last = threads.value - 1                          # the kernel's thread -> (group of tokens, features)
     assert last < 2 ** 32 - 256
     assert last // (D // 4) * per < tokens <= (last // (D // 4) + 1) * per and last % (D // 4) == D // 4 - 1
+
+
+def test_f32_cases_reach_every_tile_through_lds(bd):
+    import test_gpu_ops
+    import branch_tiles as bt
+    from ctypes import c_int
+    f = bd.load_library()._ZN5speca13gemm_f32_kindEiii
+    f.argtypes, f.restype = [c_int] * 3, c_int
+    for rows, grid, D, H, Dm, want in bt.F32_CASES:
+        for K, kind in zip((D, Dm), want):
+            assert f(rows * grid * grid, D, K) == kind and f(grid * grid, D, K) < 5, (rows, grid, D, K)
+    assert {k for c in bt.F32_CASES for k in c[5]} == {5, 6, 7, 8}
+    shapes, = [m.args[1] for m in test_gpu_ops.test_linear_f32_tiles.pytestmark if m.name == "parametrize"]
+    assert {f(*x) for x in shapes} >= {5, 6, 7, 8}
