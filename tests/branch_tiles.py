@@ -50,6 +50,14 @@ STORES = [(1, 16, 8), (33, 4, 128), (65, 140, 200), (3401, 264, 8), (257, 3304, 
 # through LDS).  A row alone runs straight from memory.
 F32_CASES = [(30, 13, 192, 3, 576, (5, 5)), (12, 13, 320, 5, 640, (6, 6)), (9, 11, 384, 6, 1536, (7, 7)), (7, 9, 384, 6, 1536, (8, 8)), (25, 9, 64, 4, 128, (8, 8))]
 
+# rows, text tokens, latent height and width (patch 2), hidden, heads, mlp_hidden, kinds (places in the table) of the launches for both streams:
+# qkv, projection, first MLP layer, second one, second one where it is verified.  Streams shorter than a tile, that end inside tiles and tiles that
+# span rows of the batch; a row alone takes 64x128.
+STREAM_LAYERS = ("qkv", "proj", "fc1", "fc2", "truth")
+STREAMS = [(64, 17, 46, 66, 256, 4, 64, (0, 0, 1, 0, 0)), (64, 40, 68, 44, 128, 2, 256, (0, 1, 0, 1, 1)), (13, 129, 40, 60, 768, 12, 768, (1, 1, 1, 1, 1)),
+           (64, 5, 38, 28, 128, 2, 64, (12, 12, 12, 12, 12)), (48, 40, 32, 52, 256, 4, 64, (13, 13, 12, 11, 13)), (64, 77, 38, 46, 128, 2, 64, (1, 11, 13, 11, 13)),
+           (9, 77, 60, 58, 512, 8, 1024, (0, 13, 0, 13, 13)), (2, 1, 16, 16, 128, 2, 512, (11, 11, 11, 11, 11))]
+
 
 def _source():
     return open(os.path.join(ROOT, "paper_2509_11628_amd", "csrc", "gemm_mfma.hip")).read()

@@ -7,6 +7,7 @@ Bars as for the DiT tests: schedules decision by decision, latents 1e-5 (fp32) /
 import numpy as np
 import pytest
 
+import branch_tiles
 import speca_inputs as si
 from oracle import mmdit as ommdit, sampler as osamp, speca_core as core
 
@@ -125,7 +126,7 @@ def test_mmdit_error_paths(tiny):
 
 
 # rows, text tokens, latent height and width (patch 2), hidden, heads, mlp_hidden: streams of one token, shorter than a tile, that end inside tiles and
-# tiles that span rows of the batch; large enough for 256x256 tiles; an MLP of 136 features, whose second layer goes row by row and stream by stream
+# tiles that span rows of the batch; qkv and the first MLP layer on 256x256 tiles; an MLP of 136 features, whose second layer goes row by row and stream by stream
 @pytest.mark.parametrize("layout", ["differences", "ring"])
 @pytest.mark.parametrize("rows,txt,h,w,D,H,Dm", [(2, 1, 16, 16, 128, 2, 512), (3, 77, 20, 22, 128, 2, 512), (3, 129, 34, 30, 512, 8, 2048),
                                                  (1, 300, 66, 62, 768, 12, 3072), (2, 40, 18, 22, 128, 2, 136), (5, 65, 128, 128, 512, 8, 2048)])
@@ -160,6 +161,53 @@ def test_dual_blocks_of_all_rows_in_one_launch(rows, txt, h, w, D, H, Dm, layout
         r = rows - 1
         exp, _ = ommdit.MMDiTOracle(s, weights).forward(x[0][r:r + 1].cpu().numpy(), 900.0, (text[r:r + 1], vec[r:r + 1]))
         assert max_abs_rel(out[0, r:r + 1].cpu().numpy(), exp) <= 2e-2
+    ctx.close()
+
+
+@pytest.mark.parametrize("layout", ["differences", "ring"])
+@pytest.mark.parametrize("case", branch_tiles.STREAMS, ids=lambda c: "x".join(map(str, c[:7])))
+def test_both_streams_on_every_tile(case, layout):
+    """Launches for both streams of a dual block on every tile that carries them, under every epilogue: after one reference step of all rows the cached
+    features and the output of three rows are those of the oracle's forward of the row; after three, and for the errors of an attempt that
+    verifies the dual block, rows together leave the bits of a row alone (another tile); the errors are the oracle's."""
+    import dataclasses
+    import paper_2509_11628_amd as sp
+    from paper_2509_11628_amd import binding as bd
+    rows, txt, h, w, D, H, Dm, _ = case
+    s = dataclasses.replace(si.mmdit_tiny("bf16"), depth_dual=1, depth_single=1, hidden=D, heads=H, mlp_hidden=Dm, txt_tokens=txt, latent_h=h, latent_w=w)
+    weights = si.make_mmdit_weights(s, 0)
+    om, ctx = ommdit.MMDiTOracle(s, weights), make_gpu(s, weights)
+    text, vec = si.make_text(rows, s, 3)
+    td, vd = torch.from_numpy(text).cuda().bfloat16(), torch.from_numpy(vec).cuda().bfloat16()
+    x = [torch.from_numpy(si.make_video_latents(rows, s, i)).cuda() for i in range(4)]
+    cfg = sp.make_cfg(order=2, interval=100, verify_block=0, layout=bd.CACHE_RING if layout == "ring" else bd.CACHE_DIFFERENCES)
+
+    def steps(which):
+        ctx.init_cache(cfg, rows)
+        out = torch.zeros((4, *x[0].shape), device="cuda")
+        f = torch.empty((2, s.n_slots, len(which), s.tokens, D), dtype=torch.bfloat16, device="cuda")
+        errors = []
+        for i, step in enumerate((0, 3, 4)):
+            ctx.full_step(x[i], step, which, out[i], timestep=900.0 - 100.0 * i, txt=td, pooled=vd)
+            if i != 1:
+                ctx.forecast(step + 2, which, f[i // 2])
+                errors.append(ctx.spec_step(x[3], step + 1, which, np.inf, out[3], timestep=500.0, txt=td, pooled=vd)[0])
+        return out, f, errors
+
+    out, f, errors = steps(list(range(rows)))
+    for r in {0, rows // 2, rows - 1}:
+        out1, f1, errors1 = steps([r])
+        assert torch.equal(out1[:, r], out[:, r]) and torch.equal(f1[:, :, 0], f[:, :, r]), r
+        assert [e[0] for e in errors1] == [e[r] for e in errors]
+        cond = text[r:r + 1], vec[r:r + 1]
+        exp, feats = om.forward(x[0][r:r + 1].cpu().numpy(), 900.0, cond)
+        assert max_abs_rel(out[0, r:r + 1].cpu().numpy(), exp) <= 2e-2
+        for j in range(s.n_slots):
+            assert max_abs_rel(f[0, j, r].float().cpu().numpy(), feats[j][0]) <= 1.5e-2, j
+        # the attempt after one reference: its forecast is the cached feature, the truth the dual block on the new latents
+        h0, c0 = om.begin(x[3][r:r + 1].cpu().numpy(), 500.0, cond)
+        e = core.relative_error(core.bf16_round(feats[1]), om.block_real(0, h0, c0)[1][-1])
+        assert abs(float(errors[0][r]) - e) <= 2e-2 * e, (r, errors[0][r], e)
     ctx.close()
 
 

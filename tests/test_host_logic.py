@@ -327,6 +327,20 @@ def test_patch_embedding_reaches_every_token(bd, tokens, n, D):
     assert last // (D // 4) * per < tokens <= (last // (D // 4) + 1) * per and last % (D // 4) == D // 4 - 1
 
 
+def test_stream_cases_reach_every_kind_in_every_mode(bd):
+    """The shapes of the GPU test of launches for both streams fall on the kinds they are meant for: every tile of these launches under every
+    epilogue (store, GELU, branch, fp32), and a row alone on another tile than the largest ones."""
+    import branch_tiles as bt
+    table, seen = bt.tile_table(), set()
+    for rows, txt, h, w, D, H, Dm, want in bt.STREAMS:
+        layers = {"qkv": (3 * D, D, False), "proj": (D, D, True), "fc1": (Dm, D, False), "fc2": (D, Dm, True), "truth": (D, Dm, False)}
+        for name, kind in zip(bt.STREAM_LAYERS, want):
+            assert streams_kind(bd, rows, h * w // 4, txt, *layers[name]) == kind, (rows, txt, D, Dm, name)
+            assert streams_kind(bd, 1, h * w // 4, txt, *layers[name]) == 11
+            seen.add((kind, {"proj": "branch", "fc2": "branch"}.get(name, name)))
+    assert seen == {(k, mode) for k, t in enumerate(table) if t[9] for mode in ("qkv", "fc1", "branch", "truth")}
+
+
 def test_f32_cases_reach_every_tile_through_lds(bd):
     import test_gpu_ops
     import branch_tiles as bt
