@@ -14,6 +14,9 @@
 // loads and computes has its matrix instructions wait for its loads to be taken: 64x64 tiles at 512 x 1152 x 4608 took 0.58 us per
 // stage where the loads alone take 0.34 (0.17 the fragments and matrix instructions).  They pass the same barriers and leave after the
 // last one.  Tiles of which two blocks share a unit load from the waves that compute (LW = 0): each block covers the other's waits.
+// So does 192x192 (hence without read-ahead, which is for launches whose blocks have a unit to themselves in eight waves): its waves take 280
+// registers, and beside loader waves they would have 256.  Spilled, it was slower, and moves next to accumulators that assembly uses gave wrong bits;
+// 192x128 spills under the branch epilogue alone, behind the last matrix instruction.
 // What keeps a stage intact between its readers and its next loads: a wave waits for its own fragment reads (lgkmcnt(0))
 // BEFORE the barrier that hands the stage on, and nothing may move across that barrier.  The barrier builtin alone does not give that:
 // matrix instructions, and with them the waits for the fragments they use, are free to sink below it, and a load that hits in L2
@@ -129,7 +132,7 @@ __global__ __launch_bounds__((WGM* WGN + LW) * 64) void gemm_ring_kernel(const u
   asm volatile("s_nop 7" ::: "memory");                      // vector writes to matrix reads
 
   const int nk = (K + COLS - 1) / COLS;
-  // Loader: group g of a stage is rows GR g .. GR g + GR - 1, loaded by wave g % NW; lane l supplies the chunk stored at
+  // Loader: group g of a stage is rows GR g .. GR g + GR - 1, loaded by loader g % LD; lane l supplies the chunk stored at
   // position l % CPR of row l / CPR, i.e. source chunk (l % CPR) ^ swz(row).  With 128-byte rows swz(row) is
   // (row & 7) ^ ((row >> 3) & 1), with 256-byte rows row & 15.  Byte offsets from the tile's first row; rows beyond M / N
   // repeat the last one (never stored).

@@ -28,7 +28,7 @@ Error launch_gemm_phase(const Operands& o, const GemmEpi& epi, hipStream_t st);
 // gemm_duo.hip: bm x 128, bm = 64, 128, 192, 256 (what gemm_phase_fits)
 Error launch_gemm_duo(int bm, const Operands& o, const GemmEpi& epi, hipStream_t st);
 
-// gemm_ring.hip: kinds 0 .. 10 (see its switch)
+// gemm_ring.hip: kinds 0 .. 8 (its switch; places 2 .. 10 of the table in gemm_mfma.hip)
 Error launch_gemm_ring(int kind, const Operands& o, const GemmEpi& epi, hipStream_t st);
 
 #define SPECA_GLL(src, dst)                                                                                       \
