@@ -251,10 +251,10 @@ def test_row_groups_are_those_that_were_measured_faster(bd, rows, tokens, D, gro
 
 @pytest.mark.parametrize("bm,bn,M,N,K,ahead", [
     # readers that would fall behind the tiles: up to 1.9 times as long with them
-    (32, 64, 39, 6144, 8192, 0), (32, 64, 94, 4608, 4608, 0), (32, 64, 8, 8192, 4608, 0), (32, 64, 173, 2304, 12288, 0), (64, 64, 186, 4608, 8192, 0),
+    (32, 64, 2, 6144, 2048, 0), (32, 64, 128, 3072, 5760, 0), (32, 64, 39, 6144, 8192, 0), (32, 64, 94, 4608, 4608, 0), (32, 64, 8, 8192, 4608, 0), (32, 64, 173, 2304, 12288, 0), (64, 64, 186, 4608, 8192, 0),
     (64, 64, 89, 6144, 4096, 0), (128, 64, 143, 6144, 8192, 0), (128, 128, 298, 8192, 16384, 0),
     # readers that stay ahead: 0.77 to 0.92 of the time
-    (32, 64, 28, 3072, 4608, 208), (32, 64, 91, 3072, 12288, 112), (32, 64, 62, 4096, 4096, 128), (64, 64, 162, 3456, 4392, 88), (64, 64, 256, 3456, 12288, 40),
+    (32, 64, 28, 3072, 4608, 208), (32, 64, 91, 3072, 12288, 112), (32, 64, 62, 4096, 4096, 128), (32, 64, 91, 3456, 12288, 88), (32, 64, 287, 1536, 7680, 40), (64, 64, 162, 3456, 4392, 88), (64, 64, 256, 3456, 12288, 40),
     (128, 64, 332, 3456, 8192, 88), (128, 64, 1280, 1536, 6144, 16), (64, 64, 637, 1536, 6184, 16), (128, 128, 460, 6144, 4608, 64), (192, 128, 714, 6144, 3072, 64), (256, 128, 1008, 6144, 4608, 64),
     # too short, too wide, 64 KB of weights for each reader at least, a full chip
     (32, 64, 28, 3072, 704, 0), (32, 64, 16, 9216, 3072, 0), (32, 64, 16, 64, 1024, 2), (192, 128, 8192, 6144, 3072, 0)])
