@@ -81,8 +81,8 @@ int compute_units() {
 // fetched already and take HBM from them.  A unit reads about 56 bytes per ns from HBM.  Tiles of 128 features pass 64 columns of all N rows
 // of W in 0.36 to 0.6 us, 0.2 to 0.35 N bytes per ns: N / 128 units.  Those of 64 features take 0.21 to 0.35 us: N / 88 units, and N / 128 up to
 // 4096 features, where tiles and readers together stay below what HBM gives.  32x64, with next to no activations to wait for, takes 0.13
-// once its weights are near: N / 32, and N / 40 up to 4096 features (of 65 rows and more then: 3456 features with 88 idle units 0.97 on the mean of 14
-// layers, 1536 with 40 0.96 of 11, 285 x 1536 x 7680 27.9 without and 25.5 with; 3072 with 64, N / 48, 1.01, 2304 with 40, N / 58, 1.07; 6144 with
+// once its weights are near: N / 32, and N / 40 up to 4096 features (of 65 rows and more then: 3456 features with 88 idle units 0.98 on the mean of 15
+// layers, 1536 with 40 0.97 of 11, 285 x 1536 x 7680 27.9 without and 25.5 with; 3072 with 64, N / 48, 1.01, 2304 with 40, N / 58, 1.07; 6144 with
 // 160, N / 38, 1.08).  us with read-ahead / without, cold weights, out of 800 layers of 1 to 8192 rows: 32x64 39 x 6144 x 8192
 // (64 idle units) 51.7 / 28.6, 94 x 4608 x 4608 (40) 34.2 / 19.3, 8 x 8192 x 4608 (128) 23.7 / 18.3, but 28 x 3072 x 4608 (208) 0.88 of the time,
 // 91 x 3072 x 12288 (112) 0.77; 64x64 186 x 4608 x 8192 (40) 38.4 / 36.9, 162 x 3456 x 4392 (88) 0.82; 128x64 143 x 6144 x 8192 (64) 49.6 / 42.2,
